@@ -216,8 +216,9 @@ size_t dhsa_static_scratch_bytes(void);
  * Output, in the half-open convention of the rest of the ABI:
  * B_dev = {0} u {i + 1 : i kept} u {L}, ascending, no repeats (the sequence end is
  * always a chunk end), N_c + 1 int32 entries, capacity L + 1; *N_c_dev = N_c.
- * Both are DEVICE memory: copy them to the host after synchronising `stream`
- * (the other entry points take B as a host array; boundaries are made once per
+ * Both are DEVICE memory or pinned host memory that the device can write (then they
+ * are complete once `stream` has been synchronised; from device memory copy them after that
+ * -- the other entry points take B as a host array; boundaries are made once per
  * prompt).  ws_dev: device scratch of dhsa_finalize_boundaries_workspace_bytes(L)
  * bytes.  Asynchronous like the path itself.  A NaN score never exceeds the
  * threshold.  Errors: NULL pointers, L outside [1, 2^31), window < 0 or a NaN

@@ -274,12 +274,14 @@ def dhsa_finalize_boundaries(scores, threshold: float, window: int) -> np.ndarra
     L = int(scores.shape[0])
     n = int(lib().dhsa_finalize_boundaries_workspace_bytes(L))
     ws = torch.empty(max(n, 1), dtype=torch.uint8, device=scores.device)
-    B = torch.empty(L + 1, dtype=torch.int32, device=scores.device)
-    N_c = torch.zeros(1, dtype=torch.int32, device=scores.device)
-    _check(lib().dhsa_finalize_boundaries(scores.data_ptr(), L, float(threshold), int(window), B.data_ptr(),
-                                          N_c.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
-    torch.cuda.synchronize()
-    return B[:int(N_c.item()) + 1].cpu().numpy()
+    # N_c and B go straight to pinned host memory (torch keeps such blocks for reuse): the boundaries are a few
+    # kilobytes, so one wait for the stream brings them, without a copy whose length the host would have to wait for
+    out = torch.empty(L + 2, dtype=torch.int32, pin_memory=True)
+    _check(lib().dhsa_finalize_boundaries(scores.data_ptr(), L, float(threshold), int(window), out.data_ptr() + 4,
+                                          out.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
+    torch.cuda.current_stream().synchronize()
+    host = out.numpy()
+    return host[1:int(host[0]) + 2].copy()
 
 
 def dhsa_recall_rows(prob, Q, K, B, plan, head: int, rows) -> Tuple["torch.Tensor", "torch.Tensor"]:

@@ -6,20 +6,34 @@
 //
 // The greedy is sequential as stated; its result is the unique set in which a
 // candidate is kept iff no better candidate within W tokens of it is kept
-// ("better" = higher score, equal scores: lower position).  That set is built
-// in rounds, all positions in parallel: a still undecided candidate that is
+// ("better" = higher score, equal scores: lower position).  Two kernels build it:
+//
+//   k_nms_windows (one workgroup per 512 positions) decides in LDS what a window
+//     of those positions and a halo on each side can decide.  A decision needs
+//     only final facts -- removed: a neighbour is kept; kept: no better neighbour
+//     is left -- so it holds whatever the rest of the sequence looks like, and the
+//     threads may take their decisions in any order.  A detector's scores (and
+//     noise) leave nothing undecided: the chain of candidates a decision hangs on
+//     has to rise in score all the way to leave the halo.
+//   k_nms_finish (one workgroup) decides what is left in rounds over the whole
+//     sequence -- long monotone runs, windows of more tokens than the halo has --
+//     and compacts the kept positions into B.
+//
+// Bound by latency (0.5 MB of scores at L = 131072): 1.1 ms when one workgroup
+// did all of it in rounds from memory.
+//
+// Rounds of k_nms_finish: a still undecided candidate that is
 // better than every undecided candidate within W tokens is kept (nothing can
 // remove it any more), then every undecided candidate within W tokens of a
 // newly kept one is removed.  The best undecided candidate of the whole
-// sequence is decided in every round, so the loop ends; on scores without long
-// monotone runs it takes a handful of rounds.  A round only visits the 64-position
+// sequence is decided in every round, so the loop ends.  A round only visits the 64-position
 // blocks in which something can change: a candidate can become the best of its
 // neighbourhood only after a better neighbour was removed, so the blocks within W
 // of a removal are the next round's work list (three bitmaps in the workspace);
 // a long monotone run then costs one cheap round per chunk end instead of a pass
-// over the sequence.  One workgroup of 1024 threads does all of it (the state is
-// one byte per position in the caller's workspace and stays in L2); it runs once
-// per prompt, not once per layer.
+// over the sequence.
+#include <algorithm>
+
 #include "dhsa_internal.h"
 
 namespace dhsa {
@@ -47,38 +61,148 @@ __device__ __forceinline__ void nms_mark(unsigned *bits, int64_t lo, int64_t hi)
         }                                                                                        \
     }
 
-__global__ __launch_bounds__(kNmsThreads) void k_finalize_boundaries(const float *__restrict__ p, int64_t L,
-                                                                     float tau, int W, uint8_t *st,
-                                                                     unsigned *bits0, unsigned *bits1,
-                                                                     unsigned *bits2, int32_t *__restrict__ B_out,
-                                                                     int32_t *__restrict__ N_c_out) {
+// ---------------------------------------------------------------------------
+// Local decisions.  The window of workgroup b is [512 b - H, 512 b + 512 + H)
+// clipped to the sequence; only its 512 positions are written to st.  `und` and
+// `kept` are bitmaps over the window.  A position is marked kept before it stops
+// being undecided, and `und` is read before `kept`, so a neighbour on its way
+// from one to the other is never missed.
+// ---------------------------------------------------------------------------
+constexpr int kNmsSeg = 512;                          // positions decided by one workgroup
+constexpr int kNmsHaloMax = 512;                      // positions looked at on each side (a multiple of 64)
+constexpr int kNmsWinMax = kNmsSeg + 2 * kNmsHaloMax;
+
+__global__ __launch_bounds__(256) void k_nms_windows(const float *__restrict__ p, int64_t L, float tau, int W, int H,
+                                                     uint8_t *__restrict__ st) {
+    __shared__ float s_p[kNmsWinMax];
+    __shared__ unsigned long long s_und[kNmsWinMax / 64], s_kept[kNmsWinMax / 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t seg0 = (int64_t)blockIdx.x * kNmsSeg;
+    const int64_t win0 = seg0 - H > 0 ? seg0 - H : 0;
+    const int64_t win1 = seg0 + kNmsSeg + H < L ? seg0 + kNmsSeg + H : L;
+    const int n = (int)(win1 - win0);                 // H and kNmsSeg are multiples of 64: so is win0
+    const bool open_lo = win0 > 0, open_hi = win1 < L;   // unseen positions on that side
+    volatile unsigned long long *und = s_und, *kept = s_kept;
+
+    // candidates: score strictly above the threshold (a NaN never is)
+    float pr[kNmsWinMax / 256];
+#pragma unroll
+    for (int e = 0; e < kNmsWinMax / 256; ++e) {
+        const int x = e * 256 + tid;
+        pr[e] = x < n ? p[win0 + x] : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < kNmsWinMax / 256; ++e) {
+        const int x = e * 256 + tid;
+        const unsigned long long c = __ballot(x < n && pr[e] > tau);
+        s_p[x] = pr[e];
+        if (lane == 0) { s_und[x >> 6] = c; s_kept[x >> 6] = 0ull; }
+    }
+    __syncthreads();
+    for (;;) {   // every round but the last decides a candidate
+        int decided = 0;
+#pragma unroll
+        for (int e = 0; e < kNmsWinMax / 256; ++e) {
+            const int x = e * 256 + tid;
+            if (x >= n || !((und[x >> 6] >> lane) & 1ull)) continue;
+            const float px = pr[e];
+            bool blocked = (W > x && open_lo) || (W >= n - x && open_hi);   // an unseen neighbour may be better
+            bool removed = false;
+            const int lo = x > W ? x - W : 0, hi = W < n - 1 - x ? x + W : n - 1;
+            for (int w = lo >> 6; w <= hi >> 6 && !removed; ++w) {
+                unsigned long long m = ~0ull;
+                if (w == lo >> 6) m &= ~0ull << (lo & 63);
+                if (w == hi >> 6) m &= ~0ull >> (63 - (hi & 63));
+                unsigned long long u = und[w] & m;
+                removed = (kept[w] & m) != 0ull;      // x is undecided, so a kept neighbour is a better one
+                while (u && !blocked) {
+                    const int y = w * 64 + __builtin_ctzll(u);
+                    u &= u - 1;
+                    const float py = s_p[y];
+                    blocked = py > px || (py == px && y < x);
+                }
+            }
+            if (removed || !blocked) {
+                unsigned *k32 = reinterpret_cast<unsigned *>(s_kept), *u32 = reinterpret_cast<unsigned *>(s_und);
+                if (!removed) atomicOr(&k32[x >> 5], 1u << (x & 31));
+                atomicAnd(&u32[x >> 5], ~(1u << (x & 31)));
+                decided = 1;
+            }
+        }
+        if (!__syncthreads_or(decided)) break;
+    }
+    // states of the segment, four positions per thread; the state array is padded to 256 bytes
+    const int64_t at = seg0 + 4 * tid, st_end = (L + 255) / 256 * 256;
+    if (tid < kNmsSeg / 4 && at < st_end) {
+        const int x = (int)(at - win0);
+        unsigned word = 0u;
+        if (x < n) {                                  // bits past n are clear
+            const unsigned u4 = (unsigned)(s_und[x >> 6] >> (x & 63)) & 15u, k4 = (unsigned)(s_kept[x >> 6] >> (x & 63)) & 15u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) word |= (((u4 >> j) & 1u) * kUndecided | ((k4 >> j) & 1u) * kKept) << (8 * j);
+        }
+        *reinterpret_cast<unsigned *>(st + at) = word;
+    }
+}
+
+constexpr int kNmsPer = 128;                          // positions per thread and slab in the compaction
+constexpr int kNmsStage = 8192;                       // boundaries staged in LDS for coalesced stores
+
+__global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restrict__ p, int64_t L, int W, uint8_t *st,
+                                                            unsigned *bits0, unsigned *bits1, unsigned *bits2,
+                                                            int32_t *__restrict__ B_out,
+                                                            int32_t *__restrict__ N_c_out) {
     __shared__ int s_cnt[kNmsWaves];
     __shared__ int s_und;          // candidates still undecided
     __shared__ int s_any;          // does the next round have a block to visit?
+    __shared__ int s_stage[kNmsStage];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t NB = (L + 63) >> 6, NW = (NB + 31) >> 5;   // 64-position blocks, bitmap words
+    const int64_t n16 = (L + 255) / 256 * 16;                // 16-byte pieces of the state array
     unsigned *dirtyA = bits0, *dirtyB = bits1, *dirtyN = bits2;   // visit now / near a new chunk end / visit next
 
-    // candidates: score strictly above the threshold (a NaN never is); every block is visited in the first pass
+    // how many candidates the windows left undecided (state kUndecided; no other state has been written yet
+    // with its low bit set)
     int und = 0;
-    for (int64_t i = tid; i < L; i += kNmsThreads) {
-        const bool c = p[i] > tau;
-        st[i] = c ? kUndecided : kOut;
-        und += c;
-    }
-    for (int64_t w = tid; w < NW; w += kNmsThreads) { dirtyA[w] = 0xffffffffu; dirtyB[w] = 0u; dirtyN[w] = 0u; }
+    for (int64_t i = tid; i < n16; i += kNmsThreads * 8) {
+        uint4 v[8];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) und += __shfl_xor(und, off);
-    if (lane == 0) s_cnt[wave] = und;
-    __syncthreads();
-    if (tid == 0) {
-        int t = 0;
-        for (int w = 0; w < kNmsWaves; ++w) t += s_cnt[w];
-        s_und = t;
+        for (int e = 0; e < 8; ++e) {
+            const int64_t at = i + (int64_t)e * kNmsThreads;
+            v[e] = at < n16 ? reinterpret_cast<const uint4 *>(st)[at] : uint4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            und += __popc(v[e].x & 0x01010101u) + __popc(v[e].y & 0x01010101u) + __popc(v[e].z & 0x01010101u) +
+                   __popc(v[e].w & 0x01010101u);
     }
-    __syncthreads();
-    int und_now = s_und;           // read between two barriers: nobody changes s_und before the second one,
-    __syncthreads();               // so every thread takes the same decision at the loop head
+    int und_now = __syncthreads_count(und > 0);
+    if (und_now > 0) {             // (the bitmaps serve the rounds only)
+        for (int64_t w = tid; w < NW; w += kNmsThreads) { dirtyA[w] = 0xffffffffu; dirtyB[w] = 0u; dirtyN[w] = 0u; }
+        // a candidate next to a window's border may be undecided there although the window on the other
+        // side of the border has kept a neighbour of it (a better one): it goes first
+        und = 0;
+        for (int64_t i = tid; i < L; i += kNmsThreads) {
+            if (st[i] != kUndecided) continue;
+            const int64_t lo = i - W < 0 ? 0 : i - W, hi = i + W > L - 1 ? L - 1 : i + W;
+            bool hit = false;
+            for (int64_t x = lo; x <= hi && !hit; ++x) hit = st[x] == kKept;
+            if (hit) st[i] = kOut; else ++und;
+        }
+        __threadfence_block();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) und += __shfl_xor(und, off);
+        if (lane == 0) s_cnt[wave] = und;
+        __syncthreads();
+        if (tid == 0) {
+            int t = 0;
+            for (int w = 0; w < kNmsWaves; ++w) t += s_cnt[w];
+            s_und = t;
+        }
+        __syncthreads();
+        und_now = s_und;           // read between two barriers: nobody changes s_und before the second one,
+        __syncthreads();           // so every thread takes the same decision at the loop head
+    }
 
     while (und_now > 0) {
         if (tid == 0) s_any = 0;   // set again only in phase 2, behind the next barrier
@@ -150,12 +274,32 @@ __global__ __launch_bounds__(kNmsThreads) void k_finalize_boundaries(const float
     }
 
     // ---- boundaries in the half-open convention: 0, (kept end + 1) ..., L; ascending ----
-    // consecutive slabs of kNmsThreads positions, exclusive scan of the kept flags within a slab
+    // A thread takes kNmsPer consecutive positions of a slab as one bit each; position L-1 is the end
+    // of the sequence anyway.
     int base = 1;                              // B_out[0] = 0
-    for (int64_t s0 = 0; s0 < L - 1; s0 += kNmsThreads) {   // position L-1 is the end of the sequence anyway
-        const int64_t i = s0 + tid;
-        const int flag = (i < L - 1) && st[i] == kKept;
-        int inc = flag;
+    for (int64_t s0 = 0; s0 < L - 1; s0 += (int64_t)kNmsThreads * kNmsPer) {
+        const int64_t i0 = s0 + (int64_t)tid * kNmsPer;
+        unsigned kb[kNmsPer / 32];
+        int mine = 0;
+        uint4 v[kNmsPer / 16];
+#pragma unroll
+        for (int e = 0; e < kNmsPer / 16; ++e)
+            v[e] = (i0 >> 4) + e < n16 ? reinterpret_cast<const uint4 *>(st + i0)[e] : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < kNmsPer / 32; ++e) {
+            const unsigned w8[8] = {v[2 * e].x, v[2 * e].y, v[2 * e].z, v[2 * e].w,
+                                    v[2 * e + 1].x, v[2 * e + 1].y, v[2 * e + 1].z, v[2 * e + 1].w};
+            kb[e] = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {      // kKept is bit 1 of a state byte: gather four of them
+                const unsigned t = (w8[j] >> 1) & 0x01010101u;
+                kb[e] |= ((t * 0x10204080u) >> 28) << (4 * j);
+            }
+            const int64_t r0 = i0 + 32 * e;
+            if (r0 + 32 > L - 1) kb[e] = r0 < L - 1 ? kb[e] & ((1u << (unsigned)(L - 1 - r0)) - 1u) : 0u;
+            mine += __popc(kb[e]);
+        }
+        int inc = mine;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int t = __shfl_up(inc, off);
@@ -165,12 +309,23 @@ __global__ __launch_bounds__(kNmsThreads) void k_finalize_boundaries(const float
         if (lane == 63) s_cnt[wave] = inc;
         __syncthreads();
         int before = 0, total = 0;
-        for (int w = 0; w < kNmsThreads / 64; ++w) {
+#pragma unroll
+        for (int w = 0; w < kNmsWaves; ++w) {
             const int x = s_cnt[w];
             if (w < wave) before += x;
             total += x;
         }
-        if (flag) B_out[base + before + inc - 1] = (int32_t)(i + 1);
+        const bool stage = total <= kNmsStage;  // through LDS: B_out may be host memory, where scattered stores cost most
+        int at = before + inc - mine;
+#pragma unroll
+        for (int e = 0; e < kNmsPer / 32; ++e)
+            for (unsigned m = kb[e]; m; m &= m - 1u, ++at) {
+                const int32_t b = (int32_t)(i0 + 32 * e + __builtin_ctz(m) + 1);
+                if (stage) s_stage[at] = b; else B_out[base + at] = b;
+            }
+        __syncthreads();
+        if (stage)
+            for (int x = tid; x < total; x += kNmsThreads) B_out[base + x] = s_stage[x];
         base += total;
     }
     if (tid == 0) {
@@ -202,7 +357,13 @@ extern "C" __attribute__((visibility("default"))) dhsa_status dhsa_finalize_boun
     uint8_t *st = (uint8_t *)ws_dev;
     unsigned *bits = (unsigned *)(st + nms_state_bytes(L));
     const int64_t bw = nms_bitmap_bytes(L) / 4;
-    hipLaunchKernelGGL(k_finalize_boundaries, dim3(1), dim3(kNmsThreads), 0, (hipStream_t)stream, scores_dev, L,
-                       threshold, (int)window, st, bits, bits + bw, bits + 2 * bw, B_dev, N_c_dev);
+    // halo: sixteen windows of tokens, where a decision has long been taken in scores that do not rise
+    // monotonically; at least 128 positions (cheap), at most what the LDS arrays hold
+    const int H = (int)std::min<int64_t>(kNmsHaloMax, std::max<int64_t>(128, ((int64_t)window * 16 + 63) / 64 * 64));
+    hipLaunchKernelGGL(k_nms_windows, dim3((unsigned)((L + kNmsSeg - 1) / kNmsSeg)), dim3(256), 0, (hipStream_t)stream,
+                       scores_dev, L, threshold, (int)window, H, st);
+    if (hipGetLastError() != hipSuccess) return DHSA_ERR_HIP;
+    hipLaunchKernelGGL(k_nms_finish, dim3(1), dim3(kNmsThreads), 0, (hipStream_t)stream, scores_dev, L, (int)window, st,
+                       bits, bits + bw, bits + 2 * bw, B_dev, N_c_dev);
     return hipGetLastError() == hipSuccess ? DHSA_OK : DHSA_ERR_HIP;
 }
