@@ -289,8 +289,8 @@ size_t dhsa_mfma_probe_scratch_bytes(void);
  * its block's list at or below the row).  hits_dev[t] = |I* n I_hat|,
  * size_dev[t] = |I*| (device int32[n_rows]); recall = hits / size.
  * plan_dev must come from dhsa_route on the same problem and boundaries.
- * rows_dev_scratch: device int64[n_rows]; ws_dev: device scratch of
- * dhsa_recall_workspace_bytes(prob, n_rows) bytes (8 L per row).  Asynchronous;
+ * rows_dev_scratch: not NULL, not touched (the rows travel as kernel arguments); ws_dev: device
+ * scratch of dhsa_recall_workspace_bytes(prob, n_rows) bytes (8 L per row).  Asynchronous;
  * cost O(L D) per row -- a diagnostic for sampled rows, not a step of the path. */
 dhsa_status dhsa_recall_rows(const dhsa_problem *prob, const void *Q_dev, const void *K_dev,
                              const int32_t *B_host, const void *plan_dev, size_t plan_bytes, int32_t head,

@@ -293,11 +293,10 @@ def dhsa_recall_rows(prob, Q, K, B, plan, head: int, rows) -> Tuple["torch.Tenso
     n = rows.shape[0]
     nb = int(lib().dhsa_recall_workspace_bytes(C.byref(prob), n))
     ws = torch.empty(max(nb, 256), dtype=torch.uint8, device=plan.device)
-    scratch = torch.empty(max(n, 1), dtype=torch.int64, device=plan.device)
     hits = torch.empty(n, dtype=torch.int32, device=plan.device)
     size = torch.empty(n, dtype=torch.int32, device=plan.device)
     _check(lib().dhsa_recall_rows(C.byref(prob), Q.data_ptr(), K.data_ptr(), _bp(B), plan.data_ptr(), plan.numel(),
-                                  head, rows.ctypes.data_as(C.POINTER(C.c_int64)), n, scratch.data_ptr(),
+                                  head, rows.ctypes.data_as(C.POINTER(C.c_int64)), n, ws.data_ptr(),
                                   ws.data_ptr(), ws.numel(), hits.data_ptr(), size.data_ptr(), _stream()))
     return hits, size
 

@@ -506,10 +506,7 @@ __attribute__((visibility("default"))) dhsa_status dhsa_recall_rows(
     if (ws_bytes < dhsa_recall_workspace_bytes(prob, n_rows)) return DHSA_ERR_WORKSPACE;
     if (n_rows == 0) return DHSA_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (hipMemcpyAsync(rows_dev_scratch, rows_host, sizeof(int64_t) * (size_t)n_rows, hipMemcpyHostToDevice, s) !=
-        hipSuccess)
-        return DHSA_ERR_HIP;
-    return hip_status(launch_recall(p, plan_view(p, pl, plan_dev), Q_dev, K_dev, head, rows_dev_scratch, n_rows,
+    return hip_status(launch_recall(p, plan_view(p, pl, plan_dev), Q_dev, K_dev, head, rows_host, n_rows,
                                     static_cast<unsigned long long *>(ws_dev), hits_dev, size_dev, s));
 }
 
