@@ -1,134 +1,280 @@
-// Sparse attention kernels of libdhsa: exact softmax attention over the keys
+// fp32 sparse attention kernel of libdhsa: exact softmax attention over the keys
 // the routing plan selects (Alg. 2 / Alg. 3 of the paper, App. C "Backend
-// implementations").  This file: k_attn_rowwise, fp32 arithmetic, one wavefront
-// per query row (the DHSA_F32 path).  The bf16 MFMA kernel is in attn_mfma.hip.
+// implementations") for DHSA_F32 inputs, fp32 throughout.  The bf16 kernel is in
+// attn_mfma.hip.
+//
+// Work unit: (query head, 16 RW consecutive rows of one row tile of the plan).  Four
+// waves; each owns every fourth block of 16 selected keys and all rows, and the
+// waves merge their softmax states at the end, so the loop over the keys has no
+// barrier and K / V go from memory straight into registers.
+//
+// v_mfma_f32_16x16x4_f32 (full fp32 products and sums).  Lane l = 16 q + n.
+// S^T (16 keys x 16 rows) += K (16 x 4) Q^T (4 x 16): the lane supplies K of key n and
+// Q of row n at d = 16 s + 4 q + j (step j of the group s: the contraction index may
+// be any order of d, this one makes both operands 16-byte loads) and receives the
+// scores of row n against keys 4 q + {0..3}, which are the B operand of
+// O^T (16 d x 16 rows) += V^T (16 x 4) P^T (4 x 16) when step i contracts the keys
+// {4 q + i : q}.  V^T of step i: 16 bytes at d = 64 t + 4 n of key 4 q + i, one element
+// for each of four output blocks (block (t, j) holds d = 64 t + 4 M + j in row M).
+//
+// Bound by the fp32 rate of the matrix unit once the chip is full; small problems by
+// the chain of loads before the first product (plan, boundaries, keys).  L = 2048, four
+// heads of D = 64, N_b = 256: 18 us; 135 us with one wave per row (no reuse of K and V, products on
+// the vector unit, one key of V at a time).
 #include "dhsa_internal.h"
 
 namespace dhsa {
 
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// ---------------------------------------------------------------------------
-// Row-wise fp32 kernel.  Each wave owns one query row: lanes compute the scores
-// of 64 selected keys at a time (online softmax over batches, Alg. 3 with
-// B_r = 1, B_c = 64), then lanes own output columns for the PV sum.
-// ---------------------------------------------------------------------------
-template <typename T> struct RowIO;
-template <> struct RowIO<float> {
-    static constexpr int kPer16 = 4;
-    __device__ static float dot16(const uint4 &u, const float *q) {
-        return __uint_as_float(u.x) * q[0] + __uint_as_float(u.y) * q[1] + __uint_as_float(u.z) * q[2] +
-               __uint_as_float(u.w) * q[3];
-    }
-    __device__ static float load(const float *p) { return *p; }
-    __device__ static void store(float *p, float x) { *p = x; }
-};
-template <> struct RowIO<bf16_t> {
-    static constexpr int kPer16 = 8;
-    __device__ static float dot16(const uint4 &u, const float *q) {
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            s += __uint_as_float(w[i] << 16) * q[2 * i] + __uint_as_float(w[i] & 0xffff0000u) * q[2 * i + 1];
-        return s;
-    }
-    __device__ static float load(const bf16_t *p) { return bf16_to_f32(p->bits); }
-    __device__ static void store(bf16_t *p, float x) {
-        uint32_t u = __float_as_uint(x);
-        u += 0x7fffu + ((u >> 16) & 1u);
-        p->bits = (uint16_t)(u >> 16);
-    }
-};
+constexpr int kF32Keys = 1024;   // selected keys whose positions and masks are in LDS at a time
+constexpr int kF32Seg = 256;     // plan entries per batch
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void k_attn_rowwise(PlanView pv, const T *__restrict__ Q,
-                                                      const T *__restrict__ K, const T *__restrict__ V,
-                                                      T *__restrict__ O, int64_t L, int G, float scale,
-                                                      int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
-                                                      int64_t vs_h, int64_t vs_l, int64_t os_h, int64_t os_l) {
-    constexpr int EP = RowIO<T>::kPer16;
-    constexpr int NC = D / 64;  // output columns per lane
-    __shared__ float s_q[4][D];
+template <int D, int RW>
+__global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *__restrict__ Q,
+                                                     const float *__restrict__ K, const float *__restrict__ V,
+                                                     float *__restrict__ O, int H_q, int G, float scale_log2e,
+                                                     int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
+                                                     int64_t vs_h, int64_t vs_l, int64_t os_h, int64_t os_l) {
+    constexpr int NR = 16 * RW;      // rows of the workgroup
+    constexpr int NS = D / 16;       // 16-byte pieces of a K / Q row per lane
+    constexpr int NT = D / 64;
+    constexpr int kPad = D + 4;
+    struct Lists {
+        int key[kF32Keys], lo[kF32Keys], hi[kF32Keys];           // a row takes the key iff lo < v < hi
+        int start[kF32Seg + 1], b0[kF32Seg], pos[kF32Seg], rem[kF32Seg];
+        int wave[8];
+    };
+    struct Merge {
+        float o[4][NR][kPad];
+        float m[4][NR], l[4][NR];
+    };
+    __shared__ __align__(16) union { Lists li; Merge me; } sm;
     if (!plan_matches(pv)) return;   // not this problem's plan: O is not written
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = blockIdx.y, g = h / G;
-    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
-    const bool live = i < L;
-    if (live)
-        for (int d = lane; d < D; d += 64) s_q[wave][d] = RowIO<T>::load(Q + (int64_t)h * qs_h + i * qs_l + d);
-    __syncthreads();
-    if (!live) return;
-    const T *Kg = K + (int64_t)g * ks_h;
-    const T *Vg = V + (int64_t)g * vs_h;
-    const int l = chunk_of_row(pv.RB, pv.N_q, i);   // the row's query group
-    const int v = (int)(i + 1 - pv.RB[l]);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, q4 = lane >> 4;
+
+    // blockIdx -> (head, tile, piece of the tile): a tile of class c has at most 4 - c pieces of 32 rows; the
+    // latest rows (most keys) of each class first
+    const int h = blockIdx.x % H_q, g = h / G;
+    int b = blockIdx.x / H_q, tile = 0, piece = 0;
+    {
+        int first = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int pieces = (4 - c) * 32 / NR, T = pv.T_cls[c];
+            if (b >= 0 && b < T * pieces) { tile = first + T - 1 - b / pieces; piece = b % pieces; }
+            b -= T * pieces;
+            first += T;
+        }
+    }
+    const int l = pv.tiles[2 * tile];
+    const int row0 = pv.tiles[2 * tile + 1] + piece * NR;
+    const int b_l = pv.RB[l], tile_end = pv.tiles[2 * tile + 1] + kRowTile;
+    const int end = pv.RB[l + 1] < tile_end ? pv.RB[l + 1] : tile_end;
+    const int nrows = end - row0 < NR ? end - row0 : NR;
+    if (nrows <= 0) return;          // the tile has fewer pieces than its class allows
+    const int v_lo = row0 + 1 - b_l, v_hi = v_lo + nrows - 1;
     const int E = pv.count[(int64_t)h * pv.N_q + l];
     const int32_t *ent = pv.entries + ((int64_t)h * pv.N_q + l) * pv.stride * 2;
-    float m_run = -INFINITY, l_lane = 0.f;
-    float o[NC];
+    const float *Kg = K + (int64_t)g * ks_h + 4 * q4;
+    const float *Vg = V + (int64_t)g * vs_h + 4 * n16;
+
+    // rows past the end repeat the last one (never stored)
+    f32x4 qf[RW][NS], oacc[RW][NT][4];
+    int v_i[RW];
+    float m[RW], lsum[RW];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) o[c] = 0.f;
-    for (int e = 0; e < E; ++e) {
-        const int w0 = ent[2 * e], rem = ent[2 * e + 1];
-        const int k = w0 & kChunkMask, pos = w0 >> kPosShift;
-        const int b0 = pv.B[k];
-        int take = entry_take(pos, rem, pv.B[k + 1] - b0, v);
-        if (pos == 3) {   // row-block form: of the block's list, the keys up to the row itself
-            const int64_t vis = i + 1 - b0;
-            if (vis < take) take = vis > 0 ? (int)vis : 0;
+    for (int r = 0; r < RW; ++r) {
+        const int row = 16 * r + n16 < nrows ? 16 * r + n16 : nrows - 1;
+        const float *qp = Q + (int64_t)h * qs_h + (int64_t)(row0 + row) * qs_l + 4 * q4;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) qf[r][s] = *reinterpret_cast<const f32x4 *>(qp + 16 * s);
+        v_i[r] = v_lo + row;
+        m[r] = -INFINITY;
+        lsum[r] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) oacc[r][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    for (int e0 = 0; e0 < E; e0 += kF32Seg) {
+        // segments (entries some row takes a key from) of this batch, compacted
+        int n_e = 0, b0_e = 0, pos_e = 0, rem_e = 0;
+        if (e0 + tid < E) {
+            const int w0 = ent[2 * (e0 + tid)];
+            rem_e = ent[2 * (e0 + tid) + 1];
+            const int k = w0 & kChunkMask;
+            pos_e = w0 >> kPosShift;
+            b0_e = pv.B[k];
+            n_e = entry_take(pos_e, rem_e, pv.B[k + 1] - b0_e, pos_e == 1 ? v_hi : v_lo);
+            if (pos_e == 3) {        // row-block form: keys past the last row are dropped
+                const int vis = row0 + nrows - b0_e;
+                n_e = vis < n_e ? (vis > 0 ? vis : 0) : n_e;
+            }
         }
-        for (int t0 = 0; t0 < take; t0 += 64) {
-            const int nv = (take - t0 < 64) ? take - t0 : 64;
-            float s = -INFINITY;
-            if (lane < nv) {
-                const T *kr = Kg + (int64_t)(b0 + t0 + lane) * ks_l;
-                float acc = 0.f;
-#pragma unroll
-                for (int d = 0; d < D; d += EP)
-                    acc += RowIO<T>::dot16(*reinterpret_cast<const uint4 *>(kr + d), &s_q[wave][d]);
-                s = acc * scale;
+        int total, nseg, start, slot;
+        block_excl_scan2(n_e, n_e > 0 ? 1 : 0, sm.li.wave, &start, &slot, &total, &nseg);
+        if (n_e > 0) {
+            sm.li.start[slot] = start;
+            sm.li.b0[slot] = b0_e;
+            sm.li.pos[slot] = pos_e;
+            sm.li.rem[slot] = rem_e;
+        }
+        if (tid == 0) sm.li.start[nseg] = total;
+        for (int x0 = 0; x0 < total; x0 += kF32Keys) {
+            const int nk = total - x0 < kF32Keys ? total - x0 : kF32Keys;
+            const int nb = (nk + 15) >> 4;
+            __syncthreads();         // the segment table is complete; the last window's lists are done with
+            for (int sg = wave; sg < nseg; sg += 4) {
+                const int st = sm.li.start[sg], en = sm.li.start[sg + 1];
+                const int lo = st > x0 ? st : x0, hi = en < x0 + nk ? en : x0 + nk;
+                if (lo >= hi) continue;
+                const int b0 = sm.li.b0[sg], pos = sm.li.pos[sg], rem = sm.li.rem[sg];
+                for (int x = lo + lane; x < hi; x += 64) {
+                    const int t = x - st, j = b0 + t;
+                    sm.li.key[x - x0] = j;
+                    // key j is at or below row i  <=>  j - b_l < v: the group's own chunk (pos 1) and every
+                    // listed key of the row-block form (pos 3)
+                    sm.li.lo[x - x0] = (pos & 1) ? (j > b_l ? j - b_l : 0) : 0;
+                    sm.li.hi[x - x0] = (pos == 2) ? rem - t : 0x7fffffff;
+                }
             }
-            float mx = s;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-            const float m_new = fmaxf(m_run, mx);  // finite: nv >= 1
-            const float alpha = __expf(m_run - m_new);
-            const float p = (lane < nv) ? __expf(s - m_new) : 0.f;
-            l_lane = l_lane * alpha + p;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) o[c] *= alpha;
-            for (int jj = 0; jj < nv; ++jj) {
-                const float pj = __shfl(p, jj);
-                const T *vr = Vg + (int64_t)(b0 + t0 + jj) * vs_l;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) o[c] += pj * RowIO<T>::load(vr + lane + 64 * c);
+            for (int x = nk + tid; x < nb * 16; x += 256) {   // padding: a row that exists, taken by nobody
+                sm.li.key[x] = row0;
+                sm.li.lo[x] = 0x7fffffff;
+                sm.li.hi[x] = 0x7fffffff;
             }
-            m_run = m_new;
+            __syncthreads();
+
+            f32x4 kf[NS], vf[4][NT];
+#define DHSA_F32_K(kb)                                                                                       \
+    {                                                                                                        \
+        const float *kp_ = Kg + (int64_t)sm.li.key[(kb) * 16 + n16] * ks_l;                                  \
+        _Pragma("unroll") for (int s = 0; s < NS; ++s) kf[s] = *reinterpret_cast<const f32x4 *>(kp_ + 16 * s); \
+    }
+#define DHSA_F32_V(kb)                                                                                       \
+    {                                                                                                        \
+        const int4 j_ = *reinterpret_cast<const int4 *>(&sm.li.key[(kb) * 16 + 4 * q4]);                     \
+        const int jj_[4] = {j_.x, j_.y, j_.z, j_.w};                                                         \
+        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                        \
+            _Pragma("unroll") for (int t = 0; t < NT; ++t)                                                   \
+                vf[i][t] = *reinterpret_cast<const f32x4 *>(Vg + (int64_t)jj_[i] * vs_l + 64 * t);           \
+    }
+            if (wave < nb) { DHSA_F32_K(wave); DHSA_F32_V(wave); }
+            for (int kb = wave; kb < nb; kb += 4) {
+                f32x4 s[RW];
+#pragma unroll
+                for (int r = 0; r < RW; ++r) s[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < NS; ++c)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int r = 0; r < RW; ++r)
+                            s[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j], qf[r][c][j], s[r], 0, 0, 0);
+                if (kb + 4 < nb) DHSA_F32_K(kb + 4);        // lands while this block is finished
+                const int4 lo = *reinterpret_cast<const int4 *>(&sm.li.lo[kb * 16 + 4 * q4]);
+                const int4 hi = *reinterpret_cast<const int4 *>(&sm.li.hi[kb * 16 + 4 * q4]);
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    s[r][0] = ((v_i[r] > lo.x) & (v_i[r] < hi.x)) ? s[r][0] : -INFINITY;
+                    s[r][1] = ((v_i[r] > lo.y) & (v_i[r] < hi.y)) ? s[r][1] : -INFINITY;
+                    s[r][2] = ((v_i[r] > lo.z) & (v_i[r] < hi.z)) ? s[r][2] : -INFINITY;
+                    s[r][3] = ((v_i[r] > lo.w) & (v_i[r] < hi.w)) ? s[r][3] : -INFINITY;
+                    float mx = fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3]));
+                    mx = fmaxf(mx, __shfl_xor(mx, 16));     // the four lanes of a row
+                    mx = fmaxf(mx, __shfl_xor(mx, 32));
+                    if (__any(mx > m[r])) {
+                        const float m_new = fmaxf(m[r], mx);
+                        const float alpha = m[r] == -INFINITY ? 0.f
+                                            : __builtin_amdgcn_exp2f((m[r] - m_new) * scale_log2e);
+                        lsum[r] *= alpha;
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) oacc[r][t][j] *= alpha;
+                        m[r] = m_new;
+                    }
+                    const float ref = m[r] == -INFINITY ? 0.f : m[r];   // no key seen yet: every p is 0
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        s[r][i] = __builtin_amdgcn_exp2f((s[r][i] - ref) * scale_log2e);
+                        lsum[r] += s[r][i];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int r = 0; r < RW; ++r)
+                                oacc[r][t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][t][j], s[r][i], oacc[r][t][j],
+                                                                                     0, 0, 0);
+                if (kb + 4 < nb) DHSA_F32_V(kb + 4);
+            }
+#undef DHSA_F32_K
+#undef DHSA_F32_V
         }
     }
-    float lsum = l_lane;
+
+    // ---- merge of the four waves, normalisation, store ----
+    __syncthreads();                 // the lists are dead
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;   // a row that sees no key of its block's list: zeros
+    for (int r = 0; r < RW; ++r) {
+        lsum[r] += __shfl_xor(lsum[r], 16);
+        lsum[r] += __shfl_xor(lsum[r], 32);
+        if (q4 == 0) {
+            sm.me.m[wave][16 * r + n16] = m[r];
+            sm.me.l[wave][16 * r + n16] = lsum[r];
+        }
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-        RowIO<T>::store(O + (int64_t)h * os_h + i * os_l + lane + 64 * c, o[c] * inv);
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                *reinterpret_cast<f32x4 *>(&sm.me.o[wave][16 * r + n16][64 * t + 16 * q4 + 4 * x]) =
+                    f32x4{oacc[r][t][0][x], oacc[r][t][1][x], oacc[r][t][2][x], oacc[r][t][3][x]};
+    }
+    __syncthreads();
+    for (int x = tid; x < nrows * (D / 4); x += 256) {
+        const int r = x / (D / 4), d = (x % (D / 4)) * 4;
+        float M = sm.me.m[0][r];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) M = fmaxf(M, sm.me.m[w][r]);
+        float L = 0.f;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float mw = sm.me.m[w][r];
+            const float a = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - M) * scale_log2e);
+            L += sm.me.l[w][r] * a;
+            acc += *reinterpret_cast<const f32x4 *>(&sm.me.o[w][r][d]) * a;
+        }
+        const float inv = L > 0.f ? 1.f / L : 0.f;   // a row that sees no key of its block's list: zeros
+        *reinterpret_cast<f32x4 *>(O + (int64_t)h * os_h + (int64_t)(row0 + r) * os_l + d) = acc * inv;
+    }
 }
 
-hipError_t launch_attn_rowwise(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
-                               void *O, hipStream_t s) {
-    dim3 grid((unsigned)((p.L + 3) / 4), p.H_q), block(256);
-#define DHSA_ROWWISE(T, DD)                                                                                  \
-    hipLaunchKernelGGL((k_attn_rowwise<T, DD>), grid, block, 0, s, pv, (const T *)Q, (const T *)K,           \
-                       (const T *)V, (T *)O, p.L, p.G, p.scale, p.qs_h, p.qs_l, p.ks_h, p.ks_l,              \
-                       p.vs_h, p.vs_l, p.os_h, p.os_l)
-    if (p.dtype == DHSA_F32) {
-        if (p.D == 64) DHSA_ROWWISE(float, 64); else DHSA_ROWWISE(float, 128);
+hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V, void *O,
+                           hipStream_t s) {
+    // 32 rows per workgroup read K and V half as often as 16; while that leaves CUs with fewer than two
+    // workgroups, 16-row ones fill the chip better and waste less on the last rows of a tile
+    const int64_t wg32 = (int64_t)p.H_q * (4 * (int64_t)pv.T_cls[0] + 3 * pv.T_cls[1] + 2 * pv.T_cls[2] + pv.T_cls[3]);
+    const bool small = wg32 < 512;
+    const dim3 grid((unsigned)(small ? 2 * wg32 : wg32)), block(256);
+#define DHSA_F32_ATTN(DD, RW)                                                                                 \
+    hipLaunchKernelGGL((k_attn_f32<DD, RW>), grid, block, 0, s, pv, (const float *)Q, (const float *)K,       \
+                       (const float *)V, (float *)O, p.H_q, p.G, p.scale * 1.4426950408889634f, p.qs_h, p.qs_l, \
+                       p.ks_h, p.ks_l, p.vs_h, p.vs_l, p.os_h, p.os_l)
+    if (p.D == 64) {
+        if (small) DHSA_F32_ATTN(64, 1); else DHSA_F32_ATTN(64, 2);
     } else {
-        if (p.D == 64) DHSA_ROWWISE(bf16_t, 64); else DHSA_ROWWISE(bf16_t, 128);
+        if (small) DHSA_F32_ATTN(128, 1); else DHSA_F32_ATTN(128, 2);
     }
-#undef DHSA_ROWWISE
+#undef DHSA_F32_ATTN
     return hipGetLastError();
 }
 

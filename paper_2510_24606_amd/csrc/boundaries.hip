@@ -19,8 +19,8 @@
 //     sequence -- long monotone runs, windows of more tokens than the halo has --
 //     and compacts the kept positions into B.
 //
-// Bound by latency (0.5 MB of scores at L = 131072): 1.1 ms when one workgroup
-// did all of it in rounds from memory.
+// Bound by latency (0.5 MB of scores at L = 131072): 9 + 10 us, against 1.1 ms when one
+// workgroup did all of it in rounds from memory.
 //
 // Rounds of k_nms_finish: a still undecided candidate that is
 // better than every undecided candidate within W tokens is kept (nothing can

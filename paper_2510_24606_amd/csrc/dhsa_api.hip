@@ -219,7 +219,7 @@ dhsa_status attend_impl(const Prob &p, const PlanLayout &pl, const void *Q, cons
                         const void *plan, void *O, hipStream_t s, hipEvent_t *ev = nullptr) {
     const PlanView pv = plan_view(p, pl, plan);
     if (p.dtype == DHSA_BF16) return hip_status(launch_attn_mfma(p, pv, Q, K, V, O, s, ev));
-    hipError_t e = launch_attn_rowwise(p, pv, Q, K, V, O, s);
+    hipError_t e = launch_attn_f32(p, pv, Q, K, V, O, s);
     for (int i = 0; ev && i < 3 && e == hipSuccess; ++i) e = hipEventRecord(ev[i], s);
     return hip_status(e);
 }

@@ -113,7 +113,7 @@ hipError_t launch_expand(const Prob &p, const PlanView &pv, int head, const int6
 hipError_t launch_recall(const Prob &p, const PlanView &pv, const void *Q, const void *K, int head,
                          const int64_t *rows_host, int n_rows, unsigned long long *ws, int32_t *hits, int32_t *size,
                          hipStream_t s);
-hipError_t launch_attn_rowwise(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
+hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
                                void *O, hipStream_t s);
 // ev (may be null): three events recorded after the launches of the tiles of more than 64 rows, of
 // 33..64 rows and of at most 32 rows

@@ -45,3 +45,27 @@ def test_recall_row_groups_ties_and_candidate_list(L, D, dtype, n_rows, integers
     h_ref, s_ref = oracle.recall_rows(Qh.float().numpy(), Kh.float().numpy(), w.B, w.N_b, 1, rows)
     np.testing.assert_array_equal(hits.cpu().numpy(), h_ref)
     np.testing.assert_array_equal(size.cpu().numpy(), s_ref)
+
+
+@pytest.mark.parametrize("L,H_q,D,N_b,lens,B_r", [(700, 2, 64, 90, ("uniform", 1, 20), 0),          # 16-row pieces
+                                                  (1500, 1, 128, 1400, ("uniform", 100, 300), 0),   # > 1024 listed keys
+                                                  (4100, 8, 64, 500, ("uniform", 90, 160), 0),      # 32-row pieces
+                                                  (4100, 8, 128, 300, ("fixed", 1), 0),             # > 256 plan entries
+                                                  (4100, 8, 128, 1100, ("uniform", 16, 64), 97),
+                                                  (900, 2, 64, 3, ("uniform", 16, 64), 128)])       # rows without a key
+def test_f32_pieces_lists_and_batches(L, H_q, D, N_b, lens, B_r):
+    w = dhsa_inputs.make("c1", L=L, H_q=H_q, H_kv=1, D=D, N_b=N_b, lens=lens)
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    O = torch.full_like(Q, float("nan"))
+    prob = dhsa.problem(Q, K, w.B, w.N_b, B_r=B_r)
+    plan, ws = dhsa.alloc(prob, w.B)
+    dhsa.dhsa_prefill(prob, Q, K, V, w.B, O, plan, ws)
+    rows = np.arange(0, L, 1 if L < 2000 else 5, dtype=np.int64)
+    f32 = [w.f32(x) for x in "QKV"]
+    if B_r:
+        ref = oracle.prefill_rows_blocks(*f32, w.B, B_r, w.N_b, rows)[0]
+    else:
+        ref = oracle.prefill_rows(*f32, w.B, w.N_b, rows)[0]
+    assert torch.isfinite(O).all()
+    err = np.abs(O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64) - ref).max()
+    assert err <= 1e-5, err
