@@ -193,16 +193,13 @@ PlanView plan_view(const Prob &p, const PlanLayout &pl, const void *plan) {
 
 dhsa_status hip_status(hipError_t e) { return e == hipSuccess ? DHSA_OK : DHSA_ERR_HIP; }
 
-// ev (may be null): events recorded after set-up, pooling, scores and ranking
+// ev (may be null): events recorded after the boundaries, set-up and pooling, scores and ranking
 dhsa_status route_impl(const Prob &p, const PlanLayout &pl, const WsLayout &wl, const void *Q, const void *K,
                        const int32_t *B_host, void *plan, void *ws, hipStream_t s, hipEvent_t *ev = nullptr) {
     int32_t *pw = static_cast<int32_t *>(plan);
     double *wd = static_cast<double *>(ws);
     // the boundaries travel as kernel arguments: no copy from (pageable) host memory, nothing that can wait
-    if (launch_put_boundaries(B_host, p.N_c + 1, pw + pl.off_B, s) != hipSuccess) return DHSA_ERR_HIP;
-    if (launch_setup(p, pl, pw, s) != hipSuccess) return DHSA_ERR_HIP;
-    if (ev && hipEventRecord(ev[0], s) != hipSuccess) return DHSA_ERR_HIP;
-    if (launch_pool(p, Q, K, pw + pl.off_B, pw + pl.off_RB, wd + wl.off_Qc, wd + wl.off_Kc, s) != hipSuccess)
+    if (launch_setup_pool(p, pl, Q, K, B_host, pw, wd + wl.off_Qc, wd + wl.off_Kc, s, ev) != hipSuccess)
         return DHSA_ERR_HIP;
     if (ev && hipEventRecord(ev[1], s) != hipSuccess) return DHSA_ERR_HIP;
     if (launch_scores(p, wd + wl.off_Qc, wd + wl.off_Kc, pw + pl.off_B, pw + pl.off_RB, wd + wl.off_Sc, s) !=

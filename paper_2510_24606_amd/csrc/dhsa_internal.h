@@ -92,9 +92,9 @@ struct BoundaryBlock {
 // ---- launchers (each enqueues on `s` and returns the launch status) ----
 // B_host[0 .. n) -> B_dev, carried by kernel arguments (no copy engine, no staging buffer)
 hipError_t launch_put_boundaries(const int32_t *B_host, int n, int32_t *B_dev, hipStream_t s);
-hipError_t launch_setup(const Prob &p, const PlanLayout &pl, int32_t *plan, hipStream_t s);
-hipError_t launch_pool(const Prob &p, const void *Q, const void *K, const int32_t *B_dev, const int32_t *RB_dev,
-                       double *Qc, double *Kc, hipStream_t s);
+// boundaries and plan set-up, pooled vectors; ev (may be null): an event recorded before the pooling kernel
+hipError_t launch_setup_pool(const Prob &p, const PlanLayout &pl, const void *Q, const void *K, const int32_t *B_host,
+                             int32_t *plan, double *Qc, double *Kc, hipStream_t s, hipEvent_t *ev);
 hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, const int32_t *B_dev,
                          const int32_t *RB_dev, double *Sc, hipStream_t s);
 hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, hipStream_t s);

@@ -5,122 +5,17 @@
 // All routing arithmetic is fp64: pooled sums of bf16 inputs are then exact
 // (order-free), and S_c carries ~1e-14 absolute error, so the ranking does not
 // hinge on summation order.
+#include <string.h>
+
 #include <algorithm>
+#include <type_traits>
+
 #include "dhsa_internal.h"
 
 namespace dhsa {
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-// ---------------------------------------------------------------------------
-// Plan header, query-group boundaries and row-tile table.  One block; B is
-// already in the plan.  The query groups are the chunks themselves, or (Alg. 1
-// as printed) row blocks of B_r rows, RB[i] = min(i B_r, L).  Tiles are the
-// <= 128-row pieces of the query groups; the table lists them by class -- more
-// than 96 rows, 65..96, 33..64, at most 32 -- each class ordered by row.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_setup(int32_t *__restrict__ plan, PlanLayout pl, int H_q, int H_kv, int D,
-                                               int N_c, int N_b, int64_t L, int B_r, int pooling) {
-    __shared__ int s_n[4][256];    // tiles of each class per query group of the slab (scanned in place)
-    __shared__ int s_carry[4];
-    const int tid = threadIdx.x;
-    const int N_q = pl.N_q;
-    int32_t *tiles = plan + pl.off_tiles;
-    if (B_r > 0) {
-        int32_t *RBw = plan + pl.off_RB;
-        for (int i = tid; i <= N_q; i += 256) {
-            const int64_t b = (int64_t)i * B_r;
-            RBw[i] = (int32_t)(b < L ? b : L);
-        }
-        __syncthreads();
-    }
-    const int32_t *B = plan + pl.off_RB;   // the boundaries the rows are grouped by
-    if (tid < kPlanHeaderWords) {
-        int32_t w = 0;
-        switch (tid) {
-            case 0: w = DHSA_PLAN_MAGIC; break;
-            case 1: w = DHSA_PLAN_VERSION; break;
-            case 2: w = H_q; break;
-            case 3: w = N_c; break;
-            case 4: w = N_b; break;
-            case 5: w = pl.stride; break;
-            case 6: w = (int32_t)L; break;
-            case 7: w = pl.T1; break;
-            case 8: w = (int32_t)pl.off_B; break;
-            case 9: w = (int32_t)pl.off_count; break;
-            case 10: w = (int32_t)pl.off_entries; break;
-            case 11: w = (int32_t)pl.off_tiles; break;
-            case 12: w = pl.T_big; break;
-            case 13: w = (int32_t)pl.off_RB; break;
-            case 14: w = N_q; break;
-            case 15: w = B_r; break;
-            case 16: w = pooling; break;
-            case 17: w = pl.b_sum; break;
-            case 18: w = H_kv; break;
-            case 19: w = D; break;
-            case 20: case 21: case 22: case 23: w = pl.T_cls[tid - 20]; break;
-            default: break;
-        }
-        plan[tid] = w;
-    }
-    if (tid == 0) {   // where each class starts in the table
-        s_carry[0] = 0;
-        s_carry[1] = pl.T_cls[0];
-        s_carry[2] = pl.T_cls[0] + pl.T_cls[1];
-        s_carry[3] = pl.T_cls[0] + pl.T_cls[1] + pl.T_cls[2];
-    }
-    __syncthreads();
-    for (int base = 0; base < N_q; base += 256) {
-        const int l = base + tid;
-        int b0 = 0, nfull = 0, rem = 0;
-        if (l < N_q) {
-            b0 = B[l];
-            const int len = B[l + 1] - b0;
-            nfull = len / kRowTile;
-            rem = len % kRowTile;
-        }
-        const int rem_cls = rem > 0 ? tile_class(rem) : -1;
-        int mine[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            mine[c] = (c == 0 ? nfull : 0) + (rem_cls == c);
-            s_n[c][tid] = mine[c];
-        }
-        __syncthreads();
-        // Hillis-Steele inclusive scans over the 256 slab entries
-        for (int off = 1; off < 256; off <<= 1) {
-            int v[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = (tid >= off) ? s_n[c][tid - off] : 0;
-            __syncthreads();
-#pragma unroll
-            for (int c = 0; c < 4; ++c) s_n[c][tid] += v[c];
-            __syncthreads();
-        }
-        int at = s_carry[0] + s_n[0][tid] - mine[0];
-        for (int t = 0; t < nfull; ++t) {
-            tiles[2 * (at + t)] = l;
-            tiles[2 * (at + t) + 1] = b0 + t * kRowTile;
-        }
-        if (rem_cls >= 0) {
-            at = s_carry[rem_cls] + s_n[rem_cls][tid] - 1;
-            tiles[2 * at] = l;
-            tiles[2 * at + 1] = b0 + nfull * kRowTile;
-        }
-        __syncthreads();
-        if (tid == 255) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) s_carry[c] += s_n[c][255];
-        }
-        __syncthreads();
-    }
-}
-
-hipError_t launch_setup(const Prob &p, const PlanLayout &pl, int32_t *plan, hipStream_t s) {
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, s, plan, pl, p.H_q, p.H_kv, p.D, p.N_c, p.N_b, p.L, p.B_r,
-                       p.pooling);
-    return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------
 // Boundaries into the plan without a copy from host memory: each launch carries
@@ -130,13 +25,17 @@ __global__ __launch_bounds__(256) void k_put_boundaries(int32_t *__restrict__ ds
     for (int i = threadIdx.x; i < blk.n; i += 256) dst[blk.first + i] = blk.b[i];
 }
 
+static void fill_block(BoundaryBlock &blk, const int32_t *B_host, int first, int n) {
+    blk.first = first;
+    blk.n = std::min(kBoundaryBlockMax, n - first);
+    memcpy(blk.b, B_host + first, sizeof(int32_t) * (size_t)blk.n);
+    memset(blk.b + blk.n, 0, sizeof(int32_t) * (size_t)(kBoundaryBlockMax - blk.n));
+}
+
 hipError_t launch_put_boundaries(const int32_t *B_host, int n, int32_t *B_dev, hipStream_t s) {
     BoundaryBlock blk;
     for (int first = 0; first < n; first += kBoundaryBlockMax) {
-        blk.first = first;
-        blk.n = std::min(kBoundaryBlockMax, n - first);
-        for (int i = 0; i < blk.n; ++i) blk.b[i] = B_host[first + i];
-        for (int i = blk.n; i < kBoundaryBlockMax; ++i) blk.b[i] = 0;
+        fill_block(blk, B_host, first, n);
         hipLaunchKernelGGL(k_put_boundaries, dim3(1), dim3(256), 0, s, B_dev, blk);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -144,40 +43,154 @@ hipError_t launch_put_boundaries(const int32_t *B_host, int n, int32_t *B_dev, h
     return hipSuccess;
 }
 
+// What the set-up block writes beside the boundaries.
+struct SetupArgs {
+    int32_t *plan;
+    PlanLayout pl;
+    int H_q, H_kv, D, N_c, N_b, B_r, pooling;
+    int64_t L;
+};
+
 // ---------------------------------------------------------------------------
-// Chunk pooling, Eq. 4: X_c[h, k, :] = (sqrt(len)/len) * sum_{i in chunk k} X[h, i, :].
+// Plan header, query-group boundaries and row-tile table, by one block.  The query
+// groups are the chunks themselves, or (Alg. 1 as printed) row blocks of B_r rows,
+// RB[i] = min(i B_r, L).  Tiles are the <= 128-row pieces of the query groups; the
+// table lists them by class -- more than 96 rows, 65..96, 33..64, at most 32 --
+// each class ordered by row.  B: the key chunk boundaries, wherever they are.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void setup_block(const SetupArgs &a, const int32_t *B) {
+    __shared__ int s_wave8[8];
+    const int tid = threadIdx.x;
+    const PlanLayout &pl = a.pl;
+    const int N_q = pl.N_q;
+    int32_t *tiles = a.plan + pl.off_tiles;
+    int32_t *RBw = a.plan + pl.off_RB;
+    if (tid < kPlanHeaderWords) {
+        int32_t w = 0;
+        switch (tid) {
+            case 0: w = DHSA_PLAN_MAGIC; break;
+            case 1: w = DHSA_PLAN_VERSION; break;
+            case 2: w = a.H_q; break;
+            case 3: w = a.N_c; break;
+            case 4: w = a.N_b; break;
+            case 5: w = pl.stride; break;
+            case 6: w = (int32_t)a.L; break;
+            case 7: w = pl.T1; break;
+            case 8: w = (int32_t)pl.off_B; break;
+            case 9: w = (int32_t)pl.off_count; break;
+            case 10: w = (int32_t)pl.off_entries; break;
+            case 11: w = (int32_t)pl.off_tiles; break;
+            case 12: w = pl.T_big; break;
+            case 13: w = (int32_t)pl.off_RB; break;
+            case 14: w = N_q; break;
+            case 15: w = a.B_r; break;
+            case 16: w = a.pooling; break;
+            case 17: w = pl.b_sum; break;
+            case 18: w = a.H_kv; break;
+            case 19: w = a.D; break;
+            case 20: case 21: case 22: case 23: w = pl.T_cls[tid - 20]; break;
+            default: break;
+        }
+        a.plan[tid] = w;
+    }
+    // where each class continues in the table (the same in every thread)
+    int at[4] = {0, pl.T_cls[0], pl.T_cls[0] + pl.T_cls[1], pl.T_cls[0] + pl.T_cls[1] + pl.T_cls[2]};
+    for (int base = 0; base < N_q; base += 256) {
+        const int l = base + tid;
+        int b0 = 0, nfull = 0, rem = 0;
+        if (l < N_q) {
+            int b1;
+            if (a.B_r > 0) {
+                const int64_t x0 = (int64_t)l * a.B_r, x1 = x0 + a.B_r;
+                b0 = (int32_t)x0;
+                b1 = (int32_t)(x1 < a.L ? x1 : a.L);
+                if (l == 0) RBw[0] = 0;
+                RBw[l + 1] = b1;
+            } else {
+                b0 = B[l];
+                b1 = B[l + 1];
+            }
+            nfull = (b1 - b0) / kRowTile;
+            rem = (b1 - b0) % kRowTile;
+        }
+        const int rem_cls = rem > 0 ? tile_class(rem) : -1;
+        int mine[4], before[4], total[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) mine[c] = (c == 0 ? nfull : 0) + (rem_cls == c);
+        block_excl_scan2(mine[0], mine[1], s_wave8, &before[0], &before[1], &total[0], &total[1]);
+        block_excl_scan2(mine[2], mine[3], s_wave8, &before[2], &before[3], &total[2], &total[3]);
+        for (int t = 0; t < nfull; ++t) {
+            tiles[2 * (at[0] + before[0] + t)] = l;
+            tiles[2 * (at[0] + before[0] + t) + 1] = b0 + t * kRowTile;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (rem_cls == c) {   // the remainder follows the group's full tiles
+                const int x = at[c] + before[c] + mine[c] - 1;
+                tiles[2 * x] = l;
+                tiles[2 * x + 1] = b0 + nfull * kRowTile;
+            }
+            at[c] += total[c];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Chunk pooling, Eq. 4: X_c[h, k, :] = (sqrt(len)/len) * sum_{i in chunk k} X[h, i, :],
+// and the plan's set-up beside it.
 // One block per (chunk, head); a row of D elements is read by D*sizeof(T)/16
 // threads with 16-byte loads, row groups are summed through LDS.  HBM-bound.
 // Keys are pooled over the chunks B; queries over the query groups RB (the
 // chunks again, or with B_r > 0 the row blocks of Alg. 1, whose representation
 // is sqrt(B_r) * mean of the block's rows).
+// grid (1 + max(N_q, N_c), H_q + H_kv): x = 0 holds the set-up block (y = 0), started first.
+// BLK: the boundaries, all of them, come as kernel arguments and the set-up block writes them
+// into the plan, so a short prompt needs one launch where boundaries, set-up and pooling took three (7.2 us of a
+// 1K-token prefill, now 4 us); otherwise they are in the plan already.
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void k_pool(const T *__restrict__ Q, const T *__restrict__ K,
-                                              const int32_t *__restrict__ B, const int32_t *__restrict__ RB,
-                                              double *__restrict__ Qc, double *__restrict__ Kc, int H_q, int N_c,
-                                              int N_q, int B_r, int pooling, int64_t qs_h, int64_t qs_l,
-                                              int64_t ks_h, int64_t ks_l) {
+struct NoBlock {};
+
+template <typename T, int D, typename BLK>
+__global__ __launch_bounds__(256) void k_pool(const T *__restrict__ Q, const T *__restrict__ K, SetupArgs a,
+                                              double *__restrict__ Qc, double *__restrict__ Kc, int64_t qs_h,
+                                              int64_t qs_l, int64_t ks_h, int64_t ks_l, BLK blk) {
     constexpr int EPT = Elem<T>::kPer16;   // elements per thread per row
     constexpr int TPR = D / EPT;           // threads per row
     constexpr int RG = 256 / TPR;          // rows in flight
+    constexpr bool kInline = !std::is_same<BLK, NoBlock>::value;
     __shared__ double s_sum[RG][D];
-    const int k = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int32_t *B;
+    if constexpr (kInline) B = blk.b; else B = a.plan + a.pl.off_B;
+    if (blockIdx.x == 0) {
+        if (blockIdx.y != 0) return;
+        if constexpr (kInline)
+            for (int i = tid; i < blk.n; i += 256) a.plan[a.pl.off_B + i] = blk.b[i];
+        setup_block(a, B);
+        return;
+    }
+    const int k = blockIdx.x - 1, N_q = a.pl.N_q;
     int h = blockIdx.y;
     const T *X;
     double *Xc;
     int64_t s_l;
-    const bool is_q = h < H_q;
-    if (k >= (is_q ? N_q : N_c)) return;   // block-uniform: the grid spans max(N_q, N_c)
+    const bool is_q = h < a.H_q;
+    if (k >= (is_q ? N_q : a.N_c)) return;   // block-uniform: the grid spans max(N_q, N_c)
     if (is_q) {
         X = Q + (int64_t)h * qs_h; s_l = qs_l; Xc = Qc + ((int64_t)h * N_q + k) * D;
     } else {
-        h -= H_q;
-        X = K + (int64_t)h * ks_h; s_l = ks_l; Xc = Kc + ((int64_t)h * N_c + k) * D;
+        h -= a.H_q;
+        X = K + (int64_t)h * ks_h; s_l = ks_l; Xc = Kc + ((int64_t)h * a.N_c + k) * D;
     }
-    const int32_t *Bx = is_q ? RB : B;
-    const int b0 = Bx[k], b1 = Bx[k + 1];
-    const int tid = threadIdx.x;
+    int b0, b1;
+    if (is_q && a.B_r > 0) {
+        const int64_t x0 = (int64_t)k * a.B_r, x1 = x0 + a.B_r;
+        b0 = (int)x0;
+        b1 = (int)(x1 < a.L ? x1 : a.L);
+    } else {
+        b0 = B[k];
+        b1 = B[k + 1];
+    }
     const int rg = tid / TPR, col = (tid % TPR) * EPT;
     double acc[EPT];
 #pragma unroll
@@ -194,18 +207,33 @@ __global__ __launch_bounds__(256) void k_pool(const T *__restrict__ Q, const T *
 #pragma unroll 4
         for (int r = 0; r < RG; ++r) sum += s_sum[r][tid];
         const double len = (double)(b1 - b0);
-        Xc[tid] = pooling == DHSA_POOL_MEAN ? sum / len                                  // plain average (ablation)
-                  : (is_q && B_r > 0)      ? sqrt((double)B_r) * (sum / len)            // Alg. 1 row blocks
+        Xc[tid] = a.pooling == DHSA_POOL_MEAN ? sum / len                                // plain average (ablation)
+                  : (is_q && a.B_r > 0)    ? sqrt((double)a.B_r) * (sum / len)          // Alg. 1 row blocks
                                            : (sqrt(len) / len) * sum;                   // Eq. 4
     }
 }
 
-hipError_t launch_pool(const Prob &p, const void *Q, const void *K, const int32_t *B_dev, const int32_t *RB_dev,
-                       double *Qc, double *Kc, hipStream_t s) {
-    dim3 grid(p.N_q > p.N_c ? p.N_q : p.N_c, p.H_q + p.H_kv), block(256);
-#define DHSA_POOL(T, DD)                                                                                  \
-    hipLaunchKernelGGL((k_pool<T, DD>), grid, block, 0, s, (const T *)Q, (const T *)K, B_dev, RB_dev, Qc, \
-                       Kc, p.H_q, p.N_c, p.N_q, p.B_r, p.pooling, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
+hipError_t launch_setup_pool(const Prob &p, const PlanLayout &pl, const void *Q, const void *K, const int32_t *B_host,
+                             int32_t *plan, double *Qc, double *Kc, hipStream_t s, hipEvent_t *ev) {
+    const bool inl = p.N_c + 1 <= kBoundaryBlockMax;
+    if (!inl) {
+        hipError_t e = launch_put_boundaries(B_host, p.N_c + 1, plan + pl.off_B, s);
+        if (e != hipSuccess) return e;
+    }
+    if (ev && hipEventRecord(ev[0], s) != hipSuccess) return hipErrorUnknown;
+    const SetupArgs a = {plan, pl, p.H_q, p.H_kv, p.D, p.N_c, p.N_b, p.B_r, p.pooling, p.L};
+    const dim3 grid(1 + (p.N_q > p.N_c ? p.N_q : p.N_c), p.H_q + p.H_kv), block(256);
+#define DHSA_POOL(T, DD)                                                                                             \
+    do {                                                                                                             \
+        if (inl) {                                                                                                   \
+            BoundaryBlock blk;                                                                                       \
+            fill_block(blk, B_host, 0, p.N_c + 1);                                                                   \
+            hipLaunchKernelGGL((k_pool<T, DD, BoundaryBlock>), grid, block, 0, s, (const T *)Q, (const T *)K, a, Qc, \
+                               Kc, p.qs_h, p.qs_l, p.ks_h, p.ks_l, blk);                                             \
+        } else                                                                                                       \
+            hipLaunchKernelGGL((k_pool<T, DD, NoBlock>), grid, block, 0, s, (const T *)Q, (const T *)K, a, Qc, Kc,   \
+                               p.qs_h, p.qs_l, p.ks_h, p.ks_l, NoBlock{});                                           \
+    } while (0)
     if (p.dtype == DHSA_F32) {
         if (p.D == 64) DHSA_POOL(float, 64); else DHSA_POOL(float, 128);
     } else {
