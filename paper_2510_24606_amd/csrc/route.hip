@@ -246,71 +246,102 @@ hipError_t launch_setup_pool(const Prob &p, const PlanLayout &pl, const void *Q,
 // ---------------------------------------------------------------------------
 // Chunk similarity S_c[h, l, k] = <Q_c[h, l], K_c[h / G, k]> for the key chunks
 // k that some row of query group l can see (B[k] < RB[l+1]; with the chunks as
-// query groups that is k <= l), fp64 MFMA (16x16x4).  A 64 x 64 output tile per
-// block; four waves in a 2 x 2 arrangement, each 32 x 32 = 2 x 2 MFMA blocks.
-// Tiles none of whose pairs is visible are skipped.
+// query groups that is k <= l), fp64 MFMA (16x16x4).  Four waves in a 2 x 2
+// arrangement; tiles none of whose pairs is visible are skipped.
+//
+// Lane 16 q + n of a wave holds d = 8 s + 2 q + {0, 1} of row n of each operand block (16 bytes) and
+// supplies one of the two to each of two products, which contract over the d the four q hold.
+//
+// k_scores (64 x 64 tiles, a wave 2 x 2 blocks): operands staged through registers into LDS in
+// slabs of 32 d, the next slab requested before the current one is multiplied; the 16-byte pieces of a row are
+// XOR-swizzled by its number, so that the 16 rows x 4 pieces of a read spread over all banks.
+// 1634 chunks x 32 heads of D = 128: 242 us (150 us of products at the fp64 rate of the matrix unit); the form with
+// 8-byte reads and padded rows took 332 us, bound by bank conflicts, one that reads its operands from memory in
+// this layout, 383 us.
+// k_scores_few (32 x 32 tiles, a wave one block, operands straight from memory, all of D
+// requested at once): fewer than 512 tiles, where the chain of one wave is what takes the time (one
+// tile of 64 x 64: 10 us in the other form, 5 us).
+//
+// Workgroups are dealt to the 8 XCDs round-robin: an XCD gets whole heads, one after the other, so that
+// its L2 holds the pooled vectors of one or two heads at a time.
 // ---------------------------------------------------------------------------
-constexpr int kScTile = 64;
-constexpr int kScKc = 32;   // reduction slab staged in LDS
-constexpr int kScPad = 1;
+__device__ __forceinline__ void score_tile(int b, int H_q, int per, int *h, int *t) {
+    if ((H_q & 7) == 0) { *t = (b >> 3) % per; *h = (b & 7) * (H_q >> 3) + (b >> 3) / per; }
+    else { *t = b % per; *h = b / per; }
+}
 
-__global__ __launch_bounds__(256) void k_scores(const double *__restrict__ Qc, const double *__restrict__ Kc,
-                                                const int32_t *__restrict__ B, const int32_t *__restrict__ RB,
-                                                double *__restrict__ Sc, int N_c, int N_q, int D, int G) {
-    const int k0 = blockIdx.x * kScTile, l0 = blockIdx.y * kScTile, h = blockIdx.z;
-    {
-        const int l_last = (l0 + kScTile < N_q ? l0 + kScTile : N_q) - 1;   // last query group of the tile
-        if (B[k0] >= RB[l_last + 1]) return;                                // its first chunk starts past every row
-    }
-    __shared__ double sA[kScTile][kScKc + kScPad];
-    __shared__ double sB[kScTile][kScKc + kScPad];
-    const double *A = Qc + (int64_t)h * N_q * D;
-    const double *Bm = Kc + (int64_t)(h / G) * N_c * D;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+constexpr int kScTile = 64;
+constexpr int kScSlab = 32;   // d staged in LDS at a time: 16 pieces of 16 bytes per row
+
+template <int D>
+__global__ __launch_bounds__(256, 4) void k_scores(const double *__restrict__ Qc, const double *__restrict__ Kc,
+                                                   const int32_t *__restrict__ B, const int32_t *__restrict__ RB,
+                                                   double *__restrict__ Sc, int N_c, int N_q, int H_q, int G, int ntk,
+                                                   int ntl, int blocks) {
+    __shared__ f64x2 sA[kScTile][kScSlab / 2], sB[kScTile][kScSlab / 2];
+    int h, t;
+    score_tile(blockIdx.x, H_q, ntk * ntl, &h, &t);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k0 = (t % ntk) * kScTile, l0 = (t / ntk) * kScTile;
+    const int l_last = (l0 + kScTile < N_q ? l0 + kScTile : N_q) - 1;   // last query group of the tile
+    if (blocks ? B[k0] >= RB[l_last + 1] : k0 > l_last) return;         // its first chunk starts past every row
+    const int n16 = lane & 15, q = lane >> 4;
     const int wl = (wave >> 1) * 32, wk = (wave & 1) * 32;
+
+    // staging: thread -> row tid / 16 (+ 16 i), piece tid % 16; rows past the end repeat the last one (not stored)
+    const int sr = tid >> 4, sp = tid & 15;
+    const double *A[4], *Bm[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int l = l0 + sr + 16 * i, k = k0 + sr + 16 * i;
+        A[i] = Qc + ((int64_t)h * N_q + (l < N_q ? l : N_q - 1)) * D + 2 * sp;
+        Bm[i] = Kc + ((int64_t)(h / G) * N_c + (k < N_c ? k : N_c - 1)) * D + 2 * sp;
+    }
     f64x4 acc[2][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = (f64x4){0.0, 0.0, 0.0, 0.0};
-
-    // 64 x 32 slabs of both operands go through registers into LDS (rows past the end read as
-    // zero); the next slab is requested from memory before the current one is multiplied
-    constexpr int kPerThread = kScTile * kScKc / 256;
-    double ra[kPerThread], rb[kPerThread];
-#define DHSA_SC_FETCH(d0_)                                                                      \
-    _Pragma("unroll") for (int i = 0; i < kPerThread; ++i) {                                    \
-        const int x = tid + 256 * i, r = x / kScKc, c = x % kScKc;                              \
-        ra[i] = (l0 + r < N_q) ? A[(int64_t)(l0 + r) * D + (d0_) + c] : 0.0;                    \
-        rb[i] = (k0 + r < N_c) ? Bm[(int64_t)(k0 + r) * D + (d0_) + c] : 0.0;                   \
+        for (int n = 0; n < 2; ++n) acc[m][n] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    f64x2 ra[4], rb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ra[i] = *reinterpret_cast<const f64x2 *>(A[i]);
+        rb[i] = *reinterpret_cast<const f64x2 *>(Bm[i]);
     }
-    DHSA_SC_FETCH(0)
-    for (int d0 = 0; d0 < D; d0 += kScKc) {
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            const int x = tid + 256 * i, r = x / kScKc, c = x % kScKc;
-            sA[r][c] = ra[i];
-            sB[r][c] = rb[i];
+    for (int d0 = 0; d0 < D; d0 += kScSlab) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sA[sr + 16 * i][sp ^ sr] = ra[i];   // row & 15 == sr
+            sB[sr + 16 * i][sp ^ sr] = rb[i];
         }
         __syncthreads();
-        if (d0 + kScKc < D) DHSA_SC_FETCH(d0 + kScKc)
+        if (d0 + kScSlab < D) {
 #pragma unroll
-        for (int kk = 0; kk < kScKc; kk += 4) {
-            double a[2], b[2];
+            for (int i = 0; i < 4; ++i) {
+                ra[i] = *reinterpret_cast<const f64x2 *>(A[i] + d0 + kScSlab);
+                rb[i] = *reinterpret_cast<const f64x2 *>(Bm[i] + d0 + kScSlab);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
+        }
+#pragma unroll
+        for (int s = 0; s < kScSlab / 8; ++s) {
+            f64x2 a[2], b[2];
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                a[m] = sA[wl + 16 * m + (lane & 15)][kk + (lane >> 4)];
-                b[m] = sB[wk + 16 * m + (lane & 15)][kk + (lane >> 4)];
+                a[m] = sA[wl + 16 * m + n16][(4 * s + q) ^ n16];
+                b[m] = sB[wk + 16 * m + n16][(4 * s + q) ^ n16];
             }
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int n = 0; n < 2; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[n], acc[m][n], 0, 0, 0);
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m][j], b[n][j], acc[m][n], 0, 0, 0);
         }
         __syncthreads();
     }
-#undef DHSA_SC_FETCH
     // D[i][j]: accumulator element v of a lane is row 4*v + lane/16, column lane % 16
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -318,17 +349,60 @@ __global__ __launch_bounds__(256) void k_scores(const double *__restrict__ Qc, c
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                int l = l0 + wl + 16 * m + 4 * v + (lane >> 4);
-                int k = k0 + wk + 16 * n + (lane & 15);
+                const int l = l0 + wl + 16 * m + 4 * v + q, k = k0 + wk + 16 * n + n16;
                 if (l < N_q && k < N_c) Sc[((int64_t)h * N_q + l) * N_c + k] = acc[m][n][v];
             }
 }
 
+template <int D>
+__global__ __launch_bounds__(256) void k_scores_few(const double *__restrict__ Qc, const double *__restrict__ Kc,
+                                                    const int32_t *__restrict__ B, const int32_t *__restrict__ RB,
+                                                    double *__restrict__ Sc, int N_c, int N_q, int H_q, int G, int ntk,
+                                                    int ntl, int blocks) {
+    int h, t;
+    score_tile(blockIdx.x, H_q, ntk * ntl, &h, &t);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k0 = (t % ntk) * 32 + (wave & 1) * 16, l0 = (t / ntk) * 32 + (wave >> 1) * 16;
+    if (k0 >= N_c || l0 >= N_q) return;
+    const int l_last = (l0 + 16 < N_q ? l0 + 16 : N_q) - 1;        // last query group of the wave
+    if (blocks ? B[k0] >= RB[l_last + 1] : k0 > l_last) return;
+    const int n16 = lane & 15, q = lane >> 4;
+    const double *A = Qc + ((int64_t)h * N_q + (l0 + n16 < N_q ? l0 + n16 : N_q - 1)) * D + 2 * q;
+    const double *Bm = Kc + ((int64_t)(h / G) * N_c + (k0 + n16 < N_c ? k0 + n16 : N_c - 1)) * D + 2 * q;
+    f64x2 a[D / 8], b[D / 8];
+#pragma unroll
+    for (int s = 0; s < D / 8; ++s) {
+        a[s] = *reinterpret_cast<const f64x2 *>(A + 8 * s);
+        b[s] = *reinterpret_cast<const f64x2 *>(Bm + 8 * s);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < D / 8; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][j], b[s][j], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int l = l0 + 4 * v + q, k = k0 + n16;
+        if (l < N_q && k < N_c) Sc[((int64_t)h * N_q + l) * N_c + k] = acc[v];
+    }
+}
+
 hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, const int32_t *B_dev,
                          const int32_t *RB_dev, double *Sc, hipStream_t s) {
-    const int ntk = (p.N_c + kScTile - 1) / kScTile, ntl = (p.N_q + kScTile - 1) / kScTile;
-    hipLaunchKernelGGL(k_scores, dim3(ntk, ntl, p.H_q), dim3(256), 0, s, Qc, Kc, B_dev, RB_dev, Sc, p.N_c, p.N_q,
-                       p.D, p.G);
+    const bool few = ((int64_t)(p.N_c + 63) / 64) * ((p.N_q + 63) / 64) * p.H_q < 512;
+    const int T = few ? 32 : kScTile;
+    const int ntk = (p.N_c + T - 1) / T, ntl = (p.N_q + T - 1) / T;
+    const dim3 grid((unsigned)((int64_t)ntk * ntl * p.H_q)), block(256);
+#define DHSA_SCORES(KERNEL)                                                                                      \
+    hipLaunchKernelGGL(KERNEL, grid, block, 0, s, Qc, Kc, B_dev, RB_dev, Sc, p.N_c, p.N_q, p.H_q, p.G, ntk, ntl, \
+                       p.B_r > 0 ? 1 : 0)
+    if (p.D == 64) {
+        if (few) DHSA_SCORES(k_scores_few<64>); else DHSA_SCORES(k_scores<64>);
+    } else {
+        if (few) DHSA_SCORES(k_scores_few<128>); else DHSA_SCORES(k_scores<128>);
+    }
+#undef DHSA_SCORES
     return hipGetLastError();
 }
 
