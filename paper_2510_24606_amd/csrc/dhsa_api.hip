@@ -86,23 +86,10 @@ int listed_bound(const Prob &p, std::vector<int32_t> &lens) {
     return std::min(p.N_c, n + 2);
 }
 
-// How many chunks the ranking kernel puts on its first, short candidate list: enough to hold the
-// budget if the best chunks were drawn at random from the length distribution, m mu - z sigma sqrt(m)
-// >= N_b with z = 2.5 (the kernel checks the list it gets and falls back to the safe bound
-// `stride`, so this only trades a rare second pass against a longer first sort).
-int first_list_guess(const Prob &p, const std::vector<int32_t> &lens) {
-    double sum = 0.0, sq = 0.0;
-    for (int32_t len : lens) { sum += len; sq += (double)len * len; }
-    const double mu = sum / p.N_c, var = std::max(0.0, sq / p.N_c - mu * mu), zs = 2.5 * sqrt(var);
-    const double rt = (zs + sqrt(zs * zs + 4.0 * mu * p.N_b)) / (2.0 * mu);
-    return (int)std::min(rt * rt + 3.0, 1048576.0);
-}
-
 PlanLayout plan_layout(const Prob &p, const int32_t *B) {
     PlanLayout pl;
     std::vector<int32_t> lens(p.N_c);
     for (int k = 0; k < p.N_c; ++k) lens[k] = B[k + 1] - B[k];
-    pl.guess = first_list_guess(p, lens);
     uint32_t fnv = 2166136261u;                   // FNV-1a over the words of B
     for (int k = 0; k <= p.N_c; ++k) fnv = (fnv ^ (uint32_t)B[k]) * 16777619u;
     pl.b_sum = (int32_t)fnv;
@@ -151,7 +138,7 @@ DecodeLayout decode_layout(int H_q, int H_kv, int D, int64_t N_b, int N_c_cap, i
     dl.off_Sc = align_up(dl.off_Qc + (int64_t)H_q * D * 8, 256);
     dl.off_plan = align_up(dl.off_Sc + (int64_t)H_q * N_c_cap * 8, 256);
     PlanLayout &pl = dl.pl;
-    pl.stride = pl.guess = pl.b_sum = 0;   // set per step
+    pl.stride = pl.b_sum = 0;   // set per step
     pl.T1 = pl.T_big = 0;
     pl.T_cls[0] = pl.T_cls[1] = pl.T_cls[2] = pl.T_cls[3] = 0;
     pl.N_q = 1;
@@ -417,7 +404,7 @@ __attribute__((visibility("default"))) dhsa_status dhsa_plan_expand_rows(
         hdr[14] != (prob->B_r > 0 ? (int32_t)((prob->L + prob->B_r - 1) / prob->B_r) : prob->N_c))
         return DHSA_ERR_PLAN;
     PlanLayout pl;
-    pl.stride = hdr[5]; pl.T1 = hdr[7]; pl.T_big = hdr[12]; pl.N_q = hdr[14]; pl.guess = 0;
+    pl.stride = hdr[5]; pl.T1 = hdr[7]; pl.T_big = hdr[12]; pl.N_q = hdr[14];
     pl.b_sum = hdr[17];                                          // no boundaries here to check it against
     pl.T_cls[0] = pl.T_cls[1] = pl.T_cls[2] = pl.T_cls[3] = 0;   // the expansion does not use the tile table
     pl.off_B = hdr[8]; pl.off_RB = hdr[13]; pl.off_count = hdr[9]; pl.off_entries = hdr[10]; pl.off_tiles = hdr[11];
@@ -457,7 +444,6 @@ __attribute__((visibility("default"))) dhsa_status dhsa_decode_step(
     if (ws_bytes < (size_t)dl.bytes) return DHSA_ERR_WORKSPACE;
     std::vector<int32_t> lens(p.N_c);
     for (int k = 0; k < p.N_c; ++k) lens[k] = B_host[k + 1] - B_host[k];
-    dl.pl.guess = first_list_guess(p, lens);
     dl.pl.stride = listed_bound(p, lens);
     // first row of the open query group: the last chunk, or the last row block
     const int rb0 = p.B_r > 0 ? (int)(((p.L - 1) / p.B_r) * p.B_r) : B_host[p.N_c - 1];

@@ -33,7 +33,6 @@ struct PlanLayout {
     int T_big;        // ... of which have more than 64 rows (listed first)
     int T_cls[4];     // tiles of > 96, 65..96, 33..64 and <= 32 rows: the order of the tile table
     int N_q;          // query groups (chunks, or row blocks)
-    int guess;        // chunks the ranking kernel lists first (see first_list_guess in dhsa_api.hip)
     int b_sum;        // checksum of the boundaries (header word 17)
     int64_t off_B, off_RB, off_count, off_entries, off_tiles, words;
 };

@@ -406,98 +406,406 @@ hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, cons
     return hipGetLastError();
 }
 
-// Value of lane (lane ^ J) of the wave, J a power of two below 64: lane-crossing moves of the
-// vector unit where there is one (quads, rows of 16), the LDS crossbar otherwise.
-template <int J>
-__device__ __forceinline__ int lane_xor(int v) {
-    if constexpr (J == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);        // quad_perm [1,0,3,2]
-    else if constexpr (J == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
-    else if constexpr (J == 4) return __builtin_amdgcn_ds_swizzle(v, 0x101F);              // xor 4 inside 32 lanes
-    else if constexpr (J == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true);  // row_ror 8 == xor 8
-    else if constexpr (J == 16) return __builtin_amdgcn_ds_swizzle(v, 0x401F);             // xor 16 inside 32 lanes
-    else return __shfl_xor(v, 32);
+// ---------------------------------------------------------------------------
+// Ranking + per-row budget for one (head, query group): Alg. 1's Argsort and walk, done
+// once for all rows of the group.  An entry of the plan is a chunk that some row takes
+// a token of, with rem = N_b - (tokens of the other chunks ranked before it; the group's own chunk
+// left out).  Row-block form (B_r > 0, Alg. 1 as printed): the candidates are the chunks that
+// start before the block's end q_max, their lengths are clipped to q_max, there is no "own chunk", and
+// an entry records how many tokens of the chunk the block's list holds (pos = 3).
+// ---------------------------------------------------------------------------
+
+// order-preserving image of a score and back; -0.0 ties with +0.0
+__device__ __forceinline__ unsigned long long score_key(double s) {
+    if (s == 0.0) s = 0.0;
+    const unsigned long long u = (unsigned long long)__double_as_longlong(s);
+    return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double key_score(unsigned long long k) {
+    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
 }
 
-// Bitonic sort of PS <= 256 (key, id) pairs, one per thread of the first PS threads, "first"
-// = larger key, or equal key and smaller id.  In: skey[0..PS), sid[0..PS); out: the same
-// arrays, sorted.  Exchanges at distances below 64 stay inside a wave, the few at 64 and 128
-// go through the arrays.  Called by all 256 threads (barriers).
-template <int PS, int SIZE, int J>
-__device__ __forceinline__ void sort_step(unsigned long long &k, int &ci, unsigned long long *skey, int *sid,
-                                          int tid, bool active) {
-    unsigned long long pk = 0ull;
-    int pi = 0;
-    if constexpr (J < 64) {
-        if (active) {
-            const int lo = lane_xor<J>((int)(unsigned)k), hi = lane_xor<J>((int)(unsigned)(k >> 32));
-            pk = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-            pi = lane_xor<J>(ci);
+// LDS traffic between the lanes of one wave: the LDS executes a wave's operations in order, so only the
+// compiler has to be kept from moving them
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lane-crossing sums and extrema of a wave on the vector unit (DPP: shifts inside rows of 16 lanes, then
+// the last lane of a row or half to the ones above it); lane 63 ends up with all 64 lanes.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+#define DHSA_DPP_STEPS(STEP) STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
+__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long x) {
+#define DHSA_STEP(CTRL, ROWS)                                                               \
+    x += ((unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)(x >> 32)) << 32) | \
+         (unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)x);
+    DHSA_DPP_STEPS(DHSA_STEP)
+#undef DHSA_STEP
+    return x;
+}
+__device__ __forceinline__ int wave_incl_scan(int x) {
+#define DHSA_STEP(CTRL, ROWS) x += dpp_or<CTRL, ROWS>(0, x);
+    DHSA_DPP_STEPS(DHSA_STEP)
+#undef DHSA_STEP
+    return x;
+}
+__device__ __forceinline__ float wave_max(float x) {
+#define DHSA_STEP(CTRL, ROWS) x = fmaxf(x, __int_as_float(dpp_or<CTRL, ROWS>(__float_as_int(x), __float_as_int(x))));
+    DHSA_DPP_STEPS(DHSA_STEP)
+#undef DHSA_STEP
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ unsigned long long wave_read(unsigned long long x, int src) {   // src: wave-uniform
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), src) << 32) |
+           (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, src);
+}
+
+// ---------------------------------------------------------------------------
+// NW waves per (head, query group).  Only chunks that some row takes a token of need a
+// rank, and the tokens ranked before such a chunk are all that is wanted of it:
+//   1. scores of the visible chunks into registers (eight per lane at a time), their range;
+//   2. tokens and chunks per score bin (256 bins over the range, best first; packed tokens << 16 | chunks,
+//      LDS atomics): the bin where the tokens reach N_b is the last one that can hold a listed
+//      chunk, whatever the order inside it, so the chunks up to that bin are the candidates.  If
+//      they are more than the list holds, the last bin is cut again over its own range (outliers
+//      far from the rest), and at last by bisection over keys and ids (ties);
+//   3. candidates into LDS, grouped by bin (the bins' counts are their places);
+//   4. tokens before a candidate = tokens of better bins + of the better candidates of its own bin (a few);
+//   5. the listed chunks set their bit, and go into the plan at the number of bits below theirs
+//      (ascending chunk id).
+// Bins are taken from the scores rounded to fp32 (which keeps their order), the order inside a bin from the fp64
+// scores.  Bound by instruction issue and by the scores' way from memory (342 MB for 1634 chunks x 32 heads).  That
+// case takes 250 us; it took 480 us with a radix select by 8-bit digits (whose first digit counts nearly all
+// scores in two or three LDS words), a bitonic sort and two scans, with ~40 block barriers.
+// ---------------------------------------------------------------------------
+constexpr int kSelBins = 256;
+constexpr int kSelPer = 8;           // scores per lane in registers
+constexpr int kSelMaxStride = 1024;  // listed chunks this kernel can hold; with more the whole row is sorted (below)
+
+static int select_cap(int stride) { return (stride + 2 + 32 + 63) / 64 * 64; }   // some to spare before a bin is cut again
+static int select_row_bytes(int NW, int cap, int N_c) {   // cap: a multiple of 64
+    return kSelBins * (NW == 1 ? 8 : 16) + cap * 20 + (N_c + 63) / 64 * 8;
+}
+
+template <int NW>
+__global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, int32_t *__restrict__ plan,
+                                                PlanLayout pl, int N_c, int N_b, int B_r, int l_first, int n_groups,
+                                                int n_rows, int cap, int row_bytes) {
+    constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned long long s_red[2 * NW];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
+    const int r = NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x;
+    if (r >= n_rows) return;             // NW == 1: waves do not wait for each other
+    const auto sync = [] { if constexpr (NW == 1) wave_lds_fence(); else __syncthreads(); };
+    unsigned char *mine8 = smem + (size_t)(NW == 1 ? wave : 0) * row_bytes;
+    unsigned long long *hist = reinterpret_cast<unsigned long long *>(mine8);              // [kSelBins]
+    unsigned long long *place = NW == 1 ? hist : hist + kSelBins;                          // [kSelBins] (one wave: in place)
+    unsigned long long *ckey = place + kSelBins;                                           // [cap]
+    unsigned long long *kept = ckey + cap;                                                 // [ceil(N_c / 64)]
+    int *cid = reinterpret_cast<int *>(kept + ((N_c + 63) >> 6));                          // [cap]  id | pos << kPosShift
+    int *clen = cid + cap, *crem = clen + cap;                                             // [cap]
+    const int32_t *B = plan + pl.off_B;
+    const bool blocks = B_r > 0;
+    // l indexes Sc, RB and the plan; the group's number in the sequence is l_first + l (a launch
+    // may cover a suffix of the groups, laid out from 0)
+    const int h = r / n_groups, l = r % n_groups;
+    const int q_max = blocks ? (plan + pl.off_RB)[l + 1] : 0x7fffffff;   // clip of the chunk lengths
+    const int own = blocks ? -1 : l_first + l;                           // the query group's own chunk
+    int n = own + 1;                                                     // visible chunks 0..n-1
+    if (blocks) {                        // the chunks that start before q_max: B ascends, 64-ary search
+        int step = (N_c + 63) >> 6;
+        n = (__popcll(__ballot(lane * step < N_c && B[lane * step < N_c ? lane * step : 0] < q_max)) - 1) * step;   // B[0] = 0 < q_max
+        int got = 0;
+        for (int k0 = 0; k0 < step; k0 += 64) {
+            const int k = n + k0 + lane;
+            got += __popcll(__ballot(k0 + lane < step && k < N_c && B[k < N_c ? k : 0] < q_max));
         }
-    } else {
-        __syncthreads();           // the previous exchange has been read
-        if (active) { skey[tid] = k; sid[tid] = ci; }
-        __syncthreads();
-        if (active) { pk = skey[tid ^ J]; pi = sid[tid ^ J]; }
+        n = __builtin_amdgcn_readfirstlane(n + got);
     }
-    if (active) {
-        const bool first = (k > pk) || (k == pk && ci < pi);
-        const bool want_first = ((tid & J) == 0) == ((tid & SIZE) == 0);
-        if (first != want_first) { k = pk; ci = pi; }
-    }
-    if constexpr (J > 1) sort_step<PS, SIZE, J / 2>(k, ci, skey, sid, tid, active);
-    else if constexpr (SIZE < PS) sort_step<PS, SIZE * 2, SIZE>(k, ci, skey, sid, tid, active);
-}
+    const double *row = Sc + ((int64_t)h * pl.N_q + l) * N_c;
+    const auto len_at = [&](int x) {
+        const int b0 = B[x], b1 = B[x + 1];
+        return x == own ? 0 : (b1 < q_max ? b1 : q_max) - b0;
+    };
 
-template <int PS>
-__device__ __forceinline__ void sort_in_registers(unsigned long long *skey, int *sid, int tid) {
-    const bool active = tid < PS;      // PS is a multiple of 64: whole waves; the others only keep the barriers company
-    unsigned long long k = active ? skey[tid] : 0ull;
-    int ci = active ? sid[tid] : 0x7fffffff;
-    sort_step<PS, 2, 1>(k, ci, skey, sid, tid, active);
-    __syncthreads();
-    if (active) { skey[tid] = k; sid[tid] = ci; }
-    __syncthreads();
+    double v[PER];
+    int len[PER];
+    const auto load = [&](int x0) {      // a thread past the end repeats the last chunk
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+            if (x0 + e * NT < n) {
+                const int x = x0 + e * NT + t < n ? x0 + e * NT + t : n - 1;
+                v[e] = row[x];
+                len[e] = len_at(x);
+            }
+    };
+// BODY for every visible chunk x (in: it exists) with score s and length n_tok, whole waves; rows longer than the
+// registers hold are read again in every pass
+#define DHSA_SEL_FOR(...)                                                                    \
+    for (int x0_ = 0; x0_ < n; x0_ += kSlab) {                                               \
+        if (n > kSlab) load(x0_);                                                            \
+        _Pragma("unroll") for (int e_ = 0; e_ < PER; ++e_) {                             \
+            if (x0_ + e_ * NT < n) {                                                         \
+                const int x = x0_ + e_ * NT + t;                                             \
+                const bool in = x < n;                                                       \
+                const double s = v[e_];                                                      \
+                const int n_tok = len[e_];                                                   \
+                __VA_ARGS__                                                                  \
+            }                                                                                \
+        }                                                                                    \
+    }
+// the same for the rare passes, always from memory
+#define DHSA_SEL_AGAIN(...)                                                                  \
+    _Pragma("unroll 1") for (int x0_ = 0; x0_ < n; x0_ += NT) {                              \
+        const int x = x0_ + t;                                                               \
+        const bool in = x < n;                                                               \
+        const double s = row[in ? x : n - 1];                                                \
+        const int n_tok = len_at(in ? x : n - 1);                                            \
+        __VA_ARGS__                                                                          \
+    }
+    // over the threads of the row (NW > 1: two barriers)
+    const auto row_range = [&](float &lo_, float &hi_) {
+        hi_ = wave_max(hi_);
+        lo_ = -wave_max(-lo_);
+        if constexpr (NW > 1) {
+            __syncthreads();
+            if (lane == 0)
+                s_red[wave] = ((unsigned long long)__float_as_uint(lo_) << 32) | __float_as_uint(hi_);
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const unsigned long long x = s_red[w];
+                lo_ = fminf(lo_, __uint_as_float((unsigned)(x >> 32)));
+                hi_ = fmaxf(hi_, __uint_as_float((unsigned)x));
+            }
+        }
+    };
+    const auto row_sum = [&](unsigned long long x) {
+        x = wave_read(wave_incl_scan(x), 63);
+        if constexpr (NW > 1) {
+            __syncthreads();
+            if (lane == 0) s_red[NW + wave] = x;
+            __syncthreads();
+            x = 0ull;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) x += s_red[NW + w];
+        }
+        return x;
+    };
+
+    for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
+    if (n <= kSlab) load(0);
+    const unsigned long long k_own = score_key(own >= 0 ? row[own] : 0.0);
+    float lo = INFINITY, hi = -INFINITY, inv;
+    DHSA_SEL_FOR({ (void)x; (void)in; (void)n_tok; lo = fminf(lo, (float)s); hi = fmaxf(hi, (float)s); })
+    row_range(lo, hi);
+    if constexpr (NW == 1) wave_lds_fence();   // hist is clear (NW > 1: row_range has a barrier)
+    const float best = hi;
+    const auto bin_of = [&](double s) {  // never decreasing as s falls
+        const int b = (int)((hi - (float)s) * inv);
+        return b < 0 ? 0 : b < kSelBins - 1 ? b : kSelBins - 1;
+    };
+
+    // candidates: chunks ranked at or before (cut_key, cut_id) once that is known (cut), or those of the bins up to tbin
+    bool cut = false;
+    unsigned long long cut_key = 0ull;
+    int cut_id = 0x7fffffff, tbin;
+    const auto is_cand = [&](double s, int x) {
+        const unsigned long long k = score_key(s);
+        return k > cut_key || (k == cut_key && x <= cut_id);
+    };
+    unsigned long long above = 0ull;     // tokens << 16 | chunks with a score above hi
+    for (int level = 0;; ++level) {
+        inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
+        if (level == 0) {
+            DHSA_SEL_FOR({ (void)x; if (in) atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull); })
+        } else {
+            sync();                      // everybody has read the last level's counts
+            for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
+            sync();
+            DHSA_SEL_AGAIN({
+                if (in && (cut ? is_cand(s, x) : ((float)s >= lo && (float)s <= hi)))
+                    atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull);
+            })
+        }
+        sync();
+        // every wave for itself: what is ranked before each bin (tokens, and chunks = the place of its first)
+        unsigned long long c[4];         // bins 4 lane .. 4 lane + 3
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = hist[4 * lane + i];
+        const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
+        unsigned long long run = above + wave_incl_scan(mine) - mine, before = 0ull, upto = 0ull;
+        int my_bin = kSelBins;           // the bin of this lane in which the tokens reach N_b
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (NW == 1 || wave == 0) place[4 * lane + i] = run;
+            if ((run >> 16) < (unsigned long long)N_b && ((run + c[i]) >> 16) >= (unsigned long long)N_b) {
+                my_bin = 4 * lane + i;
+                before = run;
+                upto = run + c[i];
+            }
+            run += c[i];
+        }
+        tbin = kSelBins - 1;
+        if (cut) break;
+        const unsigned long long found = __ballot(my_bin < kSelBins);
+        int n_upto;                      // chunks up to the last bin
+        if (found) {
+            const int src = __builtin_ctzll(found);
+            tbin = __builtin_amdgcn_readlane(my_bin, src);
+            before = wave_read(before, src);
+            n_upto = (int)(wave_read(upto, src) & 0xffffull);
+        } else {                         // all visible chunks fit the budget
+            n_upto = (int)(wave_read(run, 63) & 0xffffull);
+        }
+        if (n_upto <= cap && level == 0) break;                  // the usual end
+        if (n_upto <= cap) {             // group all candidates over one range: from the worst of them to the best
+            float worst = INFINITY, none = -INFINITY;
+            DHSA_SEL_AGAIN({
+                (void)x; (void)n_tok;
+                if (in && ((float)s > hi || ((float)s >= lo && bin_of(s) <= tbin))) worst = fminf(worst, (float)s);
+            })
+            row_range(worst, none);
+            lo = worst;
+            // every score that rounds to `worst` or more: the smallest such key
+            unsigned long long key_lo = ~0ull;
+            DHSA_SEL_AGAIN({
+                (void)x; (void)n_tok;
+                const unsigned long long k = score_key(s);
+                if (in && (float)s >= worst && k < key_lo) key_lo = k;
+            })
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const unsigned long long o = __shfl_xor(key_lo, off);
+                key_lo = o < key_lo ? o : key_lo;
+            }
+            if constexpr (NW > 1) {
+                __syncthreads();
+                if (lane == 0) s_red[wave] = key_lo;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < NW; ++w) key_lo = s_red[w] < key_lo ? s_red[w] : key_lo;
+            }
+            cut_key = key_lo;
+        } else if (level < 3 && hi > lo) {   // cut the last bin again, over its own range
+            float a = INFINITY, z = -INFINITY;
+            DHSA_SEL_AGAIN({
+                (void)x; (void)n_tok;
+                if (in && (float)s >= lo && (float)s <= hi && bin_of(s) == tbin) { a = fminf(a, (float)s); z = fmaxf(z, (float)s); }
+            })
+            above = before;
+            row_range(a, z);
+            lo = a;
+            hi = z;
+            continue;
+        } else {
+            // the largest key, then the smallest id among equal keys, down to which the tokens reach N_b (more than
+            // `cap` chunks are in sight, hence more than N_b tokens)
+            for (int bit = 63; bit >= 0; --bit) {
+                const unsigned long long k = cut_key | (1ull << bit);
+                unsigned long long sum = 0ull;
+                DHSA_SEL_AGAIN({ (void)x; if (in && score_key(s) >= k) sum += (unsigned long long)n_tok; })
+                if (row_sum(sum) >= (unsigned long long)N_b) cut_key = k;
+            }
+            int id0 = 0;                 // the ids below id0 are not enough
+            for (int bit = 13; bit >= 0; --bit) {
+                const int id = id0 | (1 << bit);
+                unsigned long long sum = 0ull;
+                DHSA_SEL_AGAIN({
+                    const unsigned long long k = score_key(s);
+                    if (in && (k > cut_key || (k == cut_key && x < id))) sum += (unsigned long long)n_tok;
+                })
+                if (row_sum(sum) < (unsigned long long)N_b) id0 = id;
+            }
+            cut_id = id0;
+            lo = (float)key_score(cut_key);
+        }
+        cut = true;                      // one more level: the bins of the candidates alone
+        above = 0ull;
+        hi = best;
+    }
+    for (int w = t; w < ((n + 63) >> 6); w += NT) kept[w] = 0ull;
+    sync();
+
+    // ---- candidates, grouped by bin: the chunk count in place[bin] moves from the place of its first to its end ----
+    DHSA_SEL_FOR({
+        const int bin = bin_of(s);
+        if (in && (cut ? is_cand(s, x) : bin <= tbin)) {
+            const int at = (int)(atomicAdd(&place[bin], 1ull) & 0xffffull);
+            const unsigned long long k = score_key(s);
+            const int pos = blocks ? 3 : x == own ? 1 : (k > k_own || (k == k_own && x < own)) ? 0 : 2;
+            if (at < cap) { ckey[at] = k; cid[at] = x | (pos << kPosShift); clen[at] = n_tok; }
+        }
+    })
+#undef DHSA_SEL_FOR
+#undef DHSA_SEL_AGAIN
+    sync();
+    int n_c = (int)(place[tbin] & 0xffffull);
+    n_c = n_c < cap ? n_c : cap;
+
+    // ---- tokens ranked before each candidate, and whether some row takes a token of it ----
+    for (int c = t; c < n_c; c += NT) {
+        const unsigned long long k = ckey[c];
+        const int w = cid[c], x = w & kChunkMask, pos = w >> kPosShift;
+        const int bin = bin_of(key_score(k));
+        const unsigned long long pb = place[bin];
+        const int j1 = (int)(pb & 0xffffull) < n_c ? (int)(pb & 0xffffull) : n_c;
+        int run = (int)(pb >> 16);
+        for (int j = bin > 0 ? (int)(place[bin - 1] & 0xffffull) : 0; j < j1; ++j) {
+            const unsigned long long kj = ckey[j];
+            const int lj = clen[j];
+            if (kj > k || (kj == k && (cid[j] & kChunkMask) < x)) run += lj;
+        }
+        int rem = N_b - run;
+        const bool need = (pos == 2) ? (rem > 1) : (rem > 0);
+        if (blocks && rem > clen[c]) rem = clen[c];     // tokens of the chunk in the block's list
+        crem[c] = need ? rem : 0;
+        if (need) atomicOr(&kept[x >> 6], 1ull << (x & 63));
+    }
+    sync();
+
+    // ---- into the plan in ascending chunk id: listed chunks below word 2 lane + {0, 1} of `kept` ----
+    const int nw = (n + 63) >> 6;                       // at most 128
+    const int c0 = 2 * lane < nw ? __popcll(kept[2 * lane]) : 0, c1 = 2 * lane + 1 < nw ? __popcll(kept[2 * lane + 1]) : 0;
+    const int upto = wave_incl_scan(c0 + c1);
+    const int total = __builtin_amdgcn_readlane(upto, 63);
+    int32_t *entries = plan + pl.off_entries + ((int64_t)h * pl.N_q + l) * pl.stride * 2;
+    for (int cb = 0; cb < n_c; cb += NT) {              // whole waves: the shuffles need their lanes
+        const int c = cb + t < n_c ? cb + t : n_c - 1;
+        const int rem = cb + t < n_c ? crem[c] : 0, w = cid[c], x = w & kChunkMask, word = x >> 6;
+        const int even = __shfl(upto - c0 - c1, word >> 1), odd = __shfl(upto - c1, word >> 1);   // all lanes read
+        const int below = (word & 1) ? odd : even;
+        const int slot = below + __popcll(kept[word] & ((1ull << (x & 63)) - 1ull));
+        if (rem > 0 && slot < pl.stride) *reinterpret_cast<int2 *>(entries + 2 * slot) = make_int2(w, rem);
+    }
+    if (t == 0) plan[pl.off_count + (int64_t)h * pl.N_q + l] = total < pl.stride ? total : pl.stride;
 }
 
 // ---------------------------------------------------------------------------
-// Ranking + per-row budget for one (head, query chunk l): Alg. 1's Argsort and
-// walk, done once for all rows of the chunk.
-//   1. scores of key chunks 0..l -> LDS as order-preserving 64-bit integers;
-//   2. only the best `stride` chunks can ever be listed (stride bounds the number
-//      of chunks whose tokens fit the budget), so for rows of more than 256 chunks a
-//      most-significant-digit radix select (8-bit digits, LDS histograms, prefix
-//      scans) first cuts the row down to a candidate list: at first a short one,
-//      sized for chunks of about the mean length (it is the answer whenever its
-//      chunks hold the budget), else one of <= 512 that holds `stride` chunks;
-//   3. bitonic sort of the candidates (of the whole row if there was no select),
-//      larger score first, equal scores lower id first; up to 256 elements are
-//      sorted in registers, one per thread, more in LDS;
-//   4. exclusive prefix sum of chunk lengths along the ranking, chunk l left out
+// The same for groups that can list more than kSelMaxStride chunks (many chunks of a few tokens): one
+// workgroup per (head, query group) sorts the whole row in LDS.
+//   1. scores of the visible chunks -> LDS as order-preserving 64-bit integers;
+//   2. bitonic sort, larger score first, equal scores lower id first;
+//   3. exclusive prefix sum of chunk lengths along the ranking, chunk l left out
 //      -> rem = N_b - (tokens of other chunks before this rank);
-//   5. a chunk is kept if some row takes a token of it; kept chunks are
+//   4. a chunk is kept if some row takes a token of it; kept chunks are
 //      compacted in ascending chunk id (prefix sum of flags) into the plan.
-// Row-block form (B_r > 0, Alg. 1 as printed): query group l is a row block,
-// the candidates are the chunks that start before the block's end q_max, their
-// lengths are clipped to q_max, there is no "own chunk", and an entry records
-// how many tokens of the chunk the block's list holds (pos = 3).
 // ---------------------------------------------------------------------------
-constexpr int kMaxCand = 512;     // candidates kept by the radix select
-constexpr int kSelectMin = 256;   // rows with more chunks than this use it; shorter rows are sorted whole, in registers
-
-__global__ __launch_bounds__(256) void k_select(const double *__restrict__ Sc, int32_t *__restrict__ plan,
-                                                PlanLayout pl, int N_c, int N_b, int B_r, int smem_bytes,
-                                                int guess, int l_first) {
+__global__ __launch_bounds__(256) void k_select_sorted(const double *__restrict__ Sc, int32_t *__restrict__ plan,
+                                                       PlanLayout pl, int N_c, int N_b, int B_r, int l_first) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_wave[4];
     __shared__ int s_p;
-    __shared__ int s_hist[256];
-    __shared__ int s_digit, s_above, s_equal;
     const int l = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int32_t *B = plan + pl.off_B;
     const bool blocks = B_r > 0;
     const int q_max = blocks ? (plan + pl.off_RB)[l + 1] : 0x7fffffff;   // clip of the chunk lengths
-    // l indexes Sc, RB and the plan; the group's number in the sequence is l_first + l (a launch
-    // may cover a suffix of the groups, laid out from 0)
     const int own = blocks ? -1 : l_first + l;                            // the query group's own chunk
     const int n = blocks ? chunk_of_row(B, N_c, (int64_t)q_max - 1) + 1 : l_first + l + 1;   // visible chunks 0..n-1
     int P = 64;
@@ -519,203 +827,89 @@ __global__ __launch_bounds__(256) void k_select(const double *__restrict__ Sc, i
         for (int e = 0; e < 8; ++e) {
             const int x = x0 + e * 256;
             if (x >= P) break;
-            unsigned long long u = 0ull;
-            int k = 0x7fffffff;
-            if (x < n) {
-                double s = sc[e];
-                if (s == 0.0) s = 0.0;  // -0.0 ties with +0.0
-                u = (unsigned long long)__double_as_longlong(s);
-                u = (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-                k = x;
-            }
-            key[x] = u;
-            id[x] = k;
+            key[x] = x < n ? score_key(sc[e]) : 0ull;
+            id[x] = x < n ? x : 0x7fffffff;
         }
     }
+    if (tid == 0) s_p = 0x7fffffff;
     __syncthreads();
 
-    // What gets sorted: the whole row in place, or the candidates of a radix select.  The select
-    // is tried first with `guess` chunks (the number that holds the budget if the best chunks
-    // have about the mean length): the sorted candidates are exactly the head of the full
-    // ranking, so if their lengths add up to the budget no later chunk can be listed and the
-    // short sort is the answer.  Otherwise the select is redone with `stride` chunks, the bound
-    // that always suffices.
-    const bool can_select = n > kSelectMin && pl.stride <= kMaxCand - 64 && P * 8 + kMaxCand * 12 <= smem_bytes;
-    int cap0 = 64;
-    while (cap0 < guess) cap0 <<= 1;
-    unsigned long long *skey = key;
-    int *sid = id;
-    int Ps = P, ns = n;
-    int p = 0x7fffffff, run = 0;
-    int lens[32];
-    bool id_intact = true;
-    for (int attempt = (can_select && guess < pl.stride && cap0 < kMaxCand) ? 0 : 1;; ++attempt) {
-        skey = key;
-        sid = id;
-        Ps = P;
-        ns = n;
-        if (can_select) {
-            // ---- radix select: smallest set {key >= threshold prefix} holding the best `need` ----
-            const int cap = attempt == 0 ? cap0 : kMaxCand;
-            const int goal = attempt == 0 ? guess : pl.stride;
-            const int need = goal < n ? goal : n;
-            unsigned long long prefix = 0ull;
-            int above = 0, equal = n, shift = 64;
-            for (int pass = 0; pass < 8 && above + equal > cap; ++pass) {
-                shift = 56 - 8 * pass;
-                s_hist[tid] = 0;
-                __syncthreads();
-                for (int x = tid; x < n; x += 256) {
-                    const unsigned long long k = key[x];
-                    if (pass == 0 || (k >> (shift + 8)) == prefix)
-                        atomicAdd(&s_hist[(int)((k >> shift) & 255ull)], 1);
+    // ---- bitonic network; "a goes first" iff key larger, or equal and id smaller ----
+    for (int size = 2; size <= P; size <<= 1) {
+        for (int j = size >> 1, lj = 31 - __clz(size >> 1); j > 0; j >>= 1, --lj) {   // j = 1 << lj
+            for (int t = tid; t < (P >> 1); t += 256) {
+                int lo = ((t >> lj) << (lj + 1)) + (t & (j - 1));
+                int hi = lo + j;
+                bool up = (lo & size) == 0;
+                unsigned long long ka = key[lo], kb = key[hi];
+                int ia = id[lo], ib = id[hi];
+                bool a_first = (ka > kb) || (ka == kb && ia < ib);
+                if (a_first != up) {
+                    key[lo] = kb; key[hi] = ka;
+                    id[lo] = ib; id[hi] = ia;
                 }
-                __syncthreads();
-                // suffix counts over digits: thread t looks at digit 255 - t
-                const int d = 255 - tid, cnt = s_hist[d];
-                int total;
-                const int gt = block_excl_scan(cnt, s_wave, &total);   // elements of the region with a larger digit
-                const int want = need - above;                         // still to be found inside the region
-                if (gt < want && gt + cnt >= want) { s_digit = d; s_above = gt; s_equal = cnt; }
-                __syncthreads();
-                above += s_above;
-                equal = s_equal;
-                prefix = (prefix << 8) | (unsigned long long)s_digit;
-                __syncthreads();
             }
-            if (above + equal <= cap) {
-                // ---- compact the candidates, in chunk-id order, into their own arrays ----
-                unsigned long long *ckey = reinterpret_cast<unsigned long long *>(smem + (size_t)P * 8);  // over id[]
-                int *cid = reinterpret_cast<int *>(ckey + kMaxCand);
-                const int per = (n + 255) / 256;
-                const bool all = shift == 64;   // no radix pass ran (n <= cap): every element is a candidate
-                int local = 0;
-                for (int e = 0; e < per; ++e) {
-                    const int x = tid * per + e;
-                    if (x < n && (all || (key[x] >> shift) >= prefix)) ++local;
-                }
-                int total;
-                int slot = block_excl_scan(local, s_wave, &total);
-                __syncthreads();               // id[] is dead (ids are positions), its space is reused now
-                id_intact = false;
-                for (int e = 0; e < per; ++e) {
-                    const int x = tid * per + e;
-                    if (x < n && (all || (key[x] >> shift) >= prefix)) { ckey[slot] = key[x]; cid[slot] = x; ++slot; }
-                }
-                ns = total;
-                Ps = 64;
-                while (Ps < ns) Ps <<= 1;
-                for (int x = ns + tid; x < Ps; x += 256) { ckey[x] = 0ull; cid[x] = 0x7fffffff; }
-                skey = ckey;
-                sid = cid;
-                __syncthreads();
-            } else if (attempt == 0) {
-                continue;                      // too many equal scores for the short sort
-            } else if (!id_intact) {           // whole-row sort after a first attempt: ids are positions
-                for (int x = tid; x < P; x += 256) id[x] = x < n ? x : 0x7fffffff;
-                __syncthreads();
-            }
+            __syncthreads();
         }
-
-        // ---- bitonic network; "a goes first" iff key larger, or equal and id smaller ----
-        if (Ps <= 256) {
-            if (Ps == 64) sort_in_registers<64>(skey, sid, tid);
-            else if (Ps == 128) sort_in_registers<128>(skey, sid, tid);
-            else sort_in_registers<256>(skey, sid, tid);
-        } else
-        for (int size = 2; size <= Ps; size <<= 1) {
-            for (int j = size >> 1, lj = 31 - __clz(size >> 1); j > 0; j >>= 1, --lj) {   // j = 1 << lj
-                for (int t = tid; t < (Ps >> 1); t += 256) {
-                    int lo = ((t >> lj) << (lj + 1)) + (t & (j - 1));
-                    int hi = lo + j;
-                    bool up = (lo & size) == 0;
-                    unsigned long long ka = skey[lo], kb = skey[hi];
-                    int ia = sid[lo], ib = sid[hi];
-                    bool a_first = (ka > kb) || (ka == kb && ia < ib);
-                    if (a_first != up) {
-                        skey[lo] = kb; skey[hi] = ka;
-                        sid[lo] = ib; sid[hi] = ia;
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        // rank of chunk l (beyond every candidate if it is not one of them)
-        if (tid == 0) s_p = 0x7fffffff;
-        __syncthreads();
-        for (int x = tid; x < ns; x += 256)
-            if (sid[x] == own) s_p = x;
-        __syncthreads();
-        p = s_p;
-        // chunk lengths along the ranking (chunk l left out) and their exclusive prefix sum
-        const int per = Ps / 256 > 0 ? Ps / 256 : 1;           // consecutive ranks per thread
-        int local = 0;
-        for (int e = 0; e < per; ++e) {
-            int r = tid * per + e;
-            int len = 0;
-            if (r < ns) {
-                int k = sid[r];
-                const int end = B[k + 1] < q_max ? B[k + 1] : q_max;
-                len = (k == own) ? 0 : end - B[k];
-            }
-            lens[e] = len;
-            local += len;
-        }
-        int total;
-        run = block_excl_scan(local, s_wave, &total);
-        if (attempt == 0 && ns < n && total < N_b) {
-            __syncthreads();                   // every thread is done with the candidates
-            continue;
-        }
-        break;
     }
+    for (int x = tid; x < n; x += 256)       // rank of the own chunk
+        if (id[x] == own) s_p = x;
+    __syncthreads();
+    const int p = s_p;
+    // chunk lengths along the ranking (chunk l left out) and their exclusive prefix sum
+    int lens[32];
+    const int per = P / 256 > 0 ? P / 256 : 1;           // consecutive ranks per thread
+    int local = 0;
+    for (int e = 0; e < per; ++e) {
+        int r = tid * per + e;
+        int len = 0;
+        if (r < n) {
+            int k = id[r];
+            const int end = B[k + 1] < q_max ? B[k + 1] : q_max;
+            len = (k == own) ? 0 : end - B[k];
+        }
+        lens[e] = len;
+        local += len;
+    }
+    int total;
+    int run = block_excl_scan(local, s_wave, &total);
     // the row's key array is dead now: reuse it as rem_by_id / pos_by_id
     int *rem_by_id = reinterpret_cast<int *>(smem);        // [P]
     int *pos_by_id = rem_by_id + P;                        // [P]
-    if (skey != key) {                                     // chunks that are no candidates are not listed
-        for (int x = tid; x < n; x += 256) rem_by_id[x] = 0;
-    }
-    __syncthreads();  // the zero fill is complete
-    {
-        const int per = Ps / 256 > 0 ? Ps / 256 : 1;
-        for (int e = 0; e < per; ++e) {
-            int r = tid * per + e;
-            if (r < ns) {
-                int k = sid[r];
-                int pos = blocks ? 3 : ((r < p) ? 0 : (r == p ? 1 : 2));
-                int rem = N_b - run;                      // may be <= 0: not needed
-                bool need = (pos == 2) ? (rem > 1) : (rem > 0);
-                if (blocks && rem > lens[e]) rem = lens[e];   // tokens of the chunk in the block's list
-                rem_by_id[k] = need ? rem : 0;
-                pos_by_id[k] = pos;
-            }
-            run += lens[e];
+    __syncthreads();
+    for (int e = 0; e < per; ++e) {
+        int r = tid * per + e;
+        if (r < n) {
+            int k = id[r];
+            int pos = blocks ? 3 : ((r < p) ? 0 : (r == p ? 1 : 2));
+            int rem = N_b - run;                      // may be <= 0: not needed
+            bool need = (pos == 2) ? (rem > 1) : (rem > 0);
+            if (blocks && rem > lens[e]) rem = lens[e];   // tokens of the chunk in the block's list
+            rem_by_id[k] = need ? rem : 0;
+            pos_by_id[k] = pos;
         }
+        run += lens[e];
     }
     __syncthreads();
     // compact in ascending chunk id
     int32_t *entries = plan + pl.off_entries + ((int64_t)h * pl.N_q + l) * pl.stride * 2;
-    {
-        const int per_id = P / 256 > 0 ? P / 256 : 1;
-        int local = 0;
-        for (int e = 0; e < per_id; ++e) {
-            int k = tid * per_id + e;
-            if (k < n && rem_by_id[k] != 0) ++local;
-        }
-        int total;
-        int slot = block_excl_scan(local, s_wave, &total);
-        for (int e = 0; e < per_id; ++e) {
-            int k = tid * per_id + e;
-            if (k < n && rem_by_id[k] != 0) {
-                if (slot < pl.stride) {
-                    entries[2 * slot] = k | (pos_by_id[k] << kPosShift);
-                    entries[2 * slot + 1] = rem_by_id[k];
-                }
-                ++slot;
-            }
-        }
-        if (tid == 0) plan[pl.off_count + (int64_t)h * pl.N_q + l] = total < pl.stride ? total : pl.stride;
+    local = 0;
+    for (int e = 0; e < per; ++e) {
+        int k = tid * per + e;
+        if (k < n && rem_by_id[k] != 0) ++local;
     }
+    int slot = block_excl_scan(local, s_wave, &total);
+    for (int e = 0; e < per; ++e) {
+        int k = tid * per + e;
+        if (k < n && rem_by_id[k] != 0) {
+            if (slot < pl.stride) {
+                entries[2 * slot] = k | (pos_by_id[k] << kPosShift);
+                entries[2 * slot + 1] = rem_by_id[k];
+            }
+            ++slot;
+        }
+    }
+    if (tid == 0) plan[pl.off_count + (int64_t)h * pl.N_q + l] = total < pl.stride ? total : pl.stride;
 }
 
 hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, hipStream_t s) {
@@ -724,16 +918,42 @@ hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, 
 
 hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, int l_first,
                                 int n_groups, hipStream_t s) {
-    int P = 64;
-    while (P < p.N_c) P <<= 1;
-    size_t shmem = (size_t)P * 8 + std::max<size_t>((size_t)P * 4, (size_t)kMaxCand * 12);   // keys + (ids | candidates)
-    if (shmem > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_select),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-        if (e != hipSuccess) return e;
+    const int n_rows = n_groups * p.H_q;
+    if (pl.stride > kSelMaxStride) {
+        int P = 64;
+        while (P < p.N_c) P <<= 1;
+        const size_t shmem = (size_t)P * 12;
+        if (shmem > 48 * 1024) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_select_sorted),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(k_select_sorted, dim3(n_groups, p.H_q), dim3(256), shmem, s, Sc, plan, pl, p.N_c, p.N_b,
+                           p.B_r, l_first);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_select, dim3(n_groups, p.H_q), dim3(256), shmem, s, Sc, plan, pl, p.N_c, p.N_b, p.B_r,
-                       (int)shmem, pl.guess > 0 ? pl.guess : 1, l_first);
+    // Waves per row: as many as hold its scores in eight registers a lane, and four where rows are few (a decoding
+    // step).  Fewer waves with more scores each repeat less, but leave fewer rows in flight: 1634 chunks x 32
+    // heads take 250 us with four waves, 315 us with one of 32 scores a lane.
+    const int cap = select_cap(pl.stride);
+    const int nw = n_rows < 512 ? 4 : p.N_c <= 512 ? 1 : p.N_c <= 1024 ? 2 : 4;
+    const int row_bytes = select_row_bytes(nw, cap, p.N_c);
+    const size_t shmem = nw == 1 ? (size_t)4 * row_bytes : row_bytes;
+    const dim3 grid(nw == 1 ? (n_rows + 3) / 4 : n_rows), block(nw == 1 ? 256 : 64 * nw);
+#define DHSA_SELECT(NW)                                                                                            \
+    do {                                                                                                           \
+        if (shmem > 48 * 1024) {                                                                                   \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_select<NW>),                       \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);            \
+            if (e != hipSuccess) return e;                                                                         \
+        }                                                                                                          \
+        hipLaunchKernelGGL(k_select<NW>, grid, block, shmem, s, Sc, plan, pl, p.N_c, p.N_b, p.B_r, l_first, n_groups, \
+                           n_rows, cap, row_bytes);                                                                \
+    } while (0)
+    if (nw == 1) DHSA_SELECT(1);
+    else if (nw == 2) DHSA_SELECT(2);
+    else DHSA_SELECT(4);
+#undef DHSA_SELECT
     return hipGetLastError();
 }
 

@@ -69,3 +69,35 @@ def test_f32_pieces_lists_and_batches(L, H_q, D, N_b, lens, B_r):
     assert torch.isfinite(O).all()
     err = np.abs(O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64) - ref).max()
     assert err <= 1e-5, err
+
+
+@pytest.mark.parametrize("B_r", [0, 96])
+@pytest.mark.parametrize("L,lens,N_b,keys", [(6100, ("fixed", 2), 300, "iid"),              # > 2048 chunks
+                                             (2300, ("fixed", 1), 1500, "iid"),             # > 1024 listed chunks
+                                             (3001, ("fixed", 4), 400, "equal"),            # all scores of a group tie
+                                             (3000, ("uniform", 1, 9), 333, "two_values"),
+                                             (3000, ("uniform", 2, 6), 200, "outliers"),    # one bin holds nearly all
+                                             (700, ("uniform", 3, 60), 2000, "iid")])       # everything fits
+def test_ranking_bins_cuts_and_ties(L, lens, N_b, keys, B_r):
+    w = dhsa_inputs.make("c1", L=L, H_q=2, H_kv=1, D=64, N_b=N_b, lens=lens)
+    K = w.K.clone()
+    k_of = torch.repeat_interleave(torch.arange(w.N_c), torch.from_numpy(np.diff(w.B).astype(np.int64)))
+    if keys == "equal":
+        K[:] = K[:, :1]
+    elif keys == "two_values":
+        K[0] = torch.where((k_of % 3 == 0)[:, None], K[0, :1], K[0, 1:2])
+    elif keys == "outliers":
+        K[0] *= torch.where(k_of % 97 == 5, 1e4, 1.0)[:, None]
+        K[0] *= torch.where(k_of % 193 == 7, -1e8, 1.0)[:, None]
+    Q, Kg = w.Q.cuda(), K.cuda()
+    prob = dhsa.problem(Q, Kg, w.B, w.N_b, B_r=B_r)
+    plan, ws = dhsa.alloc(prob, w.B)
+    plan.fill_(255)
+    dhsa.dhsa_route(prob, Q, Kg, w.B, plan, ws)
+    rows = np.arange(0, L, 3, dtype=np.int64)
+    args = (w.f32("Q"), K.numpy(), w.f32("V"), w.B)
+    ref = oracle.prefill_rows_blocks(*args, B_r, N_b, rows) if B_r else oracle.prefill_rows(*args, N_b, rows)
+    for h in range(2):
+        idx, cnt = dhsa.dhsa_plan_expand_rows(prob, plan, h, rows)
+        np.testing.assert_array_equal(cnt.cpu().numpy(), ref[2][h])
+        np.testing.assert_array_equal(idx.cpu().numpy(), ref[1][h][:, :idx.shape[1]])
