@@ -50,7 +50,6 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
         float m[4][NR], l[4][NR];
     };
     __shared__ __align__(16) union { Lists li; Merge me; } sm;
-    if (!plan_matches(pv)) return;   // not this problem's plan: O is not written
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, q4 = lane >> 4;
 
@@ -68,15 +67,21 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
             first += T;
         }
     }
-    const int l = pv.tiles[2 * tile];
-    const int row0 = pv.tiles[2 * tile + 1] + piece * NR;
-    const int b_l = pv.RB[l], tile_end = pv.tiles[2 * tile + 1] + kRowTile;
+    const int l = pv.tiles[2 * tile], tile0 = pv.tiles[2 * tile + 1];
+    if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
+    const int row0 = tile0 + piece * NR;
+    const int b_l = pv.RB[l], tile_end = tile0 + kRowTile;
     const int end = pv.RB[l + 1] < tile_end ? pv.RB[l + 1] : tile_end;
     const int nrows = end - row0 < NR ? end - row0 : NR;
     if (nrows <= 0) return;          // the tile has fewer pieces than its class allows
     const int v_lo = row0 + 1 - b_l, v_hi = v_lo + nrows - 1;
     const int E = pv.count[(int64_t)h * pv.N_q + l];
-    const int32_t *ent = pv.entries + ((int64_t)h * pv.N_q + l) * pv.stride * 2;
+    // the entries of the first batch do not wait for their number, and the query rows are requested behind what the key
+    // list hangs on
+    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)h * pv.N_q + l) * pv.stride;
+    int2 ent_e = ent[tid < pv.stride ? tid : 0];
+    if (tid >= E) ent_e = int2{0, 0};   // past the list: nothing there has been written
+    int b0_e = pv.B[ent_e.x & kChunkMask], b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
     const float *Kg = K + (int64_t)g * ks_h + 4 * q4;
     const float *Vg = V + (int64_t)g * vs_h + 4 * n16;
 
@@ -101,14 +106,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
 
     for (int e0 = 0; e0 < E; e0 += kF32Seg) {
         // segments (entries some row takes a key from) of this batch, compacted
-        int n_e = 0, b0_e = 0, pos_e = 0, rem_e = 0;
+        if (e0 > 0) {
+            ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0};
+            b0_e = pv.B[ent_e.x & kChunkMask];
+            b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
+        }
+        int n_e = 0;
+        const int pos_e = ent_e.x >> kPosShift, rem_e = ent_e.y;
         if (e0 + tid < E) {
-            const int w0 = ent[2 * (e0 + tid)];
-            rem_e = ent[2 * (e0 + tid) + 1];
-            const int k = w0 & kChunkMask;
-            pos_e = w0 >> kPosShift;
-            b0_e = pv.B[k];
-            n_e = entry_take(pos_e, rem_e, pv.B[k + 1] - b0_e, pos_e == 1 ? v_hi : v_lo);
+            n_e = entry_take(pos_e, rem_e, b1_e - b0_e, pos_e == 1 ? v_hi : v_lo);
             if (pos_e == 3) {        // row-block form: keys past the last row are dropped
                 const int vis = row0 + nrows - b0_e;
                 n_e = vis < n_e ? (vis > 0 ? vis : 0) : n_e;

@@ -135,17 +135,19 @@ static int attn_order(int want, int H_kv, int G, int T1) {
 // some row of the tile takes a key from; segments are stored compacted, in entry order: the first
 // packed position of their keys (an exclusive scan of the most tokens any row of the tile takes
 // from the entry; for the row-block form keys past the tile's last row are dropped), the chunk's
-// first token, pos and rem.  Defines `total` (packed keys of the batch), `nseg` and the wave's
+// first token, pos and rem.  The entry of this thread in the first batch (ent_e, b0_e, b1_e) has been loaded
+// already.  Defines `total` (packed keys of the batch), `nseg` and the wave's
 // segment cursor.  Contains block barriers.
 #define DHSA_SEGMENT_TABLE(e0) \
-    int n_e = 0, b0_e = 0, pos_e = 0, rem_e = 0; \
+    if (e0 > 0) { \
+        ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0}; \
+        b0_e = pv.B[ent_e.x & kChunkMask]; \
+        b1_e = pv.B[(ent_e.x & kChunkMask) + 1]; \
+    } \
+    int n_e = 0; \
+    const int pos_e = ent_e.x >> kPosShift, rem_e = ent_e.y; \
     if (e0 + tid < E) { \
-        const int w0 = ent[2 * (e0 + tid)]; \
-        rem_e = ent[2 * (e0 + tid) + 1]; \
-        const int k = w0 & kChunkMask; \
-        pos_e = w0 >> kPosShift; \
-        b0_e = pv.B[k]; \
-        n_e = entry_take(pos_e, rem_e, pv.B[k + 1] - b0_e, pos_e == 1 ? v_hi : v_lo); \
+        n_e = entry_take(pos_e, rem_e, b1_e - b0_e, pos_e == 1 ? v_hi : v_lo); \
         if (pos_e == 3) { \
             const int vis = row0 + nrows - b0_e; \
             n_e = vis < n_e ? (vis > 0 ? vis : 0) : n_e; \
@@ -232,11 +234,23 @@ struct AttnArgs {
     int64_t qs_h, qs_l, ks_h, ks_l, vs_h, vs_l, os_h, os_l;
 };
 
+// What a tile body needs first, requested as early as the addresses are known: the entries of the first
+// batch do not wait for the number of entries, and the query rows are requested behind what the key list
+// hangs on (a workgroup's prologue is a chain of dependent loads of about a microsecond each).
+#define DHSA_TILE_PROLOGUE                                                                      \
+    const int b_l = pv.RB[l];                                                                   \
+    const int rows_left = pv.RB[l + 1] - row0;                                                  \
+    const int E = pv.count[(int64_t)h * pv.N_q + l];                                            \
+    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)h * pv.N_q + l) * pv.stride; \
+    int2 ent_e = ent[tid < pv.stride ? tid : 0];                                                \
+    if (tid >= E) ent_e = int2{0, 0};   /* past the list: nothing there has been written */     \
+    int b0_e = pv.B[ent_e.x & kChunkMask], b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
+
 // One row tile of more than 64 rows (any tile of up to 128 rows is handled correctly): see the
 // header of this file.
 template <int D>
 __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const int h,
-                                             const int tile) {
+                                             const int l, const int row0) {
     using Smem = AttnSmem<D>;
     constexpr int OPR = D / 8;          // 16-byte pieces per row
     constexpr int KPT = OPR / 4;        // load instructions per wave per tile (K and V each)
@@ -257,9 +271,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     const int lr = lane & 31, g2 = lane >> 5;
 
     const int g = h / G;
-    const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
-    const int b_l = pv.RB[l];
-    const int rows_left = pv.RB[l + 1] - row0;
+    DHSA_TILE_PROLOGUE;
     const int nrows = rows_left < kRowTile ? rows_left : kRowTile;
     const int v_lo = row0 + 1 - b_l, v_hi = v_lo + nrows - 1;
     // Wave = one 32-row block of the tile (rotated per workgroup so that the waves left without
@@ -285,10 +297,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         const int r = pad_row ? nrows - 1 : rb * 32 + lr;
         const uint16_t *qp = Q + (int64_t)h * qs_h + (int64_t)(row0 + r) * qs_l + 8 * g2;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            qf[s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
-            if (pad_row) qf[s] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        }
+        for (int s = 0; s < NS; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
     }
 
     f32x16 oacc[NDB];
@@ -297,9 +306,6 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
 #pragma unroll
         for (int x = 0; x < 16; ++x) oacc[db][x] = 0.f;
     float m_ref = pad_row ? 1e30f : -INFINITY, l_run = 0.f;   // m_ref: reference used in the exponent (see DHSA_EXP)
-
-    const int E = pv.count[(int64_t)h * pv.N_q + l];
-    const int32_t *ent = pv.entries + ((int64_t)h * pv.N_q + l) * pv.stride * 2;
 
     // staging: load instruction c of this wave fills LDS window (4 c + wave) of a
     // tile (1 KiB = 64 pieces); this lane's piece there is physical piece
@@ -455,6 +461,10 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's pieces are in LDS
         __syncthreads();
         if (wave_live) {
+            if (e0 == 0 && pad_row) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) qf[s] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            }
             DHSA_QK(0, s_a);
             DHSA_MASK(0, 0, s_a, fl_cur);
             if (e0 == 0) { float mx0; DHSA_ROWMAX(s_a, mx0); m_ref = fmaxf(m_ref, mx0); }   // reference = row maxima of the first block
@@ -583,7 +593,7 @@ __device__ __forceinline__ int piece_swizzle_k16(int r, int pieces_per_row) {
 
 template <int D, int RW>
 __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const int h,
-                                             const int tile) {
+                                             const int l, const int row0) {
     using Smem = AttnSmem<D>;
     constexpr int OPR = D / 8;          // 16-byte pieces per row
     constexpr int KPT = OPR / 4;        // load instructions per wave per tile (K and V each)
@@ -604,9 +614,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
     const int n16 = lane & 15, q = lane >> 4;
 
     const int g = h / G;
-    const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];
-    const int b_l = pv.RB[l];
-    const int rows_left = pv.RB[l + 1] - row0;
+    DHSA_TILE_PROLOGUE;
     const int nrows = rows_left < 32 * RW ? rows_left : 32 * RW;   // only tiles of <= 32 RW rows come here
     const int v_lo = row0 + 1 - b_l, v_hi = v_lo + nrows - 1;
     const int rg = wave & 1, kbw = wave >> 1;        // row group, key parity
@@ -630,18 +638,12 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         v_i[r] = v_lo + rr;
         const uint16_t *qp = Q + (int64_t)h * qs_h + (int64_t)(row0 + (pad_row ? nrows - 1 : rr)) * qs_l + 8 * q;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            qf[r][t] = *reinterpret_cast<const bf16x8 *>(qp + 32 * t);
-            if (pad_row) qf[r][t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-        }
+        for (int t = 0; t < NT; ++t) qf[r][t] = *reinterpret_cast<const bf16x8 *>(qp + 32 * t);
         m_ref[r] = pad_row ? 1e30f : -INFINITY;
         l_run[r] = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) oacc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-
-    const int E = pv.count[(int64_t)h * pv.N_q + l];
-    const int32_t *ent = pv.entries + ((int64_t)h * pv.N_q + l) * pv.stride * 2;
 
     // staging (as in the kernel above; K with its own swizzle)
     constexpr int RPW = 64 / OPR;
@@ -779,6 +781,14 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         __syncthreads();
         if (wave_live) {
+            if (e0 == 0) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r)
+                    if (rbase + 16 * r + n16 >= nrows) {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) qf[r][t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                    }
+            }
             DHSA_QK16(s_a);
             DHSA_MASK16(0, s_a, fl_0);
             if (e0 == 0) {   // reference = row maxima of this wave's first block
@@ -897,19 +907,23 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
 }
 
 // One launch per tile class (a kernel that holds all three bodies measured 3-10 % slower than
-// the sum of these).  CLS 0: tiles of more than 64 rows (table classes 0 and 1), 1: 33..64 rows,
+// the sum of these), but a class too small to fill the chip joins the launch of the next taller one (launch_attn_mfma).
+// CLS 0: tiles of more than 64 rows (table classes 0 and 1), 1: 33..64 rows,
 // 2: at most 32 rows.  Inside a launch tiles are issued from the end of the sequence (most keys)
-// to its start, so that the launch ends with the cheapest workgroups.
+// to its start, so that the launch ends with the cheapest workgroups; T0 tiles of its own class first, then the
+// shorter ones.
 template <int D, int CLS>
-__global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, int H_q, int mode, int tile0, int T) {
+__global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, int H_q, int mode, int tile0, int T0,
+                                                      int T) {
     __shared__ AttnSmem<D> sm;
-    if (!plan_matches(pv)) return;   // not this problem's plan: nothing is read further, O is not written
     int h, pos;
     decode_block(mode, blockIdx.x, H_q, a.G, T, &h, &pos);
-    const int tile = tile0 + T - 1 - pos;
-    if constexpr (CLS == 0) attn_tile_32<D>(sm, pv, a, h, tile);
-    else if constexpr (CLS == 1) attn_tile_16<D, 2>(sm, pv, a, h, tile);
-    else attn_tile_16<D, 1>(sm, pv, a, h, tile);
+    const int tile = tile0 + (pos < T0 ? T0 - 1 - pos : T0 + T - 1 - pos);
+    const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
+    if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
+    if constexpr (CLS == 0) attn_tile_32<D>(sm, pv, a, h, l, row0);
+    else if constexpr (CLS == 1) attn_tile_16<D, 2>(sm, pv, a, h, l, row0);
+    else attn_tile_16<D, 1>(sm, pv, a, h, l, row0);
 }
 
 hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
@@ -928,25 +942,38 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     a.scale_log2e = p.scale * 1.4426950408889634f;
     a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
     a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
-#define DHSA_LAUNCH(CLS, tile0, T)                                                                           \
-    if ((T) > 0) {                                                                                          \
-        const int mode = attn_order(want, p.H_kv, p.G, T);                                                  \
-        if (p.D == 64)                                                                                      \
-            hipLaunchKernelGGL((k_attn_mfma<64, CLS>), dim3(p.H_q * (T)), dim3(256), 0, s, pv, a, p.H_q, mode, tile0, T);  \
-        else                                                                                                \
-            hipLaunchKernelGGL((k_attn_mfma<128, CLS>), dim3(p.H_q * (T)), dim3(256), 0, s, pv, a, p.H_q, mode, tile0, T); \
+    // tiles of each launch: its own class, and shorter ones that joined.  A launch of fewer workgroups than the chip
+    // holds at once (two per CU) takes as long as one workgroup whatever their number, while the next taller
+    // body runs such tiles in the gaps of its own (their stage time is then part of that launch's).
+    int own[3] = {pv.T_big, pv.T_cls[2], pv.T_cls[3]}, all[3] = {own[0], own[1], own[2]};
+    for (int c = 2; c > 0; --c) {
+        const int to = own[c - 1] > 0 ? c - 1 : 0;
+        if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) { all[to] += all[c]; all[c] = 0; }
+    }
+    const int first[3] = {0, own[0], own[0] + own[1]};
+#define DHSA_LAUNCH(CLS)                                                                                     \
+    if (all[CLS] > 0) {                                                                                      \
+        const int mode = attn_order(want, p.H_kv, p.G, all[CLS]);                                            \
+        const dim3 grid(p.H_q * all[CLS]);                                                                   \
+        if (p.D == 64)                                                                                       \
+            hipLaunchKernelGGL((k_attn_mfma<64, CLS>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS], \
+                               own[CLS], all[CLS]);                                                          \
+        else                                                                                                 \
+            hipLaunchKernelGGL((k_attn_mfma<128, CLS>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS], \
+                               own[CLS], all[CLS]);                                                          \
     }
     // tallest tiles first (they take longest)
-    DHSA_LAUNCH(0, 0, pv.T_big)
+    DHSA_LAUNCH(0)
     if (ev && hipEventRecord(ev[0], s) != hipSuccess) return hipErrorUnknown;
-    DHSA_LAUNCH(1, pv.T_big, pv.T_cls[2])
+    DHSA_LAUNCH(1)
     if (ev && hipEventRecord(ev[1], s) != hipSuccess) return hipErrorUnknown;
-    DHSA_LAUNCH(2, pv.T_big + pv.T_cls[2], pv.T_cls[3])
+    DHSA_LAUNCH(2)
     if (ev && hipEventRecord(ev[2], s) != hipSuccess) return hipErrorUnknown;
 #undef DHSA_LAUNCH
     return hipGetLastError();
 }
 
+#undef DHSA_TILE_PROLOGUE
 #undef DHSA_SEGMENT_TABLE
 #undef DHSA_MAKE_META
 #undef DHSA_OFFS
