@@ -12,6 +12,7 @@ import os
 from typing import Optional, Tuple
 
 import numpy as np
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdhsa.so")
@@ -29,6 +30,9 @@ EXPORTS = ["dhsa_plan_bytes", "dhsa_workspace_bytes", "dhsa_route", "dhsa_sparse
            "dhsa_recall_rows", "dhsa_recall_workspace_bytes",
            "dhsa_decode_step", "dhsa_decode_workspace_bytes",
            "dhsa_status_string", "dhsa_version"]
+
+
+_DTYPES = {torch.float32: DHSA_F32, torch.bfloat16: DHSA_BF16}
 
 
 class dhsa_problem(C.Structure):
@@ -58,7 +62,8 @@ def lib() -> C.CDLL:
             raise RuntimeError(f"{LIB_PATH} is not built: run `python -m paper_2510_24606_amd.build`")
         l = C.CDLL(LIB_PATH)
         P = C.POINTER(dhsa_problem)
-        i32p, i64p, vp = C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.c_void_p
+        i64p, vp = C.POINTER(C.c_int64), C.c_void_p
+        i32p = C.c_void_p                     # boundary arrays are handed over as addresses
         l.dhsa_plan_bytes.argtypes = [P, i32p]; l.dhsa_plan_bytes.restype = C.c_size_t
         l.dhsa_workspace_bytes.argtypes = [P, i32p]; l.dhsa_workspace_bytes.restype = C.c_size_t
         l.dhsa_route.argtypes = [P, vp, vp, i32p, vp, C.c_size_t, vp, C.c_size_t, vp]
@@ -110,28 +115,25 @@ def _b(B) -> np.ndarray:
     return np.ascontiguousarray(B, dtype=np.int32)
 
 
-def _bp(B: np.ndarray):
-    return B.ctypes.data_as(C.POINTER(C.c_int32))
+def _bp(B: np.ndarray) -> int:
+    return B.__array_interface__["data"][0]
 
 
 def _stream() -> int:
-    import torch
-    return int(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())   # current_stream() builds an object around it
 
 
 def problem(Q, K, B, N_b: int, scale: float = 0.0, B_r: int = 0, pooling: int = 0, V=None) -> dhsa_problem:
     """Describe Q [H_q, L, D] and K [H_kv, L, D] (torch tensors, last dim contiguous).
     B_r > 0 selects Alg. 1 as printed (row blocks of B_r rows, one index list per block).
     V (same shape as K) is only needed when its strides differ from a contiguous [H_kv, L, D]."""
-    import torch
     H_q, L, D = Q.shape
     H_kv = K.shape[0]
-    dt = {torch.float32: DHSA_F32, torch.bfloat16: DHSA_BF16}.get(Q.dtype, -1)
-    return dhsa_problem(L=L, H_q=H_q, H_kv=H_kv, D=D, N_c=len(B) - 1, N_b=N_b, dtype=dt, scale=scale,
-                        q_stride_h=Q.stride(0), q_stride_l=Q.stride(1),
-                        k_stride_h=K.stride(0), k_stride_l=K.stride(1),
-                        v_stride_h=0 if V is None else V.stride(0), v_stride_l=0 if V is None else V.stride(1),
-                        B_r=B_r, pooling=pooling)
+    dt = _DTYPES.get(Q.dtype, -1)
+    q_h, q_l, _ = Q.stride()
+    k_h, k_l, _ = K.stride()
+    v_h, v_l, _ = (0, 0, 0) if V is None else V.stride()
+    return dhsa_problem(L, H_q, H_kv, D, len(B) - 1, N_b, dt, scale, q_h, q_l, k_h, k_l, v_h, v_l, 0, 0, B_r, pooling)
 
 
 def dhsa_plan_bytes(prob: dhsa_problem, B) -> int:
@@ -146,11 +148,11 @@ def dhsa_workspace_bytes(prob: dhsa_problem, B) -> int:
 
 def alloc(prob: dhsa_problem, B, device="cuda"):
     """(plan, workspace) as uint8 device tensors of the sizes the library asks for."""
-    import torch
     pb, wb = dhsa_plan_bytes(prob, B), dhsa_workspace_bytes(prob, B)
     if pb == 0 or wb == 0:
         # let the library name the reason
-        _check(lib().dhsa_route(C.byref(prob), 16, 16, _bp(_b(B)), 16, 0, 16, 0, None) or 6)
+        B = _b(B)
+        _check(lib().dhsa_route(C.byref(prob), 16, 16, _bp(B), 16, 0, 16, 0, None) or 6)
     return (torch.empty(pb, dtype=torch.uint8, device=device), torch.empty(wb, dtype=torch.uint8, device=device))
 
 
@@ -162,8 +164,8 @@ def dhsa_route(prob, Q, K, B, plan, ws) -> None:
 
 def _with_vo(prob: dhsa_problem, V, O) -> dhsa_problem:
     p = dhsa_problem.from_buffer_copy(prob)
-    p.v_stride_h, p.v_stride_l = V.stride(0), V.stride(1)
-    p.o_stride_h, p.o_stride_l = O.stride(0), O.stride(1)
+    p.v_stride_h, p.v_stride_l, _ = V.stride()
+    p.o_stride_h, p.o_stride_l, _ = O.stride()
     return p
 
 
@@ -210,7 +212,6 @@ def dhsa_prefill_stage_times(prob, Q, K, V, B, O, plan, ws) -> dict:
 
 def dhsa_debug_scores(prob, B, ws):
     """S_c [H_q, N_q, N_c] fp64 (entries of chunks a query group cannot see are zero here)."""
-    import torch
     B = _b(B)
     Sc = torch.zeros((prob.H_q, n_query_groups(prob), prob.N_c), dtype=torch.float64, device=ws.device)
     _check(lib().dhsa_debug_scores(C.byref(prob), _bp(B), ws.data_ptr(), ws.numel(), Sc.data_ptr(), _stream()))
@@ -223,7 +224,6 @@ def dhsa_static_scratch_bytes() -> int:
 
 def dhsa_plan_expand_rows(prob, plan, head: int, rows) -> Tuple["torch.Tensor", "torch.Tensor"]:
     """Index sets of `rows` (host int64) for one head: (idx [n, cap] int32 ascending, -1 padded; cnt [n])."""
-    import torch
     rows = np.ascontiguousarray(rows, dtype=np.int64)
     n = rows.shape[0]
     cap = int(min(prob.N_b, prob.L))
@@ -243,7 +243,6 @@ def n_query_groups(prob) -> int:
 
 def dhsa_debug_routing(prob, B, ws, want_Sc: bool = True):
     """(Q_c, K_c, S_c) fp64 device tensors copied out of a workspace dhsa_route filled."""
-    import torch
     B = _b(B)
     dev = ws.device
     N_q = n_query_groups(prob)
@@ -257,7 +256,6 @@ def dhsa_debug_routing(prob, B, ws, want_Sc: bool = True):
 
 def dhsa_mfma_probe(random_operands: bool, iters: int = 100000):
     """(TFLOP/s, shader MHz) of the bf16 MFMA alone on the whole chip; blocks until measured."""
-    import torch
     L = lib()
     n = int(L.dhsa_mfma_probe_scratch_bytes())
     scratch = torch.empty(n, dtype=torch.uint8, device="cuda")
@@ -270,7 +268,6 @@ def dhsa_mfma_probe(random_operands: bool, iters: int = 100000):
 def dhsa_finalize_boundaries(scores, threshold: float, window: int) -> np.ndarray:
     """Boundary scores [L] (fp32 device tensor; position i = end of a chunk) -> boundaries B as a host
     int32 array [N_c + 1] (0 ... L).  Synchronises the stream to bring B to the host."""
-    import torch
     L = int(scores.shape[0])
     n = int(lib().dhsa_finalize_boundaries_workspace_bytes(L))
     ws = torch.empty(max(n, 1), dtype=torch.uint8, device=scores.device)
@@ -287,7 +284,6 @@ def dhsa_finalize_boundaries(scores, threshold: float, window: int) -> np.ndarra
 def dhsa_recall_rows(prob, Q, K, B, plan, head: int, rows) -> Tuple["torch.Tensor", "torch.Tensor"]:
     """Recall counts of the routed sets of `rows` (host int64) of one head against exact top-k
     attention: (hits [n], size [n]) int32 device tensors; recall = hits / size."""
-    import torch
     B = _b(B)
     rows = np.ascontiguousarray(rows, dtype=np.int64)
     n = rows.shape[0]
@@ -307,7 +303,6 @@ def dhsa_decode_workspace_bytes(prob: dhsa_problem, N_c_cap: int, L_cap: int) ->
 
 def alloc_decode(prob: dhsa_problem, N_c_cap: int, L_cap: int, device="cuda"):
     """Workspace of the decoding step (it keeps the pooled keys between steps)."""
-    import torch
     n = dhsa_decode_workspace_bytes(prob, N_c_cap, L_cap)
     if n == 0:
         raise DhsaError(2, "problem or caps rejected by dhsa_decode_workspace_bytes")
@@ -318,9 +313,8 @@ def dhsa_decode_step(prob, Q, K, V, B, ws, N_c_cap: int, L_cap: int, kc_valid: i
                      out=None):
     """One decoding step for the newest token (row L - 1): O_row [H_q, D] in the input dtype (written
     into `out` if given); with want_idx also (idx [H_q, min(N_b, L)] int32 ascending, cnt [H_q] int32)."""
-    import torch
     B = _b(B)
-    O_row = out if out is not None else torch.empty((prob.H_q, prob.D), dtype=Q.dtype, device=Q.device)
+    O_row = out if out is not None else Q.new_empty((prob.H_q, prob.D))
     idx = cnt = None
     if want_idx:
         idx = torch.empty((prob.H_q, min(prob.N_b, prob.L)), dtype=torch.int32, device=Q.device)

@@ -9,13 +9,18 @@
 // Kernels of this file:
 //   k_pool_decode     pooled keys (Eq. 4) of the chunks not pooled by an earlier
 //                     step, pooled queries of the open group;
-//   k_scores_decode   that group's scores against every key chunk (one wave per pooled key);
+//   k_scores_decode   that group's scores against every key chunk (fp64 MFMA, heads of a kv-group as rows);
 //   (the ranking and the walk are k_select of route.hip, launched for one group)
-//   k_attn_decode     the selected keys are split into slices of 128; one workgroup
+//   k_attn_decode     the selected keys are split into slices; one workgroup
 //                     per (slice, head) streams its K and V rows once, 16 bytes per
 //                     lane, several rows in flight, and keeps an online-softmax
-//                     state per row group; memory bound;
-//   k_decode_combine  merges the slices' states into the output row.
+//                     state per row group; memory bound.  Where the slices are few, the workgroup
+//                     that finishes a head's last one merges their states into the output row, else
+//   k_decode_combine  does that.
+// Around the stream of K and V a step is a chain of launches, each of which waits for the one before, so
+// each is made short: fewer of them, everything requested at once.
+#include <algorithm>
+
 #include "dhsa_internal.h"
 
 namespace dhsa {
@@ -29,7 +34,7 @@ namespace dhsa {
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_pool_decode(const T *__restrict__ Q, const T *__restrict__ K,
                                                      int32_t *__restrict__ B, BoundaryTail tail,
-                                                     int32_t *__restrict__ RBw,
+                                                     int32_t *__restrict__ RBw, int32_t *__restrict__ done,
                                                      double *__restrict__ Qc, double *__restrict__ Kc, int H_kv,
                                                      int N_c, int N_c_cap, int kc_valid, int rb0, int L, int B_r,
                                                      int pooling, int64_t qs_h, int64_t qs_l, int64_t ks_h,
@@ -50,6 +55,7 @@ __global__ __launch_bounds__(256) void k_pool_decode(const T *__restrict__ Q, co
         X = Q + (int64_t)h * qs_h; s_l = qs_l; Xc = Qc + (int64_t)h * D;
         b0 = rb0; b1 = L;
         if (h == 0 && tid == 0) { RBw[0] = rb0; RBw[1] = L; }   // the one query group of the step's plan
+        if (tid == 0) done[h] = 0;       // slices of the head finished so far (k_attn_decode)
         // boundaries that came as arguments go into the workspace for the kernels after this one
         if (h == 0 && tid <= tail.n && tail.n > 0) B[kc_valid + tid] = tail.b[tid];
     } else {
@@ -82,35 +88,56 @@ __global__ __launch_bounds__(256) void k_pool_decode(const T *__restrict__ Q, co
 }
 
 // ---------------------------------------------------------------------------
-// Scores of the open query group: Sc[h][k] = <Qc[h], Kc[h / G][k]>, k < N_c.
-// One wave per (kv-head g, chunk k): it reads the pooled key once and forms the
-// scores of the G query heads of the group.  grid (ceil(N_c / 4), H_kv).
+// Scores of the open query group: Sc[h][k] = <Qc[h], Kc[h / G][k]>, k < N_c: the 16 x 16 block of a wave has
+// up to 16 heads of a kv-group as rows and 16 chunks as columns, with the operand layout and the order of
+// summation of the prefill's scores.  All of D is requested at once.  grid (ceil(N_c / 64), H_kv, ceil(G / 16)).
+// 1634 chunks x 8 kv-heads of D = 128: 12 us with a wave per chunk and a sum over its lanes per head.
 // ---------------------------------------------------------------------------
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int D>
 __global__ __launch_bounds__(256) void k_scores_decode(const double *__restrict__ Qc, const double *__restrict__ Kc,
-                                                       double *__restrict__ Sc, int N_c, int N_c_cap, int D, int G) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = blockIdx.x * 4 + wave, g = blockIdx.y;
-    if (k >= N_c) return;   // wave-uniform
-    const double *kc = Kc + ((int64_t)g * N_c_cap + k) * D;
-    const double k0 = kc[lane], k1 = D > 64 ? kc[lane + 64] : 0.0;
-    for (int hh = 0; hh < G; ++hh) {
-        const int h = g * G + hh;
-        const double *q = Qc + (int64_t)h * D;
-        double acc = q[lane] * k0;
-        if (D > 64) acc += q[lane + 64] * k1;
+                                                       double *__restrict__ Sc, int N_c, int N_c_cap, int G) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k0 = blockIdx.x * 64 + wave * 16, g = blockIdx.y, h0 = blockIdx.z * 16;
+    if (k0 >= N_c) return;
+    const int n16 = lane & 15, q = lane >> 4;
+    const double *A = Qc + (int64_t)(g * G + (h0 + n16 < G ? h0 + n16 : G - 1)) * D + 2 * q;
+    const double *B = Kc + ((int64_t)g * N_c_cap + (k0 + n16 < N_c ? k0 + n16 : N_c - 1)) * D + 2 * q;
+    f64x2 a[D / 8], b[D / 8];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) Sc[(int64_t)h * N_c + k] = acc;
+    for (int s = 0; s < D / 8; ++s) {
+        b[s] = *reinterpret_cast<const f64x2 *>(B + 8 * s);
+        a[s] = *reinterpret_cast<const f64x2 *>(A + 8 * s);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
+    f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < D / 8; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][j], b[s][j], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int hh = h0 + 4 * v + q, k = k0 + n16;
+        if (hh < G && k < N_c) Sc[(int64_t)(g * G + hh) * N_c + k] = acc[v];
     }
 }
 
 // ---------------------------------------------------------------------------
 // Attention of the newest row over slice blockIdx.x of its selected keys.
 // The plan entries of (h, the open group) are walked like in the prefill
-// kernels (ascending key position); packed positions [128 s, 128 s + 128) are
+// kernels (ascending key position); packed positions [slice s, slice (s + 1)) are
 // this workgroup's.  A key row is read by TPR = D sizeof(T) / 16 adjacent lanes
 // (16 bytes each: coalesced), NG = 256 / TPR rows at a time, U batches in
-// flight.  Partial state of the slice -> part[h][s] = (m, l, o[D]).
+// flight.
+// FUSE: the state of a slice (m, l, o[D]) goes to memory with stores that bypass the XCD's own L2 (agent
+// scope), waited for, before the workgroup counts itself as done with an atomic of that scope; the one that
+// counts last reads all states of its head the same way and writes the output row.  Nothing
+// else has to become visible, so no workgroup writes back its L2 (a release fence before the count did
+// that: 150 us a step).  That saves a launch where the chip is nearly empty (a head of 512 keys: 10.9 + 3.8 us
+// -> 8 us); where it is full, workgroups that wait for their stores hold up those behind them (64 slices x 32 heads:
+// 41 us against 28 + 6 us), so the states are merged by k_decode_combine.
 // ---------------------------------------------------------------------------
 template <typename T> struct DecIO;
 template <> struct DecIO<float> {
@@ -136,11 +163,65 @@ template <> struct DecIO<bf16_t> {
     }
 };
 
-template <typename T, int D>
+// Merge of the S slice states of one head into its output row by NTHR threads: thread = (two columns, every NSG-th
+// slice), eight slices requested at a time.  AGENT: the states may have been written by workgroups of the same
+// launch.  s_m, s_l, s_o: room for NSG partial states.
+template <typename T, int D, int NTHR, bool AGENT>
+__device__ __forceinline__ void merge_slices(const float *part, int S, float *s_m, float *s_l, float (*s_o)[D], T *O) {
+    constexpr int NSG = NTHR / (D / 2);
+    const int tid = threadIdx.x, c2 = tid % (D / 2), sg = tid / (D / 2);
+    const unsigned long long *p64 = reinterpret_cast<const unsigned long long *>(part);
+    const auto get = [](const unsigned long long *p) {
+        if constexpr (AGENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else return *p;
+    };
+    float Mr = -INFINITY, lr = 0.f, o0 = 0.f, o1 = 0.f;
+    for (int s0 = sg; s0 < S; s0 += 8 * NSG) {
+        unsigned long long ml[8], ov[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const unsigned long long *ps = p64 + (int64_t)(s0 + u * NSG < S ? s0 + u * NSG : s0) * (D / 2 + 1);
+            ml[u] = get(&ps[0]);
+            ov[u] = get(&ps[1 + c2]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (s0 + u * NSG >= S) break;
+            const float mu = __uint_as_float((unsigned)ml[u]);
+            const float m_new = fmaxf(Mr, mu);
+            const float a0 = (Mr == -INFINITY) ? 0.f : __expf(Mr - m_new), a1 = (mu == -INFINITY) ? 0.f : __expf(mu - m_new);
+            lr = lr * a0 + __uint_as_float((unsigned)(ml[u] >> 32)) * a1;
+            o0 = o0 * a0 + __uint_as_float((unsigned)ov[u]) * a1;
+            o1 = o1 * a0 + __uint_as_float((unsigned)(ov[u] >> 32)) * a1;
+            Mr = m_new;
+        }
+    }
+    if (c2 == 0) { s_m[sg] = Mr; s_l[sg] = lr; }
+    s_o[sg][2 * c2] = o0;
+    s_o[sg][2 * c2 + 1] = o1;
+    __syncthreads();
+    if (tid < D) {
+        float M = -INFINITY;
+#pragma unroll
+        for (int x = 0; x < NSG; ++x) M = fmaxf(M, s_m[x]);
+        float ls = 0.f, acc = 0.f;
+#pragma unroll
+        for (int x = 0; x < NSG; ++x) {
+            const float w = (s_m[x] == -INFINITY) ? 0.f : __expf(s_m[x] - M);
+            ls += s_l[x] * w;
+            acc += s_o[x][tid] * w;
+        }
+        DecIO<T>::store(O + tid, ls > 0.f ? acc / ls : 0.f);
+    }
+}
+
+template <typename T, int D, bool FUSE>
 __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__ B, const int32_t *__restrict__ count,
                                                      const int32_t *__restrict__ entries, int stride, int rb0, int L,
                                                      const T *__restrict__ Q, const T *__restrict__ K,
-                                                     const T *__restrict__ V, float *__restrict__ part, int S,
+                                                     const T *__restrict__ V, float *__restrict__ part, int S, int slice,
+                                                     int32_t *__restrict__ done, T *__restrict__ O_row,
                                                      int32_t *__restrict__ idx, int cap, int32_t *__restrict__ cnt,
                                                      int G, float scale, int64_t qs_h, int64_t qs_l, int64_t ks_h,
                                                      int64_t ks_l, int64_t vs_h, int64_t vs_l) {
@@ -148,27 +229,37 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
     constexpr int TPR = D / EPT;               // lanes per key row (8, 16 or 32)
     constexpr int NG = 256 / TPR;              // key rows per batch
     constexpr int U = 4;                       // batches in flight
-    __shared__ int s_keys[kDecSlice];
+    __shared__ int s_keys[kDecSliceMax];
     __shared__ int s_wave[4];
     __shared__ float s_m[NG], s_l[NG];
     __shared__ float s_o[NG][D];
+    __shared__ int s_last;
     const int s = blockIdx.x, h = blockIdx.y, g = h / G, tid = threadIdx.x;
     const int i = L - 1;
     const int v = L - rb0;   // rows of the query group up to and including the newest
+    const int gi = tid / TPR, r = tid % TPR;
+    // the first batch of entries does not wait for their number
+    const int2 *ent = reinterpret_cast<const int2 *>(entries) + (int64_t)h * stride;
+    int2 ent_e = ent[tid < stride ? tid : 0];
     const int E = count[h];
-    const int32_t *ent = entries + (int64_t)h * stride * 2;
-    const int x_lo = s * kDecSlice, x_hi = x_lo + kDecSlice;
+    if (tid >= E) ent_e = int2{0, 0};   // past the list: nothing there has been written
+    int b0 = B[ent_e.x & kChunkMask], b1 = B[(ent_e.x & kChunkMask) + 1];
+    const uint4 q16 = *reinterpret_cast<const uint4 *>(Q + (int64_t)h * qs_h + (int64_t)i * qs_l + r * EPT);
+    const int x_lo = s * slice, x_hi = x_lo + slice;
 
-    if (tid < kDecSlice) s_keys[tid] = -1;
+    for (int x = tid; x < slice; x += 256) s_keys[x] = -1;
     __syncthreads();
     int base = 0;   // selected keys of the entries walked so far (block-uniform)
     for (int e0 = 0; e0 < E; e0 += 256) {
-        int take = 0, b0 = 0;
+        if (e0 > 0) {
+            ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0};
+            b0 = B[ent_e.x & kChunkMask];
+            b1 = B[(ent_e.x & kChunkMask) + 1];
+        }
+        int take = 0;
         if (e0 + tid < E) {
-            const int w0 = ent[2 * (e0 + tid)], rem = ent[2 * (e0 + tid) + 1];
-            const int k = w0 & kChunkMask, pos = w0 >> kPosShift;
-            b0 = B[k];
-            take = entry_take(pos, rem, B[k + 1] - b0, v);
+            const int pos = ent_e.x >> kPosShift;
+            take = entry_take(pos, ent_e.y, b1 - b0, v);
             if (pos == 3) {   // row-block form: of the block's list, the keys up to the row itself
                 const int vis = i + 1 - b0;
                 if (vis < take) take = vis > 0 ? vis : 0;
@@ -185,12 +276,12 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
     __syncthreads();
     if (s == 0 && tid == 0 && cnt) cnt[h] = base;
     int n_mine = base - x_lo;
-    n_mine = n_mine < 0 ? 0 : (n_mine > kDecSlice ? kDecSlice : n_mine);
-    if (idx && tid < kDecSlice && x_lo + tid < cap) idx[(int64_t)h * cap + x_lo + tid] = s_keys[tid];
+    n_mine = n_mine < 0 ? 0 : (n_mine > slice ? slice : n_mine);
+    if (idx)
+        for (int x = tid; x < slice && x_lo + x < cap; x += 256) idx[(int64_t)h * cap + x_lo + x] = s_keys[x];
 
-    const int gi = tid / TPR, r = tid % TPR;
     float q[EPT];
-    DecIO<T>::unpack(*reinterpret_cast<const uint4 *>(Q + (int64_t)h * qs_h + (int64_t)i * qs_l + r * EPT), q);
+    DecIO<T>::unpack(q16, q);
     const T *Kg = K + (int64_t)g * ks_h + r * EPT;
     const T *Vg = V + (int64_t)g * vs_h + r * EPT;
     float m = -INFINITY, l = 0.f, o[EPT];
@@ -242,48 +333,33 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
             acc += s_o[x][tid] * w;
         }
         float *pp = part + ((int64_t)h * S + s) * (D + 2);
-        pp[2 + tid] = acc;
-        if (tid == 0) { pp[0] = M; pp[1] = ls; }
+        const auto put = [](float *p, float x) {
+            if constexpr (FUSE) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *p = x;
+        };
+        put(&pp[2 + tid], acc);
+        if (tid == 0) { put(&pp[0], M); put(&pp[1], ls); }
     }
+    if constexpr (!FUSE) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the compiler's order, and
+    __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0): the stores have reached the memory side
+    __syncthreads();
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(&done[h], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+    __syncthreads();
+    if (!s_last) return;
+
+    merge_slices<T, D, 256, true>(part + (int64_t)h * S * (D + 2), S, s_m, s_l, s_o, O_row + (int64_t)h * D);
 }
 
-// Merge of the S slice states of one head into the output row.  grid H_q, block 512:
-// the slices are dealt to 512 / D groups of D threads (thread = output column), whose
-// partial sums meet in LDS.
+// grid H_q
 template <typename T, int D>
 __global__ __launch_bounds__(512) void k_decode_combine(const float *__restrict__ part, int S, T *__restrict__ O_row) {
-    constexpr int NSG = 512 / D;
-    __shared__ float s_red[8];
-    __shared__ float s_ls[NSG];
-    __shared__ float s_acc[NSG][D];
-    const int h = blockIdx.x, tid = threadIdx.x, d = tid % D, sg = tid / D;
-    const float *pp = part + (int64_t)h * S * (D + 2);
-    // reference exponent: the largest slice maximum
-    float M = -INFINITY;
-    for (int s = tid; s < S; s += 512) M = fmaxf(M, pp[(int64_t)s * (D + 2)]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-    if ((tid & 63) == 0) s_red[tid >> 6] = M;
-    __syncthreads();
-    M = s_red[0];
-#pragma unroll
-    for (int x = 1; x < 8; ++x) M = fmaxf(M, s_red[x]);
-    float ls = 0.f, acc = 0.f;
-    for (int s = sg; s < S; s += NSG) {
-        const float *ps = pp + (int64_t)s * (D + 2);
-        const float w = (ps[0] == -INFINITY) ? 0.f : __expf(ps[0] - M);
-        ls += ps[1] * w;
-        acc += ps[2 + d] * w;
-    }
-    s_acc[sg][d] = acc;
-    if (d == 0) s_ls[sg] = ls;
-    __syncthreads();
-    if (tid < D) {
-        float L = 0.f, A = 0.f;
-#pragma unroll
-        for (int x = 0; x < NSG; ++x) { L += s_ls[x]; A += s_acc[x][tid]; }
-        DecIO<T>::store(O_row + (int64_t)h * D + tid, L > 0.f ? A / L : 0.f);
-    }
+    constexpr int NSG = 512 / (D / 2);
+    __shared__ float s_m[NSG], s_l[NSG];
+    __shared__ float s_o[NSG][D];
+    const int h = blockIdx.x;
+    merge_slices<T, D, 512, false>(part + (int64_t)h * S * (D + 2), S, s_m, s_l, s_o, O_row + (int64_t)h * D);
 }
 
 hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0,
@@ -292,11 +368,12 @@ hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_ca
     double *Kc = reinterpret_cast<double *>(w8 + dl.off_Kc), *Qc = reinterpret_cast<double *>(w8 + dl.off_Qc);
     double *Sc = reinterpret_cast<double *>(w8 + dl.off_Sc);
     int32_t *plan = reinterpret_cast<int32_t *>(w8 + dl.off_plan);
+    int32_t *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
     const int n_new = p.N_c - kc_valid;
     dim3 grid(n_new > 1 ? n_new : 1, p.H_kv + p.H_q), block(256);
 #define DHSA_POOLD(T, DD)                                                                                      \
     hipLaunchKernelGGL((k_pool_decode<T, DD>), grid, block, 0, s, (const T *)Q, (const T *)K,                  \
-                       plan + dl.pl.off_B, tail, plan + dl.pl.off_RB, Qc, Kc, p.H_kv, p.N_c, N_c_cap, kc_valid, rb0, \
+                       plan + dl.pl.off_B, tail, plan + dl.pl.off_RB, done, Qc, Kc, p.H_kv, p.N_c, N_c_cap, kc_valid, rb0, \
                        (int)p.L, p.B_r, p.pooling, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
     if (p.dtype == DHSA_F32) {
         if (p.D == 64) DHSA_POOLD(float, 64); else DHSA_POOLD(float, 128);
@@ -306,8 +383,11 @@ hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_ca
 #undef DHSA_POOLD
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scores_decode, dim3((p.N_c + 3) / 4, p.H_kv), dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap,
-                       p.D, p.G);
+    const dim3 sgrid((p.N_c + 63) / 64, p.H_kv, (p.G + 15) / 16);
+    if (p.D == 64)
+        hipLaunchKernelGGL(k_scores_decode<64>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
+    else
+        hipLaunchKernelGGL(k_scores_decode<128>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // ranking + walk of the one open group: group number N_q - 1 of the sequence, group 0 of this plan
     return launch_select_groups(p, dl.pl, Sc, plan, p.N_q - 1, 1, s);
@@ -318,15 +398,24 @@ hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, 
     char *w8 = static_cast<char *>(ws);
     const int32_t *plan = reinterpret_cast<const int32_t *>(w8 + dl.off_plan);
     float *part = reinterpret_cast<float *>(w8 + dl.off_part);
-    const int S = (p.N_b + kDecSlice - 1) / kDecSlice;   // N_b is clamped to L: the row takes exactly N_b keys
+    int32_t *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
+    const int slice = decode_slice(p.H_q, p.N_b);
+    const int S = (p.N_b + slice - 1) / slice;           // N_b is clamped to L: the row takes exactly N_b keys
     dim3 grid(S, p.H_q), block(256);
+    const bool fuse = slice == kDecSliceFew;
+#define DHSA_ATTD1(T, DD, FUSE)                                                                                   \
+    hipLaunchKernelGGL((k_attn_decode<T, DD, FUSE>), grid, block, 0, s, plan + dl.pl.off_B, plan + dl.pl.off_count, \
+                       plan + dl.pl.off_entries, dl.pl.stride, rb0, (int)p.L, (const T *)Q, (const T *)K,         \
+                       (const T *)V, part, S, slice, done, (T *)O_row, idx, p.N_b, cnt, p.G, p.scale, p.qs_h,     \
+                       p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l)
 #define DHSA_ATTD(T, DD)                                                                                          \
     do {                                                                                                          \
-        hipLaunchKernelGGL((k_attn_decode<T, DD>), grid, block, 0, s, plan + dl.pl.off_B, plan + dl.pl.off_count, \
-                           plan + dl.pl.off_entries, dl.pl.stride, rb0, (int)p.L, (const T *)Q, (const T *)K,     \
-                           (const T *)V, part, S, idx, p.N_b, cnt, p.G, p.scale, p.qs_h, p.qs_l, p.ks_h, p.ks_l,  \
-                           p.vs_h, p.vs_l);                                                                       \
-        hipLaunchKernelGGL((k_decode_combine<T, DD>), dim3(p.H_q), dim3(512), 0, s, part, S, (T *)O_row);         \
+        if (fuse) {                                                                                               \
+            DHSA_ATTD1(T, DD, true);                                                                              \
+        } else {                                                                                                  \
+            DHSA_ATTD1(T, DD, false);                                                                             \
+            hipLaunchKernelGGL((k_decode_combine<T, DD>), dim3(p.H_q), dim3(512), 0, s, part, S, (T *)O_row);     \
+        }                                                                                                         \
     } while (0)
     if (p.dtype == DHSA_F32) {
         if (p.D == 64) DHSA_ATTD(float, 64); else DHSA_ATTD(float, 128);
@@ -334,6 +423,7 @@ hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, 
         if (p.D == 64) DHSA_ATTD(bf16_t, 64); else DHSA_ATTD(bf16_t, 128);
     }
 #undef DHSA_ATTD
+#undef DHSA_ATTD1
     return hipGetLastError();
 }
 

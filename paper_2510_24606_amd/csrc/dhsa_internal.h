@@ -67,11 +67,19 @@ struct WsLayout {
 // The "plan" is a one-group plan: B [N_c_cap + 1], RB [2], count [H_q], entries [H_q][stride][2]
 // (room for stride = N_c_cap), laid out by `pl` in words from off_plan.
 struct DecodeLayout {
-    int64_t off_Kc, off_Qc, off_Sc, off_plan, off_part, bytes;
+    int64_t off_Kc, off_Qc, off_Sc, off_plan, off_part, off_done, bytes;
     PlanLayout pl;
     int S_cap;   // most key slices (workgroups per head) of the attention step
 };
-constexpr int kDecSlice = 128;   // selected keys per workgroup of the decode attention step
+// Selected keys per workgroup of the decode attention step: 32 while longer slices would not make a workgroup for
+// every CU (a chain of loads then takes the time, and four times as many run side by side); else 128 and more, so many
+// that the workgroups fit the chip at once (five per CU of the bf16 kernel at D = 128).
+constexpr int kDecSlice = 128, kDecSliceFew = 32, kDecSliceMax = 512;
+inline int decode_slice(int H_q, int64_t N_b) {
+    if (H_q * ((N_b + kDecSlice - 1) / kDecSlice) < 256) return kDecSliceFew;
+    const int64_t at_once = 5 * 256 / H_q > 0 ? 5 * 256 / H_q : 1, slice = ((N_b + at_once - 1) / at_once + 15) / 16 * 16;
+    return (int)(slice < kDecSlice ? kDecSlice : slice > kDecSliceMax ? kDecSliceMax : slice);
+}
 // Boundaries B[kc_valid .. kc_valid + n] of the chunks a decoding step pools anew, passed by
 // value when they are few (n = 0: the kernels read all boundaries from the workspace).
 constexpr int kBoundaryTailMax = 6;

@@ -101,3 +101,27 @@ def test_ranking_bins_cuts_and_ties(L, lens, N_b, keys, B_r):
         idx, cnt = dhsa.dhsa_plan_expand_rows(prob, plan, h, rows)
         np.testing.assert_array_equal(cnt.cpu().numpy(), ref[2][h])
         np.testing.assert_array_equal(idx.cpu().numpy(), ref[1][h][:, :idx.shape[1]])
+
+
+@pytest.mark.parametrize("L,H_q,H_kv,D,dtype,N_b,B_r", [(900, 20, 1, 128, "bf16", 31, 0),      # > 16 heads of one kv-head
+                                                        (2000, 17, 1, 64, "f32", 1700, 0),
+                                                        (5000, 8, 8, 128, "bf16", 4095, 0),    # 128 short slices
+                                                        (9000, 8, 2, 64, "bf16", 4097, 0),     # 33 long ones
+                                                        (9000, 4, 1, 128, "f32", 8300, 0),
+                                                        (3000, 2, 1, 128, "bf16", 1, 64)])
+def test_decode_heads_slices_and_merge(L, H_q, H_kv, D, dtype, N_b, B_r):
+    w = dhsa_inputs.make("c1" if dtype == "f32" else "c3", L=L, H_q=H_q, H_kv=H_kv, D=D, N_b=N_b)
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    prob = dhsa.problem(Q, K, w.B, w.N_b, B_r=B_r)
+    ws = dhsa.alloc_decode(prob, w.N_c + 3, L + 100)
+    ws.fill_(255)
+    O_ref, I_ref, c_ref = oracle.decode_row(w.f32("Q"), w.f32("K"), w.f32("V"), w.B, w.N_b, B_r=B_r)
+    first = None
+    for valid in (0, w.N_c - 1, w.N_c - 1):            # the workspace serves step after step
+        O, idx, cnt = dhsa.dhsa_decode_step(prob, Q, K, V, w.B, ws, w.N_c + 3, L + 100, valid, want_idx=True)
+        np.testing.assert_array_equal(cnt.cpu().numpy(), c_ref)
+        np.testing.assert_array_equal(idx.cpu().numpy(), I_ref[:, :idx.shape[1]])
+        err = np.abs(O.float().cpu().numpy().astype(np.float64) - O_ref).max()
+        assert err <= (1e-5 if dtype == "f32" else 2e-2), err
+        first = O if first is None else first
+        assert torch.equal(first, O)                   # whichever workgroup merges, the order of the sum is the same
