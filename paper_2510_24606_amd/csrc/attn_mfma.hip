@@ -305,7 +305,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int x = 0; x < 16; ++x) oacc[db][x] = 0.f;
-    float m_ref = pad_row ? 1e30f : -INFINITY, l_run = 0.f;   // m_ref: reference used in the exponent (see DHSA_EXP)
+    float mc = pad_row ? 1e30f : __builtin_nanf(""), l_run = 0.f;   // reference used in the exponent (see DHSA_EXP)
 
     // staging: load instruction c of this wave fills LDS window (4 c + wave) of a
     // tile (1 KiB = 64 pieces); this lane's piece there is physical piece
@@ -383,37 +383,36 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2((S - m_ref) * c) with row sums, rounded to the two bf16 MFMA B operands
-// of the block.  m_ref is a REFERENCE for the exponent, not the running maximum:
+// P = exp2(S c - mc) with row sums, rounded to the two bf16 MFMA B operands
+// of the block.  mc is a REFERENCE for the exponent, not the running maximum:
 // O / l at the end is exact whatever reference was used, so it only has to keep
 // the exponentials in range.  It is set from the first block and moved up (with
 // a rescale of l and O) only when a block's exponentials grow past 2^20, which
-// the row sums reveal without a per-block maximum.  A row keeps m_ref = -inf
-// (and p = 0) until it meets its first unmasked key.
+// the row sums reveal without a per-block maximum.  A row keeps mc = NaN, which sends
+// it through the second branch, until it meets its first unmasked key.
 #define DHSA_EXP(sacc, pf)                                                                      \
     {                                                                                           \
-        float mc_ = (m_ref == -INFINITY) ? 0.f : m_ref * scale_log2e;                           \
         float psum_ = 0.f;                                                                      \
         _Pragma("unroll") for (int x = 0; x < 16; ++x) {                                        \
-            const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - mc_);               \
+            const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - mc);                \
             psum_ += e_;                                                                        \
             pf[x >> 3][x & 7] = (__bf16)e_;                                                     \
         }                                                                                       \
         /* too large, inf or NaN, or no reference yet (then nothing has been accumulated) */     \
-        if (__any(!(psum_ < 1048576.f) || m_ref == -INFINITY)) {                                \
+        if (__any(!(psum_ < 1048576.f))) {                                                      \
             float mx_;                                                                          \
             DHSA_ROWMAX(sacc, mx_);                                                             \
-            const float m_new_ = fmaxf(m_ref, mx_);                                             \
-            const float alpha_ = (m_ref == -INFINITY) ? 0.f                                     \
-                                 : __builtin_amdgcn_exp2f((m_ref - m_new_) * scale_log2e);      \
+            const float m_new_ = fmaxf(mc, mx_ * scale_log2e);   /* the other one if one is NaN */ \
+            const bool none_ = m_new_ == -INFINITY;                                             \
+            const float alpha_ = (mc != mc) ? 0.f : __builtin_amdgcn_exp2f(mc - m_new_);        \
             l_run *= alpha_;                                                                    \
             _Pragma("unroll") for (int db = 0; db < NDB; ++db)                                  \
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) oacc[db][x] *= alpha_;           \
-            m_ref = m_new_;                                                                     \
-            mc_ = (m_ref == -INFINITY) ? 0.f : m_ref * scale_log2e;                             \
+            const float ref_ = none_ ? 0.f : m_new_;                                            \
+            mc = none_ ? __builtin_nanf("") : m_new_;                                           \
             psum_ = 0.f;                                                                        \
             _Pragma("unroll") for (int x = 0; x < 16; ++x) {                                    \
-                const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - mc_);           \
+                const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - ref_);          \
                 psum_ += e_;                                                                    \
                 pf[x >> 3][x & 7] = (__bf16)e_;                                                 \
             }                                                                                   \
@@ -467,7 +466,11 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
             }
             DHSA_QK(0, s_a);
             DHSA_MASK(0, 0, s_a, fl_cur);
-            if (e0 == 0) { float mx0; DHSA_ROWMAX(s_a, mx0); m_ref = fmaxf(m_ref, mx0); }   // reference = row maxima of the first block
+            if (e0 == 0) {   // reference = row maxima of the first block
+                float mx0;
+                DHSA_ROWMAX(s_a, mx0);
+                if (mx0 != -INFINITY) mc = fmaxf(mc, mx0 * scale_log2e);
+            }
         }
         __syncthreads();                      // the lower half of K(0) may be overwritten from here on
 
@@ -629,7 +632,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
     // get q = 0 and, through a huge exponent reference, p = 0.
     bf16x8 qf[RW][NT];
     int v_i[RW];
-    float m_ref[RW], l_run[RW];
+    float mc[RW], l_run[RW];
     f32x4 oacc[RW][NJ];
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
@@ -639,7 +642,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         const uint16_t *qp = Q + (int64_t)h * qs_h + (int64_t)(row0 + (pad_row ? nrows - 1 : rr)) * qs_l + 8 * q;
 #pragma unroll
         for (int t = 0; t < NT; ++t) qf[r][t] = *reinterpret_cast<const bf16x8 *>(qp + 32 * t);
-        m_ref[r] = pad_row ? 1e30f : -INFINITY;
+        mc[r] = pad_row ? 1e30f : __builtin_nanf("");
         l_run[r] = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) oacc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -670,23 +673,29 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         for (int j = 0; j < NJ; ++j)
             v_off[j] = 2 * (kbw * 32 + key) * D + 16 * ((2 * j + (c >> 1)) ^ piece_swizzle(key, OPR)) + 8 * (c & 1);
     }
-    const char *const smK8 = reinterpret_cast<const char *>(sm.K);
-    const char *const smV8 = reinterpret_cast<const char *>(sm.V);
+    typedef __attribute__((address_space(3))) char lds_char;
+    lds_char *const smK8 = (lds_char *)sm.K, *const smV8 = (lds_char *)sm.V;
 
     for (int e0 = 0; e0 < E; e0 += kSegB) {
         DHSA_SEGMENT_TABLE(e0);
         const int ntiles = (total + kKT - 1) / kKT;
         if (ntiles == 0) continue;
 
-// S^T of this wave's 32-key block of the K buffer k_off points into, all row blocks
-#define DHSA_QK16(sacc)                                                                         \
+// S^T of this wave's 32-key block of the K buffer k_off points into, all row blocks.  LOAD(u), u = 0 .. 2 KPT - 1, is
+// called between the products: a load takes the memory pipeline 16 cycles, so four waves that
+// hand over all of theirs at once stand still until it has taken them.
+#define DHSA_QK16(sacc, LOAD)                                                                   \
     {                                                                                           \
+        bf16x8 kf_[2][NT];                                                                      \
+        _Pragma("unroll") for (int kh = 0; kh < 2; ++kh)                                        \
+            _Pragma("unroll") for (int t = 0; t < NT; ++t)                                      \
+                kf_[kh][t] = *(bf16x8 __attribute__((address_space(3))) *)(smK8 + k_off[t] + kh * 32 * D); \
         _Pragma("unroll") for (int kh = 0; kh < 2; ++kh) {                                      \
             _Pragma("unroll") for (int r = 0; r < RW; ++r) sacc[r][kh] = f32x4{0.f, 0.f, 0.f, 0.f}; \
             _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                    \
-                const bf16x8 kf_ = *reinterpret_cast<const bf16x8 *>(smK8 + k_off[t] + kh * 32 * D); \
                 _Pragma("unroll") for (int r = 0; r < RW; ++r)                                  \
-                    sacc[r][kh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf_, qf[r][t], sacc[r][kh], 0, 0, 0); \
+                    sacc[r][kh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf_[kh][t], qf[r][t], sacc[r][kh], 0, 0, 0); \
+                LOAD(kh * NT + t);                                                              \
             }                                                                                   \
         }                                                                                       \
     }
@@ -717,35 +726,41 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2((S - m_ref) c) per row block, with the lazily moved exponent reference of the kernel above
+// P = exp2(S c - mc) per row block, with the lazily moved exponent reference of the kernel above
 #define DHSA_EXP16(sacc, pf)                                                                    \
-    _Pragma("unroll") for (int r = 0; r < RW; ++r) {                                            \
-        float mc_ = (m_ref[r] == -INFINITY) ? 0.f : m_ref[r] * scale_log2e;                     \
-        float psum_ = 0.f;                                                                      \
-        _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                         \
-            const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - mc_); \
-            psum_ += e_;                                                                        \
-            pf[r][x] = (__bf16)e_;                                                              \
-        }                                                                                       \
-        if (__any(!(psum_ < 1048576.f) || m_ref[r] == -INFINITY)) {                             \
-            float mx_;                                                                          \
-            DHSA_ROWMAX16(sacc[r], mx_);                                                        \
-            const float m_new_ = fmaxf(m_ref[r], mx_);                                          \
-            const float alpha_ = (m_ref[r] == -INFINITY) ? 0.f                                  \
-                                 : __builtin_amdgcn_exp2f((m_ref[r] - m_new_) * scale_log2e);   \
-            l_run[r] *= alpha_;                                                                 \
-            _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                      \
-                _Pragma("unroll") for (int x = 0; x < 4; ++x) oacc[r][j][x] *= alpha_;          \
-            m_ref[r] = m_new_;                                                                  \
-            mc_ = (m_ref[r] == -INFINITY) ? 0.f : m_ref[r] * scale_log2e;                       \
-            psum_ = 0.f;                                                                        \
+    {                                                                                           \
+        float psum_[RW];                                                                        \
+        bool far_ = false;                                                                      \
+        _Pragma("unroll") for (int r = 0; r < RW; ++r) {                                        \
+            psum_[r] = 0.f;                                                                     \
             _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                     \
-                const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - mc_); \
-                psum_ += e_;                                                                    \
+                const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - mc[r]); \
+                psum_[r] += e_;                                                                 \
                 pf[r][x] = (__bf16)e_;                                                          \
             }                                                                                   \
+            far_ |= !(psum_[r] < 1048576.f);                                                    \
         }                                                                                       \
-        l_run[r] += psum_;                                                                      \
+        if (__any(far_)) {                                                                      \
+            _Pragma("unroll") for (int r = 0; r < RW; ++r) {                                    \
+                float mx_;                                                                      \
+                DHSA_ROWMAX16(sacc[r], mx_);                                                    \
+                const float m_new_ = fmaxf(mc[r], mx_ * scale_log2e);                           \
+                const bool none_ = m_new_ == -INFINITY;                                         \
+                const float alpha_ = (mc[r] != mc[r]) ? 0.f : __builtin_amdgcn_exp2f(mc[r] - m_new_); \
+                l_run[r] *= alpha_;                                                             \
+                _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                  \
+                    _Pragma("unroll") for (int x = 0; x < 4; ++x) oacc[r][j][x] *= alpha_;      \
+                const float ref_ = none_ ? 0.f : m_new_;                                        \
+                mc[r] = none_ ? __builtin_nanf("") : m_new_;                                    \
+                psum_[r] = 0.f;                                                                 \
+                _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                 \
+                    const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - ref_); \
+                    psum_[r] += e_;                                                             \
+                    pf[r][x] = (__bf16)e_;                                                      \
+                }                                                                               \
+            }                                                                                   \
+        }                                                                                       \
+        _Pragma("unroll") for (int r = 0; r < RW; ++r) l_run[r] += psum_[r];                    \
     }
 
 // O^T += V^T P^T for this wave's 32-key block of the V buffer v_off points into
@@ -754,92 +769,79 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         union { s16x4 h[2]; bf16x8 v; } vf_;                                                    \
         _Pragma("unroll") for (int kh = 0; kh < 2; ++kh)                                        \
             vf_.h[kh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(                                \
-                (s16x4 __attribute__((address_space(3))) *)(smV8 + v_off[j] + kh * 32 * D));    \
+                (s16x4 __attribute__((address_space(3))) *)(smV8 + v_off[j] + kh * 32 * D)); \
         _Pragma("unroll") for (int r = 0; r < RW; ++r)                                          \
             oacc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf_.v, pf[r], oacc[r][j], 0, 0, 0); \
     }
 
-        f32x4 s_a[RW][2], s_b[RW][2];
+        f32x4 s_a[RW][2];
         int toggle = 2 * kTile;
         unsigned ko_lo[KPT], ko_hi[KPT], vo[KPT];
         if (wave < ntiles) DHSA_MAKE_META(wave);
         __syncthreads();
-        // ---- prologue: K(0), V(0), K(1) in LDS; S(0, own block) ----
+        // ---- prologue: K(0), V(0) in LDS ----
         DHSA_OFFS(ko_lo, key_koff, 0, 0, KPT / 2);
         DHSA_OFFS(ko_hi, key_koff, 0, KPT / 2, KPT);
         DHSA_OFFS(vo, key_voff, 0, 0, KPT);
         DHSA_LOAD_K_LO(0);
         DHSA_LOAD_K_HI(0);
         DHSA_LOAD_V(0);
-        if (ntiles > 1) {
-            DHSA_OFFS(ko_lo, key_koff, 1, 0, KPT / 2);
-            DHSA_OFFS(ko_hi, key_koff, 1, KPT / 2, KPT);
-            DHSA_LOAD_K_LO(1);
-            DHSA_LOAD_K_HI(1);
+        if (e0 == 0) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (rbase + 16 * r + n16 >= nrows) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) qf[r][t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                }
         }
-        const int fl_0 = __builtin_amdgcn_readfirstlane(sm.flags[0]);
         __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         __syncthreads();
-        if (wave_live) {
-            if (e0 == 0) {
-#pragma unroll
-                for (int r = 0; r < RW; ++r)
-                    if (rbase + 16 * r + n16 >= nrows) {
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) qf[r][t] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                    }
-            }
-            DHSA_QK16(s_a);
-            DHSA_MASK16(0, s_a, fl_0);
-            if (e0 == 0) {   // reference = row maxima of this wave's first block
-#pragma unroll
-                for (int r = 0; r < RW; ++r) { float mx0; DHSA_ROWMAX16(s_a[r], mx0); m_ref[r] = fmaxf(m_ref[r], mx0); }
-            }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) k_off[t] += 2 * kTile;   // K offsets run one tile ahead of V offsets
-        }
-        __syncthreads();                      // K(0) may be overwritten from here on
 
-        int n = 0;
-        for (; n + 1 < ntiles; ++n) {
-            DHSA_OFFS(ko_lo, key_koff, n + 2, 0, KPT / 2);
-            DHSA_OFFS(ko_hi, key_koff, n + 2, KPT / 2, KPT);
+        // Tile n: scores, exponentials, O += P V, while K(n+1) and V(n+1) are on their way into the other buffers
+        for (int n = 0; n < ntiles; ++n) {
+            const bool more = n + 1 < ntiles;
+            DHSA_OFFS(ko_lo, key_koff, n + 1, 0, KPT / 2);
+            DHSA_OFFS(ko_hi, key_koff, n + 1, KPT / 2, KPT);
             DHSA_OFFS(vo, key_voff, n + 1, 0, KPT);
-            const int fl_next = __builtin_amdgcn_readfirstlane(sm.flags[(n + 1) & 7]);
-            if (n + 2 < ntiles) { DHSA_LOAD_K_LO(n + 2); DHSA_LOAD_K_HI(n + 2); }   // over K(n)
-            DHSA_LOAD_V(n + 1);                                                    // over V(n-1)
+            const int fl = __builtin_amdgcn_readfirstlane(sm.flags[n & 7]);
             if ((n & 3) == 0 && n + 4 + wave < ntiles) DHSA_MAKE_META(n + 4 + wave);
+            const unsigned dst = (((n + 1) & 1) * kTile + wave_u * 512) * 2;
+            const auto load = [&](int u) {    // u-th load of the iteration
+                if (!more) return;
+                if (u < KPT) load16_to_lds(Kg8, (u < KPT / 2 ? ko_lo[u] : ko_hi[u]) + ld_piece_bytes_k, lds_K + dst + u * 4096);
+                else load16_to_lds(Vg8, vo[u - KPT] + ld_piece_bytes_v, lds_V + dst + (u - KPT) * 4096);
+            };
             if (wave_live) {
                 bf16x8 pf[RW];
-                DHSA_QK16(s_b);
+                DHSA_QK16(s_a, load);
+                DHSA_MASK16(n, s_a, fl);
+                if (e0 == 0 && n == 0) {      // reference = row maxima of this wave's first block
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) {
+                        float mx0;
+                        DHSA_ROWMAX16(s_a[r], mx0);
+                        if (mx0 != -INFINITY) mc[r] = fmaxf(mc[r], mx0 * scale_log2e);
+                    }
+                }
                 DHSA_EXP16(s_a, pf);
                 DHSA_PV16(pf);
-                DHSA_MASK16(n + 1, s_b, fl_next);
 #pragma unroll
-                for (int r = 0; r < RW; ++r) { s_a[r][0] = s_b[r][0]; s_a[r][1] = s_b[r][1]; }
-#pragma unroll
-                for (int t = 0; t < NT; ++t) k_off[t] -= toggle;
+                for (int t = 0; t < NT; ++t) k_off[t] += toggle;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) v_off[j] += toggle;
                 toggle = -toggle;
-            }
-            __builtin_amdgcn_s_waitcnt(0x0f70);
-            __syncthreads();
-        }
-        if (wave_live) {                          // last tile of the batch
-            bf16x8 pf[RW];
-            DHSA_EXP16(s_a, pf);
-            DHSA_PV16(pf);
-        }
-        __syncthreads();                          // LDS is reused by the next batch / the merge
-        if (wave_live) {                          // leave the offsets at buffer 0 for the next batch
-            if (ntiles & 1) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) k_off[t] -= 2 * kTile;
             } else {
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) v_off[j] -= 2 * kTile;
+                for (int u = 0; u < 2 * KPT; ++u) load(u);
             }
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the pieces this wave requested have landed
+            __syncthreads();                      // (after the last tile: LDS is reused by the next batch / the merge)
+        }
+        if (wave_live && (ntiles & 1)) {          // leave the offsets at buffer 0 for the next batch
+#pragma unroll
+            for (int t = 0; t < NT; ++t) k_off[t] -= 2 * kTile;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) v_off[j] -= 2 * kTile;
         }
 #undef DHSA_QK16
 #undef DHSA_MASK16
@@ -858,7 +860,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         if (wave_live && kbw == 1) {
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
-                xch[(r * (2 + 4 * NJ)) * 64] = m_ref[r];
+                xch[(r * (2 + 4 * NJ)) * 64] = mc[r];
                 xch[(r * (2 + 4 * NJ) + 1) * 64] = l_run[r];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
@@ -871,9 +873,9 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
                 const float m1 = xch[(r * (2 + 4 * NJ)) * 64], l1 = xch[(r * (2 + 4 * NJ) + 1) * 64];
-                const float mm = fmaxf(m_ref[r], m1);
-                const float a0 = (m_ref[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_ref[r] - mm) * scale_log2e);
-                const float a1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m1 - mm) * scale_log2e);
+                const float mm = fmaxf(mc[r], m1);      // NaN: no key seen (and then the other one is taken)
+                const float a0 = (mc[r] != mc[r]) ? 0.f : __builtin_amdgcn_exp2f(mc[r] - mm);
+                const float a1 = (m1 != m1) ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
                 l_run[r] = l_run[r] * a0 + l1 * a1;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
