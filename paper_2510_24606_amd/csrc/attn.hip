@@ -48,6 +48,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
     struct Merge {
         float o[4][NR][kPad];
         float m[4][NR], l[4][NR];
+        int odd[4];
     };
     __shared__ __align__(16) union { Lists li; Merge me; } sm;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,6 +105,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
             for (int j = 0; j < 4; ++j) oacc[r][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
+    bool odd = false;                // infinities or NaN of V were left out of the products
     for (int e0 = 0; e0 < E; e0 += kF32Seg) {
         // segments (entries some row takes a key from) of this batch, compacted
         if (e0 > 0) {
@@ -210,6 +212,27 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
                         lsum[r] += s[r][i];
                     }
                 }
+                // Infinities and NaN in V of a block with keys that not every row takes: 0 V does not keep them out of
+                // the other rows, so the products get zeros and the rows that take them get them at the end.
+                if (__any(max(max(lo.x, lo.y), max(lo.z, lo.w)) >= v_lo || min(min(hi.x, hi.y), min(hi.z, hi.w)) <= v_hi)) {
+                    float z = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) z = __builtin_fmaf(vf[i][t][j], 0.f, z);
+                    if (__any(z != 0.f)) {
+                        odd = true;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                                for (int j = 0; j < 4; ++j)
+                                    vf[i][t][j] = fabsf(vf[i][t][j]) < INFINITY ? vf[i][t][j] : 0.f;
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -229,6 +252,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
 
     // ---- merge of the four waves, normalisation, store ----
     __syncthreads();                 // the lists are dead
+    if (lane == 0) sm.me.odd[wave] = odd;
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
         lsum[r] += __shfl_xor(lsum[r], 16);
@@ -260,7 +284,21 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
             acc += *reinterpret_cast<const f32x4 *>(&sm.me.o[w][r][d]) * a;
         }
         const float inv = L > 0.f ? 1.f / L : 0.f;   // a row that sees no key of its block's list: zeros
-        *reinterpret_cast<f32x4 *>(O + (int64_t)h * os_h + (int64_t)(row0 + r) * os_l + d) = acc * inv;
+        acc *= inv;
+        if (sm.me.odd[0] | sm.me.odd[1] | sm.me.odd[2] | sm.me.odd[3]) {
+            for (int e = 0; e < E; ++e) {
+                const int2 w = ent[e];
+                const int k = w.x & kChunkMask, pos = w.x >> kPosShift, b0 = pv.B[k];
+                int take = entry_take(pos, w.y, pv.B[k + 1] - b0, v_lo + r);
+                if (pos == 3 && row0 + r + 1 - b0 < take) take = row0 + r + 1 - b0;   // listed keys past the row
+                for (int t = 0; t < take; ++t) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(V + (int64_t)g * vs_h + (int64_t)(b0 + t) * vs_l + d);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[j] += fabsf(v[j]) < INFINITY ? 0.f : v[j];
+                }
+            }
+        }
+        *reinterpret_cast<f32x4 *>(O + (int64_t)h * os_h + (int64_t)(row0 + r) * os_l + d) = acc;
     }
 }
 

@@ -125,3 +125,66 @@ def test_decode_heads_slices_and_merge(L, H_q, H_kv, D, dtype, N_b, B_r):
         assert err <= (1e-5 if dtype == "f32" else 2e-2), err
         first = O if first is None else first
         assert torch.equal(first, O)                   # whichever workgroup merges, the order of the sum is the same
+
+
+@pytest.mark.parametrize("L,N_b,chunk", [(400, 40, 4), (2400, 100, 4), (4800, 400, 4)])      # one, two and four waves a row
+def test_ranking_of_infinite_and_nan_scores(L, N_b, chunk):
+    """Scores far below the rest leave all others in one bin, which is cut again; NaN rank beyond the infinities, on the
+    side of their sign, as the 64-bit images of the scores do."""
+    rng = np.random.default_rng(L)
+    B = np.arange(0, L + 1, chunk, dtype=np.int32)
+    N_c = len(B) - 1
+    Q = torch.from_numpy(rng.standard_normal((16, L, 64)).astype(np.float32))
+    K = torch.from_numpy(rng.standard_normal((1, L, 64)).astype(np.float32))
+    Q[:, :, 0] = 1.0 + 0.1 * Q[:, :, 0]
+    K[0, B[3], 0] = -1e7                                                     # the outlier
+    for k in range(5, N_c, 9):
+        K[0, B[k], 1] = float(np.copysign(np.nan, 1 if k % 2 else -1))
+    for k in range(7, N_c, 40):
+        K[0, B[k], 0] = float("inf") if k % 80 < 40 else float("-inf")
+    Q, K = Q.cuda(), K.cuda()
+    prob = dhsa.problem(Q, K, B, N_b)
+    plan, ws = dhsa.alloc(prob, B)
+    dhsa.dhsa_route(prob, Q, K, B, plan, ws)
+    S = dhsa.dhsa_debug_scores(prob, B, ws).cpu().numpy()
+    assert np.isnan(S[:, -1]).any() and np.isinf(S[:, -1]).any()
+    rows = np.array([0, L // 2 + 1, L - 3, L - 1], dtype=np.int64)
+    for h in (0, 15):
+        idx, cnt = dhsa.dhsa_plan_expand_rows(prob, plan, h, rows)
+        for t, i in enumerate(rows):
+            l = i // chunk
+            u = (S[h, l, :l + 1] + 0.0).view(np.uint64)
+            key = np.where(u >> np.uint64(63), ~u, u | np.uint64(1 << 63))
+            left, want = N_b, []
+            for k in np.lexsort((np.arange(l + 1), np.uint64(2**64 - 1) - key)):
+                n = min(left, i + 1 - B[k] if k == l else chunk)
+                want += range(B[k], B[k] + n)
+                left -= n
+            assert cnt[t].item() == len(want)
+            np.testing.assert_array_equal(idx[t, :len(want)].cpu().numpy(), np.sort(want))
+
+
+@pytest.mark.parametrize("L,D,B_r", [(300, 64, 0), (300, 128, 96), (4100, 64, 0), (4100, 128, 0)])
+def test_f32_infinite_values_reach_only_the_rows_that_take_them(L, D, B_r):
+    """Rows of a workgroup share blocks of keys that not all of them take (16- and 32-row pieces, both forms)."""
+    w = dhsa_inputs.make("c1", L=L, H_q=8, H_kv=2, D=D, N_b=60, lens=("uniform", 16, 64))
+    for j, (d, x) in enumerate([(3, float("inf")), (5, float("-inf")), (D - 1, float("nan")), (3, float("-inf"))]):
+        w.V[:, (2 * j + 1) * L // 9, d] = x
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    O = torch.empty_like(Q)
+    prob = dhsa.problem(Q, K, w.B, w.N_b, B_r=B_r)
+    plan, ws = dhsa.alloc(prob, w.B)
+    dhsa.dhsa_prefill(prob, Q, K, V, w.B, O, plan, ws)
+    rows = np.arange(0, L, 1 if L < 2000 else 7, dtype=np.int64)
+    Vh = w.f32("V")
+    odd = np.where(np.isfinite(Vh), 0.0, Vh)
+    args = (w.f32("Q"), w.f32("K"), np.where(np.isfinite(Vh), Vh, 0.0).astype(np.float32), w.B)
+    ref, I, cnt = oracle.prefill_rows_blocks(*args, B_r, w.N_b, rows) if B_r else oracle.prefill_rows(*args, w.N_b, rows)
+    for h in range(8):
+        for t, i in enumerate(rows):
+            sel = I[h, t, :cnt[h, t]]
+            with np.errstate(invalid="ignore"):
+                ref[h, t] += odd[h // 4][sel[sel <= i]].sum(0)               # a row block's list reaches past the row
+    got = O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
+    assert not np.isfinite(ref).all() and np.isfinite(ref).any()
+    np.testing.assert_allclose(got, ref, rtol=0, atol=1e-4)
