@@ -421,6 +421,11 @@ __device__ __forceinline__ unsigned long long score_key(double s) {
     const unsigned long long u = (unsigned long long)__double_as_longlong(s);
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
+// The score rounded to fp32, in the order of score_key: a NaN lies outside all other scores, on the side of its sign.
+__device__ __forceinline__ float score_f32(double s) {
+    const float f = (float)s;
+    return f == f ? f : __builtin_copysignf(INFINITY, f);
+}
 __device__ __forceinline__ double key_score(unsigned long long k) {
     return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
 }
@@ -603,13 +608,12 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     if (n <= kSlab) load(0);
     const unsigned long long k_own = score_key(own >= 0 ? row[own] : 0.0);
     float lo = INFINITY, hi = -INFINITY, inv;
-    DHSA_SEL_FOR({ (void)x; (void)in; (void)n_tok; lo = fminf(lo, (float)s); hi = fmaxf(hi, (float)s); })
+    DHSA_SEL_FOR({ (void)x; (void)in; (void)n_tok; lo = fminf(lo, score_f32(s)); hi = fmaxf(hi, score_f32(s)); })
     row_range(lo, hi);
     if constexpr (NW == 1) wave_lds_fence();   // hist is clear (NW > 1: row_range has a barrier)
     const float best = hi;
     const auto bin_of = [&](double s) {  // never decreasing as s falls
-        const int b = (int)((hi - (float)s) * inv);
-        return b < 0 ? 0 : b < kSelBins - 1 ? b : kSelBins - 1;
+        return (int)fminf(fmaxf((hi - score_f32(s)) * inv, 0.f), (float)(kSelBins - 1));   // inf - inf: bin 0
     };
 
     // candidates: chunks ranked at or before (cut_key, cut_id) once that is known (cut), or those of the bins up to tbin
@@ -630,7 +634,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
             sync();
             DHSA_SEL_AGAIN({
-                if (in && (cut ? is_cand(s, x) : ((float)s >= lo && (float)s <= hi)))
+                if (in && (cut ? is_cand(s, x) : (score_f32(s) >= lo && score_f32(s) <= hi)))
                     atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull);
             })
         }
@@ -669,7 +673,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             float worst = INFINITY, none = -INFINITY;
             DHSA_SEL_AGAIN({
                 (void)x; (void)n_tok;
-                if (in && ((float)s > hi || ((float)s >= lo && bin_of(s) <= tbin))) worst = fminf(worst, (float)s);
+                if (in && (score_f32(s) > hi || (score_f32(s) >= lo && bin_of(s) <= tbin))) worst = fminf(worst, score_f32(s));
             })
             row_range(worst, none);
             lo = worst;
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             DHSA_SEL_AGAIN({
                 (void)x; (void)n_tok;
                 const unsigned long long k = score_key(s);
-                if (in && (float)s >= worst && k < key_lo) key_lo = k;
+                if (in && score_f32(s) >= worst && k < key_lo) key_lo = k;
             })
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
@@ -697,7 +701,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             float a = INFINITY, z = -INFINITY;
             DHSA_SEL_AGAIN({
                 (void)x; (void)n_tok;
-                if (in && (float)s >= lo && (float)s <= hi && bin_of(s) == tbin) { a = fminf(a, (float)s); z = fmaxf(z, (float)s); }
+                if (in && score_f32(s) >= lo && score_f32(s) <= hi && bin_of(s) == tbin) { a = fminf(a, score_f32(s)); z = fmaxf(z, score_f32(s)); }
             })
             above = before;
             row_range(a, z);
@@ -724,7 +728,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
                 if (row_sum(sum) < (unsigned long long)N_b) id0 = id;
             }
             cut_id = id0;
-            lo = (float)key_score(cut_key);
+            lo = score_f32(key_score(cut_key));
         }
         cut = true;                      // one more level: the bins of the candidates alone
         above = 0ull;
