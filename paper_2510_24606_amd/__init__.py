@@ -130,9 +130,9 @@ def problem(Q, K, B, N_b: int, scale: float = 0.0, B_r: int = 0, pooling: int = 
     H_q, L, D = Q.shape
     H_kv = K.shape[0]
     dt = _DTYPES.get(Q.dtype, -1)
-    q_h, q_l, _ = Q.stride()
-    k_h, k_l, _ = K.stride()
-    v_h, v_l, _ = (0, 0, 0) if V is None else V.stride()
+    q_h, q_l = Q.stride()[:2]
+    k_h, k_l = K.stride()[:2]
+    v_h, v_l = (0, 0) if V is None else V.stride()[:2]
     return dhsa_problem(L, H_q, H_kv, D, len(B) - 1, N_b, dt, scale, q_h, q_l, k_h, k_l, v_h, v_l, 0, 0, B_r, pooling)
 
 
@@ -164,8 +164,8 @@ def dhsa_route(prob, Q, K, B, plan, ws) -> None:
 
 def _with_vo(prob: dhsa_problem, V, O) -> dhsa_problem:
     p = dhsa_problem.from_buffer_copy(prob)
-    p.v_stride_h, p.v_stride_l, _ = V.stride()
-    p.o_stride_h, p.o_stride_l, _ = O.stride()
+    p.v_stride_h, p.v_stride_l = V.stride()[:2]
+    p.o_stride_h, p.o_stride_l = O.stride()[:2]
     return p
 
 
