@@ -21,6 +21,8 @@
 // the chain of loads before the first product (plan, boundaries, keys).  L = 2048, four
 // heads of D = 64, N_b = 256: 18 us; 135 us with one wave per row (no reuse of K and V, products on
 // the vector unit, one key of V at a time).
+#include <algorithm>
+
 #include "dhsa_internal.h"
 
 namespace dhsa {
@@ -33,7 +35,7 @@ constexpr int kF32Seg = 256;     // plan entries per batch
 template <int D, int RW>
 __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *__restrict__ Q,
                                                      const float *__restrict__ K, const float *__restrict__ V,
-                                                     float *__restrict__ O, int H_q, int G, float scale_log2e,
+                                                     float *__restrict__ O, unsigned block0, int H_q, int G, float scale_log2e,
                                                      int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
                                                      int64_t vs_h, int64_t vs_l, int64_t os_h, int64_t os_l) {
     constexpr int NR = 16 * RW;      // rows of the workgroup
@@ -56,8 +58,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
 
     // blockIdx -> (head, tile, piece of the tile): a tile of class c has at most 4 - c pieces of 32 rows; the
     // latest rows (most keys) of each class first
-    const int h = blockIdx.x % H_q, g = h / G;
-    int b = blockIdx.x / H_q, tile = 0, piece = 0;
+    const unsigned block = block0 + blockIdx.x;
+    const int h = block % H_q, g = h / G;
+    int b = block / H_q, tile = 0, piece = 0;
     {
         int first = 0;
 #pragma unroll
@@ -308,18 +311,25 @@ hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, con
     // workgroups, 16-row ones fill the chip better and waste less on the last rows of a tile
     const int64_t wg32 = (int64_t)p.H_q * (4 * (int64_t)pv.T_cls[0] + 3 * pv.T_cls[1] + 2 * pv.T_cls[2] + pv.T_cls[3]);
     const bool small = wg32 < 512;
-    const dim3 grid((unsigned)(small ? 2 * wg32 : wg32)), block(256);
+    const int64_t n_wg = small ? 2 * wg32 : wg32;
+    const dim3 block(256);
 #define DHSA_F32_ATTN(DD, RW)                                                                                 \
     hipLaunchKernelGGL((k_attn_f32<DD, RW>), grid, block, 0, s, pv, (const float *)Q, (const float *)K,       \
-                       (const float *)V, (float *)O, p.H_q, p.G, p.scale * 1.4426950408889634f, p.qs_h, p.qs_l, \
+                       (const float *)V, (float *)O, block0, p.H_q, p.G, p.scale * 1.4426950408889634f, p.qs_h, p.qs_l, \
                        p.ks_h, p.ks_l, p.vs_h, p.vs_l, p.os_h, p.os_l)
-    if (p.D == 64) {
-        if (small) DHSA_F32_ATTN(64, 1); else DHSA_F32_ATTN(64, 2);
-    } else {
-        if (small) DHSA_F32_ATTN(128, 1); else DHSA_F32_ATTN(128, 2);
+    for (int64_t first = 0; first < n_wg; first += kGridMax) {
+        const unsigned block0 = (unsigned)first;
+        const dim3 grid((unsigned)std::min<int64_t>(kGridMax, n_wg - first));
+        if (p.D == 64) {
+            if (small) DHSA_F32_ATTN(64, 1); else DHSA_F32_ATTN(64, 2);
+        } else {
+            if (small) DHSA_F32_ATTN(128, 1); else DHSA_F32_ATTN(128, 2);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
 #undef DHSA_F32_ATTN
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace dhsa

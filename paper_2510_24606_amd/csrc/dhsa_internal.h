@@ -91,10 +91,15 @@ struct BoundaryTail {
 // Up to kBoundaryBlockMax boundaries passed by value to a kernel (a launch argument block
 // holds at most 4 KiB), for callers whose boundary array must not go through a host copy.
 constexpr int kBoundaryBlockMax = 960;
+
 struct BoundaryBlock {
     int32_t first, n;
     int32_t b[kBoundaryBlockMax];
 };
+
+// Workgroups of at most 256 threads in one dimension of a launch: a dimension holds fewer than 2^32 threads, and a
+// row-block problem can have 2^20 groups per head.
+constexpr int kGridMax = 1 << 23;
 
 // ---- launchers (each enqueues on `s` and returns the launch status) ----
 // B_host[0 .. n) -> B_dev, carried by kernel arguments (no copy engine, no staging buffer)

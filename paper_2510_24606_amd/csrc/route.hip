@@ -499,13 +499,13 @@ static int select_row_bytes(int NW, int cap, int N_c) {   // cap: a multiple of 
 template <int NW>
 __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, int32_t *__restrict__ plan,
                                                 PlanLayout pl, int N_c, int N_b, int B_r, int l_first, int n_groups,
-                                                int n_rows, int cap, int row_bytes) {
+                                                int r_first, int n_rows, int cap, int row_bytes) {
     constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned long long s_red[2 * NW];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
-    const int r = NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x;
+    const int r = r_first + (int)(NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x);
     if (r >= n_rows) return;             // NW == 1: waves do not wait for each other
     const auto sync = [] { if constexpr (NW == 1) wave_lds_fence(); else __syncthreads(); };
     unsigned char *mine8 = smem + (size_t)(NW == 1 ? wave : 0) * row_bytes;
@@ -943,7 +943,8 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
     const int nw = n_rows < 512 ? 4 : p.N_c <= 512 ? 1 : p.N_c <= 1024 ? 2 : 4;
     const int row_bytes = select_row_bytes(nw, cap, p.N_c);
     const size_t shmem = nw == 1 ? (size_t)4 * row_bytes : row_bytes;
-    const dim3 grid(nw == 1 ? (n_rows + 3) / 4 : n_rows), block(nw == 1 ? 256 : 64 * nw);
+    const int per = nw == 1 ? 4 : 1;                     // rows per workgroup
+    const dim3 block(nw == 1 ? 256 : 64 * nw);
 #define DHSA_SELECT(NW)                                                                                            \
     do {                                                                                                           \
         if (shmem > 48 * 1024) {                                                                                   \
@@ -951,14 +952,19 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);            \
             if (e != hipSuccess) return e;                                                                         \
         }                                                                                                          \
-        hipLaunchKernelGGL(k_select<NW>, grid, block, shmem, s, Sc, plan, pl, p.N_c, p.N_b, p.B_r, l_first, n_groups, \
-                           n_rows, cap, row_bytes);                                                                \
+        for (int64_t r0 = 0; r0 < n_rows; r0 += (int64_t)kGridMax * per) {                                         \
+            const dim3 grid((unsigned)std::min<int64_t>(kGridMax, (n_rows - r0 + per - 1) / per));                 \
+            hipLaunchKernelGGL(k_select<NW>, grid, block, shmem, s, Sc, plan, pl, p.N_c, p.N_b, p.B_r, l_first,    \
+                               n_groups, (int)r0, n_rows, cap, row_bytes);                                         \
+            const hipError_t e = hipGetLastError();                                                                \
+            if (e != hipSuccess) return e;                                                                         \
+        }                                                                                                          \
     } while (0)
     if (nw == 1) DHSA_SELECT(1);
     else if (nw == 2) DHSA_SELECT(2);
     else DHSA_SELECT(4);
 #undef DHSA_SELECT
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------

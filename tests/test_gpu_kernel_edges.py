@@ -188,3 +188,24 @@ def test_f32_infinite_values_reach_only_the_rows_that_take_them(L, D, B_r):
     got = O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
     assert not np.isfinite(ref).all() and np.isfinite(ref).any()
     np.testing.assert_allclose(got, ref, rtol=0, atol=1e-4)
+
+
+def test_more_workgroups_than_one_launch_holds():
+    """Row blocks of one row, 16 heads of 2^20 rows: 2^24 workgroups of the fp32 attention.  Heads are independent and
+    every row's sums have one order, so two calls of eight heads (2^23 workgroups each) give the same bits."""
+    L, H_q, D, N_b = 1 << 20, 16, 64, 16
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    Q = torch.randn(H_q, L, D, device="cuda", generator=gen)
+    K, V = (torch.randn(1, L, D, device="cuda", generator=gen) for _ in range(2))
+    B = np.array([0, 700, 300000, 300050, L], dtype=np.int32)
+
+    def prefill(q):
+        prob = dhsa.problem(q, K, B, N_b, B_r=1)
+        plan, ws = dhsa.alloc(prob, B)
+        O = torch.full_like(q, float("nan"))
+        dhsa.dhsa_prefill(prob, q, K, V, B, O, plan, ws)
+        return O
+
+    whole = prefill(Q)
+    for h in (0, 8):
+        assert torch.equal(whole[h:h + 8], prefill(Q[h:h + 8]))
