@@ -190,6 +190,24 @@ def test_f32_infinite_values_reach_only_the_rows_that_take_them(L, D, B_r):
     np.testing.assert_allclose(got, ref, rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("L,H_q,D", [(2048, 4, 64), (6001, 16, 64), (2048, 4, 128), (6001, 16, 128)])
+def test_f32_error_against_64_bits(L, H_q, D):
+    """16- and 32-row workgroups.  A score of D unit normals summed in four chains of D / 4 leaves O 1.8e-7 to 2.1e-7
+    (relative) from its 64-bit value here; along one chain of D it was 2.7e-7 to 3.3e-7 at such sizes, so the bound lies between."""
+    w = dhsa_inputs.make("c1", L=L, H_q=H_q, H_kv=H_q // 4, D=D, N_b=L // 8)
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    O = torch.empty_like(Q)
+    prob = dhsa.problem(Q, K, w.B, w.N_b)
+    plan, ws = dhsa.alloc(prob, w.B)
+    dhsa.dhsa_prefill(prob, Q, K, V, w.B, O, plan, ws)
+    rows = np.arange(5, L, L // 60, dtype=np.int64)
+    ref = oracle.prefill_rows(w.f32("Q"), w.f32("K"), w.f32("V"), w.B, w.N_b, rows)[0]
+    got = O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"L={L} D={D}: relative error {rel:.3e}")
+    assert rel < 2.4e-7
+
+
 def test_more_workgroups_than_one_launch_holds():
     """Row blocks of one row, 16 heads of 2^20 rows: 2^24 workgroups of the fp32 attention.  Heads are independent and
     every row's sums have one order, so two calls of eight heads (2^23 workgroups each) give the same bits."""
