@@ -726,7 +726,9 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2(S c - mc) per row block, with the lazily moved exponent reference of the kernel above
+// P = exp2(S c - mc) per row block, with the lazily moved exponent reference of the kernel above.  One range
+// check for all row blocks, but only those that need it move their reference: the rounding of a row's probabilities
+// hangs on no row outside its own 16.
 #define DHSA_EXP16(sacc, pf)                                                                    \
     {                                                                                           \
         float psum_[RW];                                                                        \
@@ -742,6 +744,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         }                                                                                       \
         if (__any(far_)) {                                                                      \
             _Pragma("unroll") for (int r = 0; r < RW; ++r) {                                    \
+                if (!__any(!(psum_[r] < 1048576.f))) continue;                                  \
                 float mx_;                                                                      \
                 DHSA_ROWMAX16(sacc[r], mx_);                                                    \
                 const float m_new_ = fmaxf(mc[r], mx_ * scale_log2e);                           \

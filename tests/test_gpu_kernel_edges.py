@@ -227,3 +227,31 @@ def test_more_workgroups_than_one_launch_holds():
     whole = prefill(Q)
     for h in (0, 8):
         assert torch.equal(whole[h:h + 8], prefill(Q[h:h + 8]))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [64, 49, 32])
+def test_rows_of_other_16_row_blocks_keep_their_bits(rows, D):
+    """Row tiles of at most 64 rows, two 16-row blocks per wave (at most 32 rows: one).  Logits of one block that grow
+    far past its exponent reference late in the key list move that block's reference, and nobody else's."""
+    L, H_q, H_kv = 40 * rows, 8, 2
+    w = dhsa_inputs.make("c3", L=L, H_q=H_q, H_kv=H_kv, D=D, N_b=300, lens=("fixed", rows))
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    prob = dhsa.problem(Q, K, w.B, w.N_b)
+    plan, ws = dhsa.alloc(prob, w.B)
+    dhsa.dhsa_route(prob, Q, K, w.B, plan, ws)
+
+    def attend(q):
+        O = torch.full_like(q, float("nan"))
+        dhsa.dhsa_sparse_prefill(prob, q, K, V, w.B, plan, O)
+        return O
+
+    before = attend(Q)
+    at = torch.arange(L, device="cuda") % rows
+    for block in range((rows + 15) // 16):
+        mine = at // 16 == block
+        loud = torch.where(mine[:, None], 40.0 * Q.float(), Q.float()).to(Q.dtype)    # logits of about 40 (one rms)
+        after = attend(loud)
+        assert torch.isfinite(after).all()
+        assert torch.equal(after[:, ~mine], before[:, ~mine])
+        assert not torch.equal(after[:, mine], before[:, mine])
