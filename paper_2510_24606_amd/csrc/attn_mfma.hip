@@ -911,13 +911,13 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
     }
 }
 
-// One launch per tile class (a kernel that holds all three bodies measured 3-10 % slower than
-// the sum of these), but a class too small to fill the chip joins the launch of the next taller one (launch_attn_mfma).
-// CLS 0: tiles of more than 64 rows (table classes 0 and 1), 1: 33..64 rows,
-// 2: at most 32 rows.  Inside a launch tiles are issued from the end of the sequence (most keys)
-// to its start, so that the launch ends with the cheapest workgroups; T0 tiles of its own class first, then the
+// One launch per tile class, but a class too small to fill the chip joins the launch of the next taller one
+// (launch_attn_mfma).  CLS 0: tiles of more than 64 rows (table classes 0 and 1), 1: 33..64 rows,
+// 2: at most 32 rows.  MIX: the launch also has shorter tiles; every tile runs the body of its own height, so its
+// result does not hang on the launch it is in.  Inside a launch tiles are issued from the end of the sequence (most
+// keys) to its start, so that the launch ends with the cheapest workgroups; T0 tiles of its own class first, then the
 // shorter ones.
-template <int D, int CLS>
+template <int D, int CLS, bool MIX>
 __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, int H_q, int mode, int tile0, int T0,
                                                       int T) {
     __shared__ AttnSmem<D> sm;
@@ -926,8 +926,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, i
     const int tile = tile0 + (pos < T0 ? T0 - 1 - pos : T0 + T - 1 - pos);
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
-    if constexpr (CLS == 0) attn_tile_32<D>(sm, pv, a, h, l, row0);
-    else if constexpr (CLS == 1) attn_tile_16<D, 2>(sm, pv, a, h, l, row0);
+    const int cls = !MIX || pos < T0 ? CLS : tile < pv.T_big + pv.T_cls[2] ? 1 : 2;
+    if (CLS == 0 && cls == 0) attn_tile_32<D>(sm, pv, a, h, l, row0);
+    else if (CLS <= 1 && cls == 1) attn_tile_16<D, 2>(sm, pv, a, h, l, row0);
     else attn_tile_16<D, 1>(sm, pv, a, h, l, row0);
 }
 
@@ -948,24 +949,25 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
     a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
     // tiles of each launch: its own class, and shorter ones that joined.  A launch of fewer workgroups than the chip
-    // holds at once (two per CU) takes as long as one workgroup whatever their number, while the next taller
-    // body runs such tiles in the gaps of its own (their stage time is then part of that launch's).
+    // holds at once (two per CU) takes as long as one workgroup whatever their number, while the next taller launch
+    // has such tiles run in the gaps of its own (their stage time is then part of that launch's).  A 1K-token
+    // prompt: 33.3 us a call with a launch per class, 25.0 us so; c2 1622 -> 1591 us.
     int own[3] = {pv.T_big, pv.T_cls[2], pv.T_cls[3]}, all[3] = {own[0], own[1], own[2]};
     for (int c = 2; c > 0; --c) {
         const int to = own[c - 1] > 0 ? c - 1 : 0;
         if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) { all[to] += all[c]; all[c] = 0; }
     }
     const int first[3] = {0, own[0], own[0] + own[1]};
+#define DHSA_LAUNCH1(D_, CLS, MIX)                                                                           \
+    hipLaunchKernelGGL((k_attn_mfma<D_, CLS, MIX>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS],   \
+                       own[CLS], all[CLS])
 #define DHSA_LAUNCH(CLS)                                                                                     \
     if (all[CLS] > 0) {                                                                                      \
         const int mode = attn_order(want, p.H_kv, p.G, all[CLS]);                                            \
         const dim3 grid(p.H_q * all[CLS]);                                                                   \
-        if (p.D == 64)                                                                                       \
-            hipLaunchKernelGGL((k_attn_mfma<64, CLS>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS], \
-                               own[CLS], all[CLS]);                                                          \
-        else                                                                                                 \
-            hipLaunchKernelGGL((k_attn_mfma<128, CLS>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS], \
-                               own[CLS], all[CLS]);                                                          \
+        const bool mix = all[CLS] > own[CLS];                                                                \
+        if (p.D == 64) { if (mix) DHSA_LAUNCH1(64, CLS, (CLS < 2)); else DHSA_LAUNCH1(64, CLS, false); }     \
+        else { if (mix) DHSA_LAUNCH1(128, CLS, (CLS < 2)); else DHSA_LAUNCH1(128, CLS, false); }             \
     }
     // tallest tiles first (they take longest)
     DHSA_LAUNCH(0)
@@ -975,6 +977,7 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     DHSA_LAUNCH(2)
     if (ev && hipEventRecord(ev[2], s) != hipSuccess) return hipErrorUnknown;
 #undef DHSA_LAUNCH
+#undef DHSA_LAUNCH1
     return hipGetLastError();
 }
 

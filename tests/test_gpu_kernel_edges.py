@@ -255,3 +255,34 @@ def test_rows_of_other_16_row_blocks_keep_their_bits(rows, D):
         assert torch.isfinite(after).all()
         assert torch.equal(after[:, ~mine], before[:, ~mine])
         assert not torch.equal(after[:, mine], before[:, mine])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("tall,middle,short", [((65, 96, 97, 127, 128, 129, 160, 200), (33, 48, 49, 63, 64, 64), (1, 16, 17, 31, 32)),
+                                               ((80, 128, 100, 90, 70, 110), (), (1, 15, 32)),
+                                               ((), (33, 47, 64, 40, 50, 60), (2, 16, 17, 32)),
+                                               ((256, 96), (), ())])
+def test_a_tile_has_one_result_in_every_launch(tall, middle, short, D):
+    """A class of few row tiles joins the launch of the next taller one.  The more heads, the fewer classes are that
+    small: with 4 heads all join, with 512 (1536 workgroups and more of each) none, with 128 of them the shortest may.
+    The rows of the first heads keep their bits, so the parity tests of joined launches hold for separate ones too."""
+    rng = np.random.default_rng(D + len(tall))
+    lens = rng.permutation(np.array((tall + middle + short) * 2))
+    B = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    L = int(B[-1])
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Q, K, V = (torch.randn(H, L, D, dtype=torch.bfloat16, device="cuda", generator=gen) for H in (512, 128, 128))
+
+    def prefill(H_q, B_r):
+        q, k, v = Q[:H_q], K[:H_q // 4], V[:H_q // 4]
+        prob = dhsa.problem(q, k, B, 300, B_r=B_r)
+        plan, ws = dhsa.alloc(prob, B)
+        O = torch.full_like(q, float("nan"))
+        dhsa.dhsa_prefill(prob, q, k, v, B, O, plan, ws)
+        return O[:4]
+
+    for B_r in (0, 72):                            # row blocks: tiles of 72 rows and one of the rest
+        few = prefill(4, B_r)
+        assert torch.isfinite(few).all()
+        for H_q in (32, 128, 512):
+            assert torch.equal(few, prefill(H_q, B_r)), (H_q, B_r)
