@@ -305,7 +305,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int x = 0; x < 16; ++x) oacc[db][x] = 0.f;
-    float mc = pad_row ? 1e30f : __builtin_nanf(""), l_run = 0.f;   // reference used in the exponent (see DHSA_EXP)
+    float m_ref = pad_row ? 1e30f : __builtin_nanf(""), l_run = 0.f;   // reference used in the exponent (see DHSA_EXP)
 
     // staging: load instruction c of this wave fills LDS window (4 c + wave) of a
     // tile (1 KiB = 64 pieces); this lane's piece there is physical piece
@@ -383,18 +383,19 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2(S c - mc) with row sums, rounded to the two bf16 MFMA B operands
-// of the block.  mc is a REFERENCE for the exponent, not the running maximum:
+// P = exp2(S c - m_ref c) with row sums, rounded to the two bf16 MFMA B operands
+// of the block.  m_ref is a REFERENCE for the exponent, not the running maximum:
 // O / l at the end is exact whatever reference was used, so it only has to keep
 // the exponentials in range.  It is set from the first block and moved up (with
 // a rescale of l and O) only when a block's exponentials grow past 2^20, which
-// the row sums reveal without a per-block maximum.  A row keeps mc = NaN, which sends
+// the row sums reveal without a per-block maximum.  A row keeps m_ref = NaN, which sends
 // it through the second branch, until it meets its first unmasked key.
 #define DHSA_EXP(sacc, pf)                                                                      \
     {                                                                                           \
+        const float mc_ = m_ref * scale_log2e;                                                  \
         float psum_ = 0.f;                                                                      \
         _Pragma("unroll") for (int x = 0; x < 16; ++x) {                                        \
-            const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - mc);                \
+            const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - mc_);               \
             psum_ += e_;                                                                        \
             pf[x >> 3][x & 7] = (__bf16)e_;                                                     \
         }                                                                                       \
@@ -402,14 +403,15 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         if (__any(!(psum_ < 1048576.f))) {                                                      \
             float mx_;                                                                          \
             DHSA_ROWMAX(sacc, mx_);                                                             \
-            const float m_new_ = fmaxf(mc, mx_ * scale_log2e);   /* the other one if one is NaN */ \
+            const float m_new_ = fmaxf(m_ref, mx_);   /* the other one if one is NaN */         \
             const bool none_ = m_new_ == -INFINITY;                                             \
-            const float alpha_ = (mc != mc) ? 0.f : __builtin_amdgcn_exp2f(mc - m_new_);        \
+            const float alpha_ = (m_ref != m_ref) ? 0.f                                         \
+                                 : __builtin_amdgcn_exp2f((m_ref - m_new_) * scale_log2e);      \
             l_run *= alpha_;                                                                    \
             _Pragma("unroll") for (int db = 0; db < NDB; ++db)                                  \
                 _Pragma("unroll") for (int x = 0; x < 16; ++x) oacc[db][x] *= alpha_;           \
-            const float ref_ = none_ ? 0.f : m_new_;                                            \
-            mc = none_ ? __builtin_nanf("") : m_new_;                                           \
+            const float ref_ = none_ ? 0.f : m_new_ * scale_log2e;                              \
+            m_ref = none_ ? __builtin_nanf("") : m_new_;                                        \
             psum_ = 0.f;                                                                        \
             _Pragma("unroll") for (int x = 0; x < 16; ++x) {                                    \
                 const float e_ = __builtin_amdgcn_exp2f(sacc[x] * scale_log2e - ref_);          \
@@ -469,7 +471,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
             if (e0 == 0) {   // reference = row maxima of the first block
                 float mx0;
                 DHSA_ROWMAX(s_a, mx0);
-                if (mx0 != -INFINITY) mc = fmaxf(mc, mx0 * scale_log2e);
+                if (mx0 != -INFINITY) m_ref = fmaxf(m_ref, mx0);
             }
         }
         __syncthreads();                      // the lower half of K(0) may be overwritten from here on
@@ -632,7 +634,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
     // get q = 0 and, through a huge exponent reference, p = 0.
     bf16x8 qf[RW][NT];
     int v_i[RW];
-    float mc[RW], l_run[RW];
+    float m_ref[RW], l_run[RW];
     f32x4 oacc[RW][NJ];
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
@@ -642,7 +644,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         const uint16_t *qp = Q + (int64_t)h * qs_h + (int64_t)(row0 + (pad_row ? nrows - 1 : rr)) * qs_l + 8 * q;
 #pragma unroll
         for (int t = 0; t < NT; ++t) qf[r][t] = *reinterpret_cast<const bf16x8 *>(qp + 32 * t);
-        mc[r] = pad_row ? 1e30f : __builtin_nanf("");
+        m_ref[r] = pad_row ? 1e30f : __builtin_nanf("");
         l_run[r] = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) oacc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -726,7 +728,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2(S c - mc) per row block, with the lazily moved exponent reference of the kernel above.  One range
+// P = exp2(S c - m_ref c) per row block, with the lazily moved exponent reference of the kernel above.  One range
 // check for all row blocks, but only those that need it move their reference: the rounding of a row's probabilities
 // hangs on no row outside its own 16.
 #define DHSA_EXP16(sacc, pf)                                                                    \
@@ -734,9 +736,10 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         float psum_[RW];                                                                        \
         bool far_ = false;                                                                      \
         _Pragma("unroll") for (int r = 0; r < RW; ++r) {                                        \
+            const float mc_ = m_ref[r] * scale_log2e;                                           \
             psum_[r] = 0.f;                                                                     \
             _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                     \
-                const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - mc[r]); \
+                const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - mc_); \
                 psum_[r] += e_;                                                                 \
                 pf[r][x] = (__bf16)e_;                                                          \
             }                                                                                   \
@@ -747,14 +750,15 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
                 if (!__any(!(psum_[r] < 1048576.f))) continue;                                  \
                 float mx_;                                                                      \
                 DHSA_ROWMAX16(sacc[r], mx_);                                                    \
-                const float m_new_ = fmaxf(mc[r], mx_ * scale_log2e);                           \
+                const float m_new_ = fmaxf(m_ref[r], mx_);                                      \
                 const bool none_ = m_new_ == -INFINITY;                                         \
-                const float alpha_ = (mc[r] != mc[r]) ? 0.f : __builtin_amdgcn_exp2f(mc[r] - m_new_); \
+                const float alpha_ = (m_ref[r] != m_ref[r]) ? 0.f                               \
+                                     : __builtin_amdgcn_exp2f((m_ref[r] - m_new_) * scale_log2e); \
                 l_run[r] *= alpha_;                                                             \
                 _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                  \
                     _Pragma("unroll") for (int x = 0; x < 4; ++x) oacc[r][j][x] *= alpha_;      \
-                const float ref_ = none_ ? 0.f : m_new_;                                        \
-                mc[r] = none_ ? __builtin_nanf("") : m_new_;                                    \
+                const float ref_ = none_ ? 0.f : m_new_ * scale_log2e;                          \
+                m_ref[r] = none_ ? __builtin_nanf("") : m_new_;                                 \
                 psum_[r] = 0.f;                                                                 \
                 _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                 \
                     const float e_ = __builtin_amdgcn_exp2f(sacc[r][x >> 2][x & 3] * scale_log2e - ref_); \
@@ -823,7 +827,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
                     for (int r = 0; r < RW; ++r) {
                         float mx0;
                         DHSA_ROWMAX16(s_a[r], mx0);
-                        if (mx0 != -INFINITY) mc[r] = fmaxf(mc[r], mx0 * scale_log2e);
+                        if (mx0 != -INFINITY) m_ref[r] = fmaxf(m_ref[r], mx0);
                     }
                 }
                 DHSA_EXP16(s_a, pf);
@@ -863,7 +867,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         if (wave_live && kbw == 1) {
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
-                xch[(r * (2 + 4 * NJ)) * 64] = mc[r];
+                xch[(r * (2 + 4 * NJ)) * 64] = m_ref[r];
                 xch[(r * (2 + 4 * NJ) + 1) * 64] = l_run[r];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
@@ -876,9 +880,9 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
                 const float m1 = xch[(r * (2 + 4 * NJ)) * 64], l1 = xch[(r * (2 + 4 * NJ) + 1) * 64];
-                const float mm = fmaxf(mc[r], m1);      // NaN: no key seen (and then the other one is taken)
-                const float a0 = (mc[r] != mc[r]) ? 0.f : __builtin_amdgcn_exp2f(mc[r] - mm);
-                const float a1 = (m1 != m1) ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
+                const float mm = fmaxf(m_ref[r], m1);   // NaN: no key seen (and then the other one is taken)
+                const float a0 = (m_ref[r] != m_ref[r]) ? 0.f : __builtin_amdgcn_exp2f((m_ref[r] - mm) * scale_log2e);
+                const float a1 = (m1 != m1) ? 0.f : __builtin_amdgcn_exp2f((m1 - mm) * scale_log2e);
                 l_run[r] = l_run[r] * a0 + l1 * a1;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
