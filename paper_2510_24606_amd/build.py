@@ -10,6 +10,8 @@ ROOT = os.path.dirname(HERE)
 SOURCES = ["dhsa_api.hip", "route.hip", "attn.hip", "attn_mfma.hip", "mfma_probe.hip", "boundaries.hip", "recall.hip",
            "decode.hip"]
 LIB = os.path.join(HERE, "libdhsa.so")
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-I", os.path.join(ROOT, "include")]
 
 
 def hipcc() -> str:
@@ -22,9 +24,7 @@ def hipcc() -> str:
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(HERE, "csrc", s) for s in SOURCES]
     tmp = LIB + f".tmp{os.getpid()}"
-    cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I", os.path.join(ROOT, "include"), "-o", tmp] + srcs
+    cmd = [hipcc()] + FLAGS + ["-fPIC", "-shared", "-fvisibility=hidden", "-o", tmp] + srcs
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -125,6 +125,7 @@ __global__ __launch_bounds__(256) void k_nms_windows(const float *__restrict__ p
             if (removed || !blocked) {
                 unsigned *k32 = reinterpret_cast<unsigned *>(s_kept), *u32 = reinterpret_cast<unsigned *>(s_und);
                 if (!removed) atomicOr(&k32[x >> 5], 1u << (x & 31));
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // kept before no longer undecided
                 atomicAnd(&u32[x >> 5], ~(1u << (x & 31)));
                 decided = 1;
             }

@@ -1,0 +1,28 @@
+"""Properties of the kernels that their results do not show, from the assembly of the sources as the library is built."""
+import functools
+import os
+import re
+import subprocess
+
+from paper_2510_24606_amd import build
+
+
+@functools.lru_cache(maxsize=None)
+def assembly(source):
+    """{kernel symbol: its lines}"""
+    cmd = [build.hipcc()] + build.FLAGS + ["--cuda-device-only", "-S", "-o", "-", os.path.join(build.HERE, "csrc", source)]
+    text = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, check=True).stdout
+    found = re.findall(r"^(_Z\S+):[^\n]*\n(.*?)^\.Lfunc_end", text, flags=re.S | re.M)
+    return {name: [line.strip() for line in body.splitlines()] for name, body in found}
+
+
+def test_a_kept_boundary_is_marked_before_it_stops_being_undecided():
+    """Other waves read `undecided`, then `kept`: one that sees a position as decided has to see that it is kept."""
+    (code,) = [c for name, c in assembly("boundaries.hip").items() if "k_nms_windows" in name]
+    ops = [op for op in (line.split(";")[0].strip() for line in code) if op]
+    at = [i for i, op in enumerate(ops) if op.startswith("ds_and_b32")]
+    assert at
+    for i in at:
+        back = ops[max(0, i - 8):i]
+        mark = max(j for j, op in enumerate(back) if op.startswith("ds_or_b32"))
+        assert any("lgkmcnt(0)" in op for op in back[mark:]), back
