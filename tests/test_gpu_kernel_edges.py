@@ -12,10 +12,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,W,levels", [(511, 3, 0), (512, 8, 0), (513, 8, 4), (1024, 31, 0), (1025, 32, 0),
-                                        (5000, 33, 3), (4096, 512, 0), (4097, 600, 5), (131073, 8, 0), (140001, 40, 9)])
+                                        (5000, 33, 3), (4096, 512, 0), (4097, 600, 5), (131073, 8, 0), (140001, 40, 9),
+                                        (20000, 300, 2), (20001, 511, 40), (6000, 2000, 0), (1400, 900, 50)])
 def test_boundary_windows_and_slabs(L, W, levels):
     """Windows of 512 positions, halos of 128 .. 512 (W of 512 and more decide nothing locally), compaction slabs of
-    131072; `levels` distinct scores make runs of equal ones, which a window cannot always decide."""
+    131072; `levels` distinct scores make runs of equal ones, which a window cannot always decide, next to kept positions
+    of the segment beside it."""
     rng = np.random.default_rng(L + W)
     p = rng.random(L).astype(np.float32)
     if levels:
