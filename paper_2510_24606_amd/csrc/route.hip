@@ -477,7 +477,7 @@ __device__ __forceinline__ unsigned long long wave_read(unsigned long long x, in
 //      LDS atomics): the bin where the tokens reach N_b is the last one that can hold a listed
 //      chunk, whatever the order inside it, so the chunks up to that bin are the candidates.  If
 //      they are more than the list holds, the last bin is cut again over its own range (outliers
-//      far from the rest), and at last by bisection over keys and ids (ties);
+//      far from the rest), and at last by digits of the keys and ids (ties);
 //   3. candidates into LDS, grouped by bin (the bins' counts are their places);
 //   4. tokens before a candidate = tokens of better bins + of the better candidates of its own bin (a few);
 //   5. the listed chunks set their bit, and go into the plan at the number of bits below theirs
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
                                                 int r_first, int n_rows, int cap, int row_bytes) {
     constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ unsigned long long s_red[2 * NW];
+    __shared__ unsigned long long s_red[NW];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
     const int r = r_first + (int)(NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x);
@@ -591,17 +591,25 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             }
         }
     };
-    const auto row_sum = [&](unsigned long long x) {
-        x = wave_read(wave_incl_scan(x), 63);
+    const auto row_min = [&](unsigned long long x) {     // NW > 1: two barriers
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long o = __shfl_xor(x, off);
+            x = o < x ? o : x;
+        }
         if constexpr (NW > 1) {
             __syncthreads();
-            if (lane == 0) s_red[NW + wave] = x;
+            if (lane == 0) s_red[wave] = x;
             __syncthreads();
-            x = 0ull;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) x += s_red[NW + w];
+            for (int w = 0; w < NW; ++w) x = s_red[w] < x ? s_red[w] : x;
         }
-        return x;
+        return wave_read(x, 0);          // a wave-uniform value needs no vector registers
+    };
+    const auto clear_hist = [&] {
+        sync();                          // everybody has read the last counts
+        for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
+        sync();
     };
 
     for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
@@ -625,27 +633,18 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
         return k > cut_key || (k == cut_key && x <= cut_id);
     };
     unsigned long long above = 0ull;     // tokens << 16 | chunks with a score above hi
-    for (int level = 0;; ++level) {
-        inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
-        if (level == 0) {
-            DHSA_SEL_FOR({ (void)x; if (in) atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull); })
-        } else {
-            sync();                      // everybody has read the last level's counts
-            for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
-            sync();
-            DHSA_SEL_AGAIN({
-                if (in && (cut ? is_cand(s, x) : (score_f32(s) >= lo && score_f32(s) <= hi)))
-                    atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull);
-            })
-        }
+    unsigned long long before, upto;     // ranked before the last bin, and up to it
+    // From the counts in hist, every wave for itself: what is ranked before each bin (tokens, and chunks = the place of
+    // its first) goes to place; the last bin is the one in which the tokens reach N_b (none does: the worst of all)
+    const auto find_last = [&] {
         sync();
-        // every wave for itself: what is ranked before each bin (tokens, and chunks = the place of its first)
         unsigned long long c[4];         // bins 4 lane .. 4 lane + 3
 #pragma unroll
         for (int i = 0; i < 4; ++i) c[i] = hist[4 * lane + i];
         const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
-        unsigned long long run = above + wave_incl_scan(mine) - mine, before = 0ull, upto = 0ull;
+        unsigned long long run = above + wave_incl_scan(mine) - mine;
         int my_bin = kSelBins;           // the bin of this lane in which the tokens reach N_b
+        before = upto = 0ull;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (NW == 1 || wave == 0) place[4 * lane + i] = run;
@@ -656,18 +655,29 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             }
             run += c[i];
         }
-        tbin = kSelBins - 1;
-        if (cut) break;
         const unsigned long long found = __ballot(my_bin < kSelBins);
-        int n_upto;                      // chunks up to the last bin
-        if (found) {
-            const int src = __builtin_ctzll(found);
-            tbin = __builtin_amdgcn_readlane(my_bin, src);
-            before = wave_read(before, src);
-            n_upto = (int)(wave_read(upto, src) & 0xffffull);
-        } else {                         // all visible chunks fit the budget
-            n_upto = (int)(wave_read(run, 63) & 0xffffull);
+        const int src = found ? __builtin_ctzll(found) : 63;
+        tbin = found ? __builtin_amdgcn_readlane(my_bin, src) : kSelBins - 1;
+        before = wave_read(before, src);
+        upto = wave_read(found ? upto : run, src);
+    };
+    for (int level = 0;; ++level) {
+        inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
+        if (level == 0) {
+            DHSA_SEL_FOR({ (void)x; if (in) atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull); })
+        } else {
+            clear_hist();
+            DHSA_SEL_AGAIN({
+                if (in && (cut ? is_cand(s, x) : (score_f32(s) >= lo && score_f32(s) <= hi)))
+                    atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull);
+            })
         }
+        find_last();
+        if (cut) {
+            tbin = kSelBins - 1;
+            break;
+        }
+        int n_upto = (int)(upto & 0xffffull);                    // chunks up to the last bin
         if (n_upto <= cap && level == 0) break;                  // the usual end
         if (n_upto <= cap) {             // group all candidates over one range: from the worst of them to the best
             float worst = INFINITY, none = -INFINITY;
@@ -684,19 +694,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
                 const unsigned long long k = score_key(s);
                 if (in && score_f32(s) >= worst && k < key_lo) key_lo = k;
             })
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const unsigned long long o = __shfl_xor(key_lo, off);
-                key_lo = o < key_lo ? o : key_lo;
-            }
-            if constexpr (NW > 1) {
-                __syncthreads();
-                if (lane == 0) s_red[wave] = key_lo;
-                __syncthreads();
-#pragma unroll
-                for (int w = 0; w < NW; ++w) key_lo = s_red[w] < key_lo ? s_red[w] : key_lo;
-            }
-            cut_key = key_lo;
+            cut_key = row_min(key_lo);
         } else if (level < 3 && hi > lo) {   // cut the last bin again, over its own range
             float a = INFINITY, z = -INFINITY;
             DHSA_SEL_AGAIN({
@@ -709,25 +707,50 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
             hi = z;
             continue;
         } else {
-            // the largest key, then the smallest id among equal keys, down to which the tokens reach N_b (more than
-            // `cap` chunks are in sight, hence more than N_b tokens)
-            for (int bit = 63; bit >= 0; --bit) {
-                const unsigned long long k = cut_key | (1ull << bit);
-                unsigned long long sum = 0ull;
-                DHSA_SEL_AGAIN({ (void)x; if (in && score_key(s) >= k) sum += (unsigned long long)n_tok; })
-                if (row_sum(sum) >= (unsigned long long)N_b) cut_key = k;
-            }
-            int id0 = 0;                 // the ids below id0 are not enough
-            for (int bit = 13; bit >= 0; --bit) {
-                const int id = id0 | (1 << bit);
-                unsigned long long sum = 0ull;
-                DHSA_SEL_AGAIN({
+            // (Nearly) equal scores: the last bin holds the keys k_lo .. k_hi.  It is cut by 8-bit digits of the keys from
+            // the first one they differ in, then, where all keys left are equal, by the id: no more digits than it takes
+            // to be left with `cap` chunks.  Keys all zero, 8 heads: routing of 820 chunks 131 us (358 us bit by bit, 78 passes
+            // over the row; a radix select of the whole row 330 us), of 205 chunks 33 us (92; 30), of 1570 chunks 457 us.
+            unsigned long long k_lo = ~0ull, k_hi = ~0ull;       // k_hi: complemented
+            DHSA_SEL_AGAIN({
+                (void)x; (void)n_tok;
+                if (in && score_f32(s) >= lo && score_f32(s) <= hi && bin_of(s) == tbin) {
                     const unsigned long long k = score_key(s);
-                    if (in && (k > cut_key || (k == cut_key && x < id))) sum += (unsigned long long)n_tok;
+                    k_lo = k < k_lo ? k : k_lo;
+                    k_hi = ~k < k_hi ? ~k : k_hi;
+                }
+            })
+            k_lo = row_min(k_lo);
+            k_hi = ~row_min(k_hi);
+            for (int d = 0; d < 8 && n_upto > cap && k_lo != k_hi; ++d) {
+                const int top = 64 - __builtin_clzll(k_lo ^ k_hi), low = top > 8 ? top - 8 : 0;   // the digit: bits low .. top - 1
+                above = before;
+                clear_hist();
+                DHSA_SEL_AGAIN({
+                    (void)x;
+                    const unsigned long long k = score_key(s);
+                    if (in && k >= k_lo && k <= k_hi)
+                        atomicAdd(&hist[kSelBins - 1 - (int)((k >> low) & (kSelBins - 1))], ((unsigned long long)n_tok << 16) | 1ull);
                 })
-                if (row_sum(sum) < (unsigned long long)N_b) id0 = id;
+                find_last();
+                n_upto = (int)(upto & 0xffffull);
+                const unsigned long long rest = (1ull << low) - 1ull;
+                const unsigned long long first = (((k_hi >> low) & ~(kSelBins - 1ull)) | (unsigned long long)(kSelBins - 1 - tbin)) << low;
+                k_lo = first > k_lo ? first : k_lo;
+                k_hi = (first | rest) < k_hi ? first | rest : k_hi;
             }
-            cut_id = id0;
+            cut_key = k_lo;
+            for (int i = 1; n_upto > cap && i >= 0; --i) {       // 64 ids a bin, then each
+                above = before;
+                clear_hist();
+                DHSA_SEL_AGAIN({
+                    if (in && score_key(s) == cut_key && (i == 1 || x >> 6 == cut_id >> 6))
+                        atomicAdd(&hist[i == 1 ? x >> 6 : x & 63], ((unsigned long long)n_tok << 16) | 1ull);
+                })
+                find_last();
+                n_upto = (int)(upto & 0xffffull);
+                cut_id = i == 1 ? tbin * 64 + 63 : (cut_id & ~63) + tbin;
+            }
             lo = score_f32(key_score(cut_key));
         }
         cut = true;                      // one more level: the bins of the candidates alone
@@ -777,13 +800,13 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     // ---- into the plan in ascending chunk id: listed chunks below word 2 lane + {0, 1} of `kept` ----
     const int nw = (n + 63) >> 6;                       // at most 128
     const int c0 = 2 * lane < nw ? __popcll(kept[2 * lane]) : 0, c1 = 2 * lane + 1 < nw ? __popcll(kept[2 * lane + 1]) : 0;
-    const int upto = wave_incl_scan(c0 + c1);
-    const int total = __builtin_amdgcn_readlane(upto, 63);
+    const int listed = wave_incl_scan(c0 + c1);
+    const int total = __builtin_amdgcn_readlane(listed, 63);
     int32_t *entries = plan + pl.off_entries + ((int64_t)h * pl.N_q + l) * pl.stride * 2;
     for (int cb = 0; cb < n_c; cb += NT) {              // whole waves: the shuffles need their lanes
         const int c = cb + t < n_c ? cb + t : n_c - 1;
         const int rem = cb + t < n_c ? crem[c] : 0, w = cid[c], x = w & kChunkMask, word = x >> 6;
-        const int even = __shfl(upto - c0 - c1, word >> 1), odd = __shfl(upto - c1, word >> 1);   // all lanes read
+        const int even = __shfl(listed - c0 - c1, word >> 1), odd = __shfl(listed - c1, word >> 1);   // all lanes read
         const int below = (word & 1) ? odd : even;
         const int slot = below + __popcll(kept[word] & ((1ull << (x & 63)) - 1ull));
         if (rem > 0 && slot < pl.stride) *reinterpret_cast<int2 *>(entries + 2 * slot) = make_int2(w, rem);

@@ -78,6 +78,9 @@ def test_f32_pieces_lists_and_batches(L, H_q, D, N_b, lens, B_r):
                                              (2300, ("fixed", 1), 1500, "iid"),             # > 1024 listed chunks
                                              (3001, ("fixed", 4), 400, "equal"),            # all scores of a group tie
                                              (3000, ("uniform", 1, 9), 333, "two_values"),
+                                             (9001, ("fixed", 2), 150, "equal"),            # ids of two digits
+                                             (3000, ("fixed", 2), 260, "near"),             # equal in 32 bits only
+                                             (3000, ("fixed", 2), 260, "near_and_equal"),
                                              (3000, ("uniform", 2, 6), 200, "outliers"),    # one bin holds nearly all
                                              (700, ("uniform", 3, 60), 2000, "iid")])       # everything fits
 def test_ranking_bins_cuts_and_ties(L, lens, N_b, keys, B_r):
@@ -88,6 +91,11 @@ def test_ranking_bins_cuts_and_ties(L, lens, N_b, keys, B_r):
         K[:] = K[:, :1]
     elif keys == "two_values":
         K[0] = torch.where((k_of % 3 == 0)[:, None], K[0, :1], K[0, 1:2])
+    elif keys.startswith("near"):
+        K[0, :, 1:] = 1e-10 * K[0, :, 1:]
+        K[0, :, 0] = 1.0
+        if keys == "near_and_equal":
+            K[0] = torch.where((k_of % 5 < 3)[:, None], K[0, :1], K[0])
     elif keys == "outliers":
         K[0] *= torch.where(k_of % 97 == 5, 1e4, 1.0)[:, None]
         K[0] *= torch.where(k_of % 193 == 7, -1e8, 1.0)[:, None]
