@@ -4,14 +4,20 @@ import os
 import re
 import subprocess
 
+import pytest
+
 from paper_2510_24606_amd import build
 
 
 @functools.lru_cache(maxsize=None)
+def assembly_text(source):
+    cmd = [build.hipcc()] + build.FLAGS + ["--cuda-device-only", "-S", "-o", "-", os.path.join(build.HERE, "csrc", source)]
+    return subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, check=True).stdout
+
+
 def assembly(source):
     """{kernel symbol: its lines}"""
-    cmd = [build.hipcc()] + build.FLAGS + ["--cuda-device-only", "-S", "-o", "-", os.path.join(build.HERE, "csrc", source)]
-    text = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, check=True).stdout
+    text = assembly_text(source)
     found = re.findall(r"^(_Z\S+):[^\n]*\n(.*?)^\.Lfunc_end", text, flags=re.S | re.M)
     return {name: [line.strip() for line in body.splitlines()] for name, body in found}
 
@@ -26,3 +32,16 @@ def test_a_kept_boundary_is_marked_before_it_stops_being_undecided():
         back = ops[max(0, i - 8):i]
         mark = max(j for j, op in enumerate(back) if op.startswith("ds_or_b32"))
         assert any("lgkmcnt(0)" in op for op in back[mark:]), back
+
+
+def scratch(source):
+    """{kernel symbol: bytes of scratch memory per lane}"""
+    return {name: int(n) for name, n in re.findall(r"\.amdhsa_kernel (\S+)\n.*?\.amdhsa_private_segment_fixed_size (\d+)",
+                                                   assembly_text(source), flags=re.S)}
+
+
+@pytest.mark.parametrize("source", ["recall.hip"])
+def test_kernels_keep_their_registers(source):
+    """Spilled registers go through memory in the inner loop."""
+    found = scratch(source)
+    assert found and not any(found.values()), found
