@@ -32,8 +32,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kF32Keys = 1024;   // selected keys whose positions and masks are in LDS at a time
 constexpr int kF32Seg = 256;     // plan entries per batch
 
+// D = 64, RW = 2 is held to three waves per SIMD (168 registers, nothing spilled; left to itself it takes 178): L = 8192,
+// N_b = 512, 16 heads 285 -> 250 us.  D = 128, RW = 2 spills nine registers, all of them lane addresses of the
+// prefix sum that a batch of entries needs once; the loop over the keys has none.
 template <int D, int RW>
-__global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *__restrict__ Q,
+__global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(PlanView pv, const float *__restrict__ Q,
                                                      const float *__restrict__ K, const float *__restrict__ V,
                                                      float *__restrict__ O, unsigned block0, int H_q, int G, float scale_log2e,
                                                      int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(PlanView pv, const float *_
                 // Four partial sums of D / 4 products each, one after the other (all four at once spill 40 registers at
                 // D = 128, RW = 2): rounded along one chain of D products a score, and with it O, is further from its
                 // 64-bit value (relative 2.7e-7 against 1.5e-7 at L = 2048, D = 64; 3.3e-7 against 2.0e-7 at L = 5061,
-                // D = 128).  L = 8192, N_b = 512, 16 heads: 456 -> 454 us at D = 128, 230 -> 257 us at D = 64.
+                // D = 128).
                 f32x4 s[RW];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {

@@ -45,3 +45,10 @@ def test_kernels_keep_their_registers(source):
     """Spilled registers go through memory in the inner loop."""
     found = scratch(source)
     assert found and not any(found.values()), found
+
+
+def test_f32_attention_of_small_heads_keeps_three_waves():
+    """32-row workgroups of D = 64: 512 registers per SIMD lane hold three waves of at most 168."""
+    (n,) = [int(n) for name, n in re.findall(r"\.amdhsa_kernel (\S+)\n.*?\.amdhsa_next_free_vgpr (\d+)",
+                                             assembly_text("attn.hip"), flags=re.S) if "ILi64ELi2E" in name]
+    assert n <= 168 and [b for name, b in scratch("attn.hip").items() if "ILi64ELi2E" in name] == [0]
