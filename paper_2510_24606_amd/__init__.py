@@ -12,7 +12,11 @@ import os
 from typing import Optional, Tuple
 
 import numpy as np
-import torch
+
+try:
+    import torch
+except ImportError:   # sizes, plan parsing and the build need no torch; what works on tensors does
+    torch = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdhsa.so")
@@ -32,7 +36,7 @@ EXPORTS = ["dhsa_plan_bytes", "dhsa_workspace_bytes", "dhsa_route", "dhsa_sparse
            "dhsa_status_string", "dhsa_version"]
 
 
-_DTYPES = {torch.float32: DHSA_F32, torch.bfloat16: DHSA_BF16}
+_DTYPES = {} if torch is None else {torch.float32: DHSA_F32, torch.bfloat16: DHSA_BF16}
 
 
 class dhsa_problem(C.Structure):

@@ -4,6 +4,8 @@ arguments before any device call."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -25,6 +27,21 @@ def header_symbols():
     text = open(os.path.join(ROOT, "include", "dhsa.h")).read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     return sorted(set(re.findall(r"\b(dhsa_[a-z_]+)\s*\(", text)))
+
+
+def test_sizes_and_build_module_without_torch(lib):
+    code = """
+import sys
+sys.modules["torch"] = None                        # import torch raises ImportError
+import numpy as np
+import paper_2510_24606_amd as dhsa
+import paper_2510_24606_amd.build
+p = dhsa.dhsa_problem(L=1000, H_q=4, H_kv=2, D=128, N_c=10, N_b=64, dtype=dhsa.DHSA_BF16)
+B = np.linspace(0, 1000, 11).astype(np.int32)
+assert dhsa.dhsa_plan_bytes(p, B) > 0 and dhsa.dhsa_workspace_bytes(p, B) > 0
+assert dhsa.dhsa_decode_workspace_bytes(p, 10, 1000) > 0 and dhsa.n_query_groups(p) == 10
+"""
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=300)
 
 
 def test_every_declared_symbol_is_exported(lib):
