@@ -298,12 +298,17 @@ __global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(Pl
         }
         const float inv = L > 0.f ? 1.f / L : 0.f;   // a row that sees no key of its block's list: zeros
         acc *= inv;
-        if (sm.me.odd[0] | sm.me.odd[1] | sm.me.odd[2] | sm.me.odd[3]) {
+        const bool none = L == 0.f;                  // no key at all, or only keys whose score is -inf: NaN
+        if (none | sm.me.odd[0] | sm.me.odd[1] | sm.me.odd[2] | sm.me.odd[3]) {
             for (int e = 0; e < E; ++e) {
                 const int2 w = ent[e];
                 const int k = w.x & kChunkMask, pos = w.x >> kPosShift, b0 = pv.B[k];
                 int take = entry_take(pos, w.y, pv.B[k + 1] - b0, v_lo + r);
                 if (pos == 3 && row0 + r + 1 - b0 < take) take = row0 + r + 1 - b0;   // listed keys past the row
+                if (none) {
+                    if (take > 0) acc = f32x4{NAN, NAN, NAN, NAN};
+                    continue;
+                }
                 for (int t = 0; t < take; ++t) {
                     const f32x4 v = *reinterpret_cast<const f32x4 *>(V + (int64_t)g * vs_h + (int64_t)(b0 + t) * vs_l + d);
 #pragma unroll

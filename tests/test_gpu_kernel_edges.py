@@ -200,6 +200,36 @@ def test_f32_infinite_values_reach_only_the_rows_that_take_them(L, D, B_r):
     np.testing.assert_allclose(got, ref, rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("B_r", [0, 96])
+@pytest.mark.parametrize("L,D", [(300, 64), (300, 128), (4100, 64)])
+def test_f32_rows_of_nothing_but_minus_infinity(L, D, B_r):
+    """The softmax of scores that are all -inf is NaN; beside a finite one they weigh nothing; a row without a key is zero."""
+    w = dhsa_inputs.make("c1", L=L, H_q=8, H_kv=2, D=D, N_b=60, lens=("uniform", 16, 64))
+    w.Q[:, :, 1] = 1.0
+    w.K[:, :80, 1] = float("-inf")
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    O = torch.empty_like(Q)
+    prob = dhsa.problem(Q, K, w.B, w.N_b, B_r=B_r)
+    plan, ws = dhsa.alloc(prob, w.B)
+    dhsa.dhsa_prefill(prob, Q, K, V, w.B, O, plan, ws)
+    rows = np.arange(0, L, 1 if L < 2000 else 7, dtype=np.int64)
+    Qh, Kh, Vh = (w.f32(x).astype(np.float64) for x in "QKV")
+    want = np.zeros((8, len(rows), D))
+    for h in range(8):
+        idx, cnt = (x.cpu().numpy() for x in dhsa.dhsa_plan_expand_rows(prob, plan, h, rows))
+        for t, i in enumerate(rows):
+            j = idx[t, :cnt[t]]
+            j = j[j <= i]
+            if len(j):
+                s = Kh[h // 4, j] @ Qh[h, i] / np.sqrt(D)
+                with np.errstate(invalid="ignore"):
+                    p = np.exp(s - s.max())
+                want[h, t] = p @ Vh[h // 4, j] / p.sum()
+    got = O[:, torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
+    assert np.isnan(want).any() and np.isfinite(want).any()
+    np.testing.assert_allclose(got, want, rtol=0, atol=1e-5)
+
+
 @pytest.mark.parametrize("L,H_q,D", [(2048, 4, 64), (6001, 16, 64), (2048, 4, 128), (6001, 16, 128)])
 def test_f32_error_against_64_bits(L, H_q, D):
     """16- and 32-row workgroups.  A score of D unit normals summed in four chains of D / 4 leaves O 1.8e-7 to 2.1e-7
