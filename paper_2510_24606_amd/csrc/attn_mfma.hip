@@ -962,14 +962,18 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
         if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) { all[to] += all[c]; all[c] = 0; }
     }
     const int first[3] = {0, own[0], own[0] + own[1]};
+    // a launch takes tiles of its own class from the end of their table, as many as fit a grid; the first one also takes
+    // the shorter tiles that joined (a tile has one result, whatever its launch)
+    const int per_grid = p.H_q < kGridMax ? kGridMax / p.H_q : 1;
 #define DHSA_LAUNCH1(D_, CLS, MIX)                                                                           \
-    hipLaunchKernelGGL((k_attn_mfma<D_, CLS, MIX>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, first[CLS],   \
-                       own[CLS], all[CLS])
+    hipLaunchKernelGGL((k_attn_mfma<D_, CLS, MIX>), grid, dim3(256), 0, s, pv, a, p.H_q, mode, tile0, T0, T)
 #define DHSA_LAUNCH(CLS)                                                                                     \
-    if (all[CLS] > 0) {                                                                                      \
-        const int mode = attn_order(want, p.H_kv, p.G, all[CLS]);                                            \
-        const dim3 grid(p.H_q * all[CLS]);                                                                   \
-        const bool mix = all[CLS] > own[CLS];                                                                \
+    for (int left = all[CLS] > 0 ? own[CLS] : 0, T0; left > 0; left -= T0) {                                 \
+        T0 = left < per_grid ? left : per_grid;                                                              \
+        const int tile0 = first[CLS] + left - T0, T = T0 + (left == own[CLS] ? all[CLS] - own[CLS] : 0);     \
+        const int mode = attn_order(want, p.H_kv, p.G, T);                                                   \
+        const dim3 grid(p.H_q * T);                                                                          \
+        const bool mix = T > T0;                                                                             \
         if (p.D == 64) { if (mix) DHSA_LAUNCH1(64, CLS, (CLS < 2)); else DHSA_LAUNCH1(64, CLS, false); }     \
         else { if (mix) DHSA_LAUNCH1(128, CLS, (CLS < 2)); else DHSA_LAUNCH1(128, CLS, false); }             \
     }

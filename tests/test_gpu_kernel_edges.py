@@ -248,13 +248,15 @@ def test_f32_error_against_64_bits(L, H_q, D):
     assert rel < 2.4e-7
 
 
-def test_more_workgroups_than_one_launch_holds():
-    """Row blocks of one row, 16 heads of 2^20 rows: 2^24 workgroups of the fp32 attention.  Heads are independent and
-    every row's sums have one order, so two calls of eight heads (2^23 workgroups each) give the same bits."""
-    L, H_q, D, N_b = 1 << 20, 16, 64, 16
+@pytest.mark.parametrize("dtype,H_q", [(torch.float32, 16), (torch.bfloat16, 40)])
+def test_more_workgroups_than_one_launch_holds(dtype, H_q):
+    """Row blocks of one row, heads of 2^20 rows: a workgroup of the attention each, and a quarter of one in the ranking
+    (40 heads: five launches of the attention, two of the ranking).  Heads are independent and every row's sums have one
+    order, so calls of eight heads (2^23 workgroups) give the same bits."""
+    L, D, N_b = 1 << 20, 64, 16
     gen = torch.Generator(device="cuda").manual_seed(5)
-    Q = torch.randn(H_q, L, D, device="cuda", generator=gen)
-    K, V = (torch.randn(1, L, D, device="cuda", generator=gen) for _ in range(2))
+    Q = torch.randn(H_q, L, D, dtype=dtype, device="cuda", generator=gen)
+    K, V = (torch.randn(1, L, D, dtype=dtype, device="cuda", generator=gen) for _ in range(2))
     B = np.array([0, 700, 300000, 300050, L], dtype=np.int32)
 
     def prefill(q):
@@ -265,8 +267,9 @@ def test_more_workgroups_than_one_launch_holds():
         return O
 
     whole = prefill(Q)
-    for h in (0, 8):
-        assert torch.equal(whole[h:h + 8], prefill(Q[h:h + 8]))
+    assert torch.isfinite(whole[:, -1]).all()
+    for h in (0, 8, H_q - 8):
+        assert torch.equal(whole[h:h + 8].view(torch.uint8), prefill(Q[h:h + 8]).view(torch.uint8))
 
 
 @pytest.mark.parametrize("D", [64, 128])
