@@ -51,6 +51,24 @@ def test_finalize_boundaries_parity(kind, L, tau, W):
     np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("L", [(1 << 22) - 1, 1 << 22])
+def test_long_sequences_pin_little_memory(L):
+    """Below 2^22 positions the result is written to pinned host memory, which torch keeps; from there on to the device."""
+    rng = np.random.default_rng(4)
+    p = (0.2 * rng.random(L)).astype(np.float32)
+    at = np.cumsum(rng.integers(20, 80, size=L // 20))
+    at = at[at < L - 1]
+    p[at] += 0.5
+    kept = at[np.r_[True, np.diff(at) > 8]]              # peaks are further apart than the window
+    assert len(kept) == len(at)
+    scores = torch.from_numpy(p).cuda()
+    before = torch.cuda.host_memory_stats()["allocated_bytes.allocated"]
+    got = dhsa.dhsa_finalize_boundaries(scores, 0.4, 8)
+    np.testing.assert_array_equal(got, np.r_[0, at + 1, L])
+    pinned = torch.cuda.host_memory_stats()["allocated_bytes.allocated"] - before
+    assert L < 1 << 22 or pinned < 4096                  # reading one number takes a few bytes; the result has L + 2 words
+
+
 def test_boundaries_feed_the_path():
     """Scores -> boundaries on the GPU -> the prefill path on those boundaries, against the oracle end to end."""
     import dhsa_inputs
