@@ -235,6 +235,19 @@ def main() -> int:
         return [float(per_tile[launch_of_tile == c].sum()) for c in range(3)], [int((launch_of_tile == c).sum())
                                                                                  for c in range(3)]
 
+    def launch_of_class(w, ntiles):
+        """The attention launch that runs the row tiles of each height class: its own, or the next taller one's where
+        the class has at most 512 tiles over all heads (dhsa_prefill_stage_times; fp32: one launch for all)."""
+        if w.dtype != "bf16":
+            return [0, 0, 0]
+        at, n = [0, 1, 2], list(ntiles)
+        for c in (2, 1):
+            to = c - 1 if ntiles[c - 1] > 0 else 0
+            if n[c] > 0 and ntiles[to] > 0 and w.H_q * n[c] <= 512:
+                n[to], n[c] = n[to] + n[c], 0
+                at = [to if x == c else x for x in at]
+        return at
+
     def stage_report(w, Q, K, V, O, prob, plan, ws, B_r, reps=5):
         """Per-stage and per-attention-launch milliseconds (median of `reps` passes with events between the
         kernels), the FLOP of each launch and its fraction of the bf16 MFMA peak."""
@@ -242,12 +255,13 @@ def main() -> int:
         med = {k: float(np.median([r[k] for r in runs])) for k in dhsa.STAGES}
         pairs, ntiles = attended_pairs_by_class(w, B_r, plan)
         launches = {}
+        ran_in = launch_of_class(w, ntiles)
         for c, (label, stage) in enumerate(ROW_CLASSES):
-            fl = 4.0 * w.D * pairs[c]
-            launches[label] = {"tiles_per_head": ntiles[c], "flop": fl, "ms": round(med[stage], 4),
+            fl = 4.0 * w.D * sum(p for p, at in zip(pairs, ran_in) if at == c)
+            launches[label] = {"tiles_per_head": sum(n for n, at in zip(ntiles, ran_in) if at == c), "flop": fl,
+                               "ms": round(med[stage], 4),
                                "frac_of_bf16_mfma_peak": (round(fl / (med[stage] * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, 5)
                                                           if med[stage] > 0.01 and w.dtype == "bf16" else None)}
-            # (a class of few tiles runs in the launch of the next taller one: its own stage is then empty)
         stages = {"t_setup": round(med["setup"], 4), "t_pool": round(med["pool"], 4), "t_sc": round(med["scores"], 4),
                   "t_select": round(med["select"], 4),
                   "t_attn": round(med["attn_rows_gt64"] + med["attn_rows_33_64"] + med["attn_rows_le32"], 4),
