@@ -8,11 +8,12 @@
 // position (softmax is order-free) and packed densely into tiles of 64 keys;
 // a packed key carries (row offset, lo, hi) with "row takes key <=> lo < v < hi".
 //
-// Row tiles are launched by height: tiles of more than 64 rows on the body
-// described next (attn_tile_32), tiles of at most 64 and at most 32 rows on 16-row
-// MFMA blocks (attn_tile_16, described at that function), one launch each.
+// A row tile runs the body of its height: more than 64 rows the one described next
+// (attn_tile_32), at most 64 and at most 32 rows the two of 16-row MFMA blocks
+// (attn_tile_16, described at that function).  There is a launch per height, but a
+// height of few tiles joins the launch of the next taller one (launch_attn_mfma).
 //
-// Four waves; each owns one 32-row block.  Scores are computed transposed,
+// attn_tile_32: four waves; each owns one 32-row block.  Scores are computed transposed,
 // S^T = K Q^T (keys are the MFMA M dimension), so a lane holds 16 keys of ONE
 // query row per 32-key block: the row max / sum stay in the lane (one exchange
 // with lane ^ 32), and the exponentiated scores are already laid out as the B
@@ -277,7 +278,6 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     // Wave = one 32-row block of the tile (rotated per workgroup so that the waves left without
     // rows do not always sit on the same SIMD), every 32-key block of the key list.
     const int rb = (wave + (blockIdx.x >> 3)) & 3;
-    constexpr int kbw = 0;
     const bool wave_live = rb * 32 < nrows;
     const int v_i = v_lo + rb * 32 + lr;  // this lane's query row (may be a padding row)
 
@@ -327,7 +327,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     const int k_sw = piece_swizzle(lr, OPR);
     int k_off[NS];   // points into the K buffer of the current tile; moved once per tile
 #pragma unroll
-    for (int s = 0; s < NS; ++s) k_off[s] = 2 * ((kbw * 32 + lr) * D + 8 * ((2 * s + g2) ^ k_sw));
+    for (int s = 0; s < NS; ++s) k_off[s] = 2 * (lr * D + 8 * ((2 * s + g2) ^ k_sw));
     // Transpose-read source of this lane: row 8 half + 4 g2 + c of a 16-row group,
     // logical piece P = 4 db + 2 dh + (r >> 1), physical piece P ^ swizzle(row).  The
     // swizzle's bits 2-3 are (c >> 1) and half, so the physical piece is
@@ -337,8 +337,8 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     const int tr_c = (lane & 15) >> 2, tr_r = lane & 3, tr_dh = (lane >> 4) & 1;
     const int tr_low2 = ((tr_r >> 1) ^ g2) | ((tr_dh ^ (tr_c & 1)) << 1);
     const int tr_l0 = (4 * g2 + tr_c) * D + 8 * tr_low2 + 4 * (tr_r & 1);
-    int v_base_e = 2 * (kbw * 32 * D + tr_l0 + 32 * (tr_c >> 1));   // moved once per tile
-    int v_base_o = 2 * (kbw * 32 * D + tr_l0 - 32 * (tr_c >> 1));
+    int v_base_e = 2 * (tr_l0 + 32 * (tr_c >> 1));   // moved once per tile
+    int v_base_o = 2 * (tr_l0 - 32 * (tr_c >> 1));
     const char *const smK8 = reinterpret_cast<const char *>(sm.K);
     const char *const smV8 = reinterpret_cast<const char *>(sm.V);
 
@@ -445,8 +445,6 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
         unsigned ko_lo[KPT], ko_hi[KPT], vo[KPT];   // row offsets of the loads this lane issues next
         if (wave < ntiles) DHSA_MAKE_META(wave);   // key lists of tiles 0..3
         __syncthreads();
-        {
-        // ================= tiles of more than 64 rows =================
         // ---- prologue: K(0), V(0), lower half of K(1) in LDS; S(0, block 0) ----
         DHSA_OFFS(ko_lo, key_koff, 0, 0, KPT / 2);
         DHSA_OFFS(ko_hi, key_koff, 0, KPT / 2, KPT);
@@ -535,7 +533,6 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
             v_base_e -= 2 * kTile;
             v_base_o -= 2 * kTile;
         }
-        }
 #undef DHSA_QK
 #undef DHSA_MASK
 #undef DHSA_ROWMAX
@@ -544,7 +541,7 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
     }
 
     // ---- epilogue: normalise, round to bf16, store ----
-    if (wave_live && kbw == 0) {
+    if (wave_live) {
         const float l_tot = l_run + __shfl_xor(l_run, 32);
         const int r = rb * 32 + lr;
         if (r < nrows) {
@@ -564,15 +561,14 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
 }
 
 // ---------------------------------------------------------------------------
-// Row tiles of at most 96 rows: 16-row MFMA blocks (v_mfma_f32_16x16x32_bf16).
+// Row tiles of at most 32 RW rows, RW = 1 or 2: 16-row MFMA blocks
+// (v_mfma_f32_16x16x32_bf16).
 //
-// The tile's rows are cut into two row groups of 16 RW rows (RW = 1, 2, 3: tiles
-// of at most 32, 64, 96 rows); a wave owns one row group and ONE of the two
-// 32-key blocks of every 64-key tile ("key parity" kbw), so all four waves work
-// whatever the tile's height, and the two waves of a row group merge their
-// partial softmax states at the end.  A K or V fragment read from LDS serves the
-// RW row blocks of the wave (at RW = 3 a third less LDS traffic per product
-// than one 32-row block per wave).
+// The tile's rows are cut into two row groups of 16 RW rows; a wave owns one row
+// group and ONE of the two 32-key blocks of every 64-key tile ("key parity" kbw),
+// so all four waves work whatever the tile's height, and the two waves of a row
+// group merge their partial softmax states at the end.  A K or V fragment read
+// from LDS serves the RW row blocks of the wave.
 //
 // Lane l = 16 q + n of a wave.  S^T block = K (16 keys x 32 d) Q^T (32 d x 16
 // rows): the lane holds, per row block r and key half kh, the scores of row n of
@@ -586,9 +582,9 @@ __device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv
 //
 // K rows are swizzled by row & 15 here (16-byte column reads of 16 rows x 4
 // pieces; the swizzle of the 32-row kernel would make two lanes of a bank group
-// collide), V rows as in the kernel above.  Loads, key lists and the pipeline
-// (scores of this wave's block of tile n + 1 on the matrix unit while the block
-// of tile n is exponentiated) are those of the key-parity path above.
+// collide), V rows as in the body above, whose key lists and loads are used here
+// too.  Iteration n takes tile n from scores to O += P V; only the loads run
+// ahead, those of tile n + 1, issued between the products.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -650,7 +646,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         for (int j = 0; j < NJ; ++j) oacc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // staging (as in the kernel above; K with its own swizzle)
+    // staging (as in the body above; K with its own swizzle)
     constexpr int RPW = 64 / OPR;
     const int ld_row0 = wave * RPW + lane / OPR;
     const unsigned ld_piece_bytes_k = 16u * ((lane % OPR) ^ piece_swizzle_k16(ld_row0, OPR));
@@ -728,7 +724,7 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
         mx = fmaxf(m_, __shfl_xor(m_, 32));                                                     \
     }
 
-// P = exp2(S c - m_ref c) per row block, with the lazily moved exponent reference of the kernel above.  One range
+// P = exp2(S c - m_ref c) per row block, with the lazily moved exponent reference of the body above.  One range
 // check for all row blocks, but only those that need it move their reference: the rounding of a row's probabilities
 // hangs on no row outside its own 16.
 #define DHSA_EXP16(sacc, pf)                                                                    \
@@ -942,8 +938,8 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // full tile height whose K and V of eight heads exceed the 256 MB memory-side cache while those of
     // four fit: four in flight, each on two XCDs -- the L2s then miss more often (53 % hits instead of
     // 56 % on c3) but mostly into that cache, and the step measures 4-5 % faster; the row form on the
-    // dynamic chunks, which is bound by what crosses the fabric, gains nothing from it (0-1 %) and asks
-    // the fabric for 30 % more, so it keeps eight.  Two or one in flight are slower in both forms.
+    // dynamic chunks gains nothing from it (0-1 %) and asks the fabric for 30 % more, so it keeps eight.
+    // Two or one in flight are slower in both forms.
     const double kv_head_bytes = 2.0 * (double)p.L * (double)(p.ks_l + p.vs_l);
     const int want = (p.B_r >= kRowTile && 8 * kv_head_bytes > 288e6 && 4 * kv_head_bytes <= 288e6) ? 4 : 8;
     AttnArgs a;

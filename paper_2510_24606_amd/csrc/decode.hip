@@ -341,6 +341,8 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
         if (tid == 0) { put(&pp[0], M); put(&pp[1], ls); }
     }
     if constexpr (!FUSE) return;
+    // The count below is relaxed, so by the memory model alone it orders nothing.  What it rests on is gfx950: a store of
+    // agent scope is written through the XCD's L2, and vmcnt counts it until the memory side has acknowledged it.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the compiler's order, and
     __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0): the stores have reached the memory side
     __syncthreads();

@@ -73,7 +73,9 @@ struct DecodeLayout {
 };
 // Selected keys per workgroup of the decode attention step: 32 while longer slices would not make a workgroup for
 // every CU (a chain of loads then takes the time, and four times as many run side by side); else 128 and more, so many
-// that the workgroups fit the chip at once (five per CU of the bf16 kernel at D = 128).
+// that there are at most five workgroups per CU.  That is what a CU holds of the bf16 kernel at D = 128; it would hold
+// seven at D = 64 and eight in fp32, but shorter slices gain nothing there: 32 heads of D = 64, N_b = 8192 35.5 us with
+// five, 36.6 us with seven; 16 fp32 heads of D = 64 32.8 us with five, 33.7 us with eight (128: 45.4, 45.5 us).
 constexpr int kDecSlice = 128, kDecSliceFew = 32, kDecSliceMax = 512;
 inline int decode_slice(int H_q, int64_t N_b) {
     if (H_q * ((N_b + kDecSlice - 1) / kDecSlice) < 256) return kDecSliceFew;
