@@ -489,6 +489,7 @@ __device__ __forceinline__ unsigned long long wave_read(unsigned long long x, in
 // ---------------------------------------------------------------------------
 constexpr int kSelBins = 256;
 constexpr int kSelPer = 8;           // scores per lane in registers
+constexpr int kSelCrowd = 32;        // candidates in one bin that are still compared with one another
 constexpr int kSelMaxStride = 1024;  // listed chunks this kernel can hold; with more the whole row is sorted (below)
 
 static int select_cap(int stride) { return (stride + 2 + 32 + 63) / 64 * 64; }   // some to spare before a bin is cut again
@@ -589,6 +590,8 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
                 lo_ = fminf(lo_, __uint_as_float((unsigned)(x >> 32)));
                 hi_ = fmaxf(hi_, __uint_as_float((unsigned)x));
             }
+            lo_ = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lo_)));   // the same in all lanes:
+            hi_ = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(hi_)));   // no vector registers
         }
     };
     const auto row_min = [&](unsigned long long x) {     // NW > 1: two barriers
@@ -634,6 +637,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     };
     unsigned long long above = 0ull;     // tokens << 16 | chunks with a score above hi
     unsigned long long before, upto;     // ranked before the last bin, and up to it
+    bool crowded;                        // some bin of candidates holds more than kSelCrowd of them
     // From the counts in hist, every wave for itself: what is ranked before each bin (tokens, and chunks = the place of
     // its first) goes to place; the last bin is the one in which the tokens reach N_b (none does: the worst of all)
     const auto find_last = [&] {
@@ -660,6 +664,13 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
         tbin = found ? __builtin_amdgcn_readlane(my_bin, src) : kSelBins - 1;
         before = wave_read(before, src);
         upto = wave_read(found ? upto : run, src);
+        int most = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n_bin = (int)c[i] & 0xffff;
+            most = (cut || 4 * lane + i <= tbin) && n_bin > most ? n_bin : most;
+        }
+        crowded = __ballot(most > kSelCrowd) != 0ull;
     };
     for (int level = 0;; ++level) {
         inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
@@ -773,21 +784,80 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
 #undef DHSA_SEL_FOR
 #undef DHSA_SEL_AGAIN
     sync();
-    int n_c = (int)(place[tbin] & 0xffffull);
+    int n_c = __builtin_amdgcn_readfirstlane((int)(place[tbin] & 0xffffull));
     n_c = n_c < cap ? n_c : cap;
 
+    // A bin that holds many (ties; all scores but an outlier's) would cost their number squared: the list is sorted
+    // instead, by a network whose comparisons all put the better one first, so that nothing is moved past its end,
+    // and the tokens before each candidate are a prefix sum.  Routing of 820 chunks, 32 heads, keys all zero: 1070 ->
+    // 223 us; 500 chunks of one token, 12 heads, with outliers: 874 -> 160 us (ordinary scores: 78 us)
+    if (crowded) {
+        const auto first = [&](unsigned long long ka, int wa, unsigned long long kb, int wb) {
+            return ka > kb || (ka == kb && (wa & kChunkMask) < (wb & kChunkMask));
+        };
+        bool any = false;                // equal scores, taken in ascending order of the ids, are in order already
+        for (int c = t; c + 1 < n_c; c += NT) any |= first(ckey[c + 1], cid[c + 1], ckey[c], cid[c]);
+        any = __any(any);
+        if constexpr (NW > 1) {
+            if (lane == 0) s_red[wave] = any;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < NW; ++w) any |= s_red[w] != 0ull;
+        }
+        int half = any ? 1 : 0;
+        while (any && 2 * half < n_c) half *= 2;
+#pragma unroll 1
+        for (int size = 1; size <= half; size *= 2) {    // runs of `size` are in order: join two, the second one reversed
+#pragma unroll 1
+            for (int step = size; step > 0; step >>= 1) {
+#pragma unroll 1
+                for (int p = t; p < half; p += NT) {
+                    const int in_run = p & (step - 1), lo_at = 2 * p - in_run;
+                    const int hi_at = step == size ? lo_at + 2 * (step - in_run) - 1 : lo_at + step;
+                    if (hi_at >= n_c) continue;
+                    const unsigned long long ka = ckey[lo_at], kb = ckey[hi_at];
+                    const int wa = cid[lo_at], wb = cid[hi_at];
+                    if (first(kb, wb, ka, wa)) {
+                        ckey[lo_at] = kb;
+                        ckey[hi_at] = ka;
+                        cid[lo_at] = wb;
+                        cid[hi_at] = wa;
+                    }
+                }
+                sync();
+            }
+        }
+        for (int c = t; c < n_c; c += NT) clen[c] = len_at(cid[c] & kChunkMask);   // (the lengths were left where they were)
+        sync();
+        if (NW == 1 || wave == 0) {
+            const int per = (n_c + 63) >> 6, c0 = lane * per, c1 = c0 + per < n_c ? c0 + per : n_c;
+            int mine = 0;
+            for (int c = c0; c < c1; ++c) mine += clen[c];
+            int run = wave_incl_scan(mine) - mine;
+            for (int c = c0; c < c1; ++c) {
+                crem[c] = run;
+                run += clen[c];
+            }
+        }
+        sync();
+    }
     // ---- tokens ranked before each candidate, and whether some row takes a token of it ----
     for (int c = t; c < n_c; c += NT) {
         const unsigned long long k = ckey[c];
         const int w = cid[c], x = w & kChunkMask, pos = w >> kPosShift;
-        const int bin = bin_of(key_score(k));
-        const unsigned long long pb = place[bin];
-        const int j1 = (int)(pb & 0xffffull) < n_c ? (int)(pb & 0xffffull) : n_c;
-        int run = (int)(pb >> 16);
-        for (int j = bin > 0 ? (int)(place[bin - 1] & 0xffffull) : 0; j < j1; ++j) {
-            const unsigned long long kj = ckey[j];
-            const int lj = clen[j];
-            if (kj > k || (kj == k && (cid[j] & kChunkMask) < x)) run += lj;
+        int run;
+        if (crowded) {
+            run = crem[c];
+        } else {
+            const int bin = bin_of(key_score(k));
+            const unsigned long long pb = place[bin];
+            const int j1 = (int)(pb & 0xffffull) < n_c ? (int)(pb & 0xffffull) : n_c;
+            run = (int)(pb >> 16);
+            for (int j = bin > 0 ? (int)(place[bin - 1] & 0xffffull) : 0; j < j1; ++j) {
+                const unsigned long long kj = ckey[j];
+                const int lj = clen[j];
+                if (kj > k || (kj == k && (cid[j] & kChunkMask) < x)) run += lj;
+            }
         }
         int rem = N_b - run;
         const bool need = (pos == 2) ? (rem > 1) : (rem > 0);
