@@ -404,7 +404,7 @@ hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, 
     const int slice = decode_slice(p.H_q, p.N_b);
     const int S = (p.N_b + slice - 1) / slice;           // N_b is clamped to L: the row takes exactly N_b keys
     dim3 grid(S, p.H_q), block(256);
-    const bool fuse = slice == kDecSliceFew;
+    const bool fuse = slice < kDecSlice;
 #define DHSA_ATTD1(T, DD, FUSE)                                                                                   \
     hipLaunchKernelGGL((k_attn_decode<T, DD, FUSE>), grid, block, 0, s, plan + dl.pl.off_B, plan + dl.pl.off_count, \
                        plan + dl.pl.off_entries, dl.pl.stride, rb0, (int)p.L, (const T *)Q, (const T *)K,         \

@@ -149,8 +149,10 @@ DecodeLayout decode_layout(int H_q, int H_kv, int D, int64_t N_b, int N_c_cap, i
     pl.off_tiles = pl.words = pl.off_entries + (int64_t)H_q * N_c_cap * 2;
     dl.off_part = align_up(dl.off_plan + pl.words * 4, 256);
     // most slices any step up to the caps can have: N_b keys, or the most keys that still get short slices
-    const int64_t nb = std::min<int64_t>(N_b, L_cap), few = std::min<int64_t>(nb, kDecSlice * ((255 + H_q) / H_q));
-    dl.S_cap = (int)std::max((nb + kDecSlice - 1) / kDecSlice, (few + kDecSliceFew - 1) / kDecSliceFew);
+    const int64_t nb = std::min<int64_t>(N_b, L_cap);
+    const int64_t few = std::min<int64_t>((nb + kDecSliceFew - 1) / kDecSliceFew, kDecWgFew / H_q);
+    const int64_t some = std::min<int64_t>((nb + kDecSliceSome - 1) / kDecSliceSome, kDecWgSome / H_q);
+    dl.S_cap = (int)std::max({(nb + kDecSlice - 1) / kDecSlice, few, some});
     dl.off_done = align_up(dl.off_part + (int64_t)H_q * dl.S_cap * (D + 2) * 4, 256);
     dl.bytes = align_up(dl.off_done + (int64_t)H_q * 4, 256);
     return dl;

@@ -71,14 +71,19 @@ struct DecodeLayout {
     PlanLayout pl;
     int S_cap;   // most key slices (workgroups per head) of the attention step
 };
-// Selected keys per workgroup of the decode attention step: 32 while longer slices would not make a workgroup for
-// every CU (a chain of loads then takes the time, and four times as many run side by side); else 128 and more, so many
-// that there are at most five workgroups per CU.  That is what a CU holds of the bf16 kernel at D = 128; it would hold
+// Selected keys per workgroup of the decode attention step.  While workgroups are few, a chain of loads takes the time and
+// short slices run side by side, merged by the last workgroup of a head: 32 keys up to 128 workgroups, 64 up to 256.  More
+// of them wait for one another's stores, and a head's merge gets long: one head, N_b = 8192 29.9 us with 32, 25.6 us with
+// 64, 27.1 us with 128 keys; 6 heads, N_b = 4096 32.6, 27.1, 26.1 us; 8 heads, N_b = 512 20.9, 21.4, 23.4 us.  Else 128 and
+// more (merged by a kernel), so many that there are at most five workgroups per CU.  That is what a CU holds of the bf16 kernel at D = 128; it would hold
 // seven at D = 64 and eight in fp32, but shorter slices gain nothing there: 32 heads of D = 64, N_b = 8192 35.5 us with
 // five, 36.6 us with seven; 16 fp32 heads of D = 64 32.8 us with five, 33.7 us with eight (128: 45.4, 45.5 us).
-constexpr int kDecSlice = 128, kDecSliceFew = 32, kDecSliceMax = 512;
+constexpr int kDecSlice = 128, kDecSliceMax = 512;
+constexpr int kDecSliceFew = 32, kDecWgFew = 128;      // shortest slices, and the most workgroups they make
+constexpr int kDecSliceSome = 64, kDecWgSome = 256;    // the same of middling ones
 inline int decode_slice(int H_q, int64_t N_b) {
-    if (H_q * ((N_b + kDecSlice - 1) / kDecSlice) < 256) return kDecSliceFew;
+    if (H_q * ((N_b + kDecSliceFew - 1) / kDecSliceFew) <= kDecWgFew) return kDecSliceFew;
+    if (H_q * ((N_b + kDecSliceSome - 1) / kDecSliceSome) <= kDecWgSome) return kDecSliceSome;
     const int64_t at_once = 5 * 256 / H_q > 0 ? 5 * 256 / H_q : 1, slice = ((N_b + at_once - 1) / at_once + 15) / 16 * 16;
     return (int)(slice < kDecSlice ? kDecSlice : slice > kDecSliceMax ? kDecSliceMax : slice);
 }

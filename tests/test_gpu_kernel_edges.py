@@ -147,8 +147,15 @@ def test_ranking_time_hangs_little_on_the_scores(L, chunk, N_b):
 
 @pytest.mark.parametrize("L,H_q,H_kv,D,dtype,N_b,B_r", [(900, 20, 1, 128, "bf16", 31, 0),      # > 16 heads of one kv-head
                                                         (2000, 17, 1, 64, "f32", 1700, 0),
-                                                        (5000, 8, 8, 128, "bf16", 4095, 0),    # 128 short slices
-                                                        (9000, 8, 2, 64, "bf16", 4097, 0),     # 33 long ones
+                                                        (5000, 8, 8, 128, "bf16", 4095, 0),    # slices of 128 keys
+                                                        (9000, 8, 2, 64, "bf16", 4097, 0),     # one more than 32 of them
+                                                        (5000, 8, 2, 128, "bf16", 512, 0),     # the most of 32 keys
+                                                        (5000, 8, 2, 64, "f32", 513, 0),       # ... of 64
+                                                        (5000, 8, 2, 128, "bf16", 2048, 0),    # the most of 64 keys
+                                                        (5000, 8, 2, 64, "bf16", 2049, 0),     # ... of 128
+                                                        (17000, 1, 1, 64, "bf16", 16384, 0),   # 256 slices of one head
+                                                        (3000, 129, 1, 64, "bf16", 30, 0),     # a slice of 64 keys per head
+                                                        (3000, 257, 1, 64, "bf16", 30, 0),     # ... of 128
                                                         (9000, 4, 1, 128, "f32", 8300, 0),
                                                         (3000, 2, 1, 128, "bf16", 1, 64)])
 def test_decode_heads_slices_and_merge(L, H_q, H_kv, D, dtype, N_b, B_r):
