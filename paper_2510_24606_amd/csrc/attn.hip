@@ -320,8 +320,96 @@ __global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(Pl
     }
 }
 
+// ---------------------------------------------------------------------------
+// Row blocks of so few rows that the 16-row products are mostly padding: a wave per row.  Lanes take the scores of up to
+// 64 keys of a plan entry, then own output columns.  A score is four partial sums, as above.  Bound by latency (a key
+// row per lane, one key of V at a time).  L = 6000, 8 heads, D = 128, B_r = 1: N_b = 16 694 -> 146 us, N_b = 700 4.8 -> 2.8 ms.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256) void k_attn_f32_rows(PlanView pv, const float *__restrict__ Q,
+                                                       const float *__restrict__ K, const float *__restrict__ V,
+                                                       float *__restrict__ O, int64_t L, int G, int B_r, float scale_log2e,
+                                                       int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
+                                                       int64_t vs_h, int64_t vs_l, int64_t os_h, int64_t os_l) {
+    constexpr int NC = D / 64;       // output columns per lane
+    __shared__ __align__(16) float s_q[4][D];
+    if (!plan_matches(pv)) return;   // not this problem's plan: O is not written
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = blockIdx.y, g = h / G;
+    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
+    const bool live = i < L;
+    if (live)
+        for (int d = lane; d < D; d += 64) s_q[wave][d] = Q[(int64_t)h * qs_h + i * qs_l + d];
+    __syncthreads();
+    if (!live) return;
+    const float *Kg = K + (int64_t)g * ks_h, *Vg = V + (int64_t)g * vs_h;
+    const int l = (int)(i / B_r);
+    const int E = pv.count[(int64_t)h * pv.N_q + l];
+    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)h * pv.N_q + l) * pv.stride;
+    float m = -INFINITY, lsum = 0.f, o[NC];
+    bool some = false;               // the row takes a key
+#pragma unroll
+    for (int c = 0; c < NC; ++c) o[c] = 0.f;
+    for (int e = 0; e < E; ++e) {
+        const int2 w = ent[e];
+        const int b0 = pv.B[w.x & kChunkMask];
+        const int64_t vis = i + 1 - b0;                  // listed keys past the row are dropped
+        const int take = vis < w.y ? (vis > 0 ? (int)vis : 0) : w.y;
+        some |= take > 0;
+        for (int t0 = 0; t0 < take; t0 += 64) {
+            const int nv = take - t0 < 64 ? take - t0 : 64;
+            float s = -INFINITY;
+            if (lane < nv) {
+                const float *kr = Kg + (int64_t)(b0 + t0 + lane) * ks_l;
+                f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int d = 0; d < D; d += 4) {
+                    const f32x4 k4 = *reinterpret_cast<const f32x4 *>(kr + d), q4 = *reinterpret_cast<const f32x4 *>(&s_q[wave][d]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[j] = __builtin_fmaf(k4[j], q4[j], acc[j]);
+                }
+                s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+            }
+            float mx = s;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+            const float m_new = fmaxf(m, mx), ref = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * scale_log2e);
+            const float p = lane < nv ? __builtin_amdgcn_exp2f((s - ref) * scale_log2e) : 0.f;
+            lsum = lsum * alpha + p;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) o[c] *= alpha;
+            for (int jj = 0; jj < nv; ++jj) {
+                const float pj = __shfl(p, jj);
+                const float *vr = Vg + (int64_t)(b0 + t0 + jj) * vs_l + lane;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) o[c] = __builtin_fmaf(pj, vr[64 * c], o[c]);
+            }
+            m = m_new;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+    // no key at all: zeros; only keys whose score is -inf: NaN
+    const float inv = lsum > 0.f ? 1.f / lsum : some ? NAN : 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) O[(int64_t)h * os_h + i * os_l + lane + 64 * c] = o[c] * inv;
+}
+
 hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V, void *O,
                            hipStream_t s) {
+    // A wave per row is the faster one for row blocks of one row whatever the budget, of 2 up to about 100 keys (95 us
+    // against 185 us with 16 keys, 408 against 344 us with 128; L = 6000, 8 heads, D = 64), of 3 up to 40, of 4 up to 25
+    // (D = 128: 136 against 189 us with 16 keys, 614 against 329 us with 128): B_r^2 N_b of about 400
+    if (p.B_r == 1 || (p.B_r > 0 && (int64_t)p.B_r * p.B_r * p.N_b <= 400)) {
+        const dim3 grid((unsigned)((p.L + 3) / 4), p.H_q);      // at most 2^20 row blocks: fewer than 2^32 threads
+#define DHSA_F32_ROWS(DD)                                                                                      \
+    hipLaunchKernelGGL(k_attn_f32_rows<DD>, grid, dim3(256), 0, s, pv, (const float *)Q, (const float *)K,     \
+                       (const float *)V, (float *)O, p.L, p.G, p.B_r, p.scale * 1.4426950408889634f, p.qs_h,   \
+                       p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l, p.os_h, p.os_l)
+        if (p.D == 64) DHSA_F32_ROWS(64); else DHSA_F32_ROWS(128);
+#undef DHSA_F32_ROWS
+        return hipGetLastError();
+    }
     // 32 rows per workgroup read K and V half as often as 16; while that leaves CUs with fewer than two
     // workgroups, 16-row ones fill the chip better and waste less on the last rows of a tile
     const int64_t wg32 = (int64_t)p.H_q * (4 * (int64_t)pv.T_cls[0] + 3 * pv.T_cls[1] + 2 * pv.T_cls[2] + pv.T_cls[3]);

@@ -54,7 +54,14 @@ def test_recall_row_groups_ties_and_candidate_list(L, D, dtype, n_rows, integers
                                                   (4100, 8, 64, 500, ("uniform", 90, 160), 0),      # 32-row pieces
                                                   (4100, 8, 128, 300, ("fixed", 1), 0),             # > 256 plan entries
                                                   (4100, 8, 128, 1100, ("uniform", 16, 64), 97),
-                                                  (900, 2, 64, 3, ("uniform", 16, 64), 128)])       # rows without a key
+                                                  (900, 2, 64, 3, ("uniform", 16, 64), 128),        # rows without a key
+                                                  (901, 2, 64, 90, ("uniform", 16, 64), 1),         # a wave per row
+                                                  (1100, 3, 128, 700, ("uniform", 100, 300), 1),
+                                                  (901, 2, 128, 100, ("uniform", 16, 64), 2),
+                                                  (901, 2, 128, 101, ("uniform", 16, 64), 2),       # ... and no more
+                                                  (903, 2, 64, 25, ("uniform", 1, 9), 4),
+                                                  (903, 2, 64, 26, ("uniform", 1, 9), 4),
+                                                  (903, 2, 64, 1, ("uniform", 16, 64), 20)])
 def test_f32_pieces_lists_and_batches(L, H_q, D, N_b, lens, B_r):
     w = dhsa_inputs.make("c1", L=L, H_q=H_q, H_kv=1, D=D, N_b=N_b, lens=lens)
     Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
@@ -239,7 +246,7 @@ def test_f32_infinite_values_reach_only_the_rows_that_take_them(L, D, B_r):
     np.testing.assert_allclose(got, ref, rtol=0, atol=1e-4)
 
 
-@pytest.mark.parametrize("B_r", [0, 96])
+@pytest.mark.parametrize("B_r", [0, 96, 1])
 @pytest.mark.parametrize("L,D", [(300, 64), (300, 128), (4100, 64)])
 def test_f32_rows_of_nothing_but_minus_infinity(L, D, B_r):
     """The softmax of scores that are all -inf is NaN; beside a finite one they weigh nothing; a row without a key is zero."""
@@ -287,19 +294,20 @@ def test_f32_error_against_64_bits(L, H_q, D):
     assert rel < 2.4e-7
 
 
-@pytest.mark.parametrize("dtype,H_q", [(torch.float32, 16), (torch.bfloat16, 40)])
-def test_more_workgroups_than_one_launch_holds(dtype, H_q):
-    """Row blocks of one row, heads of 2^20 rows: a workgroup of the attention each, and a quarter of one in the ranking
+@pytest.mark.parametrize("dtype,H_q,B_r,N_b", [(torch.float32, 16, 1, 16), (torch.float32, 16, 2, 128),
+                                               (torch.bfloat16, 40, 1, 16)])
+def test_more_workgroups_than_one_launch_holds(dtype, H_q, B_r, N_b):
+    """2^20 row blocks a head: a workgroup of the attention each (fp32: of two rows), and a quarter of one in the ranking
     (40 heads: five launches of the attention, two of the ranking).  Heads are independent and every row's sums have one
     order, so calls of eight heads (2^23 workgroups) give the same bits."""
-    L, D, N_b = 1 << 20, 64, 16
+    L, D = B_r << 20, 64
     gen = torch.Generator(device="cuda").manual_seed(5)
     Q = torch.randn(H_q, L, D, dtype=dtype, device="cuda", generator=gen)
     K, V = (torch.randn(1, L, D, dtype=dtype, device="cuda", generator=gen) for _ in range(2))
     B = np.array([0, 700, 300000, 300050, L], dtype=np.int32)
 
     def prefill(q):
-        prob = dhsa.problem(q, K, B, N_b, B_r=1)
+        prob = dhsa.problem(q, K, B, N_b, B_r=B_r)
         plan, ws = dhsa.alloc(prob, B)
         O = torch.full_like(q, float("nan"))
         dhsa.dhsa_prefill(prob, q, K, V, B, O, plan, ws)
