@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void k_recall_logits(PlanView pv, const T *__r
 // counted from memory; a region of at most kRcCand keys moves into LDS and is finished there
 // with 8-bit digits.  The select ends early when every key of the region belongs to the
 // top set.  Bound by latency: one CU reads the row's keys twice (256 KB each time at n = 32768;
-// 21 us for 48 rows).
+// 21 us for 48 rows).  Ties at the threshold: where the last equal key of the top set lies is found once, by counting.
 // ---------------------------------------------------------------------------
 constexpr int kRcThreads = 1024;
 constexpr int kRcBits = 14;
@@ -138,7 +138,8 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     __shared__ int s_hist[1 << kRcBits];
     __shared__ unsigned long long s_cand[kRcCand];
     __shared__ int s_wave[kRcThreads / 64];
-    __shared__ int s_digit, s_above, s_equal, s_n, s_l;
+    __shared__ unsigned long long s_bits[kRcThreads / 64][2];
+    __shared__ int s_digit, s_above, s_equal, s_n, s_l, s_cut;
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing is written
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = rows.row[t];
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     // `shift` up equal `prefix`; above = keys larger than the region's, equal = keys of the region ----
     unsigned long long prefix = 0ull;
     int above = 0, equal = n, shift = 64;
-    bool in_lds = false;
+    bool in_lds = false, stuck = false;
     while (shift > 0 && above + equal != k_top) {
         if (!in_lds && equal <= kRcCand) {
             if (tid == 0) s_n = 0;
@@ -167,6 +168,27 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
             }
             in_lds = true;
             __syncthreads();
+        }
+        if (stuck) {                 // the last digit was the same in the whole region: on to the first bit that is not
+            unsigned long long ones = 0ull, zeros = 0ull;
+            for (int x = tid; x < s_n; x += kRcThreads) {
+                const unsigned long long u = s_cand[x];
+                if ((u >> shift) == prefix) { ones |= u; zeros |= ~u; }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                ones |= __shfl_xor(ones, off);
+                zeros |= __shfl_xor(zeros, off);
+            }
+            if (lane == 0) { s_bits[wave][0] = ones; s_bits[wave][1] = zeros; }
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kRcThreads / 64; ++w) { ones |= s_bits[w][0]; zeros |= s_bits[w][1]; }
+            const unsigned long long low = (1ull << shift) - 1ull, diff = ones & zeros & low;
+            const int first = diff ? 64 - __builtin_clzll(diff) : 0;
+            prefix = (prefix << (shift - first)) | ((ones & low) >> first);
+            shift = first;
+            if (shift == 0) break;
         }
         const int bits = in_lds ? (shift < 8 ? shift : 8) : (shift < kRcBits ? shift : kRcBits);
         const int bins = 1 << bits, lower = shift - bits;
@@ -212,6 +234,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
             s_digit = d; s_above = gt; s_equal = s_hist[d];
         }
         __syncthreads();
+        stuck = in_lds && s_equal == equal;
         above += s_above;
         equal = s_equal;
         prefix = (prefix << bits) | (unsigned long long)s_digit;
@@ -222,6 +245,33 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     const int need_eq = k_top - above;
     const bool all_eq = need_eq >= equal;
     __syncthreads();                                     // s_l, where the loop did not run
+    int cut = n;                                         // the last of them; equal keys from there on are not in the top set
+    if (!all_eq) {                                       // a tie cut by the budget
+        constexpr int kPer = 8, kW = kRcThreads / 64;    // slabs of kPer rounds of kRcThreads keys; counts of a (round, wave)
+        for (int j0 = 0, before = 0; before < need_eq; j0 += kPer * kRcThreads) {   // ends: the region holds more than need_eq
+            unsigned long long m[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                const int j = j0 + e * kRcThreads + tid;
+                m[e] = __ballot(j < n && key[j < n ? j : 0] == prefix);
+                if (lane == 0) s_hist[e * kW + wave] = __popcll(m[e]);
+            }
+            __syncthreads();
+            int run = before;
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                for (int w = 0; w < kW; ++w) {
+                    if (w == wave && ((m[e] >> lane) & 1ull) &&
+                        run + __popcll(m[e] & ((1ull << lane) - 1ull)) == need_eq - 1)
+                        s_cut = j0 + e * kRcThreads + tid;
+                    run += s_hist[e * kW + w];
+                }
+            }
+            before = run;
+            __syncthreads();
+        }
+        cut = s_cut;
+    }
 
     // ---- the row's selected keys: one wave per plan entry ----
     const int l = s_l;
@@ -241,15 +291,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
         for (int x = lane; x < take; x += 64) {
             const int j = b0 + x;
             const unsigned long long u = shift == 64 ? 0ull : key[j] >> shift;   // shift 64: every key is in the top set
-            if (u > prefix) ++hits;
-            else if (u == prefix) {
-                if (all_eq) ++hits;
-                else {                                   // a tie cut by the budget: rank among the equal keys
-                    int r = 0;
-                    for (int jj = 0; jj < j; ++jj) r += key[jj] == prefix;
-                    if (r < need_eq) ++hits;
-                }
-            }
+            hits += u > prefix || (u == prefix && j <= cut);
         }
     }
 #pragma unroll

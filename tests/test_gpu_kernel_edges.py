@@ -30,6 +30,7 @@ def test_boundary_windows_and_slabs(L, W, levels):
 
 @pytest.mark.parametrize("L,D,dtype,n_rows,integers", [(300, 64, "f32", 1, False), (5000, 128, "bf16", 17, True),
                                                        (9000, 64, "bf16", 8, True), (9000, 128, "f32", 9, False),
+                                                       (20000, 64, "bf16", 5, True), (700, 64, "f32", 9, True),
                                                        (4097, 128, "f32", 513, False)])
 def test_recall_row_groups_ties_and_candidate_list(L, D, dtype, n_rows, integers):
     """Row groups of 8, 512 rows per launch, key blocks of 512, regions above and below the 4096 keys the select
