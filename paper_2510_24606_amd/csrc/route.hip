@@ -664,13 +664,16 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
         tbin = found ? __builtin_amdgcn_readlane(my_bin, src) : kSelBins - 1;
         before = wave_read(before, src);
         upto = wave_read(found ? upto : run, src);
-        int most = 0;
+        crowded = false;
+        if ((int)(upto & 0xffffull) > kSelCrowd) {
+            int most = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int n_bin = (int)c[i] & 0xffff;
-            most = (cut || 4 * lane + i <= tbin) && n_bin > most ? n_bin : most;
+            for (int i = 0; i < 4; ++i) {
+                const int n_bin = (int)c[i] & 0xffff;
+                most = (cut || 4 * lane + i <= tbin) && n_bin > most ? n_bin : most;
+            }
+            crowded = __ballot(most > kSelCrowd) != 0ull;
         }
-        crowded = __ballot(most > kSelCrowd) != 0ull;
     };
     for (int level = 0;; ++level) {
         inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
@@ -791,7 +794,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     // instead, by a network whose comparisons all put the better one first, so that nothing is moved past its end,
     // and the tokens before each candidate are a prefix sum.  Routing of 820 chunks, 32 heads, keys all zero: 1070 ->
     // 223 us; 500 chunks of one token, 12 heads, with outliers: 874 -> 160 us (ordinary scores: 78 us)
-    if (crowded) {
+    if (__builtin_expect(crowded, 0)) {
         const auto first = [&](unsigned long long ka, int wa, unsigned long long kb, int wb) {
             return ka > kb || (ka == kb && (wa & kChunkMask) < (wb & kChunkMask));
         };
