@@ -1,5 +1,8 @@
 """Sizes at which the kernels change their path or run out of a tile: edges of segments, tiles, digit widths and
 candidate lists, against the CPU oracle."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -357,6 +360,11 @@ def test_a_tile_has_one_result_in_every_launch(tall, middle, short, D):
     """A class of few row tiles joins the launch of the next taller one.  The more heads, the fewer classes are that
     small: with 4 heads all join, with 512 (1536 workgroups and more of each) none, with 128 of them the shortest may.
     The rows of the first heads keep their bits, so the parity tests of joined launches hold for separate ones too."""
+    # the launcher's rule, so that another line in it cannot empty this test
+    src = open(os.path.join(os.path.dirname(dhsa.__file__), "csrc", "attn_mfma.hip")).read()
+    (most,) = re.findall(r"p\.H_q \* all\[c\] <= (\d+)\)", src)
+    classes = [2 * len(c) for c in (tall, middle, short) if c]              # tiles, at least
+    assert all(512 * n > int(most) for n in classes) and all(4 * n <= int(most) for n in classes)
     rng = np.random.default_rng(D + len(tall))
     lens = rng.permutation(np.array((tall + middle + short) * 2))
     B = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)

@@ -65,7 +65,7 @@ def check(w, B_r, rows):
 
 
 ALL_ROWS = [
-    # both launch classes of the bf16 kernel (row tiles above and below 64 rows), ragged tails
+    # bodies of the bf16 kernel for row tiles above and below 64 rows, ragged tails
     ("c3", dict(L=8192, H_q=8, H_kv=2, N_b=512), 0),
     ("c3", dict(L=8192, H_q=8, H_kv=2, N_b=512), 128),
     # geometric chunk lengths 8..512: row tiles of every size, several tiles per chunk

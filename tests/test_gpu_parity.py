@@ -130,8 +130,9 @@ def test_small_full_parity(name, kw):
 
 def test_row_tiles_at_the_edges_of_the_height_classes():
     """Chunks whose last row tile has exactly 1, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128 rows
-    (alone and behind one or two full tiles): every wave arrangement of the attention kernels at the edge
-    of its range, all rows compared."""
+    (alone and behind one or two full tiles): every body of the attention kernels at the edge of its range, all rows
+    compared.  So few tiles share one launch, each on the body of its height; that launches of their own give the same
+    bits is test_a_tile_has_one_result_in_every_launch's to show."""
     rem = [1, 16, 17, 31, 32, 33, 48, 63, 64, 65, 80, 95, 96, 97, 112, 127, 128]
     lens = [r + 128 * f for f in (0, 1, 2) for r in rem]
     rng = np.random.default_rng(5)
