@@ -479,12 +479,13 @@ __device__ __forceinline__ unsigned long long wave_read(unsigned long long x, in
 //      they are more than the list holds, the last bin is cut again over its own range (outliers
 //      far from the rest), and at last by digits of the keys and ids (ties);
 //   3. candidates into LDS, grouped by bin (the bins' counts are their places);
-//   4. tokens before a candidate = tokens of better bins + of the better candidates of its own bin (a few);
+//   4. tokens before a candidate = tokens of better bins + of the better candidates of its own bin (a few; with a
+//      bin of many, a prefix sum over the sorted candidates);
 //   5. the listed chunks set their bit, and go into the plan at the number of bits below theirs
 //      (ascending chunk id).
 // Bins are taken from the scores rounded to fp32 (which keeps their order), the order inside a bin from the fp64
 // scores.  Bound by instruction issue and by the scores' way from memory (342 MB for 1634 chunks x 32 heads).  That
-// case takes 250 us; it took 480 us with a radix select by 8-bit digits (whose first digit counts nearly all
+// case takes 256 us; it took 480 us with a radix select by 8-bit digits (whose first digit counts nearly all
 // scores in two or three LDS words), a bitonic sort and two scans, with ~40 block barriers.
 // ---------------------------------------------------------------------------
 constexpr int kSelBins = 256;
