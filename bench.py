@@ -34,7 +34,8 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_mfma_traffic.json")
-KERNEL_SOURCES = ("paper_2510_24606_amd/csrc/attn_mfma.hip", "paper_2510_24606_amd/csrc/dhsa_internal.h")
+KERNEL_SOURCES = tuple(f"paper_2510_24606_amd/csrc/{f}" for f in ("attn_mfma.hip", "attn_wave.hip", "attn_mfma.h",
+                                                                  "dhsa_internal.h"))
 PAPER_CONTEXT = {"what": "paper Tab. 11, DHSA 6.25% @128K, LLaMA-3.1-8B bf16, attention kernel only",
                  "ms_per_layer": 214.5, "hardware": "RTX 3090"}
 ROW_CLASSES = (("rows_gt64", "attn_rows_gt64"), ("rows_33_64", "attn_rows_33_64"), ("rows_le32", "attn_rows_le32"))
@@ -232,19 +233,33 @@ def main() -> int:
                 n1 = np.maximum(0, np.minimum(r1 - 1, bb + tt - 1) - a + 1)    # rows that see a growing part of it
                 n2 = np.maximum(0, r1 - 1 - np.maximum(a - 1, bb + tt - 1))    # rows that see all t
                 per_tile[ti] = np.where(a < r1, n1 * (a + 1 - bb) + n1 * (n1 - 1) // 2 + n2 * tt, 0).sum()
-        return [float(per_tile[launch_of_tile == c].sum()) for c in range(3)], [int((launch_of_tile == c).sum())
-                                                                                 for c in range(3)]
+        heights = [int(((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64), (0, 32))]
+        return [float(per_tile[launch_of_tile == c].sum()) for c in range(3)], heights
 
-    def launch_of_class(w, ntiles):
-        """The attention launch that runs the row tiles of each height class: its own, or the next taller one's where
-        the class has at most 512 tiles over all heads (dhsa_prefill_stage_times; fp32: one launch for all)."""
+    def launch_of_class(w, tiles):
+        """The stage slot (dhsa_prefill_stage_times) that the row tiles of each height class are timed in, tiles =
+        those of more than 96 rows, 65..96, 33..64 and at most 32: its own, or a taller one's where a class of at most
+        512 tiles over all heads joins its launch (fp32: one launch for all).  Classes of many tiles have a launch of
+        their own (attn_wave_classes), which only the two shortest share."""
         if w.dtype != "bf16":
             return [0, 0, 0]
-        at, n = [0, 1, 2], list(ntiles)
+        n = [w.H_q * t for t in tiles]
+        wave = w.D == 128 and w.N_b >= 1024 and w.L >= 16 * w.N_c
+        w0, w1 = wave and n[0] >= 3584 and w.L >= 32 * w.N_c, wave and n[1] >= 3072
+        if w0 != w1 and n[1 if w0 else 0] > 0 and w.N_b < 4096:
+            w0 = w1 = False
+        w2 = wave and n[2] >= 4608
+        own = [(0 if w0 else n[0]) + (0 if w1 else n[1]), 0 if w2 else n[2], n[3]]
+        at, most = [0, 1, 2], list(own)
+        if w2 and n[3] <= 512:
+            at[2], own[2], most[2] = 1, 0, 0
         for c in (2, 1):
-            to = c - 1 if ntiles[c - 1] > 0 else 0
-            if n[c] > 0 and ntiles[to] > 0 and w.H_q * n[c] <= 512:
-                n[to], n[c] = n[to] + n[c], 0
+            to = c - 1 if own[c - 1] > 0 else 0
+            behind = c == to + 1 or n[2] == 0                  # nothing between the two in the tile table
+            if to == 0 and w1 and n[1] > 0 or not behind:
+                continue
+            if most[c] > 0 and own[to] > 0 and most[c] <= 512:
+                most[to], most[c] = most[to] + most[c], 0
                 at = [to if x == c else x for x in at]
         return at
 
@@ -253,9 +268,10 @@ def main() -> int:
         kernels), the FLOP of each launch and its fraction of the bf16 MFMA peak."""
         runs = [dhsa.dhsa_prefill_stage_times(prob, Q, K, V, w.B, O, plan, ws) for _ in range(reps + 1)][1:]
         med = {k: float(np.median([r[k] for r in runs])) for k in dhsa.STAGES}
-        pairs, ntiles = attended_pairs_by_class(w, B_r, plan)
+        pairs, heights = attended_pairs_by_class(w, B_r, plan)
         launches = {}
-        ran_in = launch_of_class(w, ntiles)
+        ran_in = launch_of_class(w, heights)
+        ntiles = [heights[0] + heights[1], heights[2], heights[3]]
         for c, (label, stage) in enumerate(ROW_CLASSES):
             fl = 4.0 * w.D * sum(p for p, at in zip(pairs, ran_in) if at == c)
             launches[label] = {"tiles_per_head": sum(n for n, at in zip(ntiles, ran_in) if at == c), "flop": fl,
@@ -310,7 +326,7 @@ def main() -> int:
                       "host_wall_per_step": round(wall_ms, 4), **stages},
         "pct_of_bf16_mfma_peak": round(100.0 * achieved / PEAK_BF16_TFLOPS, 3),
         "roofline": {"bound": "mfma",
-                     "kernel": "k_attn_mfma (one launch per height class of the row tiles: > 64 rows, 33..64, <= 32)",
+                     "kernel": "k_attn_wave2 (row tiles of 97..128 rows), k_attn_wave1 (65..96; 33..64), k_attn_mfma (the rest)",
                      "achieved": round(achieved, 3),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 5),
                      "flop_per_launch": flops, "launches": launches,

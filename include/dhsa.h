@@ -260,8 +260,8 @@ dhsa_status dhsa_debug_scores(const dhsa_problem *prob, const int32_t *B_host, c
  * set-up, 2 S_c, 3 ranking + budget (Alg. 1), 4 / 5 / 6 the attention launches
  * (Alg. 3) of the row tiles of more than 64 rows / of 33..64 rows / of at most 32
  * rows (fp32 inputs: all rows in slot 4), 7 the whole call.  Tiles of a class that
- * has at most 512 over all heads run in the launch of the next taller class there
- * is: their time is in its slot, their own is about 0.  Creates and destroys events and BLOCKS until the work is done;
+ * has at most 512 over all heads may run in the launch of a taller class: their
+ * time is in its slot then, their own is about 0.  Creates and destroys events and BLOCKS until the work is done;
  * arguments and results otherwise as dhsa_prefill. */
 dhsa_status dhsa_prefill_stage_times(const dhsa_problem *prob, const void *Q_dev, const void *K_dev,
                                      const void *V_dev, const int32_t *B_host, void *O_dev, void *plan_dev,

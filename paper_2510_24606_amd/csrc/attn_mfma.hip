@@ -41,41 +41,14 @@
 // are masked causally per token like the keys of a row's own chunk.
 #include <stddef.h>
 
+#include "attn_mfma.h"
 #include "dhsa_internal.h"
 
 namespace dhsa {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int kKT = 64;      // keys per tile
 constexpr int kSegB = 256;   // plan entries handled per batch
 constexpr int kIntMax = 0x7fffffff;
-
-// XOR swizzle of the 16-byte pieces of LDS row r (only r mod 16 matters).  Eight
-// (sixteen for 256-byte rows) consecutive rows get distinct values, so a column
-// of 16-byte reads spreads over all banks; rows r..r+3 with r % 4 == 0 differ
-// in bits 1-2, so the 32-byte row segments of a transpose read do too.
-__device__ __forceinline__ int piece_swizzle(int r, int pieces_per_row) {
-    int f = ((r & 3) << 1) | ((r >> 2) & 1);
-    if (pieces_per_row == 16) f |= ((r >> 3) & 1) << 3;
-    return f;
-}
-
-// 16 bytes per lane from global memory (uniform base + per-lane 32-bit byte
-// offset) straight into LDS: lane L of the wave writes bytes [16 L, 16 L + 16)
-// of the window at LDS byte address `lds_window` (wave-uniform, goes through
-// M0, which nothing else in this kernel uses).  Completion is tracked by vmcnt;
-// the caller waits and then passes a barrier before anyone reads the window.
-__device__ __forceinline__ void load16_to_lds(const char *base, unsigned byte_off, unsigned lds_window) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(byte_off), "s"(base), "s"(lds_window) : "memory");
-#else
-    (void)base; (void)byte_off; (void)lds_window;
-#endif
-}
 
 template <int D>
 struct AttnSmem {
@@ -96,35 +69,6 @@ struct AttnSmem {
     int flags[8];
     int s_wave[8];
 };
-
-// blockIdx -> (head, tile).  Workgroups are dealt to the 8 XCDs round-robin and
-// each XCD has its own L2.  `act` kv-heads (1, 2, 4 or 8) are worked on at a
-// time, each by 8 / act XCDs: act = 8 gives every XCD its own kv-head (best L2
-// reuse of the K/V slabs), smaller values keep fewer K/V slabs live at once
-// (they then fit the memory-side cache).  Within a kv-head the query heads of
-// the group are innermost; *tile is the tile's position in the order of issue
-// (0 = first), which the kernel maps to a row tile.  act = 0: plain order.
-__device__ __forceinline__ void decode_block(int act, int b, int H_q, int G, int T1, int *h, int *tile) {
-    if (act > 0) {
-        const int per = act * G * T1;          // workgroups per set of `act` kv-heads
-        const int p = b / per, r = b % per;
-        const int x = r & 7;
-        const int kv = p * act + (x & (act - 1));
-        const int idx = (r >> 3) * (8 / act) + x / act;
-        *tile = idx / G;
-        *h = kv * G + idx % G;
-        return;
-    }
-    *tile = b / H_q;
-    *h = b % H_q;
-}
-
-// act must divide H_kv and act * G * T1 must be a multiple of 8 for the mapping above
-static int attn_order(int want, int H_kv, int G, int T1) {
-    for (int act = want; act >= 1; act >>= 1)
-        if (H_kv % act == 0 && (act * G * T1) % 8 == 0) return act;
-    return 0;
-}
 
 // ---------------------------------------------------------------------------
 // Key lists and loads, shared by the two kernels below (they use the same names
@@ -225,15 +169,6 @@ static int attn_order(int want, int H_kv, int G, int T1) {
 #define DHSA_LOAD_V_LO(n) DHSA_GLOAD(lds_V, vo, Vg8, ld_piece_bytes_v, n, 0, KPT / 2)
 #define DHSA_LOAD_V_HI(n) DHSA_GLOAD(lds_V, vo, Vg8, ld_piece_bytes_v, n, KPT / 2, KPT)
 
-
-// Everything the tile bodies need beside the plan (kernel arguments, passed on by reference).
-struct AttnArgs {
-    const uint16_t *Q, *K, *V;
-    uint16_t *O;
-    int G;
-    float scale_log2e;
-    int64_t qs_h, qs_l, ks_h, ks_l, vs_h, vs_l, os_h, os_l;
-};
 
 // What a tile body needs first, requested as early as the addresses are known: the entries of the first
 // batch do not wait for the number of entries, and the query rows are requested behind what the key list
@@ -948,16 +883,25 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     a.scale_log2e = p.scale * 1.4426950408889634f;
     a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
     a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
-    // tiles of each launch: its own class, and shorter ones that joined.  A launch of fewer workgroups than the chip
+    // Classes of the tile table that the kernels of attn_wave.hip take.  Those of 33..64 rows take the ones of at most 32
+    // along if these are too few for a launch of their own.
+    const int T_cls0 = pv.T_cls[0], T_cls1 = pv.T_cls[1];
+    const int classes = attn_wave_classes(p, pv.T_cls);
+    const bool wave[3] = {(classes & 1) != 0, (classes & 2) != 0, (classes & 4) != 0};
+    const bool short_too = wave[2] && (int64_t)p.H_q * pv.T_cls[3] <= 512;
+    // tiles of each other launch: its own class, and shorter ones that joined.  A launch of fewer workgroups than the chip
     // holds at once (two per CU) takes as long as one workgroup whatever their number, while the next taller launch
     // has such tiles run in the gaps of its own (their stage time is then part of that launch's).  A 1K-token
-    // prompt: 33.3 us a call with a launch per class, 25.0 us so; c2 1622 -> 1591 us.
-    int own[3] = {pv.T_big, pv.T_cls[2], pv.T_cls[3]}, all[3] = {own[0], own[1], own[2]};
+    // prompt: 33.3 us a call with a launch per class, 25.0 us so; c2 1622 -> 1591 us.  The tiles of a launch lie behind one
+    // another in the table.
+    const int first[3] = {wave[0] ? T_cls0 : 0, pv.T_big, pv.T_big + pv.T_cls[2]};
+    int own[3] = {(wave[0] ? 0 : T_cls0) + (wave[1] ? 0 : T_cls1), wave[2] ? 0 : pv.T_cls[2], short_too ? 0 : pv.T_cls[3]};
+    int all[3] = {own[0], own[1], own[2]};
     for (int c = 2; c > 0; --c) {
         const int to = own[c - 1] > 0 ? c - 1 : 0;
+        if (first[to] + own[to] != first[c]) continue;
         if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) { all[to] += all[c]; all[c] = 0; }
     }
-    const int first[3] = {0, own[0], own[0] + own[1]};
     // a launch takes tiles of its own class from the end of their table, as many as fit a grid; the first one also takes
     // the shorter tiles that joined (a tile has one result, whatever its launch)
     const int per_grid = p.H_q < kGridMax ? kGridMax / p.H_q : 1;
@@ -974,8 +918,17 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
         else { if (mix) DHSA_LAUNCH1(128, CLS, (CLS < 2)); else DHSA_LAUNCH1(128, CLS, false); }             \
     }
     // tallest tiles first (they take longest)
+    for (int c = 0; c < 2; ++c)
+        if (wave[c]) {
+            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : T_cls0, pv.T_cls[c], s);
+            if (e != hipSuccess) return e;
+        }
     DHSA_LAUNCH(0)
     if (ev && hipEventRecord(ev[0], s) != hipSuccess) return hipErrorUnknown;
+    if (wave[2]) {
+        const hipError_t e = launch_attn_wave(p, pv, a, want, 2, pv.T_big, pv.T_cls[2] + (short_too ? pv.T_cls[3] : 0), s);
+        if (e != hipSuccess) return e;
+    }
     DHSA_LAUNCH(1)
     if (ev && hipEventRecord(ev[1], s) != hipSuccess) return hipErrorUnknown;
     DHSA_LAUNCH(2)

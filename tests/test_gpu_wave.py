@@ -1,0 +1,99 @@
+"""Row tiles that go to the lone-wave kernels (csrc/attn_wave.hip) because there are many of them, against the same rows of
+the first heads alone (csrc/attn_mfma.hip takes few tiles) and against the oracle."""
+import os
+import re
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_24606_amd as dhsa
+
+pytestmark = pytest.mark.gpu
+H_Q, H_KV, FEW, D = 64, 8, 8, 128
+
+
+def tensors(L, layout, seed=5):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    out = []
+    for H in (H_Q, H_KV, H_KV):
+        x = torch.randn((L, H, D) if layout == "lhd" else (H, L, D), dtype=torch.bfloat16, device="cuda", generator=gen)
+        out.append(x.transpose(0, 1) if layout == "lhd" else x)
+    return out
+
+
+def run(q, k, v, B, N_b, B_r):
+    """The output, and how many tiles of each height class there are over all heads."""
+    prob = dhsa.problem(q, k, B, N_b, B_r=B_r)
+    plan, ws = dhsa.alloc(prob, B)
+    O = torch.full_like(q, float("nan"))
+    dhsa.dhsa_prefill(prob, q, k, v, B, O, plan, ws)
+    nrows = np.sort(dhsa.parse_plan(plan.cpu().numpy())["tiles"][:, 1])
+    nrows = np.diff(np.r_[nrows, q.shape[1]])
+    return O, [int(q.shape[0] * ((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64))]
+
+
+def check_route(tiles_few, tiles_all, classes):
+    src = open(os.path.join(os.path.dirname(dhsa.__file__), "csrc", "attn_wave.hip")).read()
+    for c in classes:
+        (least,) = re.findall(rf"enough\({c}, (\d+)\)", src)
+        assert tiles_few[c] < int(least) <= tiles_all[c]
+
+
+TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
+
+
+@pytest.mark.parametrize("lens,B_r,N_b,layout,classes", [
+    ((TALL + MIDDLE) * 19 + SHORT * 25 + (1, 32), 0, 1024, "hld", (0, 1, 2)),
+    (TALL * 19 + (1, 16, 63) * 4, 0, 4096, "lhd", (0,)),                # beside classes that keep their launch
+    (MIDDLE * 19 + SHORT * 2, 0, 1087, "lhd", (1,)),
+    (SHORT * 25 + (129, 97, 65, 3), 0, 4100, "hld", (2,)),
+    ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),                 # 225 chunks: several batches of 64 entries
+    ((30, 64, 2, 50, 20) * 35, 97, 1500, "lhd", (0,)),
+    ((1, 2, 60, 3, 30, 1, 4, 40) * 40, 96, 2047, "hld", (1,)),          # more than four chunks begin among 64 keys
+    ((200, 7, 18) * 20, 65, 1024, "lhd", (1,)),
+    ((17, 40, 1) * 90, 64, 1999, "hld", (2,)),
+    ((100, 3, 33) * 20, 33, 1024, "lhd", (2,))])
+def test_many_tiles_give_what_few_give(lens, B_r, N_b, layout, classes):
+    B = np.concatenate([[0], np.cumsum(np.random.default_rng(len(lens)).permutation(lens))]).astype(np.int32)
+    L = int(B[-1])
+    q, k, v = tensors(L, layout)
+    every, tiles_all = run(q, k, v, B, N_b, B_r)
+    few, tiles_few = run(q[:FEW], k[:1], v[:1], B, N_b, B_r)
+    check_route(tiles_few, tiles_all, classes)
+    # the weights, which sum to 1, and the result are rounded to 8 bits, each by at most 2^-8 of the largest value of V (sums
+    # in 32 bits add less than 2^-14 of it); on average by a third of that, and independently: 2.3e-3 of the result's norm
+    tol = (2.0 ** -7 + 2.0 ** -14) * float(v[0].float().abs().max())
+
+    def close(got, want, sides):
+        assert np.abs(got - want).max() <= sides * tol and np.linalg.norm(got - want) <= sides * 5e-3 * np.linalg.norm(want)
+    assert bool(torch.isfinite(every).all())
+    close(every[:FEW].float().cpu().numpy(), few.float().cpu().numpy(), 2)
+    rows = np.unique(np.r_[np.linspace(0, L - 1, 40).astype(np.int64), B[1:6] - 1, L - 2])
+    f32 = [x.float().cpu().numpy() for x in (q[:2], k[:1], v[:1])]
+    ref = oracle.prefill_rows_blocks(*f32, B, B_r, N_b, rows)[0] if B_r else oracle.prefill_rows(*f32, B, N_b, rows)[0]
+    close(every[:2, torch.from_numpy(rows).cuda()].float().cpu().numpy(), ref, 1)
+
+
+@pytest.mark.parametrize("rows", [128, 96, 64])
+def test_references_that_move_and_values_that_are_not_finite(rows):
+    """Logits that outgrow their exponent reference late in the list; NaN, infinite and lowest keys and values, which
+    reach the rows that take them and no other."""
+    B = np.arange(0, 73 * rows + 1, rows, dtype=np.int32)
+    L = int(B[-1])
+    q, k, v = tensors(L, "hld", rows)
+    q *= torch.linspace(1, 8, L, device="cuda")[None, :, None]     # (a weight that vanishes would make NaN of an infinite value)
+    k, v = k.clone(), v.clone()
+    for j, (x, val) in enumerate([(v, float("inf")), (v, float("-inf")), (v, float("nan")), (k, torch.finfo(torch.bfloat16).min),
+                                  (k, float("inf")), (k, float("nan"))]):
+        x[:, (10 + 10 * j) * rows + j, j] = val
+    every, tiles_all = run(q, k, v, B, 1024, 0)
+    few, tiles_few = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
+    check_route(tiles_few, tiles_all, [{128: 0, 96: 1, 64: 2}[rows]])
+    got, want = every[:FEW].float(), few.float()
+    fin = torch.isfinite(want)
+    assert bool(torch.isnan(want).any()) and bool(torch.isinf(want).any()) and bool(fin[:, :10 * rows].all())
+    assert torch.equal(torch.nan_to_num(got, 0.0, 1.0, -1.0)[~fin], torch.nan_to_num(want, 0.0, 1.0, -1.0)[~fin])
+    tol = 2 * (2.0 ** -7 + 2.0 ** -14) * float(v[0].float().nan_to_num(0, 0, 0).abs().max())    # as above, on both sides
+    assert float((got - want)[fin].abs().max()) <= tol

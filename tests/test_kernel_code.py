@@ -52,3 +52,25 @@ def test_f32_attention_of_small_heads_keeps_three_waves():
     (n,) = [int(n) for name, n in re.findall(r"\.amdhsa_kernel (\S+)\n.*?\.amdhsa_next_free_vgpr (\d+)",
                                              assembly_text("attn.hip"), flags=re.S) if "ILi64ELi2E" in name]
     assert n <= 168 and [b for name, b in scratch("attn.hip").items() if "ILi64ELi2E" in name] == [0]
+
+
+def test_wave_accumulators_and_m0_are_left_alone():
+    """O lives in fixed accumulation registers between the assembly statements that name them, and the loads into LDS
+    count on M0: the compiler puts nothing there."""
+    kernels = {name: code for name, code in assembly("attn_wave.hip").items() if "k_attn_wave" in name}
+    assert len(kernels) == 3 and not any(scratch("attn_wave.hip").values())
+    for name, body in kernels.items():
+        mine = set(range(16 * 4 * (3 if "k_attn_wave1ILi3E" in name else 2)))      # row blocks of 32 x 32 columns
+        inside, seen = False, set()
+        for line in body:
+            if "ASMSTART" in line or "ASMEND" in line:
+                inside = "ASMSTART" in line
+                continue
+            regs = {int(x) for x in re.findall(r"\ba(\d+)\b", line)}
+            for lo, hi in re.findall(r"\ba\[(\d+):(\d+)\]", line):
+                regs |= set(range(int(lo), int(hi) + 1))
+            if inside:
+                seen |= regs & mine
+            else:
+                assert not regs & mine and not re.search(r"\bm0\b", line), (name, line)
+        assert seen == mine
