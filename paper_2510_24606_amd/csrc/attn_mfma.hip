@@ -871,10 +871,10 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
                             void *O, hipStream_t s, hipEvent_t *ev) {
     // kv-heads in flight: one per XCD (most workgroups walking the same K / V per L2).  Row blocks of
     // full tile height whose K and V of eight heads exceed the 256 MB memory-side cache while those of
-    // four fit: four in flight, each on two XCDs -- the L2s then miss more often (53 % hits instead of
-    // 56 % on c3) but mostly into that cache, and the step measures 4-5 % faster; the row form on the
-    // dynamic chunks gains nothing from it (0-1 %) and asks the fabric for 30 % more, so it keeps eight.
-    // Two or one in flight are slower in both forms.
+    // four fit: four in flight, each on two XCDs -- the L2s then miss more often but mostly into that
+    // cache.  Eight / four / two in flight, ms a call: row blocks of 128 (131072 tokens, 8192 keys)
+    // 17.6 / 17.0 / 17.1; on dynamic chunks, whose tiles have less in common, 22.7 / 24.1 / 25.1, 32768 tokens
+    // 1.52 / 1.55 / 1.62, 65536 tokens of groups of seven heads 9.3 / 10.0 / 9.6: those keep eight.
     const double kv_head_bytes = 2.0 * (double)p.L * (double)(p.ks_l + p.vs_l);
     const int want = (p.B_r >= kRowTile && 8 * kv_head_bytes > 288e6 && 4 * kv_head_bytes <= 288e6) ? 4 : 8;
     AttnArgs a;
