@@ -508,10 +508,12 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 
     // ---- tile t: phases 0 .. 2 RB - 1, one per unit ----
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), see the end of the loop
-    // A row's probabilities are rounded to bf16 relative to its exponent reference: the closer that is to the row's maximum,
-    // the less is lost on the large ones.  The same tiles have a reference for each half of the keys in attn_mfma.hip; one of
-    // the first 32 keys alone gave 1.4 % more error (against 64 bits) than those, one of the first 64 gives 0.3 % (lists of
-    // at most 4608 keys, short ones among them; 0.0 +- 0.2 % where every row has 1024).
+    // The weight of a row's exponent reference is 1 and loses nothing to the rounding to bf16: the closer that is to the row's
+    // maximum, the smaller the error.  The same tiles have a reference for each half of the keys in attn_mfma.hip.  Here it
+    // is the maximum of the first 64 keys, and of the next 64 where 16 of these weigh more than 6 together.  Error against 64
+    // bits (64 / 32 / 32 / 16 heads, lists of 1024 / 1024 / 2048 / 4096 keys), rows with a full list: attn_mfma.hip 2.330e-3, 2.326e-3,
+    // 2.342e-3, 2.335e-3; of the first 64 keys alone 2.333e-3, 2.334e-3, 2.343e-3, 2.339e-3; so 2.323e-3, 2.322e-3, 2.340e-3, 2.333e-3,
+    // for 0-2 % more time (585 -> 525 -> 537 us, 1690 -> 1546 -> 1563 us).
     float limit = dense ? 0.f : 1048576.f;
     for (int t = 0; has0 != 0; ++t) {
         // Phase P: scores of unit P + 1, then O += P V of unit P - 1; beside products up to S0 - 1 exponentials of unit P,
@@ -641,7 +643,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
         };
         static_for<2 * RB>([&](auto PC) __attribute__((always_inline)) { phase(PC); });
         toggle = -toggle;
-        limit = 1048576.f;
+        limit = dense && t == 0 ? 6.f : 1048576.f;
         int has3 = 64, fl3 = 0;
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(keys.fast) == 0, 0)) {
             has3 = keys.general(t + 3, fl3);
