@@ -1,6 +1,9 @@
 // bf16 MFMA sparse attention, one wave per SIMD (same algorithm and same results as attn_mfma.hip, which describes
 // the key lists, the masks and the exponent reference).
 //
+// A tile gets the bits that attn_mfma.hip gives it, whichever of the two takes it: the products, sums and references of
+// a row are made from the same numbers in the same order.
+//
 // A wave owns ALL rows of a tile of 33..64 or 65..96 rows (RB = 2, 3 blocks of 32), or one half of a tile of 97..128
 // rows (RB = 2, two waves side by side), and walks the tile's whole key list.  It may use all 512 registers of a SIMD
 // lane, so a K or V fragment that has been read from LDS serves all its row blocks (a third or half of the reads that
@@ -49,7 +52,11 @@ constexpr int kWaveD = 128;   // head dimension
     X(8, 128, 129, 130, 131, 132, 133, 134, 135, 136, 137, 138, 139, 140, 141, 142, 143) \
     X(9, 144, 145, 146, 147, 148, 149, 150, 151, 152, 153, 154, 155, 156, 157, 158, 159) \
     X(10, 160, 161, 162, 163, 164, 165, 166, 167, 168, 169, 170, 171, 172, 173, 174, 175) \
-    X(11, 176, 177, 178, 179, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191)
+    X(11, 176, 177, 178, 179, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191) \
+    X(12, 192, 193, 194, 195, 196, 197, 198, 199, 200, 201, 202, 203, 204, 205, 206, 207) \
+    X(13, 208, 209, 210, 211, 212, 213, 214, 215, 216, 217, 218, 219, 220, 221, 222, 223) \
+    X(14, 224, 225, 226, 227, 228, 229, 230, 231, 232, 233, 234, 235, 236, 237, 238, 239) \
+    X(15, 240, 241, 242, 243, 244, 245, 246, 247, 248, 249, 250, 251, 252, 253, 254, 255)
 #define WAVE_ACC_CLOBBER(r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15) \
     "a" #r0, "a" #r1, "a" #r2, "a" #r3, "a" #r4, "a" #r5, "a" #r6, "a" #r7, "a" #r8, "a" #r9, "a" #r10, "a" #r11, "a" #r12, \
         "a" #r13, "a" #r14, "a" #r15
@@ -144,6 +151,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 
 constexpr int kNoKey = 0x7fffffff;
+constexpr int kFirstTile = 256;         // flag of a list's first tile, beside the number of its keys that not every row takes
+constexpr float kFar = 1048576.f;       // a sum of exponentials that moves the exponent reference (as in attn_mfma.hip)
 
 // Key list of one wave.  Entry tables of four tiles of 64 packed keys; tile t of the list is at t mod 4.
 struct WaveTables {
@@ -311,7 +320,15 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     constexpr bool pair = W == 2;
     constexpr bool dense = RB == 2 && !pair;    // V fragments are read in the phase that uses the old ones last; else spread over two
     constexpr bool k_first = RB == 2;           // K fragments are read beside the products that use the old ones last; else behind them
-    constexpr int QA = 2;                       // row blocks whose Q fragments live in accumulation registers
+    // Tiles of at most 64 rows, as attn_tile_16 has them: each half of a tile's keys has its own softmax state (reference,
+    // sums, O), merged at the end; a row's sum is made in parts of 8 keys, 16 rows move their references together, and
+    // P V takes the keys in the order of a 16x16x32 product (two 32x32x16 products, one after the other, give its bits).
+    // The states cost no time (prefill of 131072 tokens 21.6 ms of attention with one state and with two) and fill the
+    // accumulation registers, so all Q fragments live in vector registers.
+    constexpr bool split = RB == 2 && !pair;
+    constexpr int NST = split ? 2 * RB : RB;    // softmax states: of row block r and key half hf: hf RB + r
+    constexpr int NP = split ? 2 : 1;           // parts of a row's sum
+    constexpr int QA = split ? 0 : 2;           // row blocks whose Q fragments live in accumulation registers
 
     const int lane = threadIdx.x & 63, wave = pair ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int lr = lane & 31, g2 = lane >> 5;
@@ -335,19 +352,21 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 
     // Q fragments (B operand of S^T = K Q^T): lane holds row lr of a row block, d = 16 s + 8 g2 .. + 7
     bf16x8 qf[RB][NS];
-    float m_ref[RB], l_run[RB];
-    int v_i[RB];
+    float m_ref[NST], l_run[NST][NP];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         const int rr = (wave * RB + r) * 32 + lr;
         const uint16_t *qp = a.Q + (int64_t)h * a.qs_h + (int64_t)(row0 + (rr >= nrows ? nrows - 1 : rr)) * a.qs_l + 8 * g2;
 #pragma unroll
         for (int s = 0; s < NS; ++s) qf[r][s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
-        v_i[r] = v_lo + rr;
-        m_ref[r] = rr >= nrows ? 1e30f : __builtin_nanf("");   // padding rows: q = 0, p = 0
-        l_run[r] = 0.f;
+#pragma unroll
+        for (int st = r; st < NST; st += RB) {
+            m_ref[st] = rr >= nrows ? 1e30f : __builtin_nanf("");   // padding rows: q = 0, p = 0
+#pragma unroll
+            for (int k = 0; k < NP; ++k) l_run[st][k] = 0.f;
+        }
     }
-    static_for<RB * NDB>([](auto G) __attribute__((always_inline)) { acc_zero<decltype(G)::value>(); });
+    static_for<NST * NDB>([](auto G) __attribute__((always_inline)) { acc_zero<decltype(G)::value>(); });
 
     keys.E = E;
     keys.row_end = row0 + nrows; keys.b_l = b_l; keys.v_lo = v_lo; keys.v_hi = v_hi;
@@ -366,15 +385,20 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     // ---- staging: lane L of a window's load fills bytes [16 L, 16 L + 16) of it: a piece of row L / OPR of the window ----
     const int c_first = wave * LPW;
     const int off_slot_rd = (lane / OPR) * NLD + c_first;
-    unsigned piece[4];   // this lane's logical piece of its row, window c (mod 4)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) piece[c] = 16u * ((lane % OPR) ^ piece_swizzle((c_first + c) * RPW + lane / OPR, OPR));
+    // byte offset of this lane's logical piece of its row in window 0; in window c the swizzle of a row 4 c further differs
+    const unsigned piece0 = 16u * ((lane % OPR) ^ piece_swizzle(lane / OPR, OPR));
+    static_assert(RPW == 4 && LPW % 4 == 0, "rows of windows c and c + 4 have the same swizzle");
+    const auto add_piece = [&](unsigned &off, int c) __attribute__((always_inline)) {
+        const unsigned flip = 16u * ((c & 1) | (c & 2) << 2);
+        if ((c & 3) == 0) off += piece0;
+        else WAVE_ASM("v_xad_u32 %0, %1, %2, %0" : "+v"(off) : "v"(piece0), "s"(flip));
+    };
     const unsigned lds_K = lds_address(sm.K) + c_first * 1024, lds_V = lds_address(sm.V) + c_first * 1024;
     unsigned offs[2][LPW];   // byte offsets of the pieces this lane fetches for an even and for an odd block, K and V alike
 #define WAVE_OFFS(t, half) \
     { \
         _Pragma("unroll") for (int c = 0; c < LPW; ++c) offs[half][c] = keys.tab.off[(t) & 3][(half) * 32 + off_slot_rd + c]; \
-        _Pragma("unroll") for (int c = 0; c < LPW; ++c) offs[half][c] += piece[c & 3]; \
+        _Pragma("unroll") for (int c = 0; c < LPW; ++c) add_piece(offs[half][c], c); \
     }
 #define WAVE_LOAD(base, dst, half, c) { load_window(base, offs[half][c], (dst) + ((c) & ~3) * 1024, (c) & 3); }
 
@@ -397,15 +421,16 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     i64x2 vf[2 * NDB];    // V^T fragments of a block
     f32x16 sc[2];         // scores of a unit, by parity
     u32x4 pf[2][2];       // P of a unit as bf16 pairs: the two B operands
-    float ex[16], psum[2] = {0.f, 0.f}, mc = 0.f, mc_next = 0.f;
+    float ex[16], psum[2][NP], mc = 0.f, mc_next = 0.f;
 #define WAVE_READ_K(s, slot) kf[s] = *(bf16x8 __attribute__((address_space(3))) *)(smK8 + k_off[s] + (slot) * SLOT);
 #define WAVE_READ_V(k, slot) /* half (k & 1) of fragment k / 2 */ \
     { \
         const int j_ = (k) / 2, half_ = (k) & 1; \
-        const int x2_ = (j_ % NDB) ^ (2 * half_); \
+        const int up8_ = split ? j_ / NDB : half_, up16_ = split ? half_ : j_ / NDB; /* keys + 8, + 16 */ \
+        const int x2_ = (j_ % NDB) ^ (2 * up8_); \
         union { s16x4 h; long u; } r_; \
         r_.h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)( \
-            smV8 + ((x2_ & 1) ? v_base_o : v_base_e) + 2 * ((16 * (j_ / NDB) + 8 * half_) * D + 32 * x2_) + (slot) * SLOT)); \
+            smV8 + ((x2_ & 1) ? v_base_o : v_base_e) + 2 * ((16 * up16_ + 8 * up8_) * D + 32 * x2_) + (slot) * SLOT)); \
         vf[j_][half_] = r_.u; \
     }
 // exponentials of elements x0 .. x1-1 of the unit of parity p; their sums and rounding
@@ -414,18 +439,25 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
         ex[x] = __builtin_amdgcn_exp2f(sc[p][x] * scale_log2e - mc); \
         WAVE_ASM("" : "+v"(ex[x])); \
     }
+#define WAVE_PART(x) (split ? ((x) >> 2) & 1 : 0)
+#define WAVE_P(p, x) pf[p][split ? ((x) >> 2) & 1 : (x) >> 3][split ? ((x) >> 3) * 2 + (((x) & 3) >> 1) : ((x) & 7) >> 1]
 #define WAVE_SUM(p, x0, x1) \
     _Pragma("unroll") for (int x = (x0); x < (x1); ++x) { \
-        psum[p] = x == 0 ? ex[0] : psum[p] + ex[x]; \
+        const int part_ = WAVE_PART(x); \
+        psum[p][part_] = x == 4 * part_ ? ex[x] : psum[p][part_] + ex[x]; \
         if (x & 1) { \
             unsigned w_; \
             WAVE_ASM("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w_) : "v"(ex[x - 1]), "v"(ex[x])); \
-            pf[p][x >> 3][(x & 7) >> 1] = w_; \
+            WAVE_P(p, x) = w_; \
         } \
-    } \
-    WAVE_ASM("" : "+v"(psum[p]));
-    // keys that not every row of the tile takes
-    const auto mask = [&](int t, int half, f32x16 &s, int v) __attribute__((always_inline)) {
+        WAVE_ASM("" : "+v"(psum[p][part_])); \
+    }
+    // What only rare branches need is made there, from a copy of the lane number that nothing can be hoisted from: there are
+    // no registers to keep it in.
+    const auto fresh_lane = [&]() __attribute__((always_inline)) { int ln = lane; WAVE_ASM("" : "+v"(ln)); return ln; };
+    // keys that not every row of the tile takes, row block r
+    const auto mask = [&](int t, int half, f32x16 &s, int r) __attribute__((always_inline)) {
+        const int ln = fresh_lane(), v = v_lo + (wave * RB + r) * 32 + (ln & 31), g2 = ln >> 5;
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const int key = half * 32 + q4 * 8 + g2 * 4;
@@ -436,6 +468,19 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
             s[q4 * 4 + 2] = ((v > lo.z) & (v < hi.z)) ? s[q4 * 4 + 2] : -INFINITY;
             s[q4 * 4 + 3] = ((v > lo.w) & (v < hi.w)) ? s[q4 * 4 + 3] : -INFINITY;
         }
+    };
+
+    // maximum of a unit of scores over the row (the two lanes of a row exchange their halves)
+    const auto row_max = [&](const f32x16 &s) __attribute__((always_inline)) {
+        float mx = s[0];
+#pragma unroll
+        for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
+        return fmaxf(mx, __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (fresh_lane() ^ 32), __float_as_int(mx))));
+    };
+    // the first block of a softmax state: its reference is the row's maximum there
+    const auto first_reference = [&](float &m, const f32x16 &s) __attribute__((always_inline)) {
+        const float mx = row_max(s);
+        if (mx != -INFINITY) m = fmaxf(m, mx);
     };
 
     // ---- lists of tiles 0..2 ----
@@ -458,8 +503,10 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             if (m_ref[r] == 1e30f) qf[r][s] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-            if (r < QA) WAVE_ASM("" : "+a"(qf[r][s]));
-            else WAVE_ASM("" : "+v"(qf[r][s]));
+            if constexpr (QA > 0) {
+                if (r < QA) WAVE_ASM("" : "+a"(qf[r][s]));
+                else WAVE_ASM("" : "+v"(qf[r][s]));
+            } else WAVE_ASM("" : "+v"(qf[r][s]));
         }
 
     // ---- first loads, scores of unit 0 and the first of its exponentials ----
@@ -490,14 +537,16 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 #pragma unroll
         for (int s = 0; s < NS; ++s) WAVE_READ_K(s, 0)
 #pragma unroll
-        for (int s = 0; s < NS; ++s) scores_mfma<true>(sc[0], kf[s], qf[0][s], s == 0);
+        for (int s = 0; s < NS; ++s) scores_mfma<(QA > 0)>(sc[0], kf[s], qf[0][s], s == 0);
         WAVE_ASM("s_nop 15\n\ts_nop 7" : "+v"(sc[0]));
         if constexpr (!pair) {
             WAVE_OFFS(1, 0)
 #pragma unroll
             for (int c = 0; c < NLD / 2; ++c) WAVE_LOAD(Kg8, lds_K, 0, c)   // (the other half in phase 0)
         }
-        if (fl0 != 0) mask(0, 0, sc[0], v_i[0]);
+        if (fl0 != 0) mask(0, 0, sc[0], 0);
+        first_reference(m_ref[0], sc[0]);
+        fl0 |= kFirstTile;
         mc = m_ref[0] * scale_log2e;
         WAVE_EXP(0, 0, NM - S0)
         WAVE_SUM(0, 0, NM - S0 - 1)
@@ -508,13 +557,6 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 
     // ---- tile t: phases 0 .. 2 RB - 1, one per unit ----
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), see the end of the loop
-    // The weight of a row's exponent reference is 1 and loses nothing to the rounding to bf16: the closer that is to the row's
-    // maximum, the smaller the error.  The same tiles have a reference for each half of the keys in attn_mfma.hip.  Here it
-    // is the maximum of the first 64 keys, and of the next 64 where 16 of these weigh more than 6 together.  Error against 64
-    // bits (64 / 32 / 32 / 16 heads, lists of 1024 / 1024 / 2048 / 4096 keys), rows with a full list: attn_mfma.hip 2.330e-3, 2.326e-3,
-    // 2.342e-3, 2.335e-3; of the first 64 keys alone 2.333e-3, 2.334e-3, 2.343e-3, 2.339e-3; so 2.323e-3, 2.322e-3, 2.340e-3, 2.333e-3,
-    // for 0-2 % more time (585 -> 525 -> 537 us, 1690 -> 1546 -> 1563 us).
-    float limit = dense ? 0.f : 1048576.f;
     for (int t = 0; has0 != 0; ++t) {
         // Phase P: scores of unit P + 1, then O += P V of unit P - 1; beside products up to S0 - 1 exponentials of unit P,
         // from S0 on of unit P + 1.
@@ -524,6 +566,8 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
             constexpr int p = P & 1, q = p ^ 1;
             constexpr int hf = P / RB;                                                  // block of unit P in the tile
             constexpr bool kref = rq == RB - 1, vref = rp == RB - 1;   // the K / V fragments of a block are used for the last time
+            constexpr int st = split ? P : r, stq = split ? (P + 1) % NST : rq, stp = split ? (P + NST - 1) % NST : rp;   // and their states
+            constexpr bool first = P + 1 < NST;                        // unit P + 1 may be the first block of its state
             unsigned long long far = 0;
             // Loads in flight when a block is needed: W = 1: those of three blocks behind V, of two behind K (of one and a half
             // where K is read first thing in the phase).  W = 2: those of the last two phases' pairs (V(j+3), K(j+4)); what a
@@ -548,7 +592,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                     if (j == 0) WAVE_ASM("s_nop 1" ::: "memory");   // (a product reads P two issues after its conversion at the earliest)
                     static_for<NDB>([&](auto DB) __attribute__((always_inline)) {
                         constexpr int db = decltype(DB)::value;
-                        if (j % NDB == db) acc_mfma<rp * NDB + db>(vf[j], pf[q][j / NDB]);
+                        if (j % NDB == db) acc_mfma<stp * NDB + db>(vf[j], pf[q][j / NDB]);
                     });
                     if (vref && dense) { WAVE_READ_V(2 * j, hf) WAVE_READ_V(2 * j + 1, hf) }
                     if (vref && !dense) WAVE_READ_V(j, hf)
@@ -561,7 +605,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                     for (int c = 0; c < LPW; ++c) {
                         if (r == 1 && i == NS + c) WAVE_LOAD(Vg8, lds_V + (hf == 0 ? 3 * SLOT - odd : odd), hf ^ 1, c)
                         if (r == 0 && i == NS) offs[hf][c] = keys.tab.off[(t + 2) & 3][hf * 32 + off_slot_rd + c];
-                        if (r == 1 && i == 2 * c) { offs[hf][c] += piece[c & 3]; }
+                        if (r == 1 && i == 2 * c) add_piece(offs[hf][c], c);
                         if (r == 1 && i == NS + LPW + c) WAVE_LOAD(Kg8, lds_K + odd + hf * SLOT, hf, c)
                     }
                     if (P == 1 && i < NS) k_off[i] += toggle;   // K(A) of the next tile is read in phase 2
@@ -577,7 +621,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                             if (RB == 2 && c == 0 && i == 2) WAVE_ASM("s_waitcnt lgkmcnt(0)" ::: "memory");   // V fragments of this slot
                             if (at_v == i) WAVE_LOAD(Vg8, lds_V + hf * SLOT, hf, c)
                             if (c / 4 == i) offs[hf ^ 1][c] = keys.tab.off[(hf ? t + 2 : t + 1) & 3][(hf ^ 1) * 32 + off_slot_rd + c];
-                            if (i == 4 + c) { offs[hf ^ 1][c] += piece[c & 3]; }
+                            if (i == 4 + c) add_piece(offs[hf ^ 1][c], c);
                             if (c < NLD / 2 && i == 12 + c) WAVE_LOAD(Kg8, lds_K + (hf ^ 1) * SLOT, hf ^ 1, c)
                         }
                         if (r == 0 && c >= NLD / 2 && i == 2 * (c - 4) + dense) WAVE_LOAD(Kg8, lds_K + hf * SLOT, hf, c)
@@ -586,10 +630,16 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                 if (i == S0) {   // the scores of unit P + 1 are complete
                     int fl = (P + 1) / RB < 2 ? fl0 : fl1;
                     WAVE_ASM("" : "+s"(fl));
-                    if (__builtin_expect(fl != 0, 0)) mask((P + 1) / RB < 2 ? t : t + 1, ((P + 1) / RB) & 1, sc[q], v_i[rq]);
+                    if (__builtin_expect(fl != 0, 0)) {
+                        if (fl & ~kFirstTile) mask((P + 1) / RB < 2 ? t : t + 1, ((P + 1) / RB) & 1, sc[q], rq);
+                        if (first && (fl & kFirstTile)) {
+                            first_reference(m_ref[stq], sc[q]);
+                            mc_next = m_ref[stq] * scale_log2e;
+                        }
+                    }
                     mc = mc_next;
                 }
-                if (i == S0 - 2) mc_next = m_ref[rq] * scale_log2e;
+                if (i == S0 - 2) mc_next = m_ref[stq] * scale_log2e;
                 {
                     const int k = (i + NM - S0) % NM, kl = (i + NM - 1 - S0) % NM;
                     WAVE_EXP((i >= S0 ? q : p), k, k + 1)
@@ -603,47 +653,48 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                     if (P == at_p && i == at_i) keys.template step<S>(t + 3);
                 });
                 if (i == S0 + 1) {
-                    far = __ballot(!(psum[p] < limit));
+                    if constexpr (split) far = __ballot(!(psum[p][0] < kFar) || !(psum[p][NP - 1] < kFar));
+                    else far = __ballot(!(psum[p][0] < kFar));
                     WAVE_ASM("" : "+s"(far));
                 }
                 if (i == S0 + 3) {
                     // unit P: too large, inf or NaN, or no reference yet: move the reference, take the exponentials again
                     if (__builtin_expect(far != 0, 0)) {
                         const f32x16 &s = sc[p];
-                        float mx = s[0];
-#pragma unroll
-                        for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
-                        mx = fmaxf(mx, __shfl_xor(mx, 32));
-                        const float m_new = fmaxf(m_ref[r], mx);   // the other one if one is NaN
+                        const bool mine = !split || (far & (0x0000ffff0000ffffull << (fresh_lane() & 16))) != 0;
+                        const float m_old = m_ref[st], mx = row_max(s);
+                        const float m_new = mine ? fmaxf(m_old, mx) : m_old;   // the other one if one is NaN
                         const bool none = m_new == -INFINITY;
-                        const float alpha = (m_ref[r] != m_ref[r]) ? 0.f : __builtin_amdgcn_exp2f((m_ref[r] - m_new) * scale_log2e);
-                        l_run[r] *= alpha;
-                        static_for<NDB>([&](auto DB) __attribute__((always_inline)) { acc_scale<r * NDB + decltype(DB)::value>(alpha); });
+                        const float alpha = (m_old != m_old) ? 0.f : __builtin_amdgcn_exp2f((m_old - m_new) * scale_log2e);
+                        static_for<NDB>([&](auto DB) __attribute__((always_inline)) { acc_scale<st * NDB + decltype(DB)::value>(alpha); });
                         const float ref = none ? 0.f : m_new * scale_log2e;
-                        m_ref[r] = none ? __builtin_nanf("") : m_new;
-                        psum[p] = 0.f;
+                        m_ref[st] = none ? __builtin_nanf("") : m_new;
+#pragma unroll
+                        for (int k = 0; k < NP; ++k) { l_run[st][k] *= alpha; psum[p][k] = 0.f; }
                         float e2[2];
 #pragma unroll
                         for (int x = 0; x < 16; ++x) {
                             float d = s[x] * scale_log2e;   // rounded like ref: the row's maximum weighs 1 however large it is
                             WAVE_ASM("" : "+v"(d));
-                            e2[x & 1] = __builtin_amdgcn_exp2f(d - ref);
-                            psum[p] += e2[x & 1];
+                            d -= ref;
+                            if (split && !mine) d = __builtin_fmaf(s[x], scale_log2e, -ref);
+                            e2[x & 1] = __builtin_amdgcn_exp2f(d);
+                            psum[p][WAVE_PART(x)] += e2[x & 1];
                             if (x & 1) {
                                 union { __bf16 b[2]; unsigned u; } w;
                                 w.b[0] = (__bf16)e2[0]; w.b[1] = (__bf16)e2[1];
-                                pf[p][x >> 3][(x & 7) >> 1] = w.u;
+                                WAVE_P(p, x) = w.u;
                             }
                         }
                     }
-                    l_run[r] += psum[p];
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) l_run[st][k] += psum[p][k];
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         };
         static_for<2 * RB>([&](auto PC) __attribute__((always_inline)) { phase(PC); });
         toggle = -toggle;
-        limit = dense && t == 0 ? 6.f : 1048576.f;
         int has3 = 64, fl3 = 0;
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(keys.fast) == 0, 0)) {
             has3 = keys.general(t + 3, fl3);
@@ -656,14 +707,27 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     if (keys.batch_end > 0)
         static_for<2 * NDB>([&](auto J) __attribute__((always_inline)) {   // O += P V of the last unit
             constexpr int j = decltype(J)::value;
-            acc_mfma<(RB - 1) * NDB + j % NDB>(vf[j], pf[1][j / NDB]);
+            acc_mfma<(NST - 1) * NDB + j % NDB>(vf[j], pf[1][j / NDB]);
         });
     WAVE_ASM("s_nop 15\n\ts_nop 7" ::: "memory");
 
     // ---- normalise, round to bf16, store ----
     static_for<RB>([&](auto R) __attribute__((always_inline)) {
         constexpr int r = decltype(R)::value;
-        const float l_tot = l_run[r] + __shfl_xor(l_run[r], 32);
+        float a0 = 1.f, a1 = 0.f;   // weights of the states of the two key halves
+        if constexpr (split) {
+            const float m0 = m_ref[r], m1 = m_ref[RB + r], mm = fmaxf(m0, m1);   // NaN: no key seen (and then the other one is taken)
+            a0 = m0 != m0 ? 0.f : __builtin_amdgcn_exp2f((m0 - mm) * scale_log2e);
+            a1 = m1 != m1 ? 0.f : __builtin_amdgcn_exp2f((m1 - mm) * scale_log2e);
+        }
+        float l_tot = 0.f;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            float l = l_run[r][k];
+            if constexpr (split) l = __builtin_fmaf(l, a0, l_run[RB + r][k] * a1);
+            l += __shfl_xor(l, 32);
+            l_tot = k == 0 ? l : l_tot + l;
+        }
         const int rr = (wave * RB + r) * 32 + lr;
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;   // no visible key (row-block form): zeros
         uint16_t *op = a.O + (int64_t)h * a.os_h + (int64_t)(row0 + rr) * a.os_l;
@@ -671,6 +735,12 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
             constexpr int db = decltype(X)::value / 4, q4 = decltype(X)::value % 4;
             float o[4];
             acc_read<r * NDB + db, q4>(o);
+            if constexpr (split) {
+                float o1[4];
+                acc_read<(RB + r) * NDB + db, q4>(o1);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o[x] = __builtin_fmaf(o[x], a0, o1[x] * a1);
+            }
             union { __bf16 b[4]; uint2 u; } pk;
 #pragma unroll
             for (int x = 0; x < 4; ++x) pk.b[x] = (__bf16)(o[x] * inv);
@@ -683,6 +753,8 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 #undef WAVE_READ_V
 #undef WAVE_EXP
 #undef WAVE_SUM
+#undef WAVE_PART
+#undef WAVE_P
 }
 
 // Tiles tile0 .. tile0 + T - 1 of 97..128 rows, two waves each, from the end of the sequence (most keys) to its start

@@ -60,7 +60,8 @@ def test_wave_accumulators_and_m0_are_left_alone():
     kernels = {name: code for name, code in assembly("attn_wave.hip").items() if "k_attn_wave" in name}
     assert len(kernels) == 3 and not any(scratch("attn_wave.hip").values())
     for name, body in kernels.items():
-        mine = set(range(16 * 4 * (3 if "k_attn_wave1ILi3E" in name else 2)))      # row blocks of 32 x 32 columns
+        # row blocks of 32 x 32 columns, twice (once per half of the keys) where a wave has a tile of at most 64 rows
+        mine = set(range(16 * 4 * {"1ILi3E": 3, "1ILi2E": 4, "2ENS": 2}[re.search(r"k_attn_wave(1ILi.E|2ENS)", name)[1]]))
         inside, seen = False, set()
         for line in body:
             if "ASMSTART" in line or "ASMEND" in line:
