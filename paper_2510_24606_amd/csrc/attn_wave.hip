@@ -151,6 +151,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 
 constexpr int kNoKey = 0x7fffffff;
+constexpr int kListPart = 256;          // plan entries after which a list goes on with a new tile (attn_mfma.hip makes lists in such parts)
 constexpr int kFirstTile = 256;         // flag of a list's first tile, beside the number of its keys that not every row takes
 constexpr float kFar = 1048576.f;       // a sum of exponentials that moves the exponent reference (as in attn_mfma.hip)
 
@@ -198,6 +199,7 @@ struct WaveKeys {
     // t: the tile whose list is being made
     __device__ __forceinline__ void next_batch(int t) {
         const int b = e0 >> 6;
+        if ((e0 & (kListPart - 1)) == 0) batch_end = (batch_end + 63) & ~63;   // the next tile's first key
         if (t < fetched + 2) { WAVE_VMCNT(0); }   // else a whole tile's loads went out behind these and have been waited for
         fetched = t;
         const int w0 = tab.ent[b & 1][lane], rem = tab.ent[b & 1][64 + lane];
@@ -234,15 +236,15 @@ struct WaveKeys {
     }
     __device__ __forceinline__ void put_offset(int t, int j) { tab.off[t & 3][off_slot_wr] = __umul24(j, row_bytes) + win_fix; }
 
-    // List of any tile (keys of several batches, keys that not every row takes, the end of the list).  Returns the number
-    // of its keys; behind the last key the last one is repeated for no row.
+    // List of any tile (keys of several batches, keys that not every row takes, the end of the list or of a part).  Returns
+    // the number of its keys; behind the last key the last one is repeated for no row.
     __device__ __forceinline__ int general(int t, int &flag) {
         int x = t * 64;
         const int xe = x + 64, xl = x + lane;
         int j = 0, lo = 0, hi = kNoKey;
         while (x < xe) {
             if (x >= batch_end) {
-                if (e0 >= E) break;
+                if (e0 >= E || ((e0 & (kListPart - 1)) == 0 && x > t * 64)) break;
                 next_batch(t);
                 continue;
             }

@@ -24,14 +24,15 @@ def tensors(L, layout, seed=5):
 
 
 def run(q, k, v, B, N_b, B_r):
-    """The output, and how many tiles of each height class there are over all heads."""
+    """The output, how many tiles of each height class there are over all heads, and the most entries of a list."""
     prob = dhsa.problem(q, k, B, N_b, B_r=B_r)
     plan, ws = dhsa.alloc(prob, B)
     O = torch.full_like(q, float("nan"))
     dhsa.dhsa_prefill(prob, q, k, v, B, O, plan, ws)
-    nrows = np.sort(dhsa.parse_plan(plan.cpu().numpy())["tiles"][:, 1])
-    nrows = np.diff(np.r_[nrows, q.shape[1]])
-    return O, [int(q.shape[0] * ((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64))]
+    parsed = dhsa.parse_plan(plan.cpu().numpy())
+    nrows = np.diff(np.r_[np.sort(parsed["tiles"][:, 1]), q.shape[1]])
+    tiles = [int(q.shape[0] * ((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64))]
+    return O, tiles, int(parsed["count"].max())
 
 
 def check_route(tiles_few, tiles_all, classes):
@@ -49,19 +50,35 @@ TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
     (TALL * 19 + (1, 16, 63) * 4, 0, 4096, "lhd", (0,)),                # beside classes that keep their launch
     (MIDDLE * 19 + SHORT * 2, 0, 1087, "lhd", (1,)),
     (SHORT * 25 + (129, 97, 65, 3), 0, 4100, "hld", (2,)),
-    ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),                 # 225 chunks: several batches of 64 entries
+    ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),
     ((30, 64, 2, 50, 20) * 35, 97, 1500, "lhd", (0,)),
     ((1, 2, 60, 3, 30, 1, 4, 40) * 40, 96, 2047, "hld", (1,)),          # more than four chunks begin among 64 keys
     ((200, 7, 18) * 20, 65, 1024, "lhd", (1,)),
     ((17, 40, 1) * 90, 64, 1999, "hld", (2,)),
     ((100, 3, 33) * 20, 33, 1024, "lhd", (2,))])
 def test_many_tiles_give_what_few_give(lens, B_r, N_b, layout, classes):
+    many_and_few(lens, B_r, N_b, layout, classes)
+
+
+@pytest.mark.parametrize("lens,B_r,N_b,layout,classes", [
+    ((20, 30, 40, 45) * 160, 128, 10007, "hld", (0,)),
+    ((17, 20, 15, 18) * 260, 96, 6007, "lhd", (1,)),
+    ((17, 20, 15, 18) * 260, 64, 7001, "hld", (2,)),
+    ((17, 20, 15, 18) * 260, 40, 7001, "lhd", (2,))])
+def test_lists_of_several_parts(lens, B_r, N_b, layout, classes):
+    """The lone-wave kernels take a list's entries 64 at a time; after 256, where attn_mfma.hip starts a new segment table,
+    both go on with a new tile."""
+    assert many_and_few(lens, B_r, N_b, layout, classes) > 300
+
+
+def many_and_few(lens, B_r, N_b, layout, classes):
+    """Checks the output of all heads; returns the most entries of a list."""
     B = np.concatenate([[0], np.cumsum(np.random.default_rng(len(lens)).permutation(lens))]).astype(np.int32)
     L = int(B[-1])
     q, k, v = tensors(L, layout)
-    every, tiles_all = run(q, k, v, B, N_b, B_r)
+    every, tiles_all, entries = run(q, k, v, B, N_b, B_r)
     for g in (0, 3, H_KV - 1):      # the query heads of a kv-head alone: a row gets the same bits
-        few, tiles_few = run(q[FEW * g:FEW * (g + 1)], k[g:g + 1], v[g:g + 1], B, N_b, B_r)
+        few, tiles_few, _ = run(q[FEW * g:FEW * (g + 1)], k[g:g + 1], v[g:g + 1], B, N_b, B_r)
         check_route(tiles_few, tiles_all, classes)
         assert torch.equal(every[FEW * g:FEW * (g + 1)], few), g
     # the weights, which sum to 1, and the result are rounded to 8 bits, each by at most 2^-8 of the largest value of V (sums
@@ -74,6 +91,7 @@ def test_many_tiles_give_what_few_give(lens, B_r, N_b, layout, classes):
     ref = oracle.prefill_rows_blocks(*f32, B, B_r, N_b, rows)[0] if B_r else oracle.prefill_rows(*f32, B, N_b, rows)[0]
     got = every[:2, torch.from_numpy(rows).cuda()].float().cpu().numpy()
     assert np.abs(got - ref).max() <= tol and np.linalg.norm(got - ref) <= 5e-3 * np.linalg.norm(ref)
+    return entries
 
 
 @pytest.mark.parametrize("rows", [128, 96, 64])
@@ -88,8 +106,8 @@ def test_references_that_move_and_values_that_are_not_finite(rows):
     for j, (x, val) in enumerate([(v, float("inf")), (v, float("-inf")), (v, float("nan")), (k, torch.finfo(torch.bfloat16).min),
                                   (k, float("inf")), (k, float("nan"))]):
         x[:, (10 + 10 * j) * rows + j, j] = val
-    every, tiles_all = run(q, k, v, B, 1024, 0)
-    few, tiles_few = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
+    every, tiles_all, _ = run(q, k, v, B, 1024, 0)
+    few, tiles_few, _ = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
     check_route(tiles_few, tiles_all, [{128: 0, 96: 1, 64: 2}[rows]])
     got, want = every[:FEW].float(), few.float()
     assert bool(torch.isnan(want).any()) and bool(torch.isinf(want).any())
