@@ -236,33 +236,6 @@ def main() -> int:
         heights = [int(((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64), (0, 32))]
         return [float(per_tile[launch_of_tile == c].sum()) for c in range(3)], heights
 
-    def launch_of_class(w, tiles):
-        """The stage slot (dhsa_prefill_stage_times) that the row tiles of each height class are timed in, tiles =
-        those of more than 96 rows, 65..96, 33..64 and at most 32: its own, or a taller one's where a class of at most
-        512 tiles over all heads joins its launch (fp32: one launch for all).  Classes of many tiles have a launch of
-        their own (attn_wave_classes), which only the two shortest share."""
-        if w.dtype != "bf16":
-            return [0, 0, 0]
-        n = [w.H_q * t for t in tiles]
-        wave = w.D == 128 and w.N_b >= 1024 and w.L >= 16 * w.N_c
-        w0, w1 = wave and n[0] >= 3584 and w.L >= 32 * w.N_c, wave and n[1] >= 3072
-        if w0 != w1 and n[1 if w0 else 0] > 0 and w.N_b < 4096:
-            w0 = w1 = False
-        w2 = wave and n[2] >= 4608
-        own = [(0 if w0 else n[0]) + (0 if w1 else n[1]), 0 if w2 else n[2], n[3]]
-        at, most = [0, 1, 2], list(own)
-        if w2 and n[3] <= 512:
-            at[2], own[2], most[2] = 1, 0, 0
-        for c in (2, 1):
-            to = c - 1 if own[c - 1] > 0 else 0
-            behind = c == to + 1 or n[2] == 0                  # nothing between the two in the tile table
-            if to == 0 and w1 and n[1] > 0 or not behind:
-                continue
-            if most[c] > 0 and own[to] > 0 and most[c] <= 512:
-                most[to], most[c] = most[to] + most[c], 0
-                at = [to if x == c else x for x in at]
-        return at
-
     def stage_report(w, Q, K, V, O, prob, plan, ws, B_r, reps=5):
         """Per-stage and per-attention-launch milliseconds (median of `reps` passes with events between the
         kernels), the FLOP of each launch and its fraction of the bf16 MFMA peak."""
@@ -270,7 +243,9 @@ def main() -> int:
         med = {k: float(np.median([r[k] for r in runs])) for k in dhsa.STAGES}
         pairs, heights = attended_pairs_by_class(w, B_r, plan)
         launches = {}
-        ran_in = launch_of_class(w, heights)
+        # the stage slots of the tiles of more than 64, 33..64 and at most 32 rows
+        slots = dhsa.dhsa_attention_kernels(prob, w.B)[1]
+        ran_in = [dhsa.STAGES.index(s) - dhsa.STAGES.index(ROW_CLASSES[0][1]) for s in slots[1:]]
         ntiles = [heights[0] + heights[1], heights[2], heights[3]]
         for c, (label, stage) in enumerate(ROW_CLASSES):
             fl = 4.0 * w.D * sum(p for p, at in zip(pairs, ran_in) if at == c)

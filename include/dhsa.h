@@ -268,6 +268,14 @@ dhsa_status dhsa_prefill_stage_times(const dhsa_problem *prob, const void *Q_dev
                                      size_t plan_bytes, void *ws_dev, size_t ws_bytes, float *ms_host,
                                      void *stream);
 
+/* Measurement aid (not a step of the method): how the attention of this problem would be launched, for the row
+ * tiles of more than 96 rows, of 65..96, of 33..64 and of at most 32 rows.  kernel_host[0..3] (HOST): -1 no such
+ * tiles, 0 four waves to a tile (fp32: k_attn_f32), 1 lone waves (k_attn_wave1 / k_attn_wave2; bf16 only);
+ * slot_host[0..3] (HOST): the slot of ms_host above that their time is in.  Needs no GPU.  The results of a tile
+ * hang on neither. */
+dhsa_status dhsa_attention_kernels(const dhsa_problem *prob, const int32_t *B_host, int32_t *kernel_host,
+                                   int32_t *slot_host);
+
 /* Measurement aid (not a step of the method): the sustained rate of the bf16
  * matrix instruction the attention kernel (Alg. 3's QK^T and PV products) is
  * built on, alone in a loop on every CU, for `iters` x 16 instructions per

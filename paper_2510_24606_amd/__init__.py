@@ -28,7 +28,7 @@ POS_SHIFT = 28
 
 EXPORTS = ["dhsa_plan_bytes", "dhsa_workspace_bytes", "dhsa_route", "dhsa_sparse_prefill", "dhsa_prefill",
            "dhsa_prefill_static", "dhsa_static_scratch_bytes", "dhsa_plan_check", "dhsa_prefill_stage_times",
-           "dhsa_debug_scores",
+           "dhsa_attention_kernels", "dhsa_debug_scores",
            "dhsa_plan_expand_rows", "dhsa_debug_routing", "dhsa_mfma_probe", "dhsa_mfma_probe_scratch_bytes",
            "dhsa_finalize_boundaries", "dhsa_finalize_boundaries_workspace_bytes",
            "dhsa_recall_rows", "dhsa_recall_workspace_bytes",
@@ -83,6 +83,7 @@ def lib() -> C.CDLL:
         l.dhsa_prefill_stage_times.argtypes = [P, vp, vp, vp, i32p, vp, vp, C.c_size_t, vp, C.c_size_t,
                                                C.POINTER(C.c_float), vp]
         l.dhsa_prefill_stage_times.restype = C.c_int
+        l.dhsa_attention_kernels.argtypes = [P, i32p, i32p, i32p]; l.dhsa_attention_kernels.restype = C.c_int
         l.dhsa_debug_scores.argtypes = [P, i32p, vp, C.c_size_t, vp, vp]; l.dhsa_debug_scores.restype = C.c_int
         l.dhsa_plan_expand_rows.argtypes = [P, vp, C.c_size_t, C.c_int32, i64p, C.c_int32, vp, vp, C.c_int32, vp, vp]
         l.dhsa_plan_expand_rows.restype = C.c_int
@@ -212,6 +213,15 @@ def dhsa_prefill_stage_times(prob, Q, K, V, B, O, plan, ws) -> dict:
     _check(lib().dhsa_prefill_stage_times(C.byref(p), Q.data_ptr(), K.data_ptr(), V.data_ptr(), _bp(B), O.data_ptr(),
                                           plan.data_ptr(), plan.numel(), ws.data_ptr(), ws.numel(), ms, _stream()))
     return dict(zip(STAGES, (float(x) for x in ms)))
+
+
+def dhsa_attention_kernels(prob, B):
+    """How the row tiles of more than 96 rows, of 65..96, of 33..64 and of at most 32 rows would be attended: ([kernel of
+    each: None no such tiles, 0 four waves to a tile, 1 lone waves], [the entry of STAGES their time is in])."""
+    B = _b(B)
+    kernel, slot = np.empty(4, dtype=np.int32), np.empty(4, dtype=np.int32)
+    _check(lib().dhsa_attention_kernels(C.byref(prob), _bp(B), _bp(kernel), _bp(slot)))
+    return [None if k < 0 else int(k) for k in kernel], [STAGES[s] for s in slot]
 
 
 def dhsa_debug_scores(prob, B, ws):

@@ -73,6 +73,17 @@ struct AttnArgs {
 
 template <int N> struct Int { static constexpr int value = N; };
 
+// Which launch takes the tiles of each height class of the tile table (T_cls tiles per head).
+struct AttnLaunches {
+    bool wave[3];    // classes 0, 1, 2 with a launch of the kernels of attn_wave.hip
+    bool short_too;  // class 3 runs in class 2's wave launch
+    // Launches of k_attn_mfma<., c, .>: first tile, tiles of their own, and these with the shorter ones that joined; the
+    // tiles of a launch lie behind one another in the table.
+    int first[3], own[3], all[3];
+    int slot[4];     // 0, 1, 2: the event of launch_attn_mfma behind which the tiles of a class are done
+};
+AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls);
+
 // attn_wave.hip: the height classes of the tile table that its kernels take, and T tiles of one from tile0 on
 int attn_wave_classes(const Prob &p, const int32_t *T_cls);
 hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int want, int cls, int tile0, int T, hipStream_t s);

@@ -867,6 +867,45 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, i
     else attn_tile_16<D, 1>(sm, pv, a, h, l, row0);
 }
 
+AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls) {
+    AttnLaunches at;
+    int *first = at.first, *own = at.own, *all = at.all;
+    const int classes = attn_wave_classes(p, T_cls), T_big = T_cls[0] + T_cls[1];
+    for (int c = 0; c < 3; ++c) at.wave[c] = (classes & 1 << c) != 0;
+    // The kernel of 33..64 rows takes the tiles of at most 32 along if these are too few for a launch of their own.
+    at.short_too = at.wave[2] && (int64_t)p.H_q * T_cls[3] <= 512;
+    first[0] = at.wave[0] ? T_cls[0] : 0;
+    first[1] = T_big;
+    first[2] = T_big + T_cls[2];
+    own[0] = (at.wave[0] ? 0 : T_cls[0]) + (at.wave[1] ? 0 : T_cls[1]);
+    own[1] = at.wave[2] ? 0 : T_cls[2];
+    own[2] = at.short_too ? 0 : T_cls[3];
+    for (int c = 0; c < 3; ++c) all[c] = own[c];
+    at.slot[0] = at.slot[1] = 0; at.slot[2] = 1; at.slot[3] = at.short_too ? 1 : 2;
+    // A launch of fewer workgroups than the chip holds at once (two per CU) takes as long as one workgroup whatever their
+    // number, while the next taller launch has such tiles run in the gaps of its own (their stage time is then part of
+    // that launch's).  A 1K-token prompt: 33.3 us a call with a launch per class, 25.0 us so; c2 1622 -> 1591 us.
+    for (int c = 2; c > 0; --c) {
+        const int to = own[c - 1] > 0 ? c - 1 : 0;
+        if (first[to] + own[to] != first[c]) continue;
+        if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) {
+            all[to] += all[c];
+            all[c] = 0;
+            for (int &slot : at.slot)
+                if (slot == c) slot = to;
+        }
+    }
+    return at;
+}
+
+void attn_mfma_kernels(const Prob &p, const int32_t *T_cls, int32_t *kernel, int32_t *slot) {
+    const AttnLaunches at = attn_launches(p, T_cls);
+    for (int c = 0; c < 4; ++c) {
+        kernel[c] = T_cls[c] == 0 ? -1 : c < 3 ? at.wave[c] : at.short_too;
+        slot[c] = at.slot[c];
+    }
+}
+
 hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
                             void *O, hipStream_t s, hipEvent_t *ev) {
     // kv-heads in flight: one per XCD (most workgroups walking the same K / V per L2).  Row blocks of
@@ -883,25 +922,9 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     a.scale_log2e = p.scale * 1.4426950408889634f;
     a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
     a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
-    // Classes of the tile table that the kernels of attn_wave.hip take.  Those of 33..64 rows take the ones of at most 32
-    // along if these are too few for a launch of their own.
-    const int T_cls0 = pv.T_cls[0], T_cls1 = pv.T_cls[1];
-    const int classes = attn_wave_classes(p, pv.T_cls);
-    const bool wave[3] = {(classes & 1) != 0, (classes & 2) != 0, (classes & 4) != 0};
-    const bool short_too = wave[2] && (int64_t)p.H_q * pv.T_cls[3] <= 512;
-    // tiles of each other launch: its own class, and shorter ones that joined.  A launch of fewer workgroups than the chip
-    // holds at once (two per CU) takes as long as one workgroup whatever their number, while the next taller launch
-    // has such tiles run in the gaps of its own (their stage time is then part of that launch's).  A 1K-token
-    // prompt: 33.3 us a call with a launch per class, 25.0 us so; c2 1622 -> 1591 us.  The tiles of a launch lie behind one
-    // another in the table.
-    const int first[3] = {wave[0] ? T_cls0 : 0, pv.T_big, pv.T_big + pv.T_cls[2]};
-    int own[3] = {(wave[0] ? 0 : T_cls0) + (wave[1] ? 0 : T_cls1), wave[2] ? 0 : pv.T_cls[2], short_too ? 0 : pv.T_cls[3]};
-    int all[3] = {own[0], own[1], own[2]};
-    for (int c = 2; c > 0; --c) {
-        const int to = own[c - 1] > 0 ? c - 1 : 0;
-        if (first[to] + own[to] != first[c]) continue;
-        if (all[c] > 0 && own[to] > 0 && (int64_t)p.H_q * all[c] <= 512) { all[to] += all[c]; all[c] = 0; }
-    }
+    const AttnLaunches at = attn_launches(p, pv.T_cls);
+    const bool *wave = at.wave;
+    const int *first = at.first, *own = at.own, *all = at.all;
     // a launch takes tiles of its own class from the end of their table, as many as fit a grid; the first one also takes
     // the shorter tiles that joined (a tile has one result, whatever its launch)
     const int per_grid = p.H_q < kGridMax ? kGridMax / p.H_q : 1;
@@ -920,13 +943,13 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // tallest tiles first (they take longest)
     for (int c = 0; c < 2; ++c)
         if (wave[c]) {
-            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : T_cls0, pv.T_cls[c], s);
+            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : pv.T_cls[0], pv.T_cls[c], s);
             if (e != hipSuccess) return e;
         }
     DHSA_LAUNCH(0)
     if (ev && hipEventRecord(ev[0], s) != hipSuccess) return hipErrorUnknown;
     if (wave[2]) {
-        const hipError_t e = launch_attn_wave(p, pv, a, want, 2, pv.T_big, pv.T_cls[2] + (short_too ? pv.T_cls[3] : 0), s);
+        const hipError_t e = launch_attn_wave(p, pv, a, want, 2, pv.T_big, pv.T_cls[2] + (at.short_too ? pv.T_cls[3] : 0), s);
         if (e != hipSuccess) return e;
     }
     DHSA_LAUNCH(1)

@@ -386,6 +386,21 @@ __attribute__((visibility("default"))) dhsa_status dhsa_prefill_stage_times(
     return st;
 }
 
+__attribute__((visibility("default"))) dhsa_status dhsa_attention_kernels(const dhsa_problem *prob,
+                                                                          const int32_t *B_host,
+                                                                          int32_t *kernel_host, int32_t *slot_host) {
+    Prob p;
+    const dhsa_status st = resolve(prob, B_host, &p);
+    if (st != DHSA_OK) return st;
+    if (!kernel_host || !slot_host) return DHSA_ERR_NULL;
+    const PlanLayout pl = plan_layout(p, B_host);
+    if (p.dtype == DHSA_BF16) attn_mfma_kernels(p, pl.T_cls, kernel_host, slot_host);
+    else
+        for (int c = 0; c < 4; ++c) { kernel_host[c] = pl.T_cls[c] > 0 ? 0 : -1; slot_host[c] = 0; }
+    for (int c = 0; c < 4; ++c) slot_host[c] += 4;
+    return DHSA_OK;
+}
+
 __attribute__((visibility("default"))) dhsa_status dhsa_plan_expand_rows(
     const dhsa_problem *prob, const void *plan_dev, size_t plan_bytes, int32_t head, const int64_t *rows_host,
     int32_t n_rows, int64_t *rows_dev_scratch, int32_t *idx_dev, int32_t cap, int32_t *cnt_dev, void *stream) {

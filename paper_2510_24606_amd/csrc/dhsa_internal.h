@@ -138,6 +138,8 @@ hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, con
 // 33..64 rows and of at most 32 rows
 hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
                             void *O, hipStream_t s, hipEvent_t *ev = nullptr);
+// the kernels and events of launch_attn_mfma by height class (dhsa_attention_kernels)
+void attn_mfma_kernels(const Prob &p, const int32_t *T_cls, int32_t *kernel, int32_t *slot);
 
 // ---- small device helpers ----
 // bf16 storage type (a bare 16-bit pattern; the kernels convert by hand)

@@ -181,6 +181,32 @@ def test_static_scratch_plan_check_and_stage_times_reject_bad_arguments_on_the_h
     assert lib.dhsa_debug_scores(C.byref(p), bp(B), 16, 8, 16, None) == 6
 
 
+def test_attention_kernels_by_height_class(lib):
+    p, B = mk(), bounds()
+    bp = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
+    out = np.zeros(4, dtype=np.int32)
+    assert lib.dhsa_attention_kernels(C.byref(p), bp(B), None, bp(out)) == 1
+    assert lib.dhsa_attention_kernels(C.byref(p), bp(B), bp(out), None) == 1
+    assert lib.dhsa_attention_kernels(C.byref(mk(D=96)), bp(B), bp(out), bp(out)) == 2
+    tall, middle, short = "attn_rows_gt64", "attn_rows_33_64", "attn_rows_le32"
+
+    def ask(lens, H_q, dtype=dhsa.DHSA_BF16, N_b=4096, D=128):
+        B = np.r_[0, np.cumsum(lens)].astype(np.int32)
+        return dhsa.dhsa_attention_kernels(mk(L=int(B[-1]), H_q=H_q, H_kv=H_q // 4, N_c=len(lens), N_b=N_b, dtype=dtype, D=D), B)
+
+    four = (128, 80, 50, 20)
+    assert ask(four, 8) == ([0] * 4, [tall] * 4)                             # few of each: one launch
+    assert ask(four * 20, 32) == ([0] * 4, [tall, tall, middle, short])      # 640 of each
+    assert ask(four * 20, 32, dhsa.DHSA_F32) == ([0] * 4, [tall] * 4)
+    assert ask((128,) * 20 + (50,) * 16 + (20,) * 17, 32)[1][2:] == [tall, short]    # 512 join, 544 do not
+    assert ask((50,) * 20 + (20,), 32) == ([None, None, 0, 0], [tall, tall, middle, middle])
+    # lone waves: many tiles of D = 128, long lists; the shortest may ride with those of 33..64 rows
+    assert ask((128, 80, 50) * 150 + (20,), 32) == ([1] * 4, [tall, tall, middle, middle])
+    assert ask((128, 80, 50) * 150 + (20,) * 17, 32) == ([1, 1, 1, 0], [tall, tall, middle, short])
+    assert ask((128, 80, 50) * 150, 32, N_b=1000)[0] == [0, 0, 0, None]
+    assert ask((128, 80, 50) * 150, 32, D=64)[0] == [0, 0, 0, None]
+
+
 def test_mfma_probe_rejects_bad_arguments_on_the_host(lib):
     import ctypes as C
     tf = C.c_double(0.0)

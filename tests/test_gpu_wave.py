@@ -1,8 +1,5 @@
 """Row tiles that go to the lone-wave kernels (csrc/attn_wave.hip) because there are many of them, against the same rows of
 few heads alone (csrc/attn_mfma.hip takes few tiles), whose bits they have, and against the oracle."""
-import os
-import re
-
 import numpy as np
 import pytest
 import torch
@@ -24,22 +21,17 @@ def tensors(L, layout, seed=5):
 
 
 def run(q, k, v, B, N_b, B_r):
-    """The output, how many tiles of each height class there are over all heads, and the most entries of a list."""
-    prob = dhsa.problem(q, k, B, N_b, B_r=B_r)
-    plan, ws = dhsa.alloc(prob, B)
+    """The output, the kernels that take the height classes, and the most entries of a list."""
     O = torch.full_like(q, float("nan"))
+    prob = dhsa._with_vo(dhsa.problem(q, k, B, N_b, B_r=B_r), v, O)
+    plan, ws = dhsa.alloc(prob, B)
     dhsa.dhsa_prefill(prob, q, k, v, B, O, plan, ws)
-    parsed = dhsa.parse_plan(plan.cpu().numpy())
-    nrows = np.diff(np.r_[np.sort(parsed["tiles"][:, 1]), q.shape[1]])
-    tiles = [int(q.shape[0] * ((nrows > lo) & (nrows <= hi)).sum()) for lo, hi in ((96, 128), (64, 96), (32, 64))]
-    return O, tiles, int(parsed["count"].max())
+    return O, dhsa.dhsa_attention_kernels(prob, B)[0], int(dhsa.parse_plan(plan.cpu().numpy())["count"].max())
 
 
-def check_route(tiles_few, tiles_all, classes):
-    src = open(os.path.join(os.path.dirname(dhsa.__file__), "csrc", "attn_wave.hip")).read()
-    for c in classes:
-        (least,) = re.findall(rf"enough\({c}, (\d+)\)", src)
-        assert tiles_few[c] < int(least) <= tiles_all[c]
+def check_route(few, every, classes):
+    """`every` has the height classes `classes` taken by lone waves, `few` none."""
+    assert [c for c in range(3) if every[c] == 1] == list(classes) and 1 not in few, (few, every)
 
 
 TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
@@ -51,7 +43,7 @@ TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
     (MIDDLE * 19 + SHORT * 2, 0, 1087, "lhd", (1,)),
     (SHORT * 25 + (129, 97, 65, 3), 0, 4100, "hld", (2,)),
     ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),
-    ((30, 64, 2, 50, 20) * 35, 97, 1500, "lhd", (0,)),
+    ((30, 64, 2, 50, 20) * 35, 97, 4100, "lhd", (0,)),
     ((1, 2, 60, 3, 30, 1, 4, 40) * 40, 96, 2047, "hld", (1,)),          # more than four chunks begin among 64 keys
     ((200, 7, 18) * 20, 65, 1024, "lhd", (1,)),
     ((17, 40, 1) * 90, 64, 1999, "hld", (2,)),
@@ -76,10 +68,10 @@ def many_and_few(lens, B_r, N_b, layout, classes):
     B = np.concatenate([[0], np.cumsum(np.random.default_rng(len(lens)).permutation(lens))]).astype(np.int32)
     L = int(B[-1])
     q, k, v = tensors(L, layout)
-    every, tiles_all, entries = run(q, k, v, B, N_b, B_r)
+    every, kernels, entries = run(q, k, v, B, N_b, B_r)
     for g in (0, 3, H_KV - 1):      # the query heads of a kv-head alone: a row gets the same bits
-        few, tiles_few, _ = run(q[FEW * g:FEW * (g + 1)], k[g:g + 1], v[g:g + 1], B, N_b, B_r)
-        check_route(tiles_few, tiles_all, classes)
+        few, kernels_few, _ = run(q[FEW * g:FEW * (g + 1)], k[g:g + 1], v[g:g + 1], B, N_b, B_r)
+        check_route(kernels_few, kernels, classes)
         assert torch.equal(every[FEW * g:FEW * (g + 1)], few), g
     # the weights, which sum to 1, and the result are rounded to 8 bits, each by at most 2^-8 of the largest value of V (sums
     # in 32 bits add less than 2^-14 of it); on average by a third of that, and independently: 2.3e-3 of the result's norm
@@ -106,9 +98,9 @@ def test_references_that_move_and_values_that_are_not_finite(rows):
     for j, (x, val) in enumerate([(v, float("inf")), (v, float("-inf")), (v, float("nan")), (k, torch.finfo(torch.bfloat16).min),
                                   (k, float("inf")), (k, float("nan"))]):
         x[:, (10 + 10 * j) * rows + j, j] = val
-    every, tiles_all, _ = run(q, k, v, B, 1024, 0)
-    few, tiles_few, _ = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
-    check_route(tiles_few, tiles_all, [{128: 0, 96: 1, 64: 2}[rows]])
+    every, kernels, _ = run(q, k, v, B, 1024, 0)
+    few, kernels_few, _ = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
+    check_route(kernels_few, kernels, [{128: 0, 96: 1, 64: 2}[rows]])
     got, want = every[:FEW].float(), few.float()
     assert bool(torch.isnan(want).any()) and bool(torch.isinf(want).any())
     assert bool(torch.isfinite(want[:, :10 * rows]).all())
