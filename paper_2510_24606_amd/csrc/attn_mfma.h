@@ -75,8 +75,8 @@ template <int N> struct Int { static constexpr int value = N; };
 
 // Which launch takes the tiles of each height class of the tile table (T_cls tiles per head).
 struct AttnLaunches {
-    bool wave[3];    // classes 0, 1, 2 with a launch of the kernels of attn_wave.hip
-    bool short_too;  // class 3 runs in class 2's wave launch
+    bool wave[3];               // classes 0, 1, 2 with a launch of the kernels of attn_wave.hip
+    bool middle_too, short_too; // class 1 runs in the wave launch of class 0, class 3 in that of class 2
     // Launches of k_attn_mfma<., c, .>: first tile, tiles of their own, and these with the shorter ones that joined; the
     // tiles of a launch lie behind one another in the table.
     int first[3], own[3], all[3];

@@ -872,12 +872,14 @@ AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls) {
     int *first = at.first, *own = at.own, *all = at.all;
     const int classes = attn_wave_classes(p, T_cls), T_big = T_cls[0] + T_cls[1];
     for (int c = 0; c < 3; ++c) at.wave[c] = (classes & 1 << c) != 0;
-    // The kernel of 33..64 rows takes the tiles of at most 32 along if these are too few for a launch of their own.
+    // The kernels of 97..128 and of 33..64 rows take the tiles of the next class along if these are too few for a launch of
+    // their own.
+    at.middle_too = at.wave[0] && !at.wave[1] && (int64_t)p.H_q * T_cls[1] <= 512;
     at.short_too = at.wave[2] && (int64_t)p.H_q * T_cls[3] <= 512;
     first[0] = at.wave[0] ? T_cls[0] : 0;
     first[1] = T_big;
     first[2] = T_big + T_cls[2];
-    own[0] = (at.wave[0] ? 0 : T_cls[0]) + (at.wave[1] ? 0 : T_cls[1]);
+    own[0] = (at.wave[0] ? 0 : T_cls[0]) + (at.wave[1] || at.middle_too ? 0 : T_cls[1]);
     own[1] = at.wave[2] ? 0 : T_cls[2];
     own[2] = at.short_too ? 0 : T_cls[3];
     for (int c = 0; c < 3; ++c) all[c] = own[c];
@@ -901,7 +903,8 @@ AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls) {
 void attn_mfma_kernels(const Prob &p, const int32_t *T_cls, int32_t *kernel, int32_t *slot) {
     const AttnLaunches at = attn_launches(p, T_cls);
     for (int c = 0; c < 4; ++c) {
-        kernel[c] = T_cls[c] == 0 ? -1 : c < 3 ? at.wave[c] : at.short_too;
+        const bool lone = c == 3 ? at.short_too : at.wave[c] || (c == 1 && at.middle_too);
+        kernel[c] = T_cls[c] == 0 ? -1 : lone;
         slot[c] = at.slot[c];
     }
 }
@@ -943,7 +946,8 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // tallest tiles first (they take longest)
     for (int c = 0; c < 2; ++c)
         if (wave[c]) {
-            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : pv.T_cls[0], pv.T_cls[c], s);
+            const int T = pv.T_cls[c] + (c == 0 && at.middle_too ? pv.T_cls[1] : 0);
+            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : pv.T_cls[0], T, s);
             if (e != hipSuccess) return e;
         }
     DHSA_LAUNCH(0)

@@ -759,7 +759,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 #undef WAVE_P
 }
 
-// Tiles tile0 .. tile0 + T - 1 of 97..128 rows, two waves each, from the end of the sequence (most keys) to its start
+// Tiles tile0 .. tile0 + T - 1 of 97..128 rows (or 65..96 that ride along), two waves each, from the end of the sequence (most keys) to its start
 __global__ __launch_bounds__(128, 1) void k_attn_wave2(PlanView pv, AttnArgs a, int H_q, int mode, int tile0, int T) {
     __shared__ WaveSmem<2> sm;
     int h, pos;
@@ -793,7 +793,9 @@ __global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, i
 // Heads of 64 have half the products for the same exponentials and lists: 9000 tiles of each class gain 2 %, 4700 lose 3 %.
 // The two tall classes share a launch in attn_mfma.hip: one of them leaves it only where lists are longer still (5264 tiles
 // of class 0 beside 1932 of class 1, 2048 keys: 1228 -> 1240 us; 10752 and 3416, 8192 keys: class 0 alone 9712 -> 9676 us,
-// both 9883 -> 9618 us).
+// both 9883 -> 9618 us).  A few tiles of class 1 ride in class 0's launch (row blocks of 128 and a last one of 80 rows, four
+// waves / a launch of their own / riding: 3584 tiles, 8192 keys 1328 / 1367 / 1264 us; 8192 tiles, 2048 keys, where they
+// switched class 0 off, 1140 / - / 1096 us).
 // Chunks so short that a tile of 64 keys spans more than four make its key list a `general` one; a pair of waves, which
 // makes each list twice, loses by it from 32 tokens on average down (20 tokens: 1063 -> 1090 us), a single one does not
 // (20 tokens, tiles of 96 rows: 465 -> 440 us).  Offsets are 32 bits with room for a window, made by a 24-bit product, the
@@ -805,11 +807,12 @@ int attn_wave_classes(const Prob &p, const int32_t *T_cls) {
         return 0;
     const auto enough = [&](int c, int64_t least) { return p.H_q * (int64_t)T_cls[c] >= least && p.H_q * (int64_t)T_cls[c] <= kGridMax; };
     bool w0 = enough(0, 3584) && p.L >= 32 * (int64_t)p.N_c, w1 = enough(1, 3072);
-    if (w0 != w1 && T_cls[w0 ? 1 : 0] > 0 && p.N_b < 4096) w0 = w1 = false;
+    const bool few1 = p.H_q * (int64_t)T_cls[1] <= 512;   // (they run in class 0's launch)
+    if (w0 != w1 && T_cls[w0 ? 1 : 0] > 0 && !(w0 && few1) && p.N_b < 4096) w0 = w1 = false;
     return (w0 ? 1 : 0) | (w1 ? 2 : 0) | (enough(2, 4608) ? 4 : 0);
 }
 
-// T tiles of class cls from tile0 on: 0: 97..128 rows, 1: 65..96, 2: at most 64 rows
+// T tiles from tile0 on for the kernel of class cls: 0: 65..128 rows, 1: 65..96, 2: at most 64 rows
 hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int want, int cls, int tile0, int T, hipStream_t s) {
     const int mode = attn_order(want, p.H_kv, p.G, T);
     const dim3 grid(p.H_q * T);

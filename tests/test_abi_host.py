@@ -203,6 +203,8 @@ def test_attention_kernels_by_height_class(lib):
     # lone waves: many tiles of D = 128, long lists; the shortest may ride with those of 33..64 rows
     assert ask((128, 80, 50) * 150 + (20,), 32) == ([1] * 4, [tall, tall, middle, middle])
     assert ask((128, 80, 50) * 150 + (20,) * 17, 32) == ([1, 1, 1, 0], [tall, tall, middle, short])
+    assert ask((128,) * 120 + (80,) * 16, 32)[0] == [1, 1, None, None]       # few of 65..96 rows ride too
+    assert ask((128,) * 120 + (80,) * 17, 32)[0][1] == 0
     assert ask((128, 80, 50) * 150, 32, N_b=1000)[0] == [0, 0, 0, None]
     assert ask((128, 80, 50) * 150, 32, D=64)[0] == [0, 0, 0, None]
 

@@ -43,7 +43,7 @@ TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
     (MIDDLE * 19 + SHORT * 2, 0, 1087, "lhd", (1,)),
     (SHORT * 25 + (129, 97, 65, 3), 0, 4100, "hld", (2,)),
     ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),
-    ((30, 64, 2, 50, 20) * 35, 97, 4100, "lhd", (0,)),
+    ((30, 64, 2, 50, 20) * 35, 97, 1600, "lhd", (0, 1)),            # the last block has 87 rows
     ((1, 2, 60, 3, 30, 1, 4, 40) * 40, 96, 2047, "hld", (1,)),          # more than four chunks begin among 64 keys
     ((200, 7, 18) * 20, 65, 1024, "lhd", (1,)),
     ((17, 40, 1) * 90, 64, 1999, "hld", (2,)),
@@ -53,7 +53,7 @@ def test_many_tiles_give_what_few_give(lens, B_r, N_b, layout, classes):
 
 
 @pytest.mark.parametrize("lens,B_r,N_b,layout,classes", [
-    ((20, 30, 40, 45) * 160, 128, 10007, "hld", (0,)),
+    ((20, 30, 40, 45) * 160, 128, 10007, "hld", (0, 1)),
     ((17, 20, 15, 18) * 260, 96, 6007, "lhd", (1,)),
     ((17, 20, 15, 18) * 260, 64, 7001, "hld", (2,)),
     ((17, 20, 15, 18) * 260, 40, 7001, "lhd", (2,))])
