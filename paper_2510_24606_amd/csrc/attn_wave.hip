@@ -782,20 +782,26 @@ __global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, i
     attn_wave<RB, 1>(sm, pv, a, h, l, row0);
 }
 
-// Which height classes of the tile table (bit c = class c) the kernels of this file take; `tall` tells those of more than 64
-// rows.  A wave has to itself what four waves share in attn_mfma.hip: it is faster per tile, but a tile takes longer, its
-// prologue (6 us) is hidden by nothing, and a round is 1024 waves.  Hence heads of 128, lists of a thousand keys or more
-// and so many tiles that the last ones leave few SIMDs without work.  Measured against attn_mfma.hip (LLaMA head shape, 32
-// heads, chunks of 32..128 tokens; tiles of classes 0, 1, 2 over all heads):
-//   3808 4800 4704, 4096 keys  2645 -> 2434 us     1024 keys   832 ->  831 us     8256 9024 8768, 2048 keys  3053 -> 2726 us
-//   tiles of 64 rows only (row blocks): 32768 of them 5716 -> 4267 us, 16384 1339 -> 1135 us, 15008 1628 -> 1426 us
-//   below the limits: 2848 tiles of class 0 +4 % (1536 keys), 2064 +4 % (4096 keys), 3612 of class 2 +1 % (8192 keys)
+// Which height classes of the tile table (bit c = class c) the kernels of this file take.  A wave has to itself what four
+// waves share in attn_mfma.hip: it is faster per tile, but a tile takes longer, its prologue (6 us) is hidden by nothing,
+// and a round is 1024 waves.  Hence heads of 128, lists of a thousand keys or more and so many tiles that the last ones
+// leave few SIMDs without work.  Both sides below are four waves -> lone waves, us of attention, 32 heads of the LLaMA shape:
+//   tiles of 33..64 rows: 4608 of them, 1024 keys 214 -> 208, 2048 344 -> 321, 8192 779 -> 701
+//   tiles of 65..96 rows alone: 3840, 1024 keys 251 -> 232, 4096 700 -> 615
+//   tiles of 97..128 rows alone, row blocks of 128: 3584, 1024 keys 281 -> 286, 1536 379 -> 375, 4096 814 -> 781;
+//     8192, 1024 keys 652 -> 657, 1536 899 -> 875
+//   on dynamic chunks, whose tiles have lists of their own, they gain less, and the denser the lists, the more the four-wave
+//     kernel gets out of the L2s: 112 rows, 9216 tiles of 32256 tokens: 2048 keys 1298 -> 1293, 8192 3999 -> 4263; 18720 of
+//     65520: 2048 keys 2732 -> 2686, 8192 9559 -> 9573; 128 rows, 32768 of 131072: 4096 keys 9592 -> 9206
+//   both tall classes: half and half, 3755 of each, 1024 keys 527 -> 550, 1536 767 -> 741; 5461, 1024 keys 779 -> 770;
+//     10900, 2048 keys 2974 -> 2715.  attn_mfma.hip runs both in one launch; class 0 alone leaves it only for long lists
+//     (5640 tiles beside 1640, 4096 keys 1757 -> 1696), class 1 alone too (6300 beside 190 of 97 rows, 2048 keys 714 ->
+//     about 714, 4096 1247 -> 1164; 3100, 4096 keys 582 -> 588)
+// A few tiles of 65..96 rows ride in the launch of the taller ones (row blocks of 128 and a last one of 80 rows: 3584
+// tiles, 8192 keys 1328 -> 1264; 8192 tiles, 2048 keys 1140 -> 1096).  A few of at most 64 rows are `left` with a launch
+// that takes as long as a list, where four-wave kernels would take them along: row blocks of 128 and a last one of 50 rows
+// 3584, 2048 keys 489 -> 497, 4096 832 -> 820; tiles of 80 rows and one of 30, 3072, 1024 keys 203 -> 205, 1536 275 -> 266.
 // Heads of 64 have half the products for the same exponentials and lists: 9000 tiles of each class gain 2 %, 4700 lose 3 %.
-// The two tall classes share a launch in attn_mfma.hip: one of them leaves it only where lists are longer still (5264 tiles
-// of class 0 beside 1932 of class 1, 2048 keys: 1228 -> 1240 us; 10752 and 3416, 8192 keys: class 0 alone 9712 -> 9676 us,
-// both 9883 -> 9618 us).  A few tiles of class 1 ride in class 0's launch (row blocks of 128 and a last one of 80 rows, four
-// waves / a launch of their own / riding: 3584 tiles, 8192 keys 1328 / 1367 / 1264 us; 8192 tiles, 2048 keys, where they
-// switched class 0 off, 1140 / - / 1096 us).
 // Chunks so short that a tile of 64 keys spans more than four make its key list a `general` one; a pair of waves, which
 // makes each list twice, loses by it from 32 tokens on average down (20 tokens: 1063 -> 1090 us), a single one does not
 // (20 tokens, tiles of 96 rows: 465 -> 440 us).  Offsets are 32 bits with room for a window, made by a 24-bit product, the
@@ -805,10 +811,18 @@ int attn_wave_classes(const Prob &p, const int32_t *T_cls) {
     if (p.D != kWaveD || p.N_b < 1024 || p.L < 16 * (int64_t)p.N_c || p.ks_l != p.vs_l || p.L >= 1 << 24 || row_bytes >= 1 << 24 ||
         p.L * row_bytes > 0xffffffffll - 4096)
         return 0;
-    const auto enough = [&](int c, int64_t least) { return p.H_q * (int64_t)T_cls[c] >= least && p.H_q * (int64_t)T_cls[c] <= kGridMax; };
+    int64_t n[4];                           // tiles of each class over all heads
+    for (int c = 0; c < 4; ++c) n[c] = p.H_q * (int64_t)T_cls[c];
+    const auto enough = [&](int c, int64_t least) { return n[c] >= least && n[c] <= kGridMax; };
+    const int64_t keys = p.N_b;             // of a full list
     bool w0 = enough(0, 3584) && p.L >= 32 * (int64_t)p.N_c, w1 = enough(1, 3072);
-    const bool few1 = p.H_q * (int64_t)T_cls[1] <= 512;   // (they run in class 0's launch)
-    if (w0 != w1 && T_cls[w0 ? 1 : 0] > 0 && !(w0 && few1) && p.N_b < 4096) w0 = w1 = false;
+    const bool left = n[2] > 0 ? n[2] <= 512 : n[3] > 0 && n[3] <= 512;
+    if (w0 && w1) w0 = w1 = n[0] * keys >= 3584 * 1536;
+    else if (w0 && n[1] > 512) w0 = keys >= 4096;
+    else if (w0 && p.B_r > 0) w0 = keys >= 1536 && (!left || n[0] * keys >= 3584 * 4096);
+    else if (w0) w0 = keys >= 2048 && p.L >= 16 * keys && n[0] >= (left ? 16384 : 8192);
+    else if (w1 && n[0] > 0) w1 = keys >= 4096 && n[1] * keys >= 4608 * 4096;
+    else if (w1) w1 = !left || n[1] * keys >= 3072 * 1536;
     return (w0 ? 1 : 0) | (w1 ? 2 : 0) | (enough(2, 4608) ? 4 : 0);
 }
 

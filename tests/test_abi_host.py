@@ -203,10 +203,36 @@ def test_attention_kernels_by_height_class(lib):
     # lone waves: many tiles of D = 128, long lists; the shortest may ride with those of 33..64 rows
     assert ask((128, 80, 50) * 150 + (20,), 32) == ([1] * 4, [tall, tall, middle, middle])
     assert ask((128, 80, 50) * 150 + (20,) * 17, 32) == ([1, 1, 1, 0], [tall, tall, middle, short])
-    assert ask((128,) * 120 + (80,) * 16, 32)[0] == [1, 1, None, None]       # few of 65..96 rows ride too
-    assert ask((128,) * 120 + (80,) * 17, 32)[0][1] == 0
     assert ask((128, 80, 50) * 150, 32, N_b=1000)[0] == [0, 0, 0, None]
     assert ask((128, 80, 50) * 150, 32, D=64)[0] == [0, 0, 0, None]
+
+
+def test_tall_classes_leave_the_four_wave_kernels_where_that_was_measured_faster(lib):
+    def ask(lens, N_b, B_r=0, H_q=32):
+        B = np.r_[0, np.cumsum(lens)].astype(np.int32)
+        p = mk(L=int(B[-1]), H_q=H_q, H_kv=8, N_c=len(lens), N_b=N_b, B_r=B_r)
+        return dhsa.dhsa_attention_kernels(p, B)[0][:2]
+
+    def blocks(L, B_r, N_b):
+        return ask((64,) * (L // 64) + ((L % 64,) if L % 64 else ()), N_b, B_r)
+
+    # row blocks: lists of 1536 keys; a few tiles of 65..96 rows ride, shorter ones ask for longer lists
+    assert [blocks(112 * 128, 128, n)[0] for n in (1024, 1535, 1536)] == [0, 0, 1]
+    assert blocks(111 * 128, 128, 8192)[0] == 0
+    assert blocks(112 * 128 + 80, 128, 1536) == [1, 1]
+    assert [blocks(112 * 128 + 50, 128, n)[0] for n in (2048, 4095, 4096)] == [0, 0, 1]
+    assert [blocks(112 * 128 + 20, 128, n)[0] for n in (4095, 4096)] == [0, 1]
+    assert [blocks(96 * 96 + r, 96, 1024)[1] for r in (0, 20, 50)] == [1, 0, 0]
+    assert [blocks(96 * 96 + r, 96, 1536)[1] for r in (0, 20, 50)] == [1, 1, 1]
+    # tall tiles of dynamic chunks alone: sparse lists, 8192 tiles, twice as many if short ones are left
+    assert [ask((112,) * 293, n)[0] for n in (2047, 2048, 2052)] == [0, 1, 0]      # 32816 tokens
+    assert ask((112,) * 288, 2048)[0] == 0 and ask((112,) * 288, 8192)[0] == 0
+    assert ask((112,) * 300 + (50,), 2048)[0] == 0 and ask((112,) * 512 + (50,), 2048)[0] == 1
+    # both tall classes, one many and the other few
+    assert [ask((112, 80) * 118, n) for n in (1024, 1536)] == [[0, 0], [1, 1]] and ask((112, 80) * 168, 1024) == [1, 1]
+    assert [ask((112,) * 160 + (80,) * 50, n) for n in (4095, 4096)] == [[0, 0], [1, 0]]
+    assert [ask((112,) * 160 + (80,) * 16, n) for n in (2048, 1200)] == [[0, 0], [0, 0]]
+    assert ask((97,) * 2 + (80,) * 97, 4096) == [0, 0] and ask((97,) * 2 + (80,) * 144, 4096) == [0, 1]
 
 
 def test_mfma_probe_rejects_bad_arguments_on_the_host(lib):

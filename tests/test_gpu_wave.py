@@ -38,14 +38,14 @@ TALL, MIDDLE, SHORT = (97, 128, 110), (65, 96, 80), (33, 64, 50)
 
 
 @pytest.mark.parametrize("lens,B_r,N_b,layout,classes", [
-    ((TALL + MIDDLE) * 19 + SHORT * 25 + (1, 32), 0, 1024, "hld", (0, 1, 2)),
-    (TALL * 19 + (1, 16, 63) * 4, 0, 4096, "lhd", (0,)),                # beside classes that keep their launch
-    (MIDDLE * 19 + SHORT * 2, 0, 1087, "lhd", (1,)),
+    ((TALL + MIDDLE) * 19 + SHORT * 25 + (1, 32), 0, 1536, "hld", (0, 1, 2)),
+    (TALL * 100 + (1, 16, 63) * 4, 0, 2048, "lhd", (0,)),               # beside classes that keep their launch
+    (MIDDLE * 19 + SHORT * 2, 0, 1301, "lhd", (1,)),
     (SHORT * 25 + (129, 97, 65, 3), 0, 4100, "hld", (2,)),
-    ((16, 64, 48, 2, 33) * 45, 128, 1025, "hld", (0,)),
+    ((16, 64, 48, 2, 33) * 45, 128, 4101, "hld", (0,)),
     ((30, 64, 2, 50, 20) * 35, 97, 1600, "lhd", (0, 1)),            # the last block has 87 rows
     ((1, 2, 60, 3, 30, 1, 4, 40) * 40, 96, 2047, "hld", (1,)),          # more than four chunks begin among 64 keys
-    ((200, 7, 18) * 20, 65, 1024, "lhd", (1,)),
+    ((200, 7, 18) * 20, 65, 1100, "lhd", (1,)),
     ((17, 40, 1) * 90, 64, 1999, "hld", (2,)),
     ((100, 3, 33) * 20, 33, 1024, "lhd", (2,))])
 def test_many_tiles_give_what_few_give(lens, B_r, N_b, layout, classes):
@@ -98,8 +98,9 @@ def test_references_that_move_and_values_that_are_not_finite(rows):
     for j, (x, val) in enumerate([(v, float("inf")), (v, float("-inf")), (v, float("nan")), (k, torch.finfo(torch.bfloat16).min),
                                   (k, float("inf")), (k, float("nan"))]):
         x[:, (10 + 10 * j) * rows + j, j] = val
-    every, kernels, _ = run(q, k, v, B, 1024, 0)
-    few, kernels_few, _ = run(q[:FEW], k[:1], v[:1], B, 1024, 0)
+    B_r = rows if rows == 128 else 0      # (few tiles of 128 rows of a chunk each stay with four waves)
+    every, kernels, _ = run(q, k, v, B, 1536, B_r)
+    few, kernels_few, _ = run(q[:FEW], k[:1], v[:1], B, 1536, B_r)
     check_route(kernels_few, kernels, [{128: 0, 96: 1, 64: 2}[rows]])
     got, want = every[:FEW].float(), few.float()
     assert bool(torch.isnan(want).any()) and bool(torch.isinf(want).any())
