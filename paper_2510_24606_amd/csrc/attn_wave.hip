@@ -462,6 +462,7 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
         const int ln = fresh_lane(), v = v_lo + (wave * RB + r) * 32 + (ln & 31), g2 = ln >> 5;
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
+            __builtin_amdgcn_sched_barrier(0);   // one after another: there are few registers
             const int key = half * 32 + q4 * 8 + g2 * 4;
             const int4 lo = *reinterpret_cast<const int4 *>(&keys.tab.lo[t & 3][key]);
             const int4 hi = *reinterpret_cast<const int4 *>(&keys.tab.hi[t & 3][key]);
@@ -665,21 +666,23 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
                         const f32x16 &s = sc[p];
                         const bool mine = !split || (far & (0x0000ffff0000ffffull << (fresh_lane() & 16))) != 0;
                         const float m_old = m_ref[st], mx = row_max(s);
+                        float scale = scale_log2e;   // one of its own: else the products below are made before the branch
+                        WAVE_ASM("" : "+s"(scale));
                         const float m_new = mine ? fmaxf(m_old, mx) : m_old;   // the other one if one is NaN
                         const bool none = m_new == -INFINITY;
-                        const float alpha = (m_old != m_old) ? 0.f : __builtin_amdgcn_exp2f((m_old - m_new) * scale_log2e);
+                        const float alpha = (m_old != m_old) ? 0.f : __builtin_amdgcn_exp2f((m_old - m_new) * scale);
                         static_for<NDB>([&](auto DB) __attribute__((always_inline)) { acc_scale<st * NDB + decltype(DB)::value>(alpha); });
-                        const float ref = none ? 0.f : m_new * scale_log2e;
+                        const float ref = none ? 0.f : m_new * scale;
                         m_ref[st] = none ? __builtin_nanf("") : m_new;
 #pragma unroll
                         for (int k = 0; k < NP; ++k) { l_run[st][k] *= alpha; psum[p][k] = 0.f; }
                         float e2[2];
 #pragma unroll
                         for (int x = 0; x < 16; ++x) {
-                            float d = s[x] * scale_log2e;   // rounded like ref: the row's maximum weighs 1 however large it is
+                            float d = s[x] * scale;   // rounded like ref: the row's maximum weighs 1 however large it is
                             WAVE_ASM("" : "+v"(d));
                             d -= ref;
-                            if (split && !mine) d = __builtin_fmaf(s[x], scale_log2e, -ref);
+                            if (split && !mine) d = __builtin_fmaf(s[x], scale, -ref);
                             e2[x & 1] = __builtin_amdgcn_exp2f(d);
                             psum[p][WAVE_PART(x)] += e2[x & 1];
                             if (x & 1) {

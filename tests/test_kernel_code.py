@@ -75,3 +75,20 @@ def test_wave_accumulators_and_m0_are_left_alone():
             else:
                 assert not regs & mine and not re.search(r"\bm0\b", line), (name, line)
         assert seen == mine
+
+
+def wave_kernels():
+    """{(row blocks of a wave, waves of a tile): lines of the kernel}"""
+    kernels = {name: code for name, code in assembly("attn_wave.hip").items() if "k_attn_wave" in name}
+    return {{"1ILi3E": (3, 1), "1ILi2E": (2, 1), "2ENS": (2, 2)}[re.search(r"k_attn_wave(1ILi.E|2ENS)", name)[1]]: code
+            for name, code in kernels.items()}
+
+
+@pytest.mark.parametrize("shape", [(2, 1), (3, 1), (2, 2)])
+def test_wave_loops_make_no_products_for_their_rare_branches(shape):
+    """The vector unit has no issue cycles to spare beside the matrix products.  A unit (32 keys of a row block) needs one
+    product, its scaled reference; the compiler has made those of the branch that moves references, 16 a unit, before it."""
+    blocks = re.split(r"^(?:\.LBB\S+:.*|; %bb.*)$", "\n".join(wave_kernels()[shape]), flags=re.M)
+    hot = [b for b in blocks if b.count("v_mfma") > 2]
+    assert sum(b.count("v_mfma") for b in hot) >= 2 * shape[0] * 16
+    assert sum(len(re.findall(r"^v_mul_f32", b, flags=re.M)) for b in hot) <= 2 * shape[0]
