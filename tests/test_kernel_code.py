@@ -92,3 +92,63 @@ def test_wave_loops_make_no_products_for_their_rare_branches(shape):
     hot = [b for b in blocks if b.count("v_mfma") > 2]
     assert sum(b.count("v_mfma") for b in hot) >= 2 * shape[0] * 16
     assert sum(len(re.findall(r"^v_mul_f32", b, flags=re.M)) for b in hot) <= 2 * shape[0]
+
+
+def registers(op, after=0):
+    """Names of the vector and accumulation registers among the operands of an instruction, from operand `after` on."""
+    found = set()
+    for text in op.split(None, 1)[1].split(",")[after:] if " " in op else []:
+        for kind, lo, hi in re.findall(r"\b([va])(?:(\d+)\b|\[)(?=(?:\d+:(\d+)\])?)", text):
+            if lo:
+                found.add(kind + lo)
+            elif hi:
+                first = int(re.search(rf"\b{kind}\[(\d+):{hi}\]", text)[1])
+                found |= {f"{kind}{n}" for n in range(first, int(hi) + 1)}
+    return found
+
+
+def within(ops, labels, i, states, visit):
+    """Calls visit(instruction) for all that can follow ops[i] within so many wait states, over both ways of a branch."""
+    seen, todo = {}, [(i + 1, 0)]
+    while todo:
+        at, waited = todo.pop()
+        if at >= len(ops) or waited >= states or seen.get(at, states) <= waited:
+            continue
+        seen[at] = waited
+        op = ops[at]
+        visit(op)
+        if op.startswith(("s_branch", "s_cbranch")):
+            todo.append((labels[op.split()[1]], waited + 1))
+        if not op.startswith(("s_branch", "s_endpgm")):
+            todo.append((at + 1, waited + (int(op.split()[1]) + 1 if op.startswith("s_nop") else 1)))
+
+
+@pytest.mark.parametrize("shape", [(2, 1), (3, 1), (2, 2)])
+def test_distances_that_the_hardware_does_not_keep_for_products_in_assembly(shape):
+    """The compiler keeps them for its own instructions only.  A product of 8 passes: 12 wait states until anything but a
+    product touches its result (and none may have it as a factor sooner); 2 from a vector instruction's result to the product
+    that reads it."""
+    ops, labels = [], {}
+    for line in wave_kernels()[shape]:
+        line = line.split(";")[0].strip()
+        if line.endswith(":"):
+            labels[line[:-1]] = len(ops)
+        elif line and not line.startswith("."):
+            ops.append(line)
+    products = 0
+    for i, op in enumerate(ops):
+        result = registers(op.split(",")[0])
+        if op.startswith("v_mfma"):
+            products += 1
+
+            def late(other, result=result, op=op):
+                mine = registers(other, 1) if other.startswith("v_mfma") else registers(other)
+                if other.startswith("v_mfma") and registers(other.split(",")[0]) == result:
+                    mine -= result                                   # the next product of the sum
+                assert not mine & result, (op, other)
+            within(ops, labels, i, 12, late)
+        elif op.startswith("v_") and result:
+            def soon(other, result=result, op=op):
+                assert not other.startswith("v_mfma") or not registers(other, 1) & result, (op, other)
+            within(ops, labels, i, 2, soon)
+    assert products >= 2 * shape[0] * 16
