@@ -1,14 +1,13 @@
-// bf16 MFMA sparse attention, one wave per SIMD (same algorithm and same results as attn_mfma.hip, which describes
-// the key lists, the masks and the exponent reference).
-//
-// A tile gets the bits that attn_mfma.hip gives it, whichever of the two takes it: the products, sums and references of
-// a row are made from the same numbers in the same order.
+// bf16 MFMA sparse attention, one wave per SIMD (same algorithm as attn_mfma.hip, which describes the key lists, the masks
+// and the exponent reference).  A tile gets the bits that attn_mfma.hip gives it, whichever of the two takes it: the
+// products, sums and references of a row are made from the same numbers in the same order.
 //
 // A wave owns ALL rows of a tile of 33..64 or 65..96 rows (RB = 2, 3 blocks of 32), or one half of a tile of 97..128
 // rows (RB = 2, two waves side by side), and walks the tile's whole key list.  It may use all 512 registers of a SIMD
 // lane, so a K or V fragment that has been read from LDS serves all its row blocks (a third or half of the reads that
-// four waves of one row block each need), a tile of 65..96 rows leaves no wave without rows, and nothing waits at a
-// block-wide barrier: each wave has its own ring of K and V blocks in LDS and waits for its own loads only.
+// four waves of one row block each need), and a tile of 65..96 rows leaves no wave without rows.  A wave that has a tile
+// to itself has its own ring of K and V blocks in LDS, waits for its own loads only and meets no barrier; two waves of a
+// tile fetch half of each block of a common ring and pass a barrier per block.
 //
 // What bounds a lone wave is its own instruction stream: a 32x32x16 product takes the matrix unit 32 cycles, of which
 // issuing it takes 8; the rest holds six vector instructions (an exponential counts twice, an LDS read or a load three

@@ -74,7 +74,8 @@ def many_and_few(lens, B_r, N_b, layout, classes):
         check_route(kernels_few, kernels, classes)
         assert torch.equal(every[FEW * g:FEW * (g + 1)], few), g
     # the weights, which sum to 1, and the result are rounded to 8 bits, each by at most 2^-8 of the largest value of V (sums
-    # in 32 bits add less than 2^-14 of it); on average by a third of that, and independently: 2.3e-3 of the result's norm
+    # in 32 bits add less than 2^-14 of it).  In the norm each rounding is a uniform error of at most 2^-8 of its value, and the
+    # two are independent: sqrt(2 / 3) 2^-8 = 3.2e-3 of the result at most (values are not all just above a power of two: 2.3e-3)
     tol = (2.0 ** -7 + 2.0 ** -14) * float(v[0].float().abs().max())
 
     assert bool(torch.isfinite(every).all())
@@ -82,14 +83,14 @@ def many_and_few(lens, B_r, N_b, layout, classes):
     f32 = [x.float().cpu().numpy() for x in (q[:2], k[:1], v[:1])]
     ref = oracle.prefill_rows_blocks(*f32, B, B_r, N_b, rows)[0] if B_r else oracle.prefill_rows(*f32, B, N_b, rows)[0]
     got = every[:2, torch.from_numpy(rows).cuda()].float().cpu().numpy()
-    assert np.abs(got - ref).max() <= tol and np.linalg.norm(got - ref) <= 5e-3 * np.linalg.norm(ref)
+    assert np.abs(got - ref).max() <= tol and np.linalg.norm(got - ref) <= 3.2e-3 * np.linalg.norm(ref)
     return entries
 
 
 @pytest.mark.parametrize("rows", [128, 96, 64])
 def test_references_that_move_and_values_that_are_not_finite(rows):
-    """Logits that outgrow their exponent reference late in the list; NaN, infinite and lowest keys and values, which
-    reach the rows that take them and no other."""
+    """Logits that outgrow their exponent reference late in the list; NaN, infinite and lowest keys and values: what the
+    four-wave kernels make of them, and nothing in chunks before the first."""
     B = np.arange(0, 73 * rows + 1, rows, dtype=np.int32)
     L = int(B[-1])
     q, k, v = tensors(L, "hld", rows)
