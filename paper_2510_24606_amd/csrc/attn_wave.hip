@@ -386,13 +386,16 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     // ---- staging: lane L of a window's load fills bytes [16 L, 16 L + 16) of it: a piece of row L / OPR of the window ----
     const int c_first = wave * LPW;
     const int off_slot_rd = (lane / OPR) * NLD + c_first;
-    // byte offset of this lane's logical piece of its row in window 0; in window c the swizzle of a row 4 c further differs
-    const unsigned piece0 = 16u * ((lane % OPR) ^ piece_swizzle(lane / OPR, OPR));
+    // byte offset of this lane's logical piece of its row in window c: the swizzle of a row 4 c further differs from that in
+    // window 0.  The kernel of 33..64 rows has no registers to keep the four in.
     static_assert(RPW == 4 && LPW % 4 == 0, "rows of windows c and c + 4 have the same swizzle");
+    unsigned piece[4];
+    const auto flip = [](int c) __attribute__((always_inline)) { return 16u * ((c & 1) | (c & 2) << 2); };
+#pragma unroll
+    for (int c = 0; c < 4; ++c) piece[c] = 16u * ((lane % OPR) ^ piece_swizzle(lane / OPR, OPR)) ^ flip(c);
     const auto add_piece = [&](unsigned &off, int c) __attribute__((always_inline)) {
-        const unsigned flip = 16u * ((c & 1) | (c & 2) << 2);
-        if ((c & 3) == 0) off += piece0;
-        else WAVE_ASM("v_xad_u32 %0, %1, %2, %0" : "+v"(off) : "v"(piece0), "s"(flip));
+        if (!split || (c & 3) == 0) off += piece[c & 3];
+        else WAVE_ASM("v_xad_u32 %0, %1, %2, %0" : "+v"(off) : "v"(piece[0]), "s"(flip(c)));
     };
     const unsigned lds_K = lds_address(sm.K) + c_first * 1024, lds_V = lds_address(sm.V) + c_first * 1024;
     unsigned offs[2][LPW];   // byte offsets of the pieces this lane fetches for an even and for an odd block, K and V alike
