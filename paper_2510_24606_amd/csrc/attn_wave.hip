@@ -22,7 +22,7 @@
 // of a product: scores are used two products after their last one, O by the vector unit at least eight after.
 //
 // 131072 tokens, 32 heads, 8192 keys: tiles of more than 64 rows 17.4 -> 15.9 ms, of 33..64 rows 6.0 -> 5.8 ms, the call
-// 24.3 -> 22.5 ms, with row blocks of 128 17.3 -> 16.4 ms.  The chip lowers its clock as the matrix units are busier (its
+// 24.7 -> 22.7 ms, with row blocks of 128 17.5 -> 16.3 ms.  The chip lowers its clock as the matrix units are busier (its
 // power limit), so time falls by less than the cycles do.
 #include "attn_mfma.h"
 
@@ -324,8 +324,8 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
     // Tiles of at most 64 rows, as attn_tile_16 has them: each half of a tile's keys has its own softmax state (reference,
     // sums, O), merged at the end; a row's sum is made in parts of 8 keys, 16 rows move their references together, and
     // P V takes the keys in the order of a 16x16x32 product (two 32x32x16 products, one after the other, give its bits).
-    // The states cost no time (prefill of 131072 tokens 21.6 ms of attention with one state and with two) and fill the
-    // accumulation registers, so all Q fragments live in vector registers.
+    // The states cost a third of a percent of a prefill of 131072 tokens (22.31 -> 22.37 ms) and fill the accumulation
+    // registers, so all Q fragments live in vector registers.
     constexpr bool split = RB == 2 && !pair;
     constexpr int NST = split ? 2 * RB : RB;    // softmax states: of row block r and key half hf: hf RB + r
     constexpr int NP = split ? 2 : 1;           // parts of a row's sum
