@@ -792,6 +792,13 @@ __global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, i
 // and a round is 1024 waves.  Hence heads of 128, lists of a thousand keys or more and so many tiles that the last ones
 // leave few SIMDs without work.  Both sides below are four waves -> lone waves, us of attention, 32 heads of the LLaMA shape:
 //   tiles of 33..64 rows: 4608 of them, 1024 keys 214 -> 208, 2048 344 -> 321, 8192 779 -> 701
+//   ... of dynamic chunks: twice as many tiles are in flight, and their walks drift apart (a partly taken chunk makes a tile's
+//     list a slow one), so the L2s serve less (131072 tokens, 16 heads, 8192 keys: 31 % against 53 %, row blocks of 64 64 % against
+//     55 %).  That costs time where lists are dense or K and V of the heads in flight exceed the 256 MB memory-side cache:
+//     16384 tokens, 2048 keys 863 -> 788; 32768, 4096 keys 3311 -> 3148; 51585, 3224 keys 4565 -> 4493, 6448 keys 8137 -> 8849;
+//     four kv-heads of 131072 tokens, 8192 keys 8666 -> 8372, eight: 2800 keys 6107 -> 5955, 3328 7024 -> 7121, 8192 14918 -> 18036;
+//     where taller tiles are more: eight kv-heads of 81920, 5120 keys 4681 -> 4513, of 65536, 8192 keys 5572 -> 5392, of
+//     131072, 4096 keys 6377 -> 6243, 8192 keys 12411 -> 12947 and 11111 -> 11222
 //   tiles of 65..96 rows alone: 3840, 1024 keys 251 -> 232, 4096 700 -> 615
 //   tiles of 97..128 rows alone, row blocks of 128: 3584, 1024 keys 281 -> 286, 1536 379 -> 375, 4096 814 -> 781;
 //     8192, 1024 keys 652 -> 657, 1536 899 -> 875
@@ -828,7 +835,14 @@ int attn_wave_classes(const Prob &p, const int32_t *T_cls) {
     else if (w0) w0 = keys >= 2048 && p.L >= 16 * keys && n[0] >= (left ? 16384 : 8192);
     else if (w1 && n[0] > 0) w1 = keys >= 4096 && n[1] * keys >= 4608 * 4096;
     else if (w1) w1 = !left || n[1] * keys >= 3072 * 1536;
-    return (w0 ? 1 : 0) | (w1 ? 2 : 0) | (enough(2, 4608) ? 4 : 0);
+    bool w2 = enough(2, 4608);
+    if (w2 && p.B_r == 0) {
+        const bool alone = n[2] > n[0] + n[1];
+        const double live = 4.0 * p.D * p.L * (p.H_kv < 8 ? p.H_kv : 8);   // bytes of K and V of the kv-heads in flight
+        if (live > (alone ? 288e6 : 384e6)) w2 = keys <= (alone ? 3072 : 4096);
+        else if (alone) w2 = keys <= 4096 || p.L >= 16 * keys;
+    }
+    return (w0 ? 1 : 0) | (w1 ? 2 : 0) | (w2 ? 4 : 0);
 }
 
 // T tiles from tile0 on for the kernel of class cls: 0: 65..128 rows, 1: 65..96, 2: at most 64 rows

@@ -235,6 +235,23 @@ def test_tall_classes_leave_the_four_wave_kernels_where_that_was_measured_faster
     assert ask((97,) * 2 + (80,) * 97, 4096) == [0, 0] and ask((97,) * 2 + (80,) * 144, 4096) == [0, 1]
 
 
+def test_short_tiles_leave_the_four_wave_kernels_where_that_was_measured_faster(lib):
+    def ask(lens, N_b, H_q, H_kv, B_r=0):
+        B = np.r_[0, np.cumsum(lens)].astype(np.int32)
+        return dhsa.dhsa_attention_kernels(mk(L=int(B[-1]), H_q=H_q, H_kv=H_kv, N_c=len(lens), N_b=N_b, B_r=B_r), B)[0][2]
+
+    assert [ask((48,) * n, 1024, 32, 8) for n in (143, 144)] == [0, 1] and ask((48,) * 144, 1023, 32, 8) == 0
+    # dynamic chunks of 33..64 rows: 51600 tokens by density, 131040 by what the kv-heads in flight hold
+    assert [ask((48,) * 1075, n, 32, 8) for n in (4096, 4097, 6448)] == [1, 0, 0]
+    assert [ask((48,) * 2730, n, 16, 8) for n in (3072, 3073, 8190)] == [1, 0, 0]
+    assert [ask((48,) * 2730, n, 8, 4) for n in (8190, 8191)] == [1, 0]
+    assert ask((48,) * 2730, 8192, 16, 8, B_r=64) == 1
+    # taller tiles beside them
+    assert [ask((48, 80) * 1024, n, 16, 8) for n in (4096, 4097)] == [1, 0]
+    assert [ask((48, 80) * n, 8192, 16, 8) for n in (732, 733)] == [1, 0]
+
+
+
 def test_mfma_probe_rejects_bad_arguments_on_the_host(lib):
     import ctypes as C
     tf = C.c_double(0.0)
