@@ -798,7 +798,8 @@ __global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, i
 //     16384 tokens, 2048 keys 863 -> 788; 32768, 4096 keys 3311 -> 3148; 51585, 3224 keys 4565 -> 4493, 6448 keys 8137 -> 8849;
 //     four kv-heads of 131072 tokens, 8192 keys 8666 -> 8372, eight: 2800 keys 6107 -> 5955, 3328 7024 -> 7121, 8192 14918 -> 18036;
 //     where taller tiles are more: eight kv-heads of 81920, 5120 keys 4681 -> 4513, of 65536, 8192 keys 5572 -> 5392, of
-//     131072, 4096 keys 6377 -> 6243, 8192 keys 12411 -> 12947 and 11111 -> 11222
+//     131072, 4096 keys 6377 -> 6243, 8192 keys 12411 -> 12947 with every other tile of them and, with every third,
+//     11111 -> 11222, 32 heads 22233 -> 22615 on random keys, 22757 -> 22449 with needles among them, every fifth 14230 -> 14068
 //   tiles of 65..96 rows alone: 3840, 1024 keys 251 -> 232, 4096 700 -> 615
 //   tiles of 97..128 rows alone, row blocks of 128: 3584, 1024 keys 281 -> 286, 1536 379 -> 375, 4096 814 -> 781;
 //     8192, 1024 keys 652 -> 657, 1536 899 -> 875
@@ -839,7 +840,8 @@ int attn_wave_classes(const Prob &p, const int32_t *T_cls) {
     if (w2 && p.B_r == 0) {
         const bool alone = n[2] > n[0] + n[1];
         const double live = 4.0 * p.D * p.L * (p.H_kv < 8 ? p.H_kv : 8);   // bytes of K and V of the kv-heads in flight
-        if (live > (alone ? 288e6 : 384e6)) w2 = keys <= (alone ? 3072 : 4096);
+        const bool few_of_all = 5 * n[2] <= 2 * (n[0] + n[1] + n[2]);
+        if (live > (alone ? 288e6 : 384e6)) w2 = keys <= (alone ? 3072 : 4096) || few_of_all;
         else if (alone) w2 = keys <= 4096 || p.L >= 16 * keys;
     }
     return (w0 ? 1 : 0) | (w1 ? 2 : 0) | (w2 ? 4 : 0);

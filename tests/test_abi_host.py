@@ -249,6 +249,7 @@ def test_short_tiles_leave_the_four_wave_kernels_where_that_was_measured_faster(
     # taller tiles beside them
     assert [ask((48, 80) * 1024, n, 16, 8) for n in (4096, 4097)] == [1, 0]
     assert [ask((48, 80) * n, 8192, 16, 8) for n in (732, 733)] == [1, 0]
+    assert ask((48, 80) * 600 + (112,) * 300, 8192, 16, 8) == 1 and ask((48, 80) * 600 + (112,) * 299, 8192, 16, 8) == 0
 
 
 
