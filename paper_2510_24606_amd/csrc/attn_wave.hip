@@ -212,12 +212,7 @@ struct WaveKeys {
                 n = vis < n ? (vis > 0 ? vis : 0) : n;
             }
         }
-        int inc = n;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int x = __shfl_up(inc, off);
-            if (lane >= off) inc += x;
-        }
+        const int inc = wave_incl_scan(n);
         const unsigned long long keep = __ballot(n > 0);
         const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(keep >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)keep, 0));
         const int to = 4 * (n > 0 ? below : __popcll(keep) + lane - below);   // segments without keys go behind the others

@@ -320,12 +320,7 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
             if (r0 + 32 > L - 1) kb[e] = r0 < L - 1 ? kb[e] & ((1u << (unsigned)(L - 1 - r0)) - 1u) : 0u;
             mine += __popc(kb[e]);
         }
-        int inc = mine;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int t = __shfl_up(inc, off);
-            if (lane >= off) inc += t;
-        }
+        const int inc = wave_incl_scan(mine);
         __syncthreads();
         if (lane == 63) s_cnt[wave] = inc;
         __syncthreads();

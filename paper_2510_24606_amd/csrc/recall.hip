@@ -217,12 +217,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
         int local = 0;
         if (tid * per < bins)
             for (int e = 0; e < per; ++e) local += s_hist[bins - 1 - tid * per - e];
-        int inc = local;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int x = __shfl_up(inc, off);
-            if (lane >= off) inc += x;
-        }
+        const int inc = wave_incl_scan(local);
         if (lane == 63) s_wave[wave] = inc;
         __syncthreads();
         int gt = inc - local;                            // keys of the region with a larger digit

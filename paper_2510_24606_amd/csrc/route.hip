@@ -437,23 +437,11 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Lane-crossing sums and extrema of a wave on the vector unit (DPP: shifts inside rows of 16 lanes, then
-// the last lane of a row or half to the ones above it); lane 63 ends up with all 64 lanes.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
-}
-#define DHSA_DPP_STEPS(STEP) STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf) STEP(0x142, 0xa) STEP(0x143, 0xc)
+// Wider sums and extrema with the steps of wave_incl_scan.
 __device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long x) {
 #define DHSA_STEP(CTRL, ROWS)                                                               \
     x += ((unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)(x >> 32)) << 32) | \
          (unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)x);
-    DHSA_DPP_STEPS(DHSA_STEP)
-#undef DHSA_STEP
-    return x;
-}
-__device__ __forceinline__ int wave_incl_scan(int x) {
-#define DHSA_STEP(CTRL, ROWS) x += dpp_or<CTRL, ROWS>(0, x);
     DHSA_DPP_STEPS(DHSA_STEP)
 #undef DHSA_STEP
     return x;
