@@ -216,6 +216,8 @@ __device__ __forceinline__ void merge_slices(const float *part, int S, float *s_
     }
 }
 
+constexpr int kDecOwn = 8;   // keys of a chunk that a thread writes into the list of its slice by itself
+
 template <typename T, int D, bool FUSE>
 __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__ B, const int32_t *__restrict__ count,
                                                      const int32_t *__restrict__ entries, int stride, int rb0, int L,
@@ -230,6 +232,8 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
     constexpr int NG = 256 / TPR;              // key rows per batch
     constexpr int U = 4;                       // batches in flight
     __shared__ int s_keys[kDecSliceMax];
+    __shared__ int4 s_seg[kDecSliceMax / (kDecOwn + 1) + 1];   // long pieces of chunks: first and last position in the slice, key - position
+    __shared__ int s_nseg;
     __shared__ int s_wave[4];
     __shared__ float s_m[NG], s_l[NG];
     __shared__ float s_o[NG][D];
@@ -247,8 +251,7 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
     const uint4 q16 = *reinterpret_cast<const uint4 *>(Q + (int64_t)h * qs_h + (int64_t)i * qs_l + r * EPT);
     const int x_lo = s * slice, x_hi = x_lo + slice;
 
-    for (int x = tid; x < slice; x += 256) s_keys[x] = -1;
-    __syncthreads();
+    if (tid == 0) s_nseg = 0;   // (the scan has barriers)
     int base = 0;   // selected keys of the entries walked so far (block-uniform)
     for (int e0 = 0; e0 < E; e0 += 256) {
         if (e0 > 0) {
@@ -269,16 +272,28 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
         const int start = base + block_excl_scan(take, s_wave, &total);
         const int lo = start > x_lo ? start : x_lo;
         const int hi = start + take < x_hi ? start + take : x_hi;
-        for (int x = lo; x < hi; ++x) s_keys[x - x_lo] = b0 + (x - start);
+        // a thread writes few keys by itself; a long piece (a slice holds a handful of them) is written by a wave
+        if (hi - lo <= kDecOwn) {
+            for (int x = lo; x < hi; ++x) s_keys[x - x_lo] = b0 + (x - start);
+        } else {
+            s_seg[atomicAdd(&s_nseg, 1)] = make_int4(lo - x_lo, hi - x_lo, b0 - start + x_lo, 0);
+        }
+        __syncthreads();
+        for (int sg = tid >> 6, n_seg = s_nseg; sg < n_seg; sg += 4) {
+            const int4 w = s_seg[sg];
+            for (int x = w.x + (tid & 63); x < w.y; x += 64) s_keys[x] = x + w.z;
+        }
         base += total;
         if (base >= x_hi && s != 0) break;   // slice 0 walks on: it reports the row's key count
+        __syncthreads();
+        if (tid == 0) s_nseg = 0;
     }
     __syncthreads();
     if (s == 0 && tid == 0 && cnt) cnt[h] = base;
     int n_mine = base - x_lo;
     n_mine = n_mine < 0 ? 0 : (n_mine > slice ? slice : n_mine);
     if (idx)
-        for (int x = tid; x < slice && x_lo + x < cap; x += 256) idx[(int64_t)h * cap + x_lo + x] = s_keys[x];
+        for (int x = tid; x < slice && x_lo + x < cap; x += 256) idx[(int64_t)h * cap + x_lo + x] = x < n_mine ? s_keys[x] : -1;
 
     float q[EPT];
     DecIO<T>::unpack(q16, q);

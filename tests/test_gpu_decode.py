@@ -28,6 +28,11 @@ CASES = [
     ("c3", dict(L=8192, H_q=8, H_kv=2, N_b=512), 128),                   # Alg. 1 row blocks
     ("c1", dict(L=1000, N_b=100), 48),                                   # row blocks, fp32, ragged open block
     ("c2", dict(L=5000, H_q=6, H_kv=3, N_b=1), 0),                       # a budget of one key
+    # pieces of chunks in a slice's key list: of as many keys as a thread writes by itself, one more, a wave's and one more
+    ("c2", dict(L=4001, H_q=8, H_kv=2, N_b=700, lens=("fixed", 8)), 0),
+    ("c2", dict(L=4001, H_q=8, H_kv=2, N_b=1501, lens=("fixed", 9)), 0),
+    ("c1", dict(L=4001, D=128, N_b=999, lens=("fixed", 64)), 0),
+    ("c3", dict(L=9001, H_q=32, H_kv=4, N_b=8000, lens=("fixed", 65)), 0),
 ]
 
 
