@@ -38,28 +38,28 @@ __device__ __forceinline__ void load16_to_lds(const char *base, unsigned byte_of
 // reuse of the K/V slabs), smaller values keep fewer K/V slabs live at once
 // (they then fit the memory-side cache).  Within a kv-head the query heads of
 // the group are innermost; *tile is the tile's position in the order of issue
-// (0 = first), which the kernel maps to a row tile.  act = 0: plain order.
-__device__ __forceinline__ void decode_block(int act, int b, int H_q, int G, int T1, int *h, int *tile) {
-    if (act > 0) {
-        const int per = act * G * T1;          // workgroups per set of `act` kv-heads
-        const int p = b / per, r = b % per;
-        const int x = r & 7;
-        const int kv = p * act + (x & (act - 1));
-        const int idx = (r >> 3) * (8 / act) + x / act;
-        *tile = idx / G;
-        *h = kv * G + idx % G;
-        return;
-    }
-    *tile = b / H_q;
-    *h = b % H_q;
+// (0 = first), which the kernel maps to a row tile.  False: a block that only
+// makes the share of every XCD equal, without a tile.
+__device__ __forceinline__ bool decode_block(int act, int b, int G, int T, int *h, int *tile) {
+    const int per = 8 * ((act * G * T + 7) / 8);   // workgroups per set of `act` kv-heads
+    const int p = b / per, r = b % per;
+    const int x = r & 7;
+    const int kv = p * act + (x & (act - 1));
+    const int idx = (r >> 3) * (8 / act) + x / act;
+    *tile = idx / G;
+    *h = kv * G + idx % G;
+    return *tile < T;
 }
 
-// act must divide H_kv and act * G * T1 must be a multiple of 8 for the mapping above
-inline int attn_order(int want, int H_kv, int G, int T1) {
-    for (int act = want; act >= 1; act >>= 1)
-        if (H_kv % act == 0 && (act * G * T1) % 8 == 0) return act;
-    return 0;
+// kv-heads at a time (at most `want`), and the blocks of a launch of T tiles a head.  The share of an XCD is rounded up:
+// an odd number of tiles of four kv-heads with seven query heads each is no multiple of 8 workgroups, and such a launch,
+// dealt out in plain order, has every XCD walk all kv-heads: 65536 tokens, 8192 keys 10207 -> 8778 us a call.
+inline int attn_order(int want, int H_kv) {
+    int act = want;
+    while (H_kv % act != 0) act >>= 1;
+    return act;
 }
+inline int attn_grid(int act, int H_kv, int G, int T) { return H_kv / act * (8 * ((act * G * T + 7) / 8)); }
 
 // Everything the tile bodies need beside the plan (kernel arguments, passed on by reference).
 struct AttnArgs {
@@ -86,6 +86,6 @@ AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls);
 
 // attn_wave.hip: the height classes of the tile table that its kernels take, and T tiles of one from tile0 on
 int attn_wave_classes(const Prob &p, const int32_t *T_cls);
-hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int want, int cls, int tile0, int T, hipStream_t s);
+hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int act, int cls, int tile0, int T, hipStream_t s);
 
 }  // namespace dhsa
