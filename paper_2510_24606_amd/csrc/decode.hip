@@ -10,7 +10,8 @@
 //   k_pool_decode     pooled keys (Eq. 4) of the chunks not pooled by an earlier
 //                     step, pooled queries of the open group;
 //   k_scores_decode   that group's scores against every key chunk (fp64 MFMA, heads of a kv-group as rows);
-//   (the ranking and the walk are k_select of route.hip, launched for one group)
+//   (the ranking and the walk are k_select of route.hip, launched for one group; with few chunks all of the routing
+//   is k_route_decode of that file)
 //   k_attn_decode     the selected keys are split into slices; one workgroup
 //                     per (slice, head) streams its K and V rows once, 16 bytes per
 //                     lane, several rows in flight, and keeps an online-softmax
@@ -386,6 +387,8 @@ hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_ca
     double *Sc = reinterpret_cast<double *>(w8 + dl.off_Sc);
     int32_t *plan = reinterpret_cast<int32_t *>(w8 + dl.off_plan);
     int32_t *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
+    if (route_decode_ok(p, dl.pl, rb0, tail))
+        return launch_route_decode(p, dl.pl, N_c_cap, kc_valid, rb0, tail, Q, K, Kc, plan, done, s);
     const int n_new = p.N_c - kc_valid;
     dim3 grid(n_new > 1 ? n_new : 1, p.H_kv + p.H_q), block(256);
 #define DHSA_POOLD(T, DD)                                                                                      \

@@ -117,6 +117,10 @@ hipError_t launch_setup_pool(const Prob &p, const PlanLayout &pl, const void *Q,
 hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, const int32_t *B_dev,
                          const int32_t *RB_dev, double *Sc, hipStream_t s);
 hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, hipStream_t s);
+// the two in one launch, for problems that score_select_ok takes
+bool score_select_ok(const Prob &p, const PlanLayout &pl);
+hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double *Qc, const double *Kc, double *Sc, int32_t *plan,
+                               hipStream_t s);
 // query groups [l_first, l_first + n_groups) only; `pl`, `Sc` and `plan` are indexed by group - l_first
 hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, int l_first,
                                 int n_groups, hipStream_t s);
@@ -125,6 +129,10 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
 // rb0 = first row of the open query group; the boundaries are already in the step's plan
 hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0,
                                const BoundaryTail &tail, const void *Q, const void *K, void *ws, hipStream_t s);
+// ... all of it in one launch, for steps that route_decode_ok takes
+bool route_decode_ok(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail);
+hipError_t launch_route_decode(const Prob &p, const PlanLayout &pl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
+                               const void *Q, const void *K, double *Kc, int32_t *plan, int32_t *done, hipStream_t s);
 hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, const void *Q, const void *K,
                                 const void *V, void *ws, void *O_row, int32_t *idx, int32_t *cnt, hipStream_t s);
 hipError_t launch_expand(const Prob &p, const PlanView &pv, int head, const int64_t *rows_dev, int n_rows,

@@ -486,33 +486,24 @@ static int select_row_bytes(int NW, int cap, int N_c) {   // cap: a multiple of 
     return kSelBins * (NW == 1 ? 8 : 16) + cap * 20 + (N_c + 63) / 64 * 8;
 }
 
-template <int NW>
-__global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, int32_t *__restrict__ plan,
-                                                PlanLayout pl, int N_c, int N_b, int B_r, int l_first, int n_groups,
-                                                int r_first, int n_rows, int cap, int row_bytes) {
-    constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ unsigned long long s_red[NW];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
-    const int r = r_first + (int)(NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x);
-    if (r >= n_rows) return;             // NW == 1: waves do not wait for each other
-    const auto sync = [] { if constexpr (NW == 1) wave_lds_fence(); else __syncthreads(); };
-    unsigned char *mine8 = smem + (size_t)(NW == 1 ? wave : 0) * row_bytes;
-    unsigned long long *hist = reinterpret_cast<unsigned long long *>(mine8);              // [kSelBins]
-    unsigned long long *place = NW == 1 ? hist : hist + kSelBins;                          // [kSelBins] (one wave: in place)
-    unsigned long long *ckey = place + kSelBins;                                           // [cap]
-    unsigned long long *kept = ckey + cap;                                                 // [ceil(N_c / 64)]
-    int *cid = reinterpret_cast<int *>(kept + ((N_c + 63) >> 6));                          // [cap]  id | pos << kPosShift
-    int *clen = cid + cap, *crem = clen + cap;                                             // [cap]
-    const int32_t *B = plan + pl.off_B;
-    const bool blocks = B_r > 0;
-    // l indexes Sc, RB and the plan; the group's number in the sequence is l_first + l (a launch
-    // may cover a suffix of the groups, laid out from 0)
-    const int h = r / n_groups, l = r % n_groups;
-    const int q_max = blocks ? (plan + pl.off_RB)[l + 1] : 0x7fffffff;   // clip of the chunk lengths
-    const int own = blocks ? -1 : l_first + l;                           // the query group's own chunk
-    int n = own + 1;                                                     // visible chunks 0..n-1
+struct SelectArgs {
+    int32_t *plan;
+    PlanLayout pl;
+    int N_c, N_b, B_r;
+    int l_first, n_groups;   // the groups of the launch, laid out from 0: l indexes Sc, RB and the plan, l_first + l is the group's number
+    int r_first, n_rows, cap, row_bytes;
+};
+
+// The chunks a query group ranks: own = the group's own chunk, q_max = the clip of the chunk lengths, n = visible chunks 0..n-1
+struct Visible {
+    int own, q_max, n;
+};
+__device__ __forceinline__ Visible visible_chunks(const SelectArgs &a, const int32_t *B, int l) {
+    const int lane = threadIdx.x & 63, N_c = a.N_c;
+    const bool blocks = a.B_r > 0;
+    const int q_max = blocks ? (a.plan + a.pl.off_RB)[l + 1] : 0x7fffffff;
+    const int own = blocks ? -1 : a.l_first + l;
+    int n = own + 1;
     if (blocks) {                        // the chunks that start before q_max: B ascends, 64-ary search
         int step = (N_c + 63) >> 6;
         n = (__popcll(__ballot(lane * step < N_c && B[lane * step < N_c ? lane * step : 0] < q_max)) - 1) * step;   // B[0] = 0 < q_max
@@ -523,7 +514,31 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
         }
         n = __builtin_amdgcn_readfirstlane(n + got);
     }
-    const double *row = Sc + ((int64_t)h * pl.N_q + l) * N_c;
+    return {own, q_max, n};
+}
+
+// Ranks the scores row[0 .. vis.n) of group l of head h; mine8: row_bytes of LDS, s_red: NW words of it.  row and B in
+// memory or LDS.
+template <int NW>
+__device__ __forceinline__ void select_row(const SelectArgs &a, const double *row, const int32_t *B, const Visible vis,
+                                           const int h, const int l, unsigned char *mine8, unsigned long long *s_red) {
+    constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
+    const int N_c = a.N_c, N_b = a.N_b, cap = a.cap;
+    int32_t *const plan = a.plan;
+    const PlanLayout &pl = a.pl;
+    const auto sync = [] { if constexpr (NW == 1) wave_lds_fence(); else __syncthreads(); };
+    unsigned long long *hist = reinterpret_cast<unsigned long long *>(mine8);              // [kSelBins]
+    unsigned long long *place = NW == 1 ? hist : hist + kSelBins;                          // [kSelBins] (one wave: in place)
+    unsigned long long *ckey = place + kSelBins;                                           // [cap]
+    unsigned long long *kept = ckey + cap;                                                 // [ceil(N_c / 64)]
+    int *cid = reinterpret_cast<int *>(kept + ((N_c + 63) >> 6));                          // [cap]  id | pos << kPosShift
+    int *clen = cid + cap, *crem = clen + cap;                                             // [cap]
+    const bool blocks = a.B_r > 0;
+    const int own = vis.own, q_max = vis.q_max, n = vis.n;
+    // (an unsigned offset: a 64-bit address per lane that lives through the rare passes has no registers)
+    const auto score_at = [&](int x) { return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(row) + 8u * (unsigned)x); };
     const auto len_at = [&](int x) {
         const int b0 = B[x], b1 = B[x + 1];
         return x == own ? 0 : (b1 < q_max ? b1 : q_max) - b0;
@@ -536,7 +551,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
         for (int e = 0; e < PER; ++e)
             if (x0 + e * NT < n) {
                 const int x = x0 + e * NT + t < n ? x0 + e * NT + t : n - 1;
-                v[e] = row[x];
+                v[e] = score_at(x);
                 len[e] = len_at(x);
             }
     };
@@ -560,7 +575,7 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     _Pragma("unroll 1") for (int x0_ = 0; x0_ < n; x0_ += NT) {                              \
         const int x = x0_ + t;                                                               \
         const bool in = x < n;                                                               \
-        const double s = row[in ? x : n - 1];                                                \
+        const double s = score_at(in ? x : n - 1);                                                \
         const int n_tok = len_at(in ? x : n - 1);                                            \
         __VA_ARGS__                                                                          \
     }
@@ -876,6 +891,147 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     if (t == 0) plan[pl.off_count + (int64_t)h * pl.N_q + l] = total < pl.stride ? total : pl.stride;
 }
 
+template <int NW>
+__global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, SelectArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned long long s_red[NW];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = a.r_first + (int)(NW == 1 ? blockIdx.x * (blockDim.x >> 6) + wave : blockIdx.x);
+    if (r >= a.n_rows) return;           // NW == 1: waves do not wait for each other
+    const int h = r / a.n_groups, l = r % a.n_groups;
+    const int32_t *B = a.plan + a.pl.off_B;
+    select_row<NW>(a, Sc + ((int64_t)h * a.pl.N_q + l) * a.N_c, B, visible_chunks(a, B, l), h, l,
+                   smem + (size_t)(NW == 1 ? wave : 0) * a.row_bytes, s_red);
+}
+
+// ---------------------------------------------------------------------------
+// Scores of one query group against the chunks 0 .. n-1 by the NW waves of a workgroup: a wave takes 16 chunks at a time, as
+// columns, and repeats the group's vector as all 16 rows, so that a score is made of the same products in the same
+// order as in k_scores.  key(k): the pooled vector of chunk k.
+// ---------------------------------------------------------------------------
+template <int D, int NW, typename KEY>
+__device__ __forceinline__ void score_row(const double *q_c, const KEY &key, int n, double *s_row) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16 = lane & 15, q = lane >> 4;
+    f64x2 a[D / 8], b[2][D / 8];
+    const auto load = [&](int k0, f64x2 (&to)[D / 8]) {
+        const double *Bm = key(k0 + n16 < n ? k0 + n16 : n - 1) + 2 * q;
+#pragma unroll
+        for (int s = 0; s < D / 8; ++s) to[s] = *reinterpret_cast<const f64x2 *>(Bm + 8 * s);
+    };
+    const auto block = [&](int k0, const f64x2 (&b_)[D / 8]) {
+        f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < D / 8; ++s)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][j], b_[s][j], acc, 0, 0, 0);
+        if (q == 0 && k0 + n16 < n) s_row[k0 + n16] = acc[0];
+    };
+    int k0 = wave * 16;
+    if (k0 >= n) return;
+    load(k0, b[0]);
+#pragma unroll
+    for (int s = 0; s < D / 8; ++s) a[s] = *reinterpret_cast<const f64x2 *>(q_c + 2 * q + 8 * s);
+    __builtin_amdgcn_sched_barrier(0);
+    for (;; k0 += 32 * NW) {             // the next 16 chunks are requested before these are multiplied
+        if (k0 + 16 * NW < n) load(k0 + 16 * NW, b[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        block(k0, b[0]);
+        if (k0 + 16 * NW >= n) break;
+        if (k0 + 32 * NW < n) load(k0 + 32 * NW, b[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        block(k0 + 16 * NW, b[1]);
+        if (k0 + 32 * NW >= n) break;
+    }
+}
+
+// Scores and ranking of one (head, query group) by a workgroup of four waves, for problems of few groups and few chunks,
+// where a launch takes longer than the scores of a group.  Bound by a chain: one memory latency, 32 products in a row, the ranking.
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_score_select(const double *__restrict__ Qc, const double *__restrict__ Kc,
+                                                         double *__restrict__ Sc, int G, SelectArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned long long s_red[4];
+    const int h = blockIdx.x / a.n_groups, l = blockIdx.x % a.n_groups;
+    const int32_t *B = a.plan + a.pl.off_B;
+    const Visible vis = visible_chunks(a, B, l);
+    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
+    const double *K = Kc + (int64_t)(h / G) * a.N_c * D;
+    score_row<D, 4>(Qc + ((int64_t)h * a.pl.N_q + l) * D, [&](int k) { return K + (int64_t)k * D; }, vis.n, s_row);
+    __syncthreads();
+    double *row = Sc + ((int64_t)h * a.pl.N_q + l) * a.N_c;
+    for (int x = threadIdx.x; x < vis.n; x += 256) row[x] = s_row[x];
+    select_row<4>(a, s_row, B, vis, h, l, smem, s_red);
+}
+
+// ---------------------------------------------------------------------------
+// Routing of one decoding step, all of it, by one workgroup of eight waves per query head: the open group's queries and the
+// new key chunks are pooled (the first four waves and the others side by side, in k_pool_decode's order), then scored and
+// ranked.  The heads of a kv-group pool the same key chunks; the first of them stores them for later steps.  Boundaries and
+// pooled keys that come with the step are taken from LDS, the others from the workspace.
+// ---------------------------------------------------------------------------
+constexpr int kRouteDecodeNew = 3;   // key chunks to pool: with the group's queries two rounds of the workgroup's halves
+
+template <typename T, int D>
+__global__ __launch_bounds__(512, 2) void k_route_decode(const T *__restrict__ Q, const T *__restrict__ K, BoundaryTail tail,
+                                                         int32_t *__restrict__ done, double *__restrict__ Kc, SelectArgs a,
+                                                         int H_kv, int G, int N_c_cap, int kc_valid, int rb0, int L,
+                                                         int pooling, int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l) {
+    constexpr int EPT = Elem<T>::kPer16, TPR = D / EPT, RG = 256 / TPR;   // as in k_pool_decode
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double s_sum[2][RG][D];
+    __shared__ double s_pool[1 + kRouteDecodeNew][D];       // the queries, then the new chunks
+    __shared__ unsigned long long s_red[8];
+    const int h = blockIdx.x, g = h / G, tid = threadIdx.x, half = __builtin_amdgcn_readfirstlane(tid >> 8), th = tid & 255;
+    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
+    int32_t *s_B = reinterpret_cast<int32_t *>(s_row + a.N_c);
+    int32_t *B = a.plan + a.pl.off_B, *RBw = a.plan + a.pl.off_RB;
+    for (int k = tid; k < kc_valid; k += 512) s_B[k] = B[k];
+    if (tid <= tail.n) s_B[kc_valid + tid] = tail.b[tid];
+    if (tid == 0) done[h] = 0;                              // slices of the head finished so far (k_attn_decode)
+    if (h == 0) {                                           // for the kernels after this one
+        if (tid <= tail.n) B[kc_valid + tid] = tail.b[tid];
+        if (tid == 0) { RBw[0] = rb0; RBw[1] = L; }
+    }
+    const int rg = th / TPR, col = (th % TPR) * EPT;
+    for (int x0 = 0; x0 <= tail.n; x0 += 2) {
+        const int x = x0 + half;
+        const bool is_q = x == 0;
+        const T *X = is_q ? Q + (int64_t)h * qs_h : K + (int64_t)g * ks_h;
+        const int64_t s_l = is_q ? qs_l : ks_l;
+        int b0 = rb0, b1 = L;
+        if (!is_q) { b0 = x <= tail.n ? tail.b[x - 1] : 0; b1 = x <= tail.n ? tail.b[x] : 0; }
+        double acc[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) acc[e] = 0.0;
+        for (int i = b0 + rg; i < b1; i += RG) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(X + (int64_t)i * s_l + col);
+            Elem<T>::unpack(u, acc);
+        }
+        if (x0 > 0) __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) s_sum[half][rg][col + e] = acc[e];
+        __syncthreads();
+        if (th < D && x <= tail.n) {
+            double sum = 0.0;
+#pragma unroll 4
+            for (int r = 0; r < RG; ++r) sum += s_sum[half][r][th];
+            const double len = (double)(b1 - b0);
+            const double pooled = pooling == DHSA_POOL_MEAN ? sum / len                        // plain average (ablation)
+                                  : (is_q && a.B_r > 0)    ? sqrt((double)a.B_r) * (sum / len)  // Alg. 1 row blocks
+                                                           : (sqrt(len) / len) * sum;           // Eq. 4
+            s_pool[x][th] = pooled;
+            if (!is_q && h == g * G) Kc[((int64_t)g * N_c_cap + kc_valid + x - 1) * D + th] = pooled;
+        }
+    }
+    __syncthreads();
+    const double *Kg = Kc + (int64_t)g * N_c_cap * D;
+    score_row<D, 8>(s_pool[0], [&](int k) { return k < kc_valid ? Kg + (int64_t)k * D : s_pool[1 + k - kc_valid]; }, a.N_c, s_row);
+    __syncthreads();
+    const Visible vis = {a.B_r > 0 ? -1 : a.N_c - 1, L, a.N_c};   // the last group sees all chunks
+    select_row<8>(a, s_row, s_B, vis, h, 0, smem, s_red);
+}
+
 // ---------------------------------------------------------------------------
 // The same for groups that can list more than kSelMaxStride chunks (many chunks of a few tokens): one
 // workgroup per (head, query group) sorts the whole row in LDS.
@@ -1005,6 +1161,52 @@ hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, 
     return launch_select_groups(p, pl, Sc, plan, 0, p.N_q, s);
 }
 
+// A launch (and its scores' way through memory) costs more than scoring every group by itself while a workgroup's four waves
+// score all chunks in one go; from then on fifteen of sixteen rows of each product are what it pays for.  Routing in us,
+// two launches -> one: 8 heads of 25 chunks 13.3 -> 10.4, of 60 chunks 15.2 -> 13.8 (row blocks 15.5 -> 13.1), 4 heads of 100
+// chunks 15.2 -> 15.3, of 127 chunks 15.5 -> 18.9.  prefill of 1021 tokens 24.5 -> 21.8, of 2048 tokens in fp32 29.8 -> 27.4.
+constexpr int kScoreSelectMax = 64;
+bool score_select_ok(const Prob &p, const PlanLayout &pl) {
+    return (int64_t)p.H_q * p.N_q < 512 && p.N_c <= kScoreSelectMax && pl.stride <= kSelMaxStride;
+}
+
+hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double *Qc, const double *Kc, double *Sc, int32_t *plan,
+                               hipStream_t s) {
+    const int cap = select_cap(pl.stride), n_rows = p.H_q * p.N_q, row_bytes = (select_row_bytes(4, cap, p.N_c) + 15) / 16 * 16;
+    const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, n_rows, cap, row_bytes};
+    const size_t shmem = row_bytes + 8 * (size_t)p.N_c;
+    if (p.D == 64) hipLaunchKernelGGL(k_score_select<64>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
+    else hipLaunchKernelGGL(k_score_select<128>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
+    return hipGetLastError();
+}
+
+// One launch instead of three while scoring all chunks by eight waves and pooling side by side take no longer than a launch.
+// A step in us, apart -> joined: 8 heads of 38 chunks 18.9 -> 16.2, with two chunks to pool 19.3 -> 18.0, 100 chunks 19.4 -> 17.8
+// and 19.8 -> 19.5, 128 chunks 19.4 -> 18.5 and 19.7 -> 20.2, 200 chunks 19.6 -> 21.6; 32 heads of 128 chunks 20.0 -> 18.9.
+// Long chunks, pooled by every head, would make the pooling the longest part.
+bool route_decode_ok(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail) {
+    int64_t longest = p.L - rb0;
+    for (int j = 0; j < tail.n; ++j) longest = std::max<int64_t>(longest, tail.b[j + 1] - tail.b[j]);
+    return tail.n > 0 && tail.n <= kRouteDecodeNew && p.N_c * tail.n <= 128 && longest <= 512 && pl.stride <= kSelMaxStride;
+}
+
+hipError_t launch_route_decode(const Prob &p, const PlanLayout &pl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
+                               const void *Q, const void *K, double *Kc, int32_t *plan, int32_t *done, hipStream_t s) {
+    const int cap = select_cap(pl.stride), row_bytes = (select_row_bytes(8, cap, p.N_c) + 15) / 16 * 16;
+    const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, p.N_q - 1, 1, 0, p.H_q, cap, row_bytes};
+    const size_t shmem = row_bytes + 8 * (size_t)p.N_c + 4 * (size_t)(p.N_c + 1);
+#define DHSA_ROUTED(T, DD)                                                                                              \
+    hipLaunchKernelGGL((k_route_decode<T, DD>), dim3(p.H_q), dim3(512), shmem, s, (const T *)Q, (const T *)K, tail, done, Kc, a, \
+                       p.H_kv, p.G, N_c_cap, kc_valid, rb0, (int)p.L, p.pooling, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
+    if (p.dtype == DHSA_F32) {
+        if (p.D == 64) DHSA_ROUTED(float, 64); else DHSA_ROUTED(float, 128);
+    } else {
+        if (p.D == 64) DHSA_ROUTED(bf16_t, 64); else DHSA_ROUTED(bf16_t, 128);
+    }
+#undef DHSA_ROUTED
+    return hipGetLastError();
+}
+
 hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, int l_first,
                                 int n_groups, hipStream_t s) {
     const int n_rows = n_groups * p.H_q;
@@ -1039,8 +1241,8 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
         }                                                                                                          \
         for (int64_t r0 = 0; r0 < n_rows; r0 += (int64_t)kGridMax * per) {                                         \
             const dim3 grid((unsigned)std::min<int64_t>(kGridMax, (n_rows - r0 + per - 1) / per));                 \
-            hipLaunchKernelGGL(k_select<NW>, grid, block, shmem, s, Sc, plan, pl, p.N_c, p.N_b, p.B_r, l_first,    \
-                               n_groups, (int)r0, n_rows, cap, row_bytes);                                         \
+            const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, l_first, n_groups, (int)r0, n_rows, cap, row_bytes}; \
+            hipLaunchKernelGGL(k_select<NW>, grid, block, shmem, s, Sc, a);                                        \
             const hipError_t e = hipGetLastError();                                                                \
             if (e != hipSuccess) return e;                                                                         \
         }                                                                                                          \

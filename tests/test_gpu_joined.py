@@ -1,0 +1,72 @@
+"""Routing whose launches are joined because a problem is small (k_score_select, k_route_decode), against the same routing by
+the launches of larger problems: scores, plans and outputs are the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_24606_amd as dhsa
+
+pytestmark = pytest.mark.gpu
+DTYPES = {"bf16": torch.bfloat16, "f32": torch.float32}
+
+
+def tensors(H_q, H_kv, L, D, dtype, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randn((H, L, D), dtype=DTYPES[dtype], device="cuda", generator=gen) for H in (H_q, H_kv, H_kv)]
+
+
+def boundaries(N_c, longest, seed):
+    return np.concatenate([[0], np.cumsum(np.random.default_rng(seed).integers(1, longest + 1, N_c))]).astype(np.int32)
+
+
+@pytest.mark.parametrize("N_c,D,dtype,B_r,pooling", [
+    (1, 128, "bf16", 0, 0), (2, 64, "f32", 0, 0), (15, 128, "f32", 0, 1), (16, 64, "bf16", 0, 0), (17, 128, "bf16", 7, 0),
+    (33, 128, "bf16", 0, 0), (48, 64, "f32", 32, 1), (63, 128, "bf16", 100, 0), (64, 128, "f32", 0, 0), (64, 64, "bf16", 0, 0),
+    (65, 128, "bf16", 0, 0)])
+def test_few_groups_get_the_scores_and_plans_of_many(N_c, D, dtype, B_r, pooling):
+    B = boundaries(N_c, 20, N_c)
+    L = int(B[-1])
+    q, k, _ = tensors(2, 1, L, D, dtype, N_c)
+    N_b = max(1, L // 5)
+
+    def route(q, k):
+        prob = dhsa.problem(q, k, B, N_b, B_r=B_r, pooling=pooling)
+        plan, ws = dhsa.alloc(prob, B)
+        ws.fill_(255)
+        dhsa.dhsa_route(prob, q, k, B, plan, ws)
+        return dhsa.parse_plan(plan.cpu().numpy()), dhsa.dhsa_debug_scores(prob, B, ws)
+
+    few, s_few = route(q, k)
+    N_q = s_few.shape[1]
+    times = -(-512 // (2 * N_q))                      # as many heads as 512 groups take
+    many, s_many = route(q.repeat(times, 1, 1), k.repeat(times, 1, 1))
+    ends = np.minimum((np.arange(N_q) + 1) * B_r, L) if B_r else B[1:]
+    seen = torch.from_numpy(B[None, :-1] < ends[:, None]).cuda()
+    for h in range(2):
+        assert torch.equal(s_few[h][seen], s_many[h][seen]) and bool(torch.isfinite(s_few[h][seen]).all())
+        assert np.array_equal(few["count"][h], many["count"][h])
+        for l in range(N_q):
+            n = few["count"][h][l]
+            assert np.array_equal(few["entries"][h][l][:n], many["entries"][h][l][:n]), (h, l)
+
+
+@pytest.mark.parametrize("N_c,n_new,D,dtype,B_r,pooling", [
+    (2, 1, 128, "bf16", 0, 0), (5, 3, 64, "f32", 0, 1), (16, 2, 128, "bf16", 0, 0), (17, 1, 128, "f32", 0, 0), (40, 3, 64, "bf16", 50, 0),
+    (64, 2, 128, "bf16", 128, 1), (100, 1, 128, "bf16", 0, 0), (128, 1, 64, "f32", 0, 0), (129, 1, 128, "bf16", 0, 0)])
+def test_joined_decoding_steps_give_what_separate_ones_give(N_c, n_new, D, dtype, B_r, pooling):
+    B = boundaries(N_c, 60, N_c)
+    L = int(B[-1])
+    q, k, v = tensors(6, 2, L, D, dtype, N_c)
+    prob = dhsa.problem(q, k, B, max(1, L // 3), B_r=B_r, pooling=pooling, V=v)
+    caps = (N_c + 4, L + 100)
+    ws = dhsa.alloc_decode(prob, *caps)
+    want = dhsa.dhsa_decode_step(prob, q, k, v, B, ws, *caps, 0, want_idx=True)      # pools all keys: never joined
+    ws2 = dhsa.alloc_decode(prob, *caps)
+    old = B[:N_c - n_new + 1].copy()                                                 # the sequence before its newest chunks
+    Lo = int(old[-1])
+    qo, ko, vo = (x[:, :Lo].contiguous() for x in (q, k, v))
+    dhsa.dhsa_decode_step(dhsa.problem(qo, ko, old, max(1, L // 3), B_r=B_r, pooling=pooling, V=vo), qo, ko, vo, old, ws2, *caps, 0)
+    for valid in (N_c - n_new, N_c - 1):      # the second step takes what the first one has pooled
+        got = dhsa.dhsa_decode_step(prob, q, k, v, B, ws2, *caps, valid, want_idx=True)
+        for x, y in zip(got, want):
+            assert torch.equal(x, y), valid
