@@ -22,7 +22,7 @@
 // each is made short: fewer of them, everything requested at once.
 #include <algorithm>
 
-#include "dhsa_internal.h"
+#include "select.h"
 
 namespace dhsa {
 
@@ -94,9 +94,6 @@ __global__ __launch_bounds__(256) void k_pool_decode(const T *__restrict__ Q, co
 // summation of the prefill's scores.  All of D is requested at once.  grid (ceil(N_c / 64), H_kv, ceil(G / 16)).
 // 1634 chunks x 8 kv-heads of D = 128: 12 us with a wave per chunk and a sum over its lanes per head.
 // ---------------------------------------------------------------------------
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
 template <int D>
 __global__ __launch_bounds__(256) void k_scores_decode(const double *__restrict__ Qc, const double *__restrict__ Kc,
                                                        double *__restrict__ Sc, int N_c, int N_c_cap, int G) {
@@ -219,49 +216,62 @@ __device__ __forceinline__ void merge_slices(const float *part, int S, float *s_
 
 constexpr int kDecOwn = 8;   // keys of a chunk that a thread writes into the list of its slice by itself
 
-template <typename T, int D, bool FUSE>
-__global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__ B, const int32_t *__restrict__ count,
-                                                     const int32_t *__restrict__ entries, int stride, int rb0, int L,
-                                                     const T *__restrict__ Q, const T *__restrict__ K,
-                                                     const T *__restrict__ V, float *__restrict__ part, int S, int slice,
-                                                     int32_t *__restrict__ done, T *__restrict__ O_row,
-                                                     int32_t *__restrict__ idx, int cap, int32_t *__restrict__ cnt,
-                                                     int G, float scale, int64_t qs_h, int64_t qs_l, int64_t ks_h,
-                                                     int64_t ks_l, int64_t vs_h, int64_t vs_l) {
-    constexpr int EPT = 16 / (int)sizeof(T);   // elements per 16 bytes
-    constexpr int TPR = D / EPT;               // lanes per key row (8, 16 or 32)
-    constexpr int NG = 256 / TPR;              // key rows per batch
+template <typename T>
+struct AttendArgs {
+    const T *Q, *K, *V;
+    T *O_row;
+    float *part;
+    int32_t *done, *idx, *cnt;
+    int S, slice, stride, rb0, L, cap, G;
+    float scale;
+    int64_t qs_h, qs_l, ks_h, ks_l, vs_h, vs_l;
+};
+
+template <typename T, int D>
+struct AttendSmem {
+    static constexpr int EPT = 16 / (int)sizeof(T);   // elements per 16 bytes
+    static constexpr int TPR = D / EPT;               // lanes per key row (8, 16 or 32)
+    static constexpr int NG = 256 / TPR;              // key rows per batch
+    int keys[kDecSliceMax];
+    int4 seg[kDecSliceMax / (kDecOwn + 1) + 1];       // long pieces of chunks: first and last position in the slice, key - position
+    int nseg;
+    int wave[8];
+    float m[NG], l[NG];
+    float o[NG][D];
+    int last;
+};
+
+// Slice s of head h by the first 256 threads of a workgroup of NTHR, over the plan entries ent[0 .. *count) and the
+// boundaries B, in memory or LDS.
+template <typename T, int D, bool FUSE, int NTHR>
+__device__ __forceinline__ void attend_slice(AttendSmem<T, D> &sm, const AttendArgs<T> &a, int s, int h, const int2 *ent,
+                                             const int32_t *count, const int32_t *B) {
+    using Smem = AttendSmem<T, D>;
+    constexpr int EPT = Smem::EPT, TPR = Smem::TPR, NG = Smem::NG;
     constexpr int U = 4;                       // batches in flight
-    __shared__ int s_keys[kDecSliceMax];
-    __shared__ int4 s_seg[kDecSliceMax / (kDecOwn + 1) + 1];   // long pieces of chunks: first and last position in the slice, key - position
-    __shared__ int s_nseg;
-    __shared__ int s_wave[4];
-    __shared__ float s_m[NG], s_l[NG];
-    __shared__ float s_o[NG][D];
-    __shared__ int s_last;
-    const int s = blockIdx.x, h = blockIdx.y, g = h / G, tid = threadIdx.x;
-    const int i = L - 1;
-    const int v = L - rb0;   // rows of the query group up to and including the newest
+    const int g = h / a.G, tid = threadIdx.x, slice = a.slice;
+    const int i = a.L - 1;
+    const int v = a.L - a.rb0;   // rows of the query group up to and including the newest
+    const bool on = NTHR == 256 || tid < 256;
     const int gi = tid / TPR, r = tid % TPR;
     // the first batch of entries does not wait for their number
-    const int2 *ent = reinterpret_cast<const int2 *>(entries) + (int64_t)h * stride;
-    int2 ent_e = ent[tid < stride ? tid : 0];
-    const int E = count[h];
-    if (tid >= E) ent_e = int2{0, 0};   // past the list: nothing there has been written
+    int2 ent_e = ent[on && tid < a.stride ? tid : 0];
+    const int E = *count;
+    if (!on || tid >= E) ent_e = int2{0, 0};   // past the list: nothing there has been written
     int b0 = B[ent_e.x & kChunkMask], b1 = B[(ent_e.x & kChunkMask) + 1];
-    const uint4 q16 = *reinterpret_cast<const uint4 *>(Q + (int64_t)h * qs_h + (int64_t)i * qs_l + r * EPT);
+    const uint4 q16 = *reinterpret_cast<const uint4 *>(a.Q + (int64_t)h * a.qs_h + (int64_t)i * a.qs_l + r * EPT);
     const int x_lo = s * slice, x_hi = x_lo + slice;
 
-    if (tid == 0) s_nseg = 0;   // (the scan has barriers)
+    if (tid == 0) sm.nseg = 0;   // (the scan has barriers)
     int base = 0;   // selected keys of the entries walked so far (block-uniform)
     for (int e0 = 0; e0 < E; e0 += 256) {
         if (e0 > 0) {
-            ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0};
+            ent_e = on && e0 + tid < E ? ent[e0 + tid] : int2{0, 0};
             b0 = B[ent_e.x & kChunkMask];
             b1 = B[(ent_e.x & kChunkMask) + 1];
         }
         int take = 0;
-        if (e0 + tid < E) {
+        if (on && e0 + tid < E) {
             const int pos = ent_e.x >> kPosShift;
             take = entry_take(pos, ent_e.y, b1 - b0, v);
             if (pos == 3) {   // row-block form: of the block's list, the keys up to the row itself
@@ -270,85 +280,87 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
             }
         }
         int total;
-        const int start = base + block_excl_scan(take, s_wave, &total);
+        const int start = base + block_excl_scan(take, sm.wave, &total);   // (waves past the fourth add nothing)
         const int lo = start > x_lo ? start : x_lo;
         const int hi = start + take < x_hi ? start + take : x_hi;
         // a thread writes few keys by itself; a long piece (a slice holds a handful of them) is written by a wave
         if (hi - lo <= kDecOwn) {
-            for (int x = lo; x < hi; ++x) s_keys[x - x_lo] = b0 + (x - start);
-        } else {
-            s_seg[atomicAdd(&s_nseg, 1)] = make_int4(lo - x_lo, hi - x_lo, b0 - start + x_lo, 0);
+            for (int x = lo; x < hi; ++x) sm.keys[x - x_lo] = b0 + (x - start);
+        } else if (on) {
+            sm.seg[atomicAdd(&sm.nseg, 1)] = make_int4(lo - x_lo, hi - x_lo, b0 - start + x_lo, 0);
         }
         __syncthreads();
-        for (int sg = tid >> 6, n_seg = s_nseg; sg < n_seg; sg += 4) {
-            const int4 w = s_seg[sg];
-            for (int x = w.x + (tid & 63); x < w.y; x += 64) s_keys[x] = x + w.z;
+        for (int sg = tid >> 6, n_seg = sm.nseg; sg < n_seg; sg += NTHR / 64) {
+            const int4 w = sm.seg[sg];
+            for (int x = w.x + (tid & 63); x < w.y; x += 64) sm.keys[x] = x + w.z;
         }
         base += total;
         if (base >= x_hi && s != 0) break;   // slice 0 walks on: it reports the row's key count
         __syncthreads();
-        if (tid == 0) s_nseg = 0;
+        if (tid == 0) sm.nseg = 0;
     }
     __syncthreads();
-    if (s == 0 && tid == 0 && cnt) cnt[h] = base;
+    if (s == 0 && tid == 0 && a.cnt) a.cnt[h] = base;
     int n_mine = base - x_lo;
     n_mine = n_mine < 0 ? 0 : (n_mine > slice ? slice : n_mine);
-    if (idx)
-        for (int x = tid; x < slice && x_lo + x < cap; x += 256) idx[(int64_t)h * cap + x_lo + x] = x < n_mine ? s_keys[x] : -1;
+    if (a.idx)
+        for (int x = tid; x < slice && x_lo + x < a.cap; x += NTHR) a.idx[(int64_t)h * a.cap + x_lo + x] = x < n_mine ? sm.keys[x] : -1;
 
-    float q[EPT];
-    DecIO<T>::unpack(q16, q);
-    const T *Kg = K + (int64_t)g * ks_h + r * EPT;
-    const T *Vg = V + (int64_t)g * vs_h + r * EPT;
-    float m = -INFINITY, l = 0.f, o[EPT];
+    if (on) {
+        float q[EPT];
+        DecIO<T>::unpack(q16, q);
+        const T *Kg = a.K + (int64_t)g * a.ks_h + r * EPT;
+        const T *Vg = a.V + (int64_t)g * a.vs_h + r * EPT;
+        float m = -INFINITY, l = 0.f, o[EPT];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) o[e] = 0.f;
-    for (int j0 = gi; j0 < n_mine; j0 += NG * U) {
-        uint4 kf[U], vf[U];
-        bool ok[U];
+        for (int e = 0; e < EPT; ++e) o[e] = 0.f;
+        for (int j0 = gi; j0 < n_mine; j0 += NG * U) {
+            uint4 kf[U], vf[U];
+            bool ok[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int jj = j0 + u * NG;
-            ok[u] = jj < n_mine;
-            const int key = ok[u] ? s_keys[jj] : s_keys[j0];   // a valid row either way
-            kf[u] = *reinterpret_cast<const uint4 *>(Kg + (int64_t)key * ks_l);
-            vf[u] = *reinterpret_cast<const uint4 *>(Vg + (int64_t)key * vs_l);
-        }
+            for (int u = 0; u < U; ++u) {
+                const int jj = j0 + u * NG;
+                ok[u] = jj < n_mine;
+                const int key = ok[u] ? sm.keys[jj] : sm.keys[j0];   // a valid row either way
+                kf[u] = *reinterpret_cast<const uint4 *>(Kg + (int64_t)key * a.ks_l);
+                vf[u] = *reinterpret_cast<const uint4 *>(Vg + (int64_t)key * a.vs_l);
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float kx[EPT], vx[EPT];
-            DecIO<T>::unpack(kf[u], kx);
-            DecIO<T>::unpack(vf[u], vx);
-            float d = 0.f;
+            for (int u = 0; u < U; ++u) {
+                float kx[EPT], vx[EPT];
+                DecIO<T>::unpack(kf[u], kx);
+                DecIO<T>::unpack(vf[u], vx);
+                float d = 0.f;
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) d += q[e] * kx[e];
+                for (int e = 0; e < EPT; ++e) d += q[e] * kx[e];
 #pragma unroll
-            for (int off = TPR / 2; off > 0; off >>= 1) d += __shfl_xor(d, off);
-            if (ok[u]) {
-                const float sc = d * scale;
-                const float m_new = fmaxf(m, sc);
-                const float alpha = __expf(m - m_new), p = __expf(sc - m_new);
-                l = l * alpha + p;
+                for (int off = TPR / 2; off > 0; off >>= 1) d += __shfl_xor(d, off);
+                if (ok[u]) {
+                    const float sc = d * a.scale;
+                    const float m_new = fmaxf(m, sc);
+                    const float alpha = __expf(m - m_new), p = __expf(sc - m_new);
+                    l = l * alpha + p;
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) o[e] = o[e] * alpha + p * vx[e];
-                m = m_new;
+                    for (int e = 0; e < EPT; ++e) o[e] = o[e] * alpha + p * vx[e];
+                    m = m_new;
+                }
             }
         }
-    }
-    if (r == 0) { s_m[gi] = m; s_l[gi] = l; }
+        if (r == 0) { sm.m[gi] = m; sm.l[gi] = l; }
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) s_o[gi][r * EPT + e] = o[e];
+        for (int e = 0; e < EPT; ++e) sm.o[gi][r * EPT + e] = o[e];
+    }
     __syncthreads();
     if (tid < D) {
         float M = -INFINITY;
-        for (int x = 0; x < NG; ++x) M = fmaxf(M, s_m[x]);
+        for (int x = 0; x < NG; ++x) M = fmaxf(M, sm.m[x]);
         float ls = 0.f, acc = 0.f;
         for (int x = 0; x < NG; ++x) {
-            const float w = (s_m[x] == -INFINITY) ? 0.f : __expf(s_m[x] - M);
-            ls += s_l[x] * w;
-            acc += s_o[x][tid] * w;
+            const float w = (sm.m[x] == -INFINITY) ? 0.f : __expf(sm.m[x] - M);
+            ls += sm.l[x] * w;
+            acc += sm.o[x][tid] * w;
         }
-        float *pp = part + ((int64_t)h * S + s) * (D + 2);
+        float *pp = a.part + ((int64_t)h * a.S + s) * (D + 2);
         const auto put = [](float *p, float x) {
             if constexpr (FUSE) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else *p = x;
@@ -362,12 +374,99 @@ __global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the compiler's order, and
     __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0): the stores have reached the memory side
     __syncthreads();
-    if (tid == 0)
-        s_last = __hip_atomic_fetch_add(&done[h], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+    if (tid == 0) {
+        sm.last = __hip_atomic_fetch_add(&a.done[h], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.S - 1;
+        if (sm.last) __hip_atomic_store(&a.done[h], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next step
+    }
     __syncthreads();
-    if (!s_last) return;
+    if (!sm.last || !on) return;
+    merge_slices<T, D, 256, true>(a.part + (int64_t)h * a.S * (D + 2), a.S, sm.m, sm.l, sm.o, a.O_row + (int64_t)h * D);
+}
 
-    merge_slices<T, D, 256, true>(part + (int64_t)h * S * (D + 2), S, s_m, s_l, s_o, O_row + (int64_t)h * D);
+template <typename T, int D, bool FUSE>
+__global__ __launch_bounds__(256) void k_attn_decode(const int32_t *__restrict__ B, const int32_t *__restrict__ count,
+                                                     const int2 *__restrict__ entries, AttendArgs<T> a) {
+    __shared__ AttendSmem<T, D> sm;
+    const int s = blockIdx.x, h = blockIdx.y;
+    attend_slice<T, D, FUSE, 256>(sm, a, s, h, entries + (int64_t)h * a.stride, count + h, B);
+}
+
+// ---------------------------------------------------------------------------
+// A step over few chunks by workgroups of eight waves.  Each does the whole routing of its head: the open group's queries and
+// the new key chunks are pooled (the first four waves and the others side by side, in k_pool_decode's order), then scored and
+// ranked.  The heads of a kv-group pool the same key chunks; the first workgroup of the first of them stores them for later
+// steps.  Boundaries and pooled keys that come with the step are taken from LDS, the others from the workspace.
+// ONE: a workgroup per slice goes on with the attention of it, over a list that never leaves LDS: the step is one launch.
+// Else a workgroup per head leaves the plan to k_attn_decode.
+// ---------------------------------------------------------------------------
+constexpr int kDecodeFewChunks = 128;
+constexpr int kDecodeFewNew = 3;     // key chunks to pool: with the group's queries two rounds of the workgroup's halves
+
+template <typename T, int D, bool ONE>
+__global__ __launch_bounds__(512, 2) void k_decode_few(AttendArgs<T> at, SelectArgs a, BoundaryTail tail, double *__restrict__ Kc,
+                                                       int N_c_cap, int kc_valid, int pooling) {
+    constexpr int EPT = Elem<T>::kPer16, TPR = D / EPT, RG = 256 / TPR;   // as in k_pool_decode
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double s_sum[2][RG][D];
+    __shared__ __align__(16) double s_pool[1 + kDecodeFewNew][D];       // the queries, then the new chunks
+    __shared__ unsigned long long s_red[8];
+    __shared__ int2 s_ent[kDecodeFewChunks];
+    __shared__ int s_count;
+    __shared__ AttendSmem<T, D> sm;
+    const int h = blockIdx.y, g = h / at.G, rb0 = at.rb0, L = at.L, tid = threadIdx.x;
+    const bool first = !ONE || blockIdx.x == 0;             // of the head's workgroups
+    const int half = __builtin_amdgcn_readfirstlane(tid >> 8), th = tid & 255;
+    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
+    int32_t *s_B = reinterpret_cast<int32_t *>(s_row + a.N_c);
+    int32_t *B = a.plan + a.pl.off_B;
+    for (int k = tid; k < kc_valid; k += 512) s_B[k] = B[k];
+    if (tid <= tail.n) s_B[kc_valid + tid] = tail.b[tid];
+    if (first && h == 0 && tid <= tail.n) B[kc_valid + tid] = tail.b[tid];   // for later steps and launches
+    const int rg = th / TPR, col = (th % TPR) * EPT;
+    for (int x0 = 0; x0 <= tail.n; x0 += 2) {
+        const int x = x0 + half;
+        const bool is_q = x == 0;
+        const T *X = is_q ? at.Q + (int64_t)h * at.qs_h : at.K + (int64_t)g * at.ks_h;
+        const int64_t s_l = is_q ? at.qs_l : at.ks_l;
+        int b0 = rb0, b1 = L;
+        if (!is_q) { b0 = x <= tail.n ? tail.b[x - 1] : 0; b1 = x <= tail.n ? tail.b[x] : 0; }
+        double acc[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) acc[e] = 0.0;
+        for (int i = b0 + rg; i < b1; i += RG) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(X + (int64_t)i * s_l + col);
+            Elem<T>::unpack(u, acc);
+        }
+        if (x0 > 0) __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) s_sum[half][rg][col + e] = acc[e];
+        __syncthreads();
+        if (th < D && x <= tail.n) {
+            double sum = 0.0;
+#pragma unroll 4
+            for (int r = 0; r < RG; ++r) sum += s_sum[half][r][th];
+            const double len = (double)(b1 - b0);
+            const double pooled = pooling == DHSA_POOL_MEAN ? sum / len                        // plain average (ablation)
+                                  : (is_q && a.B_r > 0)    ? sqrt((double)a.B_r) * (sum / len)  // Alg. 1 row blocks
+                                                           : (sqrt(len) / len) * sum;           // Eq. 4
+            s_pool[x][th] = pooled;
+            if (!is_q && first && h == g * at.G) Kc[((int64_t)g * N_c_cap + kc_valid + x - 1) * D + th] = pooled;
+        }
+    }
+    __syncthreads();
+    const double *Kg = Kc + (int64_t)g * N_c_cap * D;
+    score_row<D, 8>(s_pool[0], [&](int k) { return k < kc_valid ? Kg + (int64_t)k * D : s_pool[1 + k - kc_valid]; }, a.N_c, s_row);
+    __syncthreads();
+    const Visible vis = {a.B_r > 0 ? -1 : a.N_c - 1, L, a.N_c};   // the last group sees all chunks
+    int2 *entries = ONE ? s_ent : reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + (int64_t)h * a.pl.stride;
+    const int n = select_row<8>(a, s_row, s_B, vis, smem, s_red, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    if constexpr (ONE) {
+        if (tid == 0) s_count = n;
+        __syncthreads();
+        attend_slice<T, D, true, 512>(sm, at, blockIdx.x, h, s_ent, &s_count, s_B);
+    } else if (tid == 0) {
+        a.plan[a.pl.off_count + h] = n;
+    }
 }
 
 // grid H_q
@@ -380,71 +479,83 @@ __global__ __launch_bounds__(512) void k_decode_combine(const float *__restrict_
     merge_slices<T, D, 512, false>(part + (int64_t)h * S * (D + 2), S, s_m, s_l, s_o, O_row + (int64_t)h * D);
 }
 
-hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0,
-                               const BoundaryTail &tail, const void *Q, const void *K, void *ws, hipStream_t s) {
+// One launch instead of three while scoring all chunks by eight waves and pooling side by side take no longer than a launch.
+// A step in us, apart -> joined: 8 heads of 38 chunks 18.9 -> 16.2, with two chunks to pool 19.3 -> 18.0, 100 chunks 19.4 -> 17.8
+// and 19.8 -> 19.5, 128 chunks 19.4 -> 18.5 and 19.7 -> 20.2, 200 chunks 19.6 -> 21.6; 32 heads of 128 chunks 20.0 -> 18.9.
+// Long chunks, pooled by every head, would make the pooling the longest part.
+static bool decode_few(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail) {
+    int64_t longest = p.L - rb0;
+    for (int j = 0; j < tail.n; ++j) longest = std::max<int64_t>(longest, tail.b[j + 1] - tail.b[j]);
+    return tail.n > 0 && tail.n <= kDecodeFewNew && p.N_c * tail.n <= kDecodeFewChunks && longest <= 512 && pl.stride <= kDecodeFewChunks;
+}
+
+hipError_t launch_decode_step(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
+                              const void *Q, const void *K, const void *V, void *ws, void *O_row, int32_t *idx, int32_t *cnt,
+                              hipStream_t s) {
     char *w8 = static_cast<char *>(ws);
     double *Kc = reinterpret_cast<double *>(w8 + dl.off_Kc), *Qc = reinterpret_cast<double *>(w8 + dl.off_Qc);
     double *Sc = reinterpret_cast<double *>(w8 + dl.off_Sc);
-    int32_t *plan = reinterpret_cast<int32_t *>(w8 + dl.off_plan);
-    int32_t *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
-    if (route_decode_ok(p, dl.pl, rb0, tail))
-        return launch_route_decode(p, dl.pl, N_c_cap, kc_valid, rb0, tail, Q, K, Kc, plan, done, s);
-    const int n_new = p.N_c - kc_valid;
-    dim3 grid(n_new > 1 ? n_new : 1, p.H_kv + p.H_q), block(256);
+    int32_t *plan = reinterpret_cast<int32_t *>(w8 + dl.off_plan), *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
+    float *part = reinterpret_cast<float *>(w8 + dl.off_part);
+    const int slice = decode_slice(p.H_q, p.N_b);
+    const int S = (p.N_b + slice - 1) / slice;           // N_b is clamped to L: the row takes exactly N_b keys
+    const bool fuse = slice < kDecSlice, few = decode_few(p, dl.pl, rb0, tail);
+#define DHSA_TYPES(CALL)                                                                       \
+    do {                                                                                       \
+        if (p.dtype == DHSA_F32) {                                                             \
+            if (p.D == 64) CALL(float, 64); else CALL(float, 128);                             \
+        } else {                                                                               \
+            if (p.D == 64) CALL(bf16_t, 64); else CALL(bf16_t, 128);                           \
+        }                                                                                      \
+        if ((e = hipGetLastError()) != hipSuccess) return e;                                   \
+    } while (0)
+#define DHSA_ARGS(T)                                                                                                              \
+    AttendArgs<T>{(const T *)Q, (const T *)K, (const T *)V, (T *)O_row, part, done, idx, cnt, S, slice, dl.pl.stride, rb0,         \
+                  (int)p.L, p.N_b, p.G, p.scale, p.qs_h, p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l}
+    hipError_t e;
+    if (few) {
+        const int cap = select_cap(dl.pl.stride), row_bytes = (select_row_bytes(8, cap, p.N_c) + 15) / 16 * 16;
+        const SelectArgs a = {plan, dl.pl, p.N_c, p.N_b, p.B_r, p.N_q - 1, 1, 0, p.H_q, cap, row_bytes};
+        const size_t shmem = row_bytes + 8 * (size_t)p.N_c + 4 * (size_t)(p.N_c + 1);
+#define DHSA_FEW1(T, DD, ONE)                                                                                                 \
+    hipLaunchKernelGGL((k_decode_few<T, DD, ONE>), dim3(ONE ? S : 1, p.H_q), dim3(512), shmem, s, DHSA_ARGS(T), a, tail, Kc, \
+                       N_c_cap, kc_valid, p.pooling)
+#define DHSA_FEW(T, DD) do { if (fuse) DHSA_FEW1(T, DD, true); else DHSA_FEW1(T, DD, false); } while (0)
+        DHSA_TYPES(DHSA_FEW);
+#undef DHSA_FEW
+#undef DHSA_FEW1
+        if (fuse) return hipSuccess;
+    } else {
+        const int n_new = p.N_c - kc_valid;
+        const dim3 grid(n_new > 1 ? n_new : 1, p.H_kv + p.H_q), block(256);
 #define DHSA_POOLD(T, DD)                                                                                      \
     hipLaunchKernelGGL((k_pool_decode<T, DD>), grid, block, 0, s, (const T *)Q, (const T *)K,                  \
                        plan + dl.pl.off_B, tail, plan + dl.pl.off_RB, done, Qc, Kc, p.H_kv, p.N_c, N_c_cap, kc_valid, rb0, \
                        (int)p.L, p.B_r, p.pooling, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
-    if (p.dtype == DHSA_F32) {
-        if (p.D == 64) DHSA_POOLD(float, 64); else DHSA_POOLD(float, 128);
-    } else {
-        if (p.D == 64) DHSA_POOLD(bf16_t, 64); else DHSA_POOLD(bf16_t, 128);
-    }
+        DHSA_TYPES(DHSA_POOLD);
 #undef DHSA_POOLD
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 sgrid((p.N_c + 63) / 64, p.H_kv, (p.G + 15) / 16);
-    if (p.D == 64)
-        hipLaunchKernelGGL(k_scores_decode<64>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
-    else
-        hipLaunchKernelGGL(k_scores_decode<128>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // ranking + walk of the one open group: group number N_q - 1 of the sequence, group 0 of this plan
-    return launch_select_groups(p, dl.pl, Sc, plan, p.N_q - 1, 1, s);
-}
-
-hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, const void *Q, const void *K,
-                                const void *V, void *ws, void *O_row, int32_t *idx, int32_t *cnt, hipStream_t s) {
-    char *w8 = static_cast<char *>(ws);
-    const int32_t *plan = reinterpret_cast<const int32_t *>(w8 + dl.off_plan);
-    float *part = reinterpret_cast<float *>(w8 + dl.off_part);
-    int32_t *done = reinterpret_cast<int32_t *>(w8 + dl.off_done);
-    const int slice = decode_slice(p.H_q, p.N_b);
-    const int S = (p.N_b + slice - 1) / slice;           // N_b is clamped to L: the row takes exactly N_b keys
-    dim3 grid(S, p.H_q), block(256);
-    const bool fuse = slice < kDecSlice;
-#define DHSA_ATTD1(T, DD, FUSE)                                                                                   \
-    hipLaunchKernelGGL((k_attn_decode<T, DD, FUSE>), grid, block, 0, s, plan + dl.pl.off_B, plan + dl.pl.off_count, \
-                       plan + dl.pl.off_entries, dl.pl.stride, rb0, (int)p.L, (const T *)Q, (const T *)K,         \
-                       (const T *)V, part, S, slice, done, (T *)O_row, idx, p.N_b, cnt, p.G, p.scale, p.qs_h,     \
-                       p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l)
-#define DHSA_ATTD(T, DD)                                                                                          \
-    do {                                                                                                          \
-        if (fuse) {                                                                                               \
-            DHSA_ATTD1(T, DD, true);                                                                              \
-        } else {                                                                                                  \
-            DHSA_ATTD1(T, DD, false);                                                                             \
-            hipLaunchKernelGGL((k_decode_combine<T, DD>), dim3(p.H_q), dim3(512), 0, s, part, S, (T *)O_row);     \
-        }                                                                                                         \
-    } while (0)
-    if (p.dtype == DHSA_F32) {
-        if (p.D == 64) DHSA_ATTD(float, 64); else DHSA_ATTD(float, 128);
-    } else {
-        if (p.D == 64) DHSA_ATTD(bf16_t, 64); else DHSA_ATTD(bf16_t, 128);
+        const dim3 sgrid((p.N_c + 63) / 64, p.H_kv, (p.G + 15) / 16);
+        if (p.D == 64)
+            hipLaunchKernelGGL(k_scores_decode<64>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
+        else
+            hipLaunchKernelGGL(k_scores_decode<128>, sgrid, dim3(256), 0, s, Qc, Kc, Sc, p.N_c, N_c_cap, p.G);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        // ranking + walk of the one open group: group number N_q - 1 of the sequence, group 0 of this plan
+        if ((e = launch_select_groups(p, dl.pl, Sc, plan, p.N_q - 1, 1, s)) != hipSuccess) return e;
     }
+#define DHSA_ATTD1(T, DD, FUSE)                                                                                           \
+    hipLaunchKernelGGL((k_attn_decode<T, DD, FUSE>), dim3(S, p.H_q), dim3(256), 0, s, plan + dl.pl.off_B, plan + dl.pl.off_count, \
+                       (const int2 *)(plan + dl.pl.off_entries), DHSA_ARGS(T))
+#define DHSA_ATTD(T, DD) do { if (fuse) DHSA_ATTD1(T, DD, true); else DHSA_ATTD1(T, DD, false); } while (0)
+    DHSA_TYPES(DHSA_ATTD);
 #undef DHSA_ATTD
 #undef DHSA_ATTD1
-    return hipGetLastError();
+#define DHSA_COMB(T, DD) hipLaunchKernelGGL((k_decode_combine<T, DD>), dim3(p.H_q), dim3(512), 0, s, part, S, (T *)O_row)
+    if (!fuse) DHSA_TYPES(DHSA_COMB);
+#undef DHSA_COMB
+#undef DHSA_ARGS
+#undef DHSA_TYPES
+    return hipSuccess;
 }
 
 }  // namespace dhsa

@@ -147,14 +147,15 @@ DecodeLayout decode_layout(int H_q, int H_kv, int D, int64_t N_b, int N_c_cap, i
     pl.off_count = pl.off_RB + 4;
     pl.off_entries = align_up(pl.off_count + H_q, 4);
     pl.off_tiles = pl.words = pl.off_entries + (int64_t)H_q * N_c_cap * 2;
-    dl.off_part = align_up(dl.off_plan + pl.words * 4, 256);
+    // (in front of what depends on the budget: the counters are zero between steps, whatever budget the next one has)
+    dl.off_done = align_up(dl.off_plan + pl.words * 4, 256);
+    dl.off_part = align_up(dl.off_done + (int64_t)H_q * 4, 256);
     // most slices any step up to the caps can have: N_b keys, or the most keys that still get short slices
     const int64_t nb = std::min<int64_t>(N_b, L_cap);
     const int64_t few = std::min<int64_t>((nb + kDecSliceFew - 1) / kDecSliceFew, kDecWgFew / H_q);
     const int64_t some = std::min<int64_t>((nb + kDecSliceSome - 1) / kDecSliceSome, kDecWgSome / H_q);
     dl.S_cap = (int)std::max({(nb + kDecSlice - 1) / kDecSlice, few, some});
-    dl.off_done = align_up(dl.off_part + (int64_t)H_q * dl.S_cap * (D + 2) * 4, 256);
-    dl.bytes = align_up(dl.off_done + (int64_t)H_q * 4, 256);
+    dl.bytes = align_up(dl.off_part + (int64_t)H_q * dl.S_cap * (D + 2) * 4, 256);
     return dl;
 }
 
@@ -483,9 +484,8 @@ __attribute__((visibility("default"))) dhsa_status dhsa_decode_step(
     } else if (launch_put_boundaries(B_host, p.N_c + 1, plan + dl.pl.off_B, s) != hipSuccess) {
         return DHSA_ERR_HIP;
     }
-    if (launch_decode_route(p, dl, N_c_cap, kc_valid, rb0, tail, Q_dev, K_dev, ws_dev, s) != hipSuccess)
-        return DHSA_ERR_HIP;
-    return hip_status(launch_decode_attend(p, dl, rb0, Q_dev, K_dev, V_dev, ws_dev, O_row_dev, idx_dev, cnt_dev, s));
+    return hip_status(launch_decode_step(p, dl, N_c_cap, kc_valid, rb0, tail, Q_dev, K_dev, V_dev, ws_dev, O_row_dev, idx_dev,
+                                         cnt_dev, s));
 }
 
 __attribute__((visibility("default"))) size_t dhsa_recall_workspace_bytes(const dhsa_problem *prob,

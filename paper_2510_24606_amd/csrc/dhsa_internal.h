@@ -67,7 +67,7 @@ struct WsLayout {
 // The "plan" is a one-group plan: B [N_c_cap + 1], RB [2], count [H_q], entries [H_q][stride][2]
 // (room for stride = N_c_cap), laid out by `pl` in words from off_plan.
 struct DecodeLayout {
-    int64_t off_Kc, off_Qc, off_Sc, off_plan, off_part, off_done, bytes;
+    int64_t off_Kc, off_Qc, off_Sc, off_plan, off_done, off_part, bytes;
     PlanLayout pl;
     int S_cap;   // most key slices (workgroups per head) of the attention step
 };
@@ -124,17 +124,11 @@ hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double
 // query groups [l_first, l_first + n_groups) only; `pl`, `Sc` and `plan` are indexed by group - l_first
 hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, int l_first,
                                 int n_groups, hipStream_t s);
-// one decoding step: the kernels of decode.hip (pooling of the new chunks and the open query group,
-// scores of that group, and after the ranking the attention of the newest row)
-// rb0 = first row of the open query group; the boundaries are already in the step's plan
-hipError_t launch_decode_route(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0,
-                               const BoundaryTail &tail, const void *Q, const void *K, void *ws, hipStream_t s);
-// ... all of it in one launch, for steps that route_decode_ok takes
-bool route_decode_ok(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail);
-hipError_t launch_route_decode(const Prob &p, const PlanLayout &pl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
-                               const void *Q, const void *K, double *Kc, int32_t *plan, int32_t *done, hipStream_t s);
-hipError_t launch_decode_attend(const Prob &p, const DecodeLayout &dl, int rb0, const void *Q, const void *K,
-                                const void *V, void *ws, void *O_row, int32_t *idx, int32_t *cnt, hipStream_t s);
+// one decoding step (decode.hip).  rb0 = first row of the open query group; boundaries that are not in `tail` are already in
+// the step's plan
+hipError_t launch_decode_step(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
+                              const void *Q, const void *K, const void *V, void *ws, void *O_row, int32_t *idx, int32_t *cnt,
+                              hipStream_t s);
 hipError_t launch_expand(const Prob &p, const PlanView &pv, int head, const int64_t *rows_dev, int n_rows,
                          int32_t *idx, int cap, int32_t *cnt, hipStream_t s);
 hipError_t launch_recall(const Prob &p, const PlanView &pv, const void *Q, const void *K, int head,

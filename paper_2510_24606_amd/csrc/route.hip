@@ -10,12 +10,9 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "dhsa_internal.h"
+#include "select.h"
 
 namespace dhsa {
-
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Boundaries into the plan without a copy from host memory: each launch carries
@@ -406,491 +403,6 @@ hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, cons
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Ranking + per-row budget for one (head, query group): Alg. 1's Argsort and walk, done
-// once for all rows of the group.  An entry of the plan is a chunk that some row takes
-// a token of, with rem = N_b - (tokens of the other chunks ranked before it; the group's own chunk
-// left out).  Row-block form (B_r > 0, Alg. 1 as printed): the candidates are the chunks that
-// start before the block's end q_max, their lengths are clipped to q_max, there is no "own chunk", and
-// an entry records how many tokens of the chunk the block's list holds (pos = 3).
-// ---------------------------------------------------------------------------
-
-// order-preserving image of a score and back; -0.0 ties with +0.0
-__device__ __forceinline__ unsigned long long score_key(double s) {
-    if (s == 0.0) s = 0.0;
-    const unsigned long long u = (unsigned long long)__double_as_longlong(s);
-    return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-}
-// The score rounded to fp32, in the order of score_key: a NaN lies outside all other scores, on the side of its sign.
-__device__ __forceinline__ float score_f32(double s) {
-    const float f = (float)s;
-    return f == f ? f : __builtin_copysignf(INFINITY, f);
-}
-__device__ __forceinline__ double key_score(unsigned long long k) {
-    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
-}
-
-// LDS traffic between the lanes of one wave: the LDS executes a wave's operations in order, so only the
-// compiler has to be kept from moving them
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Wider sums and extrema with the steps of wave_incl_scan.
-__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long x) {
-#define DHSA_STEP(CTRL, ROWS)                                                               \
-    x += ((unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)(x >> 32)) << 32) | \
-         (unsigned long long)(unsigned)dpp_or<CTRL, ROWS>(0, (int)(unsigned)x);
-    DHSA_DPP_STEPS(DHSA_STEP)
-#undef DHSA_STEP
-    return x;
-}
-__device__ __forceinline__ float wave_max(float x) {
-#define DHSA_STEP(CTRL, ROWS) x = fmaxf(x, __int_as_float(dpp_or<CTRL, ROWS>(__float_as_int(x), __float_as_int(x))));
-    DHSA_DPP_STEPS(DHSA_STEP)
-#undef DHSA_STEP
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-__device__ __forceinline__ unsigned long long wave_read(unsigned long long x, int src) {   // src: wave-uniform
-    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), src) << 32) |
-           (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, src);
-}
-
-// ---------------------------------------------------------------------------
-// NW waves per (head, query group).  Only chunks that some row takes a token of need a
-// rank, and the tokens ranked before such a chunk are all that is wanted of it:
-//   1. scores of the visible chunks into registers (eight per lane at a time), their range;
-//   2. tokens and chunks per score bin (256 bins over the range, best first; packed tokens << 16 | chunks,
-//      LDS atomics): the bin where the tokens reach N_b is the last one that can hold a listed
-//      chunk, whatever the order inside it, so the chunks up to that bin are the candidates.  If
-//      they are more than the list holds, the last bin is cut again over its own range (outliers
-//      far from the rest), and at last by digits of the keys and ids (ties);
-//   3. candidates into LDS, grouped by bin (the bins' counts are their places);
-//   4. tokens before a candidate = tokens of better bins + of the better candidates of its own bin (a few; with a
-//      bin of many, a prefix sum over the sorted candidates);
-//   5. the listed chunks set their bit, and go into the plan at the number of bits below theirs
-//      (ascending chunk id).
-// Bins are taken from the scores rounded to fp32 (which keeps their order), the order inside a bin from the fp64
-// scores.  Bound by instruction issue and by the scores' way from memory (342 MB for 1634 chunks x 32 heads).  That
-// case takes 256 us; it took 480 us with a radix select by 8-bit digits (whose first digit counts nearly all
-// scores in two or three LDS words), a bitonic sort and two scans, with ~40 block barriers.
-// ---------------------------------------------------------------------------
-constexpr int kSelBins = 256;
-constexpr int kSelPer = 8;           // scores per lane in registers
-constexpr int kSelCrowd = 32;        // candidates in one bin that are still compared with one another
-constexpr int kSelMaxStride = 1024;  // listed chunks this kernel can hold; with more the whole row is sorted (below)
-
-static int select_cap(int stride) { return (stride + 2 + 32 + 63) / 64 * 64; }   // some to spare before a bin is cut again
-static int select_row_bytes(int NW, int cap, int N_c) {   // cap: a multiple of 64
-    return kSelBins * (NW == 1 ? 8 : 16) + cap * 20 + (N_c + 63) / 64 * 8;
-}
-
-struct SelectArgs {
-    int32_t *plan;
-    PlanLayout pl;
-    int N_c, N_b, B_r;
-    int l_first, n_groups;   // the groups of the launch, laid out from 0: l indexes Sc, RB and the plan, l_first + l is the group's number
-    int r_first, n_rows, cap, row_bytes;
-};
-
-// The chunks a query group ranks: own = the group's own chunk, q_max = the clip of the chunk lengths, n = visible chunks 0..n-1
-struct Visible {
-    int own, q_max, n;
-};
-__device__ __forceinline__ Visible visible_chunks(const SelectArgs &a, const int32_t *B, int l) {
-    const int lane = threadIdx.x & 63, N_c = a.N_c;
-    const bool blocks = a.B_r > 0;
-    const int q_max = blocks ? (a.plan + a.pl.off_RB)[l + 1] : 0x7fffffff;
-    const int own = blocks ? -1 : a.l_first + l;
-    int n = own + 1;
-    if (blocks) {                        // the chunks that start before q_max: B ascends, 64-ary search
-        int step = (N_c + 63) >> 6;
-        n = (__popcll(__ballot(lane * step < N_c && B[lane * step < N_c ? lane * step : 0] < q_max)) - 1) * step;   // B[0] = 0 < q_max
-        int got = 0;
-        for (int k0 = 0; k0 < step; k0 += 64) {
-            const int k = n + k0 + lane;
-            got += __popcll(__ballot(k0 + lane < step && k < N_c && B[k < N_c ? k : 0] < q_max));
-        }
-        n = __builtin_amdgcn_readfirstlane(n + got);
-    }
-    return {own, q_max, n};
-}
-
-// Ranks the scores row[0 .. vis.n) of group l of head h; mine8: row_bytes of LDS, s_red: NW words of it.  row and B in
-// memory or LDS.
-template <int NW>
-__device__ __forceinline__ void select_row(const SelectArgs &a, const double *row, const int32_t *B, const Visible vis,
-                                           const int h, const int l, unsigned char *mine8, unsigned long long *s_red) {
-    constexpr int NT = 64 * NW, PER = kSelPer, kSlab = PER * NT;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = NW == 1 ? lane : (int)threadIdx.x;                     // thread of the row
-    const int N_c = a.N_c, N_b = a.N_b, cap = a.cap;
-    int32_t *const plan = a.plan;
-    const PlanLayout &pl = a.pl;
-    const auto sync = [] { if constexpr (NW == 1) wave_lds_fence(); else __syncthreads(); };
-    unsigned long long *hist = reinterpret_cast<unsigned long long *>(mine8);              // [kSelBins]
-    unsigned long long *place = NW == 1 ? hist : hist + kSelBins;                          // [kSelBins] (one wave: in place)
-    unsigned long long *ckey = place + kSelBins;                                           // [cap]
-    unsigned long long *kept = ckey + cap;                                                 // [ceil(N_c / 64)]
-    int *cid = reinterpret_cast<int *>(kept + ((N_c + 63) >> 6));                          // [cap]  id | pos << kPosShift
-    int *clen = cid + cap, *crem = clen + cap;                                             // [cap]
-    const bool blocks = a.B_r > 0;
-    const int own = vis.own, q_max = vis.q_max, n = vis.n;
-    // (an unsigned offset: a 64-bit address per lane that lives through the rare passes has no registers)
-    const auto score_at = [&](int x) { return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(row) + 8u * (unsigned)x); };
-    const auto len_at = [&](int x) {
-        const int b0 = B[x], b1 = B[x + 1];
-        return x == own ? 0 : (b1 < q_max ? b1 : q_max) - b0;
-    };
-
-    double v[PER];
-    int len[PER];
-    const auto load = [&](int x0) {      // a thread past the end repeats the last chunk
-#pragma unroll
-        for (int e = 0; e < PER; ++e)
-            if (x0 + e * NT < n) {
-                const int x = x0 + e * NT + t < n ? x0 + e * NT + t : n - 1;
-                v[e] = score_at(x);
-                len[e] = len_at(x);
-            }
-    };
-// BODY for every visible chunk x (in: it exists) with score s and length n_tok, whole waves; rows longer than the
-// registers hold are read again in every pass
-#define DHSA_SEL_FOR(...)                                                                    \
-    for (int x0_ = 0; x0_ < n; x0_ += kSlab) {                                               \
-        if (n > kSlab) load(x0_);                                                            \
-        _Pragma("unroll") for (int e_ = 0; e_ < PER; ++e_) {                             \
-            if (x0_ + e_ * NT < n) {                                                         \
-                const int x = x0_ + e_ * NT + t;                                             \
-                const bool in = x < n;                                                       \
-                const double s = v[e_];                                                      \
-                const int n_tok = len[e_];                                                   \
-                __VA_ARGS__                                                                  \
-            }                                                                                \
-        }                                                                                    \
-    }
-// the same for the rare passes, always from memory
-#define DHSA_SEL_AGAIN(...)                                                                  \
-    _Pragma("unroll 1") for (int x0_ = 0; x0_ < n; x0_ += NT) {                              \
-        const int x = x0_ + t;                                                               \
-        const bool in = x < n;                                                               \
-        const double s = score_at(in ? x : n - 1);                                                \
-        const int n_tok = len_at(in ? x : n - 1);                                            \
-        __VA_ARGS__                                                                          \
-    }
-    // over the threads of the row (NW > 1: two barriers)
-    const auto row_range = [&](float &lo_, float &hi_) {
-        hi_ = wave_max(hi_);
-        lo_ = -wave_max(-lo_);
-        if constexpr (NW > 1) {
-            __syncthreads();
-            if (lane == 0)
-                s_red[wave] = ((unsigned long long)__float_as_uint(lo_) << 32) | __float_as_uint(hi_);
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const unsigned long long x = s_red[w];
-                lo_ = fminf(lo_, __uint_as_float((unsigned)(x >> 32)));
-                hi_ = fmaxf(hi_, __uint_as_float((unsigned)x));
-            }
-            lo_ = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lo_)));   // the same in all lanes:
-            hi_ = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(hi_)));   // no vector registers
-        }
-    };
-    const auto row_min = [&](unsigned long long x) {     // NW > 1: two barriers
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const unsigned long long o = __shfl_xor(x, off);
-            x = o < x ? o : x;
-        }
-        if constexpr (NW > 1) {
-            __syncthreads();
-            if (lane == 0) s_red[wave] = x;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < NW; ++w) x = s_red[w] < x ? s_red[w] : x;
-        }
-        return wave_read(x, 0);          // a wave-uniform value needs no vector registers
-    };
-    const auto clear_hist = [&] {
-        sync();                          // everybody has read the last counts
-        for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
-        sync();
-    };
-
-    for (int b = t; b < kSelBins; b += NT) hist[b] = 0ull;
-    if (n <= kSlab) load(0);
-    const unsigned long long k_own = score_key(own >= 0 ? row[own] : 0.0);
-    float lo = INFINITY, hi = -INFINITY, inv;
-    DHSA_SEL_FOR({ (void)x; (void)in; (void)n_tok; lo = fminf(lo, score_f32(s)); hi = fmaxf(hi, score_f32(s)); })
-    row_range(lo, hi);
-    if constexpr (NW == 1) wave_lds_fence();   // hist is clear (NW > 1: row_range has a barrier)
-    const float best = hi;
-    const auto bin_of = [&](double s) {  // never decreasing as s falls
-        return (int)fminf(fmaxf((hi - score_f32(s)) * inv, 0.f), (float)(kSelBins - 1));   // inf - inf: bin 0
-    };
-
-    // candidates: chunks ranked at or before (cut_key, cut_id) once that is known (cut), or those of the bins up to tbin
-    bool cut = false;
-    unsigned long long cut_key = 0ull;
-    int cut_id = 0x7fffffff, tbin;
-    const auto is_cand = [&](double s, int x) {
-        const unsigned long long k = score_key(s);
-        return k > cut_key || (k == cut_key && x <= cut_id);
-    };
-    unsigned long long above = 0ull;     // tokens << 16 | chunks with a score above hi
-    unsigned long long before, upto;     // ranked before the last bin, and up to it
-    bool crowded;                        // some bin of candidates holds more than kSelCrowd of them
-    // From the counts in hist, every wave for itself: what is ranked before each bin (tokens, and chunks = the place of
-    // its first) goes to place; the last bin is the one in which the tokens reach N_b (none does: the worst of all)
-    const auto find_last = [&] {
-        sync();
-        unsigned long long c[4];         // bins 4 lane .. 4 lane + 3
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = hist[4 * lane + i];
-        const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
-        unsigned long long run = above + wave_incl_scan(mine) - mine;
-        int my_bin = kSelBins;           // the bin of this lane in which the tokens reach N_b
-        before = upto = 0ull;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (NW == 1 || wave == 0) place[4 * lane + i] = run;
-            if ((run >> 16) < (unsigned long long)N_b && ((run + c[i]) >> 16) >= (unsigned long long)N_b) {
-                my_bin = 4 * lane + i;
-                before = run;
-                upto = run + c[i];
-            }
-            run += c[i];
-        }
-        const unsigned long long found = __ballot(my_bin < kSelBins);
-        const int src = found ? __builtin_ctzll(found) : 63;
-        tbin = found ? __builtin_amdgcn_readlane(my_bin, src) : kSelBins - 1;
-        before = wave_read(before, src);
-        upto = wave_read(found ? upto : run, src);
-        crowded = false;
-        if ((int)(upto & 0xffffull) > kSelCrowd) {
-            int most = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int n_bin = (int)c[i] & 0xffff;
-                most = (cut || 4 * lane + i <= tbin) && n_bin > most ? n_bin : most;
-            }
-            crowded = __ballot(most > kSelCrowd) != 0ull;
-        }
-    };
-    for (int level = 0;; ++level) {
-        inv = hi > lo ? fminf((float)kSelBins / (hi - lo), 1e30f) : 0.f;
-        if (level == 0) {
-            DHSA_SEL_FOR({ (void)x; if (in) atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull); })
-        } else {
-            clear_hist();
-            DHSA_SEL_AGAIN({
-                if (in && (cut ? is_cand(s, x) : (score_f32(s) >= lo && score_f32(s) <= hi)))
-                    atomicAdd(&hist[bin_of(s)], ((unsigned long long)n_tok << 16) | 1ull);
-            })
-        }
-        find_last();
-        if (cut) {
-            tbin = kSelBins - 1;
-            break;
-        }
-        int n_upto = (int)(upto & 0xffffull);                    // chunks up to the last bin
-        if (n_upto <= cap && level == 0) break;                  // the usual end
-        if (n_upto <= cap) {             // group all candidates over one range: from the worst of them to the best
-            float worst = INFINITY, none = -INFINITY;
-            DHSA_SEL_AGAIN({
-                (void)x; (void)n_tok;
-                if (in && (score_f32(s) > hi || (score_f32(s) >= lo && bin_of(s) <= tbin))) worst = fminf(worst, score_f32(s));
-            })
-            row_range(worst, none);
-            lo = worst;
-            // every score that rounds to `worst` or more: the smallest such key
-            unsigned long long key_lo = ~0ull;
-            DHSA_SEL_AGAIN({
-                (void)x; (void)n_tok;
-                const unsigned long long k = score_key(s);
-                if (in && score_f32(s) >= worst && k < key_lo) key_lo = k;
-            })
-            cut_key = row_min(key_lo);
-        } else if (level < 3 && hi > lo) {   // cut the last bin again, over its own range
-            float a = INFINITY, z = -INFINITY;
-            DHSA_SEL_AGAIN({
-                (void)x; (void)n_tok;
-                if (in && score_f32(s) >= lo && score_f32(s) <= hi && bin_of(s) == tbin) { a = fminf(a, score_f32(s)); z = fmaxf(z, score_f32(s)); }
-            })
-            above = before;
-            row_range(a, z);
-            lo = a;
-            hi = z;
-            continue;
-        } else {
-            // (Nearly) equal scores: the last bin holds the keys k_lo .. k_hi.  It is cut by 8-bit digits of the keys from
-            // the first one they differ in, then, where all keys left are equal, by the id: no more digits than it takes
-            // to be left with `cap` chunks.  Keys all zero, 8 heads: routing of 820 chunks 131 us (358 us bit by bit, 78 passes
-            // over the row; a radix select of the whole row 330 us), of 205 chunks 33 us (92; 30), of 1570 chunks 457 us.
-            unsigned long long k_lo = ~0ull, k_hi = ~0ull;       // k_hi: complemented
-            DHSA_SEL_AGAIN({
-                (void)x; (void)n_tok;
-                if (in && score_f32(s) >= lo && score_f32(s) <= hi && bin_of(s) == tbin) {
-                    const unsigned long long k = score_key(s);
-                    k_lo = k < k_lo ? k : k_lo;
-                    k_hi = ~k < k_hi ? ~k : k_hi;
-                }
-            })
-            k_lo = row_min(k_lo);
-            k_hi = ~row_min(k_hi);
-            for (int d = 0; d < 8 && n_upto > cap && k_lo != k_hi; ++d) {
-                const int top = 64 - __builtin_clzll(k_lo ^ k_hi), low = top > 8 ? top - 8 : 0;   // the digit: bits low .. top - 1
-                above = before;
-                clear_hist();
-                DHSA_SEL_AGAIN({
-                    (void)x;
-                    const unsigned long long k = score_key(s);
-                    if (in && k >= k_lo && k <= k_hi)
-                        atomicAdd(&hist[kSelBins - 1 - (int)((k >> low) & (kSelBins - 1))], ((unsigned long long)n_tok << 16) | 1ull);
-                })
-                find_last();
-                n_upto = (int)(upto & 0xffffull);
-                const unsigned long long rest = (1ull << low) - 1ull;
-                const unsigned long long first = (((k_hi >> low) & ~(kSelBins - 1ull)) | (unsigned long long)(kSelBins - 1 - tbin)) << low;
-                k_lo = first > k_lo ? first : k_lo;
-                k_hi = (first | rest) < k_hi ? first | rest : k_hi;
-            }
-            cut_key = k_lo;
-            for (int i = 1; n_upto > cap && i >= 0; --i) {       // 64 ids a bin, then each
-                above = before;
-                clear_hist();
-                DHSA_SEL_AGAIN({
-                    if (in && score_key(s) == cut_key && (i == 1 || x >> 6 == cut_id >> 6))
-                        atomicAdd(&hist[i == 1 ? x >> 6 : x & 63], ((unsigned long long)n_tok << 16) | 1ull);
-                })
-                find_last();
-                n_upto = (int)(upto & 0xffffull);
-                cut_id = i == 1 ? tbin * 64 + 63 : (cut_id & ~63) + tbin;
-            }
-            lo = score_f32(key_score(cut_key));
-        }
-        cut = true;                      // one more level: the bins of the candidates alone
-        above = 0ull;
-        hi = best;
-    }
-    for (int w = t; w < ((n + 63) >> 6); w += NT) kept[w] = 0ull;
-    sync();
-
-    // ---- candidates, grouped by bin: the chunk count in place[bin] moves from the place of its first to its end ----
-    DHSA_SEL_FOR({
-        const int bin = bin_of(s);
-        if (in && (cut ? is_cand(s, x) : bin <= tbin)) {
-            const int at = (int)(atomicAdd(&place[bin], 1ull) & 0xffffull);
-            const unsigned long long k = score_key(s);
-            const int pos = blocks ? 3 : x == own ? 1 : (k > k_own || (k == k_own && x < own)) ? 0 : 2;
-            if (at < cap) { ckey[at] = k; cid[at] = x | (pos << kPosShift); clen[at] = n_tok; }
-        }
-    })
-#undef DHSA_SEL_FOR
-#undef DHSA_SEL_AGAIN
-    sync();
-    int n_c = __builtin_amdgcn_readfirstlane((int)(place[tbin] & 0xffffull));
-    n_c = n_c < cap ? n_c : cap;
-
-    // A bin that holds many (ties; all scores but an outlier's) would cost their number squared: the list is sorted
-    // instead, by a network whose comparisons all put the better one first, so that nothing is moved past its end,
-    // and the tokens before each candidate are a prefix sum.  Routing of 820 chunks, 32 heads, keys all zero: 1070 ->
-    // 223 us; 500 chunks of one token, 12 heads, with outliers: 874 -> 160 us (ordinary scores: 78 us)
-    if (__builtin_expect(crowded, 0)) {
-        const auto first = [&](unsigned long long ka, int wa, unsigned long long kb, int wb) {
-            return ka > kb || (ka == kb && (wa & kChunkMask) < (wb & kChunkMask));
-        };
-        bool any = false;                // equal scores, taken in ascending order of the ids, are in order already
-        for (int c = t; c + 1 < n_c; c += NT) any |= first(ckey[c + 1], cid[c + 1], ckey[c], cid[c]);
-        any = __any(any);
-        if constexpr (NW > 1) {
-            if (lane == 0) s_red[wave] = any;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < NW; ++w) any |= s_red[w] != 0ull;
-        }
-        int half = any ? 1 : 0;
-        while (any && 2 * half < n_c) half *= 2;
-#pragma unroll 1
-        for (int size = 1; size <= half; size *= 2) {    // runs of `size` are in order: join two, the second one reversed
-#pragma unroll 1
-            for (int step = size; step > 0; step >>= 1) {
-#pragma unroll 1
-                for (int p = t; p < half; p += NT) {
-                    const int in_run = p & (step - 1), lo_at = 2 * p - in_run;
-                    const int hi_at = step == size ? lo_at + 2 * (step - in_run) - 1 : lo_at + step;
-                    if (hi_at >= n_c) continue;
-                    const unsigned long long ka = ckey[lo_at], kb = ckey[hi_at];
-                    const int wa = cid[lo_at], wb = cid[hi_at];
-                    if (first(kb, wb, ka, wa)) {
-                        ckey[lo_at] = kb;
-                        ckey[hi_at] = ka;
-                        cid[lo_at] = wb;
-                        cid[hi_at] = wa;
-                    }
-                }
-                sync();
-            }
-        }
-        for (int c = t; c < n_c; c += NT) clen[c] = len_at(cid[c] & kChunkMask);   // (the lengths were left where they were)
-        sync();
-        if (NW == 1 || wave == 0) {
-            const int per = (n_c + 63) >> 6, c0 = lane * per, c1 = c0 + per < n_c ? c0 + per : n_c;
-            int mine = 0;
-            for (int c = c0; c < c1; ++c) mine += clen[c];
-            int run = wave_incl_scan(mine) - mine;
-            for (int c = c0; c < c1; ++c) {
-                crem[c] = run;
-                run += clen[c];
-            }
-        }
-        sync();
-    }
-    // ---- tokens ranked before each candidate, and whether some row takes a token of it ----
-    for (int c = t; c < n_c; c += NT) {
-        const unsigned long long k = ckey[c];
-        const int w = cid[c], x = w & kChunkMask, pos = w >> kPosShift;
-        int run;
-        if (crowded) {
-            run = crem[c];
-        } else {
-            const int bin = bin_of(key_score(k));
-            const unsigned long long pb = place[bin];
-            const int j1 = (int)(pb & 0xffffull) < n_c ? (int)(pb & 0xffffull) : n_c;
-            run = (int)(pb >> 16);
-            for (int j = bin > 0 ? (int)(place[bin - 1] & 0xffffull) : 0; j < j1; ++j) {
-                const unsigned long long kj = ckey[j];
-                const int lj = clen[j];
-                if (kj > k || (kj == k && (cid[j] & kChunkMask) < x)) run += lj;
-            }
-        }
-        int rem = N_b - run;
-        const bool need = (pos == 2) ? (rem > 1) : (rem > 0);
-        if (blocks && rem > clen[c]) rem = clen[c];     // tokens of the chunk in the block's list
-        crem[c] = need ? rem : 0;
-        if (need) atomicOr(&kept[x >> 6], 1ull << (x & 63));
-    }
-    sync();
-
-    // ---- into the plan in ascending chunk id: listed chunks below word 2 lane + {0, 1} of `kept` ----
-    const int nw = (n + 63) >> 6;                       // at most 128
-    const int c0 = 2 * lane < nw ? __popcll(kept[2 * lane]) : 0, c1 = 2 * lane + 1 < nw ? __popcll(kept[2 * lane + 1]) : 0;
-    const int listed = wave_incl_scan(c0 + c1);
-    const int total = __builtin_amdgcn_readlane(listed, 63);
-    int32_t *entries = plan + pl.off_entries + ((int64_t)h * pl.N_q + l) * pl.stride * 2;
-    for (int cb = 0; cb < n_c; cb += NT) {              // whole waves: the shuffles need their lanes
-        const int c = cb + t < n_c ? cb + t : n_c - 1;
-        const int rem = cb + t < n_c ? crem[c] : 0, w = cid[c], x = w & kChunkMask, word = x >> 6;
-        const int even = __shfl(listed - c0 - c1, word >> 1), odd = __shfl(listed - c1, word >> 1);   // all lanes read
-        const int below = (word & 1) ? odd : even;
-        const int slot = below + __popcll(kept[word] & ((1ull << (x & 63)) - 1ull));
-        if (rem > 0 && slot < pl.stride) *reinterpret_cast<int2 *>(entries + 2 * slot) = make_int2(w, rem);
-    }
-    if (t == 0) plan[pl.off_count + (int64_t)h * pl.N_q + l] = total < pl.stride ? total : pl.stride;
-}
-
 template <int NW>
 __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, SelectArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -900,49 +412,11 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     if (r >= a.n_rows) return;           // NW == 1: waves do not wait for each other
     const int h = r / a.n_groups, l = r % a.n_groups;
     const int32_t *B = a.plan + a.pl.off_B;
-    select_row<NW>(a, Sc + ((int64_t)h * a.pl.N_q + l) * a.N_c, B, visible_chunks(a, B, l), h, l,
-                   smem + (size_t)(NW == 1 ? wave : 0) * a.row_bytes, s_red);
-}
-
-// ---------------------------------------------------------------------------
-// Scores of one query group against the chunks 0 .. n-1 by the NW waves of a workgroup: a wave takes 16 chunks at a time, as
-// columns, and repeats the group's vector as all 16 rows, so that a score is made of the same products in the same
-// order as in k_scores.  key(k): the pooled vector of chunk k.
-// ---------------------------------------------------------------------------
-template <int D, int NW, typename KEY>
-__device__ __forceinline__ void score_row(const double *q_c, const KEY &key, int n, double *s_row) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n16 = lane & 15, q = lane >> 4;
-    f64x2 a[D / 8], b[2][D / 8];
-    const auto load = [&](int k0, f64x2 (&to)[D / 8]) {
-        const double *Bm = key(k0 + n16 < n ? k0 + n16 : n - 1) + 2 * q;
-#pragma unroll
-        for (int s = 0; s < D / 8; ++s) to[s] = *reinterpret_cast<const f64x2 *>(Bm + 8 * s);
-    };
-    const auto block = [&](int k0, const f64x2 (&b_)[D / 8]) {
-        f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int s = 0; s < D / 8; ++s)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][j], b_[s][j], acc, 0, 0, 0);
-        if (q == 0 && k0 + n16 < n) s_row[k0 + n16] = acc[0];
-    };
-    int k0 = wave * 16;
-    if (k0 >= n) return;
-    load(k0, b[0]);
-#pragma unroll
-    for (int s = 0; s < D / 8; ++s) a[s] = *reinterpret_cast<const f64x2 *>(q_c + 2 * q + 8 * s);
-    __builtin_amdgcn_sched_barrier(0);
-    for (;; k0 += 32 * NW) {             // the next 16 chunks are requested before these are multiplied
-        if (k0 + 16 * NW < n) load(k0 + 16 * NW, b[1]);
-        __builtin_amdgcn_sched_barrier(0);
-        block(k0, b[0]);
-        if (k0 + 16 * NW >= n) break;
-        if (k0 + 32 * NW < n) load(k0 + 32 * NW, b[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        block(k0 + 16 * NW, b[1]);
-        if (k0 + 32 * NW >= n) break;
-    }
+    const int64_t group = (int64_t)h * a.pl.N_q + l;
+    int2 *entries = reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + group * a.pl.stride;
+    const int n = select_row<NW>(a, Sc + group * a.N_c, B, visible_chunks(a, B, l), smem + (size_t)(NW == 1 ? wave : 0) * a.row_bytes,
+                                 s_red, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    if ((NW == 1 ? threadIdx.x & 63 : threadIdx.x) == 0) a.plan[a.pl.off_count + group] = n;
 }
 
 // Scores and ranking of one (head, query group) by a workgroup of four waves, for problems of few groups and few chunks,
@@ -959,77 +433,11 @@ __global__ __launch_bounds__(256, 2) void k_score_select(const double *__restric
     const double *K = Kc + (int64_t)(h / G) * a.N_c * D;
     score_row<D, 4>(Qc + ((int64_t)h * a.pl.N_q + l) * D, [&](int k) { return K + (int64_t)k * D; }, vis.n, s_row);
     __syncthreads();
-    double *row = Sc + ((int64_t)h * a.pl.N_q + l) * a.N_c;
-    for (int x = threadIdx.x; x < vis.n; x += 256) row[x] = s_row[x];
-    select_row<4>(a, s_row, B, vis, h, l, smem, s_red);
-}
-
-// ---------------------------------------------------------------------------
-// Routing of one decoding step, all of it, by one workgroup of eight waves per query head: the open group's queries and the
-// new key chunks are pooled (the first four waves and the others side by side, in k_pool_decode's order), then scored and
-// ranked.  The heads of a kv-group pool the same key chunks; the first of them stores them for later steps.  Boundaries and
-// pooled keys that come with the step are taken from LDS, the others from the workspace.
-// ---------------------------------------------------------------------------
-constexpr int kRouteDecodeNew = 3;   // key chunks to pool: with the group's queries two rounds of the workgroup's halves
-
-template <typename T, int D>
-__global__ __launch_bounds__(512, 2) void k_route_decode(const T *__restrict__ Q, const T *__restrict__ K, BoundaryTail tail,
-                                                         int32_t *__restrict__ done, double *__restrict__ Kc, SelectArgs a,
-                                                         int H_kv, int G, int N_c_cap, int kc_valid, int rb0, int L,
-                                                         int pooling, int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l) {
-    constexpr int EPT = Elem<T>::kPer16, TPR = D / EPT, RG = 256 / TPR;   // as in k_pool_decode
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double s_sum[2][RG][D];
-    __shared__ double s_pool[1 + kRouteDecodeNew][D];       // the queries, then the new chunks
-    __shared__ unsigned long long s_red[8];
-    const int h = blockIdx.x, g = h / G, tid = threadIdx.x, half = __builtin_amdgcn_readfirstlane(tid >> 8), th = tid & 255;
-    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
-    int32_t *s_B = reinterpret_cast<int32_t *>(s_row + a.N_c);
-    int32_t *B = a.plan + a.pl.off_B, *RBw = a.plan + a.pl.off_RB;
-    for (int k = tid; k < kc_valid; k += 512) s_B[k] = B[k];
-    if (tid <= tail.n) s_B[kc_valid + tid] = tail.b[tid];
-    if (tid == 0) done[h] = 0;                              // slices of the head finished so far (k_attn_decode)
-    if (h == 0) {                                           // for the kernels after this one
-        if (tid <= tail.n) B[kc_valid + tid] = tail.b[tid];
-        if (tid == 0) { RBw[0] = rb0; RBw[1] = L; }
-    }
-    const int rg = th / TPR, col = (th % TPR) * EPT;
-    for (int x0 = 0; x0 <= tail.n; x0 += 2) {
-        const int x = x0 + half;
-        const bool is_q = x == 0;
-        const T *X = is_q ? Q + (int64_t)h * qs_h : K + (int64_t)g * ks_h;
-        const int64_t s_l = is_q ? qs_l : ks_l;
-        int b0 = rb0, b1 = L;
-        if (!is_q) { b0 = x <= tail.n ? tail.b[x - 1] : 0; b1 = x <= tail.n ? tail.b[x] : 0; }
-        double acc[EPT];
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) acc[e] = 0.0;
-        for (int i = b0 + rg; i < b1; i += RG) {
-            const uint4 u = *reinterpret_cast<const uint4 *>(X + (int64_t)i * s_l + col);
-            Elem<T>::unpack(u, acc);
-        }
-        if (x0 > 0) __syncthreads();
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) s_sum[half][rg][col + e] = acc[e];
-        __syncthreads();
-        if (th < D && x <= tail.n) {
-            double sum = 0.0;
-#pragma unroll 4
-            for (int r = 0; r < RG; ++r) sum += s_sum[half][r][th];
-            const double len = (double)(b1 - b0);
-            const double pooled = pooling == DHSA_POOL_MEAN ? sum / len                        // plain average (ablation)
-                                  : (is_q && a.B_r > 0)    ? sqrt((double)a.B_r) * (sum / len)  // Alg. 1 row blocks
-                                                           : (sqrt(len) / len) * sum;           // Eq. 4
-            s_pool[x][th] = pooled;
-            if (!is_q && h == g * G) Kc[((int64_t)g * N_c_cap + kc_valid + x - 1) * D + th] = pooled;
-        }
-    }
-    __syncthreads();
-    const double *Kg = Kc + (int64_t)g * N_c_cap * D;
-    score_row<D, 8>(s_pool[0], [&](int k) { return k < kc_valid ? Kg + (int64_t)k * D : s_pool[1 + k - kc_valid]; }, a.N_c, s_row);
-    __syncthreads();
-    const Visible vis = {a.B_r > 0 ? -1 : a.N_c - 1, L, a.N_c};   // the last group sees all chunks
-    select_row<8>(a, s_row, s_B, vis, h, 0, smem, s_red);
+    const int64_t group = (int64_t)h * a.pl.N_q + l;
+    for (int x = threadIdx.x; x < vis.n; x += 256) Sc[group * a.N_c + x] = s_row[x];
+    int2 *entries = reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + group * a.pl.stride;
+    const int n = select_row<4>(a, s_row, B, vis, smem, s_red, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    if (threadIdx.x == 0) a.plan[a.pl.off_count + group] = n;
 }
 
 // ---------------------------------------------------------------------------
@@ -1177,33 +585,6 @@ hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double
     const size_t shmem = row_bytes + 8 * (size_t)p.N_c;
     if (p.D == 64) hipLaunchKernelGGL(k_score_select<64>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
     else hipLaunchKernelGGL(k_score_select<128>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
-    return hipGetLastError();
-}
-
-// One launch instead of three while scoring all chunks by eight waves and pooling side by side take no longer than a launch.
-// A step in us, apart -> joined: 8 heads of 38 chunks 18.9 -> 16.2, with two chunks to pool 19.3 -> 18.0, 100 chunks 19.4 -> 17.8
-// and 19.8 -> 19.5, 128 chunks 19.4 -> 18.5 and 19.7 -> 20.2, 200 chunks 19.6 -> 21.6; 32 heads of 128 chunks 20.0 -> 18.9.
-// Long chunks, pooled by every head, would make the pooling the longest part.
-bool route_decode_ok(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail) {
-    int64_t longest = p.L - rb0;
-    for (int j = 0; j < tail.n; ++j) longest = std::max<int64_t>(longest, tail.b[j + 1] - tail.b[j]);
-    return tail.n > 0 && tail.n <= kRouteDecodeNew && p.N_c * tail.n <= 128 && longest <= 512 && pl.stride <= kSelMaxStride;
-}
-
-hipError_t launch_route_decode(const Prob &p, const PlanLayout &pl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
-                               const void *Q, const void *K, double *Kc, int32_t *plan, int32_t *done, hipStream_t s) {
-    const int cap = select_cap(pl.stride), row_bytes = (select_row_bytes(8, cap, p.N_c) + 15) / 16 * 16;
-    const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, p.N_q - 1, 1, 0, p.H_q, cap, row_bytes};
-    const size_t shmem = row_bytes + 8 * (size_t)p.N_c + 4 * (size_t)(p.N_c + 1);
-#define DHSA_ROUTED(T, DD)                                                                                              \
-    hipLaunchKernelGGL((k_route_decode<T, DD>), dim3(p.H_q), dim3(512), shmem, s, (const T *)Q, (const T *)K, tail, done, Kc, a, \
-                       p.H_kv, p.G, N_c_cap, kc_valid, rb0, (int)p.L, p.pooling, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
-    if (p.dtype == DHSA_F32) {
-        if (p.D == 64) DHSA_ROUTED(float, 64); else DHSA_ROUTED(float, 128);
-    } else {
-        if (p.D == 64) DHSA_ROUTED(bf16_t, 64); else DHSA_ROUTED(bf16_t, 128);
-    }
-#undef DHSA_ROUTED
     return hipGetLastError();
 }
 
