@@ -406,20 +406,23 @@ template <typename T, int D, bool ONE>
 __global__ __launch_bounds__(512, 2) void k_decode_few(AttendArgs<T> at, SelectArgs a, BoundaryTail tail, double *__restrict__ Kc,
                                                        int N_c_cap, int kc_valid, int pooling) {
     constexpr int EPT = Elem<T>::kPer16, TPR = D / EPT, RG = 256 / TPR;   // as in k_pool_decode
-    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double s_sum[2][RG][D];
     __shared__ __align__(16) double s_pool[1 + kDecodeFewNew][D];       // the queries, then the new chunks
-    __shared__ unsigned long long s_red[8];
+    __shared__ double s_row[kDecodeFewChunks];
+    __shared__ int32_t s_B[kDecodeFewChunks + 1];
+    __shared__ FewSmem<512, kDecodeFewChunks> s_few;
     __shared__ int2 s_ent[kDecodeFewChunks];
     __shared__ int s_count;
     __shared__ AttendSmem<T, D> sm;
     const int h = blockIdx.y, g = h / at.G, rb0 = at.rb0, L = at.L, tid = threadIdx.x;
     const bool first = !ONE || blockIdx.x == 0;             // of the head's workgroups
     const int half = __builtin_amdgcn_readfirstlane(tid >> 8), th = tid & 255;
-    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
-    int32_t *s_B = reinterpret_cast<int32_t *>(s_row + a.N_c);
+    // 16 chunks for each wave: their pooled keys are requested before anything is pooled
+    const int lane = tid & 63, k = (tid >> 6) * 16 + (lane & 15), k_c = k < a.N_c ? k : a.N_c - 1;
+    f64x2 key[D / 8];
+    load_pooled<D>(key, Kc + ((int64_t)g * N_c_cap + (k_c < kc_valid ? k_c : kc_valid - 1)) * D);
     int32_t *B = a.plan + a.pl.off_B;
-    for (int k = tid; k < kc_valid; k += 512) s_B[k] = B[k];
+    if (tid < kc_valid) s_B[tid] = B[tid];
     if (tid <= tail.n) s_B[kc_valid + tid] = tail.b[tid];
     if (first && h == 0 && tid <= tail.n) B[kc_valid + tid] = tail.b[tid];   // for later steps and launches
     const int rg = th / TPR, col = (th % TPR) * EPT;
@@ -454,12 +457,18 @@ __global__ __launch_bounds__(512, 2) void k_decode_few(AttendArgs<T> at, SelectA
         }
     }
     __syncthreads();
-    const double *Kg = Kc + (int64_t)g * N_c_cap * D;
-    score_row<D, 8>(s_pool[0], [&](int k) { return k < kc_valid ? Kg + (int64_t)k * D : s_pool[1 + k - kc_valid]; }, a.N_c, s_row);
+    if (k - (lane & 15) < a.N_c) {
+        if (k_c >= kc_valid) load_pooled<D>(key, s_pool[1 + k_c - kc_valid]);
+        f64x2 q[D / 8];
+        load_pooled<D>(q, s_pool[0]);
+        const double score = score_16<D>(q, key);
+        if (lane < 16 && k < a.N_c) s_row[k] = score;
+    }
     __syncthreads();
     const Visible vis = {a.B_r > 0 ? -1 : a.N_c - 1, L, a.N_c};   // the last group sees all chunks
     int2 *entries = ONE ? s_ent : reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + (int64_t)h * a.pl.stride;
-    const int n = select_row<8>(a, s_row, s_B, vis, smem, s_red, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    const int n = select_few<512, kDecodeFewChunks>(a, s_row, s_B, vis, s_few,
+                                                    [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
     if constexpr (ONE) {
         if (tid == 0) s_count = n;
         __syncthreads();
@@ -514,11 +523,9 @@ hipError_t launch_decode_step(const Prob &p, const DecodeLayout &dl, int N_c_cap
                   (int)p.L, p.N_b, p.G, p.scale, p.qs_h, p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l}
     hipError_t e;
     if (few) {
-        const int cap = select_cap(dl.pl.stride), row_bytes = (select_row_bytes(8, cap, p.N_c) + 15) / 16 * 16;
-        const SelectArgs a = {plan, dl.pl, p.N_c, p.N_b, p.B_r, p.N_q - 1, 1, 0, p.H_q, cap, row_bytes};
-        const size_t shmem = row_bytes + 8 * (size_t)p.N_c + 4 * (size_t)(p.N_c + 1);
+        const SelectArgs a = {plan, dl.pl, p.N_c, p.N_b, p.B_r, p.N_q - 1, 1, 0, p.H_q, 0, 0};
 #define DHSA_FEW1(T, DD, ONE)                                                                                                 \
-    hipLaunchKernelGGL((k_decode_few<T, DD, ONE>), dim3(ONE ? S : 1, p.H_q), dim3(512), shmem, s, DHSA_ARGS(T), a, tail, Kc, \
+    hipLaunchKernelGGL((k_decode_few<T, DD, ONE>), dim3(ONE ? S : 1, p.H_q), dim3(512), 0, s, DHSA_ARGS(T), a, tail, Kc, \
                        N_c_cap, kc_valid, p.pooling)
 #define DHSA_FEW(T, DD) do { if (fuse) DHSA_FEW1(T, DD, true); else DHSA_FEW1(T, DD, false); } while (0)
         DHSA_TYPES(DHSA_FEW);

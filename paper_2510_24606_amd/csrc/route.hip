@@ -421,22 +421,32 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
 
 // Scores and ranking of one (head, query group) by a workgroup of four waves, for problems of few groups and few chunks,
 // where a launch takes longer than the scores of a group.  Bound by a chain: one memory latency, 32 products in a row, the ranking.
+constexpr int kScoreSelectMax = 64;   // 16 chunks for each wave
+
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_score_select(const double *__restrict__ Qc, const double *__restrict__ Kc,
                                                          double *__restrict__ Sc, int G, SelectArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ unsigned long long s_red[4];
+    __shared__ double s_row[kScoreSelectMax];
+    __shared__ FewSmem<256, kScoreSelectMax> sm;
     const int h = blockIdx.x / a.n_groups, l = blockIdx.x % a.n_groups;
+    const int64_t group = (int64_t)h * a.pl.N_q + l;
     const int32_t *B = a.plan + a.pl.off_B;
     const Visible vis = visible_chunks(a, B, l);
-    double *s_row = reinterpret_cast<double *>(smem + a.row_bytes);
-    const double *K = Kc + (int64_t)(h / G) * a.N_c * D;
-    score_row<D, 4>(Qc + ((int64_t)h * a.pl.N_q + l) * D, [&](int k) { return K + (int64_t)k * D; }, vis.n, s_row);
+    const int lane = threadIdx.x & 63, k0 = (int)(threadIdx.x >> 6) * 16, k = k0 + (lane & 15);
+    if (k0 < vis.n) {
+        f64x2 q[D / 8], b[D / 8];
+        load_pooled<D>(b, Kc + ((int64_t)(h / G) * a.N_c + (k < vis.n ? k : vis.n - 1)) * D);
+        load_pooled<D>(q, Qc + group * D);
+        __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
+        const double score = score_16<D>(q, b);
+        if (lane < 16 && k < vis.n) {
+            s_row[k] = score;
+            Sc[group * a.N_c + k] = score;
+        }
+    }
     __syncthreads();
-    const int64_t group = (int64_t)h * a.pl.N_q + l;
-    for (int x = threadIdx.x; x < vis.n; x += 256) Sc[group * a.N_c + x] = s_row[x];
     int2 *entries = reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + group * a.pl.stride;
-    const int n = select_row<4>(a, s_row, B, vis, smem, s_red, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    const int n = select_few<256, kScoreSelectMax>(a, s_row, B, vis, sm, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
     if (threadIdx.x == 0) a.plan[a.pl.off_count + group] = n;
 }
 
@@ -573,18 +583,16 @@ hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, 
 // score all chunks in one go; from then on fifteen of sixteen rows of each product are what it pays for.  Routing in us,
 // two launches -> one: 8 heads of 25 chunks 13.3 -> 10.4, of 60 chunks 15.2 -> 13.8 (row blocks 15.5 -> 13.1), 4 heads of 100
 // chunks 15.2 -> 15.3, of 127 chunks 15.5 -> 18.9.  prefill of 1021 tokens 24.5 -> 21.8, of 2048 tokens in fp32 29.8 -> 27.4.
-constexpr int kScoreSelectMax = 64;
 bool score_select_ok(const Prob &p, const PlanLayout &pl) {
-    return (int64_t)p.H_q * p.N_q < 512 && p.N_c <= kScoreSelectMax && pl.stride <= kSelMaxStride;
+    return (int64_t)p.H_q * p.N_q < 512 && p.N_c <= kScoreSelectMax;
 }
 
 hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double *Qc, const double *Kc, double *Sc, int32_t *plan,
                                hipStream_t s) {
-    const int cap = select_cap(pl.stride), n_rows = p.H_q * p.N_q, row_bytes = (select_row_bytes(4, cap, p.N_c) + 15) / 16 * 16;
-    const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, n_rows, cap, row_bytes};
-    const size_t shmem = row_bytes + 8 * (size_t)p.N_c;
-    if (p.D == 64) hipLaunchKernelGGL(k_score_select<64>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
-    else hipLaunchKernelGGL(k_score_select<128>, dim3(n_rows), dim3(256), shmem, s, Qc, Kc, Sc, p.G, a);
+    const int n_rows = p.H_q * p.N_q;
+    const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, n_rows, 0, 0};
+    if (p.D == 64) hipLaunchKernelGGL(k_score_select<64>, dim3(n_rows), dim3(256), 0, s, Qc, Kc, Sc, p.G, a);
+    else hipLaunchKernelGGL(k_score_select<128>, dim3(n_rows), dim3(256), 0, s, Qc, Kc, Sc, p.G, a);
     return hipGetLastError();
 }
 
