@@ -257,8 +257,7 @@ dhsa_status dhsa_debug_scores(const dhsa_problem *prob, const int32_t *B_host, c
  * between its launches.  ms_host[0..7] (HOST floats) receive the milliseconds of:
  * 0 the launches that bring the boundaries into the plan (none, about 0, for up to
  * 959 chunks: they travel with the pooling), 1 chunk pooling (Eq. 4) and plan
- * set-up, 2 S_c, 3 ranking + budget (Alg. 1; with at most 64 chunks and 511 groups over all heads also S_c, 2 is
- * about 0 then), 4 / 5 / 6 the attention launches
+ * set-up, 2 S_c, 3 ranking + budget (Alg. 1; of few groups and at most 128 chunks also S_c, 2 is about 0 then), 4 / 5 / 6 the attention launches
  * (Alg. 3) of the row tiles of more than 64 rows / of 33..64 rows / of at most 32
  * rows (fp32 inputs: all rows in slot 4), 7 the whole call.  Tiles of a class that
  * has at most 512 over all heads may run in the launch of a taller class: their

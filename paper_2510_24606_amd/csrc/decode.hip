@@ -488,14 +488,16 @@ __global__ __launch_bounds__(512) void k_decode_combine(const float *__restrict_
     merge_slices<T, D, 512, false>(part + (int64_t)h * S * (D + 2), S, s_m, s_l, s_o, O_row + (int64_t)h * D);
 }
 
-// One launch instead of three while scoring all chunks by eight waves and pooling side by side take no longer than a launch.
-// A step in us, apart -> joined: 8 heads of 38 chunks 18.9 -> 16.2, with two chunks to pool 19.3 -> 18.0, 100 chunks 19.4 -> 17.8
-// and 19.8 -> 19.5, 128 chunks 19.4 -> 18.5 and 19.7 -> 20.2, 200 chunks 19.6 -> 21.6; 32 heads of 128 chunks 20.0 -> 18.9.
-// Long chunks, pooled by every head, would make the pooling the longest part.
-static bool decode_few(const Prob &p, const PlanLayout &pl, int rb0, const BoundaryTail &tail) {
+// Few chunks: one launch instead of three before the attention, or of four.  A step in us, launches apart -> this: 8 heads of 38
+// chunks 18.9 -> 13.0, with two and three chunks to pool 19.2 -> 14.7 and 15.0, of 128 chunks 19.5 -> 17.4, 19.8 -> 18.9 and
+// 19.2, of 16 chunks of 500 tokens 19.8 -> 13.9; 32 heads of 128 chunks, 512 keys 20.0 -> 17.7, 2048 keys (slices too many to be
+// routed one by one) 23.8 -> 23.1, with two chunks to pool 24.3 -> 25.2; 64 heads of 16 chunks of 500 tokens 28.6 -> 25.8, with two
+// and three to pool 33.5 -> 36.8 and 41.9: every head pools the chunks of its kv-head, one after the other.
+static bool decode_few(const Prob &p, int rb0, const BoundaryTail &tail, bool fuse) {
     int64_t longest = p.L - rb0;
     for (int j = 0; j < tail.n; ++j) longest = std::max<int64_t>(longest, tail.b[j + 1] - tail.b[j]);
-    return tail.n > 0 && tail.n <= kDecodeFewNew && p.N_c * tail.n <= kDecodeFewChunks && longest <= 512 && pl.stride <= kDecodeFewChunks;
+    if (p.N_c > kDecodeFewChunks || tail.n < 1 || tail.n > kDecodeFewNew) return false;
+    return tail.n == 1 ? longest <= 512 : fuse && longest <= 128;
 }
 
 hipError_t launch_decode_step(const Prob &p, const DecodeLayout &dl, int N_c_cap, int kc_valid, int rb0, const BoundaryTail &tail,
@@ -508,7 +510,7 @@ hipError_t launch_decode_step(const Prob &p, const DecodeLayout &dl, int N_c_cap
     float *part = reinterpret_cast<float *>(w8 + dl.off_part);
     const int slice = decode_slice(p.H_q, p.N_b);
     const int S = (p.N_b + slice - 1) / slice;           // N_b is clamped to L: the row takes exactly N_b keys
-    const bool fuse = slice < kDecSlice, few = decode_few(p, dl.pl, rb0, tail);
+    const bool fuse = slice < kDecSlice, few = decode_few(p, rb0, tail, fuse);
 #define DHSA_TYPES(CALL)                                                                       \
     do {                                                                                       \
         if (p.dtype == DHSA_F32) {                                                             \

@@ -195,7 +195,7 @@ dhsa_status route_impl(const Prob &p, const PlanLayout &pl, const WsLayout &wl, 
     if (launch_setup_pool(p, pl, Q, K, B_host, pw, wd + wl.off_Qc, wd + wl.off_Kc, s, ev) != hipSuccess)
         return DHSA_ERR_HIP;
     if (ev && hipEventRecord(ev[1], s) != hipSuccess) return DHSA_ERR_HIP;
-    const bool joined = score_select_ok(p, pl);
+    const bool joined = score_select_ok(p);
     if (joined && launch_score_select(p, pl, wd + wl.off_Qc, wd + wl.off_Kc, wd + wl.off_Sc, pw, s) != hipSuccess)
         return DHSA_ERR_HIP;
     if (!joined && launch_scores(p, wd + wl.off_Qc, wd + wl.off_Kc, pw + pl.off_B, pw + pl.off_RB, wd + wl.off_Sc, s) !=

@@ -118,7 +118,7 @@ hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, cons
                          const int32_t *RB_dev, double *Sc, hipStream_t s);
 hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, int32_t *plan, hipStream_t s);
 // the two in one launch, for problems that score_select_ok takes
-bool score_select_ok(const Prob &p, const PlanLayout &pl);
+bool score_select_ok(const Prob &p);
 hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double *Qc, const double *Kc, double *Sc, int32_t *plan,
                                hipStream_t s);
 // query groups [l_first, l_first + n_groups) only; `pl`, `Sc` and `plan` are indexed by group - l_first

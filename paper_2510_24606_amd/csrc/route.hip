@@ -419,15 +419,13 @@ __global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc
     if ((NW == 1 ? threadIdx.x & 63 : threadIdx.x) == 0) a.plan[a.pl.off_count + group] = n;
 }
 
-// Scores and ranking of one (head, query group) by a workgroup of four waves, for problems of few groups and few chunks,
+// Scores and ranking of one (head, query group) by a workgroup, for problems of few groups and few chunks,
 // where a launch takes longer than the scores of a group.  Bound by a chain: one memory latency, 32 products in a row, the ranking.
-constexpr int kScoreSelectMax = 64;   // 16 chunks for each wave
-
-template <int D>
-__global__ __launch_bounds__(256, 2) void k_score_select(const double *__restrict__ Qc, const double *__restrict__ Kc,
+template <int D, int X>   // at most X chunks, 16 for each wave
+__global__ __launch_bounds__(4 * X, X == 64 ? 2 : 1) void k_score_select(const double *__restrict__ Qc, const double *__restrict__ Kc,
                                                          double *__restrict__ Sc, int G, SelectArgs a) {
-    __shared__ double s_row[kScoreSelectMax];
-    __shared__ FewSmem<256, kScoreSelectMax> sm;
+    __shared__ double s_row[X];
+    __shared__ FewSmem<4 * X, X> sm;
     const int h = blockIdx.x / a.n_groups, l = blockIdx.x % a.n_groups;
     const int64_t group = (int64_t)h * a.pl.N_q + l;
     const int32_t *B = a.plan + a.pl.off_B;
@@ -446,7 +444,7 @@ __global__ __launch_bounds__(256, 2) void k_score_select(const double *__restric
     }
     __syncthreads();
     int2 *entries = reinterpret_cast<int2 *>(a.plan + a.pl.off_entries) + group * a.pl.stride;
-    const int n = select_few<256, kScoreSelectMax>(a, s_row, B, vis, sm, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
+    const int n = select_few<4 * X, X>(a, s_row, B, vis, sm, [&](int i, int w, int rem) { entries[i] = make_int2(w, rem); });
     if (threadIdx.x == 0) a.plan[a.pl.off_count + group] = n;
 }
 
@@ -579,20 +577,24 @@ hipError_t launch_select(const Prob &p, const PlanLayout &pl, const double *Sc, 
     return launch_select_groups(p, pl, Sc, plan, 0, p.N_q, s);
 }
 
-// A launch (and its scores' way through memory) costs more than scoring every group by itself while a workgroup's four waves
-// score all chunks in one go; from then on fifteen of sixteen rows of each product are what it pays for.  Routing in us,
-// two launches -> one: 8 heads of 25 chunks 13.3 -> 10.4, of 60 chunks 15.2 -> 13.8 (row blocks 15.5 -> 13.1), 4 heads of 100
-// chunks 15.2 -> 15.3, of 127 chunks 15.5 -> 18.9.  prefill of 1021 tokens 24.5 -> 21.8, of 2048 tokens in fp32 29.8 -> 27.4.
-bool score_select_ok(const Prob &p, const PlanLayout &pl) {
-    return (int64_t)p.H_q * p.N_q < 512 && p.N_c <= kScoreSelectMax;
+// A launch (and its scores' way through memory) costs more than scoring every group by itself while there is one product
+// chain or two for each SIMD; fifteen of sixteen rows of each product are what it pays for.  Routing in us, two launches ->
+// one, heads of 128 (heads of 64): 8 heads of 25 chunks 13.1 -> 8.4 (11.8 -> 8.1), of 60 chunks 14.8 -> 12.0 (13.1 -> 9.8), row
+// blocks 15.4 -> 11.4; 2 heads of 128 chunks 14.6 -> 13.9 (12.8 -> 11.4); 4 heads of 100 chunks 14.8 -> 17.5 (13.1 -> 11.4), of
+// 127 15.1 -> 22.8 (13.3 -> 14.3); 1 head of 140 chunks 14.5 -> 17.7 (12.8 -> 13.3).
+bool score_select_ok(const Prob &p) {
+    const int64_t rows = (int64_t)p.H_q * p.N_q;
+    return p.N_c <= 64 ? rows < 512 : p.N_c <= 128 && rows <= 256;
 }
 
 hipError_t launch_score_select(const Prob &p, const PlanLayout &pl, const double *Qc, const double *Kc, double *Sc, int32_t *plan,
                                hipStream_t s) {
     const int n_rows = p.H_q * p.N_q;
     const SelectArgs a = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, n_rows, 0, 0};
-    if (p.D == 64) hipLaunchKernelGGL(k_score_select<64>, dim3(n_rows), dim3(256), 0, s, Qc, Kc, Sc, p.G, a);
-    else hipLaunchKernelGGL(k_score_select<128>, dim3(n_rows), dim3(256), 0, s, Qc, Kc, Sc, p.G, a);
+#define DHSA_SCORE_SELECT(DD, X) hipLaunchKernelGGL((k_score_select<DD, X>), dim3(n_rows), dim3(4 * X), 0, s, Qc, Kc, Sc, p.G, a)
+    if (p.N_c <= 64) { if (p.D == 64) DHSA_SCORE_SELECT(64, 64); else DHSA_SCORE_SELECT(128, 64); }
+    else { if (p.D == 64) DHSA_SCORE_SELECT(64, 128); else DHSA_SCORE_SELECT(128, 128); }
+#undef DHSA_SCORE_SELECT
     return hipGetLastError();
 }
 

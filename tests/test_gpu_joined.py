@@ -22,7 +22,7 @@ def boundaries(N_c, longest, seed):
 @pytest.mark.parametrize("N_c,D,dtype,B_r,pooling", [
     (1, 128, "bf16", 0, 0), (2, 64, "f32", 0, 0), (15, 128, "f32", 0, 1), (16, 64, "bf16", 0, 0), (17, 128, "bf16", 7, 0),
     (33, 128, "bf16", 0, 0), (48, 64, "f32", 32, 1), (63, 128, "bf16", 100, 0), (64, 128, "f32", 0, 0), (64, 64, "bf16", 0, 0),
-    (65, 128, "bf16", 0, 0)])
+    (65, 128, "bf16", 0, 0), (100, 64, "f32", 0, 0), (128, 128, "bf16", 0, 1), (128, 64, "bf16", 33, 0), (129, 128, "bf16", 0, 0)])
 def test_few_groups_get_the_scores_and_plans_of_many(N_c, D, dtype, B_r, pooling):
     B = boundaries(N_c, 20, N_c)
     L = int(B[-1])
@@ -52,7 +52,7 @@ def test_few_groups_get_the_scores_and_plans_of_many(N_c, D, dtype, B_r, pooling
 
 @pytest.mark.parametrize("N_c,n_new,D,dtype,B_r,pooling", [
     (2, 1, 128, "bf16", 0, 0), (5, 3, 64, "f32", 0, 1), (16, 2, 128, "bf16", 0, 0), (17, 1, 128, "f32", 0, 0), (40, 3, 64, "bf16", 50, 0),
-    (64, 2, 128, "bf16", 128, 1), (100, 1, 128, "bf16", 0, 0), (128, 1, 64, "f32", 0, 0), (129, 1, 128, "bf16", 0, 0)])
+    (64, 2, 128, "bf16", 128, 1), (100, 1, 128, "bf16", 0, 0), (128, 1, 64, "f32", 0, 0), (128, 3, 128, "bf16", 0, 0), (129, 1, 128, "bf16", 0, 0)])
 def test_joined_decoding_steps_give_what_separate_ones_give(N_c, n_new, D, dtype, B_r, pooling):
     B = boundaries(N_c, 60, N_c)
     L = int(B[-1])
