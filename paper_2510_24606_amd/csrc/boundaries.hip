@@ -19,7 +19,7 @@
 //     sequence -- long monotone runs, windows of more tokens than the halo has --
 //     and compacts the kept positions into B.
 //
-// Bound by latency (0.5 MB of scores at L = 131072): 9 + 10 us, against 1.1 ms when one
+// Bound by latency (0.5 MB of scores at L = 131072): 6.4 + 6.2 us, against 1.1 ms when one
 // workgroup did all of it in rounds from memory.
 //
 // Rounds of k_nms_finish: a still undecided candidate that is
@@ -71,8 +71,12 @@ __device__ __forceinline__ void nms_mark(unsigned *bits, int64_t lo, int64_t hi)
 constexpr int kNmsSeg = 512;                          // positions decided by one workgroup
 constexpr int kNmsHaloMax = 512;                      // positions looked at on each side (a multiple of 64)
 constexpr int kNmsWinMax = kNmsSeg + 2 * kNmsHaloMax;
+// A thread for each position of the smallest window: a round is a chain of LDS reads, which a thread with three positions
+// goes through three times: 131072 positions 9.7 -> 6.4 us.
+constexpr int kNmsWinThreads = kNmsSeg + 2 * 128;
+static_assert(kNmsWinMax % kNmsWinThreads == 0, "whole passes");
 
-__global__ __launch_bounds__(256) void k_nms_windows(const float *__restrict__ p, int64_t L, float tau, int W, int H,
+__global__ __launch_bounds__(kNmsWinThreads) void k_nms_windows(const float *__restrict__ p, int64_t L, float tau, int W, int H,
                                                      uint8_t *__restrict__ st) {
     __shared__ float s_p[kNmsWinMax];
     __shared__ unsigned long long s_und[kNmsWinMax / 64], s_kept[kNmsWinMax / 64];
@@ -85,15 +89,15 @@ __global__ __launch_bounds__(256) void k_nms_windows(const float *__restrict__ p
     volatile unsigned long long *und = s_und, *kept = s_kept;
 
     // candidates: score strictly above the threshold (a NaN never is)
-    float pr[kNmsWinMax / 256];
+    float pr[kNmsWinMax / kNmsWinThreads];
 #pragma unroll
-    for (int e = 0; e < kNmsWinMax / 256; ++e) {
-        const int x = e * 256 + tid;
+    for (int e = 0; e < kNmsWinMax / kNmsWinThreads; ++e) {
+        const int x = e * kNmsWinThreads + tid;
         pr[e] = x < n ? p[win0 + x] : 0.f;
     }
 #pragma unroll
-    for (int e = 0; e < kNmsWinMax / 256; ++e) {
-        const int x = e * 256 + tid;
+    for (int e = 0; e < kNmsWinMax / kNmsWinThreads; ++e) {
+        const int x = e * kNmsWinThreads + tid;
         const unsigned long long c = __ballot(x < n && pr[e] > tau);
         s_p[x] = pr[e];
         if (lane == 0) { s_und[x >> 6] = c; s_kept[x >> 6] = 0ull; }
@@ -102,8 +106,8 @@ __global__ __launch_bounds__(256) void k_nms_windows(const float *__restrict__ p
     for (;;) {   // every round but the last decides a candidate
         int decided = 0;
 #pragma unroll
-        for (int e = 0; e < kNmsWinMax / 256; ++e) {
-            const int x = e * 256 + tid;
+        for (int e = 0; e < kNmsWinMax / kNmsWinThreads; ++e) {
+            const int x = e * kNmsWinThreads + tid;
             if (x >= n || !((und[x >> 6] >> lane) & 1ull)) continue;
             const float px = pr[e];
             bool blocked = (W > x && open_lo) || (W >= n - x && open_hi);   // an unseen neighbour may be better
@@ -157,6 +161,7 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
     __shared__ int s_und;          // candidates still undecided
     __shared__ int s_any;          // does the next round have a block to visit?
     __shared__ int s_stage[kNmsStage];
+    __shared__ __align__(16) uint16_t s_kept[kNmsThreads * kNmsPer / 16];   // bits of kept positions: a slab, or all of a short sequence
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t NB = (L + 63) >> 6, NW = (NB + 31) >> 5;   // 64-position blocks, bitmap words
     const int64_t n16 = (L + 255) / 256 * 16;                // 16-byte pieces of the state array
@@ -164,6 +169,16 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
 
     // how many candidates the windows left undecided (state kUndecided; no other state has been written yet
     // with its low bit set)
+    // A sequence of one slab leaves its kept positions in LDS by the way: reading the states again, 128 bytes in a row for a
+    // thread, made 10.0 us of the kernel's 6.2 at L = 131072.
+    const bool once = n16 <= (int64_t)kNmsThreads * 8;
+    const auto kept_bits = [](const uint4 &v) {   // kKept is bit 1 of a state byte: gather the bits of 16
+        const unsigned w[4] = {(v.x >> 1) & 0x01010101u, (v.y >> 1) & 0x01010101u, (v.z >> 1) & 0x01010101u, (v.w >> 1) & 0x01010101u};
+        unsigned bits = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bits |= ((w[j] * 0x10204080u) >> 28) << (4 * j);
+        return (uint16_t)bits;
+    };
     int und = 0;
     for (int64_t i = tid; i < n16; i += kNmsThreads * 8) {
         uint4 v[8];
@@ -173,11 +188,14 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
             v[e] = at < n16 ? reinterpret_cast<const uint4 *>(st)[at] : uint4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
+        for (int e = 0; e < 8; ++e) {
             und += __popc(v[e].x & 0x01010101u) + __popc(v[e].y & 0x01010101u) + __popc(v[e].z & 0x01010101u) +
                    __popc(v[e].w & 0x01010101u);
+            if (once) s_kept[tid + e * kNmsThreads] = kept_bits(v[e]);
+        }
     }
     int und_now = __syncthreads_count(und > 0);
+    const bool in_lds = once && und_now == 0;
     if (und_now > 0) {             // (the bitmaps serve the rounds only)
         for (int64_t w = tid; w < NW; w += kNmsThreads) { dirtyA[w] = 0xffffffffu; dirtyB[w] = 0u; dirtyN[w] = 0u; }
         // A candidate next to a segment's border may be undecided although the window on the other side of the border
@@ -300,22 +318,20 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
     int base = 1;                              // B_out[0] = 0
     for (int64_t s0 = 0; s0 < L - 1; s0 += (int64_t)kNmsThreads * kNmsPer) {
         const int64_t i0 = s0 + (int64_t)tid * kNmsPer;
-        unsigned kb[kNmsPer / 32];
         int mine = 0;
-        uint4 v[kNmsPer / 16];
+        if (!in_lds) {
+            __syncthreads();                   // the slab before is done with
 #pragma unroll
-        for (int e = 0; e < kNmsPer / 16; ++e)
-            v[e] = (i0 >> 4) + e < n16 ? reinterpret_cast<const uint4 *>(st + i0)[e] : uint4{0u, 0u, 0u, 0u};
+            for (int e = 0; e < kNmsPer / 16; ++e) {
+                const int64_t at = (s0 >> 4) + e * kNmsThreads + tid;
+                s_kept[e * kNmsThreads + tid] = kept_bits(at < n16 ? reinterpret_cast<const uint4 *>(st)[at] : uint4{0u, 0u, 0u, 0u});
+            }
+            __syncthreads();
+        }
+        const uint4 k4 = *reinterpret_cast<const uint4 *>(&s_kept[tid * (kNmsPer / 16)]);
+        unsigned kb[kNmsPer / 32] = {k4.x, k4.y, k4.z, k4.w};
 #pragma unroll
         for (int e = 0; e < kNmsPer / 32; ++e) {
-            const unsigned w8[8] = {v[2 * e].x, v[2 * e].y, v[2 * e].z, v[2 * e].w,
-                                    v[2 * e + 1].x, v[2 * e + 1].y, v[2 * e + 1].z, v[2 * e + 1].w};
-            kb[e] = 0u;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {      // kKept is bit 1 of a state byte: gather four of them
-                const unsigned t = (w8[j] >> 1) & 0x01010101u;
-                kb[e] |= ((t * 0x10204080u) >> 28) << (4 * j);
-            }
             const int64_t r0 = i0 + 32 * e;
             if (r0 + 32 > L - 1) kb[e] = r0 < L - 1 ? kb[e] & ((1u << (unsigned)(L - 1 - r0)) - 1u) : 0u;
             mine += __popc(kb[e]);
@@ -376,7 +392,7 @@ extern "C" __attribute__((visibility("default"))) dhsa_status dhsa_finalize_boun
     // halo: sixteen windows of tokens, where a decision has long been taken in scores that do not rise
     // monotonically; at least 128 positions (cheap), at most what the LDS arrays hold
     const int H = (int)std::min<int64_t>(kNmsHaloMax, std::max<int64_t>(128, ((int64_t)window * 16 + 63) / 64 * 64));
-    hipLaunchKernelGGL(k_nms_windows, dim3((unsigned)((L + kNmsSeg - 1) / kNmsSeg)), dim3(256), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(k_nms_windows, dim3((unsigned)((L + kNmsSeg - 1) / kNmsSeg)), dim3(kNmsWinThreads), 0, (hipStream_t)stream,
                        scores_dev, L, threshold, (int)window, H, st);
     if (hipGetLastError() != hipSuccess) return DHSA_ERR_HIP;
     hipLaunchKernelGGL(k_nms_finish, dim3(1), dim3(kNmsThreads), 0, (hipStream_t)stream, scores_dev, L, (int)window, st,

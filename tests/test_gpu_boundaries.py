@@ -90,3 +90,14 @@ def test_boundaries_feed_the_path():
         np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref[h])
     err = np.abs(O[:, torch.from_numpy(rows).cuda()].float().cpu().numpy().astype(np.float64) - O_ref).max()
     assert err <= 2e-2, err
+
+
+@pytest.mark.parametrize("L", [511, 768, 769, 131071, 131072, 131073, 262145])
+@pytest.mark.parametrize("kind,W", [("peaks", 8), ("noise", 33), ("mixed", 8)])
+def test_edges_of_passes_and_slabs(kind, L, W):
+    """Windows of one and two passes, sequences of one slab and more, with candidates left for the rounds and without."""
+    p = scores("peaks" if kind == "mixed" else kind, L, L)
+    if kind == "mixed":          # a run that no window decides, among ordinary peaks
+        p[L // 3:L // 3 + 900] = np.linspace(0.5, 0.9, len(p[L // 3:L // 3 + 900]))
+    p[-1] = p[0] = 1.0
+    np.testing.assert_array_equal(dhsa.dhsa_finalize_boundaries(torch.from_numpy(p).cuda(), 0.4, W), oracle.finalize_boundaries(p, 0.4, W))
