@@ -423,8 +423,12 @@ __global__ __launch_bounds__(512, 2) void k_decode_few(AttendArgs<T> at, SelectA
     load_pooled<D>(key, Kc + ((int64_t)g * N_c_cap + (k_c < kc_valid ? k_c : kc_valid - 1)) * D);
     int32_t *B = a.plan + a.pl.off_B;
     if (tid < kc_valid) s_B[tid] = B[tid];
-    if (tid <= tail.n) s_B[kc_valid + tid] = tail.b[tid];
-    if (first && h == 0 && tid <= tail.n) B[kc_valid + tid] = tail.b[tid];   // for later steps and launches
+#pragma unroll
+    for (int j = 0; j <= kDecodeFewNew; ++j)                // (from scalar registers: kernel arguments are far from the vector unit)
+        if (tid == 64 * j && j <= tail.n) {
+            s_B[kc_valid + j] = tail.b[j];
+            if (first && h == 0) B[kc_valid + j] = tail.b[j];   // for later steps and launches
+        }
     const int rg = th / TPR, col = (th % TPR) * EPT;
     for (int x0 = 0; x0 <= tail.n; x0 += 2) {
         const int x = x0 + half;

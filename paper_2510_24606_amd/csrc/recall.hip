@@ -4,8 +4,8 @@
 // attention scores, k = min(N_b, i + 1), equal scores by lower index).
 //
 // Two kernels:
-//   k_recall_logits  logits q_i . k_j, j <= i, in fp64, summed in the order d = 0, 1, ... by one
-//      thread per key (the products of bf16 / fp32 values are exact in fp64, so the
+//   k_recall_logits  logits q_i . k_j, j <= i, in fp64, summed in the order d = 0, 1, ...
+//      (the products of bf16 / fp32 values are exact in fp64, so the
 //      value is the same on any machine that sums in that order), stored as
 //      order-preserving 64-bit integers in the caller's workspace;
 //   k_recall_count  one workgroup per sampled row: the k-th largest of them by a
@@ -28,93 +28,106 @@ struct RecallRows {
     int32_t row[kRecallRows];
 };
 
-// A thread owns kLgKeys keys and kLgRows of the sampled rows, so that an element of q read from LDS
-// (a broadcast) serves kLgKeys products and a converted element of K serves kLgRows.  Bound by
-// the fp64 rate of the vector unit and the LDS reads of q, about equally.  A key row is
-// read 64 bytes at a time by its thread.  48 rows of L = 32768, D = 128: 24 us.
-constexpr int kLgKeys = 2, kLgRows = 8;
+// Logits by the fp64 matrix unit, 16 sampled rows x 16 keys a product: v_mfma_f64_16x16x4_f64 adds the products of its four d
+// to the sum one after the other, d ascending, each rounded once -- the fused multiply-adds of the order above, bit for bit
+// (checked against them over 650000 sums of bf16 and fp32 values; infinities and NaN included).  Lane 16 q + n supplies d = 4 s + q
+// of row n and of key n to product s.  A wave keeps its rows in registers, converted, and takes kLgTiles times 16
+// keys; the four lanes of a key read a quarter of its row each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024
+// multiply-adds takes 64 cycles) and the memory latency in front of it: 48 rows of L = 32768, D = 128 16 us; 24.6 us on the
+// vector unit, with the rows' elements broadcast from LDS, whose reads were what took the time; 26 us when every lane read all
+// of its key's row.
+constexpr int kLgRows = 16, kLgTiles = 1, kLgKeys = 4 * 16 * kLgTiles;   // rows, keys of a wave in 16s, keys of a workgroup
 
-template <typename T> struct RecallElem;
-template <> struct RecallElem<float> {
-    static constexpr int kPerWord = 1;
-    __device__ static double get(uint32_t w, int) { return (double)__uint_as_float(w); }
-    __device__ static double load(const float *p) { return (double)*p; }
-};
-template <> struct RecallElem<bf16_t> {
-    static constexpr int kPerWord = 2;
-    __device__ static double get(uint32_t w, int half) {
-        return (double)__uint_as_float(half ? w & 0xffff0000u : w << 16);
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// This lane's elements d = 4 s + q of a row, in fp64
+template <typename T, int D> struct RecallRow;
+template <int D> struct RecallRow<float, D> {
+    float v[D / 4];
+    __device__ void load(const float *row, int q) {
+#pragma unroll
+        for (int s = 0; s < D / 4; ++s) v[s] = row[4 * s + q];
     }
-    __device__ static double load(const bf16_t *p) { return (double)__uint_as_float((uint32_t)p->bits << 16); }
+    __device__ void deal() {}
+    __device__ double get(int s, int) const { return (double)v[s]; }
+};
+template <int D> struct RecallRow<bf16_t, D> {
+    // w: the 16-byte pieces 4 m + q of the row; v[m][i]: two elements, one of them this lane's, of product 8 m + i
+    unsigned w[D / 32][4], v[D / 32][8];
+    __device__ void load(const bf16_t *row, int q) {
+#pragma unroll
+        for (int m = 0; m < D / 32; ++m) {
+            const uint4 u = reinterpret_cast<const uint4 *>(row)[4 * m + q];
+            w[m][0] = u.x; w[m][1] = u.y; w[m][2] = u.z; w[m][3] = u.w;
+        }
+    }
+    // Product 2 P + half takes element q of four from word 2 half + (q >> 1) of piece P: words 0 and 2 of all four pieces go to
+    // the lower half of the wave, 1 and 3 to the upper one, then the two 16s of a half give one another theirs.
+    __device__ void deal() {
+#pragma unroll
+        for (int m = 0; m < D / 32; ++m)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const auto a = __builtin_amdgcn_permlane32_swap(w[m][2 * half], w[m][2 * half + 1], false, false);
+                const auto b = __builtin_amdgcn_permlane16_swap(a[0], a[0], false, false);   // pieces 0 and 1 of four
+                const auto c = __builtin_amdgcn_permlane16_swap(a[1], a[1], false, false);   // 2 and 3
+                v[m][half] = b[0]; v[m][2 + half] = b[1]; v[m][4 + half] = c[0]; v[m][6 + half] = c[1];
+            }
+    }
+    __device__ double get(int s, int q) const {          // the 16 bits of the lane's element, above zeros
+        const unsigned x = v[s / 8][s % 8];
+        return (double)__uint_as_float(q & 1 ? x & 0xffff0000u : x << 16);
+    }
 };
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void k_recall_logits(PlanView pv, const T *__restrict__ Q, const T *__restrict__ K,
-                                                       int G, int head, RecallRows rows, int64_t L,
-                                                       unsigned long long *__restrict__ ws, int64_t qs_h, int64_t qs_l,
-                                                       int64_t ks_h, int64_t ks_l) {
-    __shared__ double s_q[kLgRows][D];
-    if (!plan_matches(pv)) return;   // not this problem's plan: nothing is written
-    const int tid = threadIdx.x;
+__global__ __launch_bounds__(256, 2) void k_recall_logits(PlanView pv, const T *__restrict__ Q, const T *__restrict__ K,
+                                                          int G, int head, RecallRows rows, int64_t L,
+                                                          unsigned long long *__restrict__ ws, int64_t qs_h, int64_t qs_l,
+                                                          int64_t ks_h, int64_t ks_l) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n16 = lane & 15, q = lane >> 4;
     const int t0 = blockIdx.y * kLgRows;
     const int nr = rows.n - t0 < kLgRows ? rows.n - t0 : kLgRows;
-    int last = 0;                    // last row of the group
-    for (int r = 0; r < nr; ++r) last = rows.row[t0 + r] > last ? rows.row[t0 + r] : last;
-    const int j0 = blockIdx.x * 256 * kLgKeys;
-    if (j0 > last) return;           // no row sees these keys (block-uniform)
-    for (int x = tid; x < kLgRows * D; x += 256) {
-        const int r = x / D < nr ? x / D : 0;
-        s_q[x / D][x % D] = RecallElem<T>::load(Q + (int64_t)head * qs_h + (int64_t)rows.row[t0 + r] * qs_l + x % D);
+    int my_row = rows.row[t0], last = my_row;   // the lane's row; the last of the group
+#pragma unroll
+    for (int r = 1; r < kLgRows; ++r) {         // (scalar loads: the vector unit reads kernel arguments from far away)
+        const int i = rows.row[t0 + (r < nr ? r : 0)];
+        my_row = n16 == r ? i : my_row;
+        last = i > last ? i : last;
     }
-    __syncthreads();
-    const T *kr[kLgKeys];
+    const int j0 = blockIdx.x * kLgKeys + wave * 16 * kLgTiles;
+    if (!plan_matches(pv)) return;   // not this problem's plan: nothing is written
+    if (j0 > last) return;           // no row sees these keys
+    RecallRow<T, D> kr[kLgTiles], qr;
+    qr.load(Q + (int64_t)head * qs_h + (int64_t)my_row * qs_l, q);
 #pragma unroll
-    for (int k = 0; k < kLgKeys; ++k) {
-        const int j = j0 + k * 256 + tid;
-        kr[k] = K + (int64_t)(head / G) * ks_h + (int64_t)(j < last ? j : last) * ks_l;   // a row that exists
+    for (int k = 0; k < kLgTiles; ++k) {
+        const int j = j0 + 16 * k + n16;
+        kr[k].load(K + (int64_t)(head / G) * ks_h + (int64_t)(j < last ? j : last) * ks_l, q);   // a row that exists
     }
-    double acc[kLgKeys][kLgRows];
+    __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
+    qr.deal();
 #pragma unroll
-    for (int k = 0; k < kLgKeys; ++k)
+    for (int k = 0; k < kLgTiles; ++k) kr[k].deal();
+    f64x4 acc[kLgTiles];
 #pragma unroll
-        for (int r = 0; r < kLgRows; ++r) acc[k][r] = 0.0;
-    constexpr int kEl = 64 / (int)sizeof(T);            // elements per 64 bytes
-#pragma unroll 1   // all of D at once makes <float, 64> spill 774 registers: 426 us at that size, 39 us so
-    for (int d0 = 0; d0 < D; d0 += kEl) {
-        uint4 u[kLgKeys][4];
+    for (int k = 0; k < kLgTiles; ++k) acc[k] = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int k = 0; k < kLgKeys; ++k)
+    for (int s = 0; s < D / 4; ++s) {
+        const double a = qr.get(s, q);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) u[k][c] = reinterpret_cast<const uint4 *>(kr[k] + d0)[c];
-#pragma unroll
-        for (int w = 0; w < 16; ++w)
-#pragma unroll
-            for (int half = 0; half < RecallElem<T>::kPerWord; ++half) {
-                double kx[kLgKeys];
-#pragma unroll
-                for (int k = 0; k < kLgKeys; ++k) {
-                    const uint4 &v = u[k][w / 4];
-                    const uint32_t word = (w & 3) == 0 ? v.x : (w & 3) == 1 ? v.y : (w & 3) == 2 ? v.z : v.w;
-                    kx[k] = RecallElem<T>::get(word, half);
-                }
-                const int d = d0 + w * RecallElem<T>::kPerWord + half;
-#pragma unroll
-                for (int r = 0; r < kLgRows; ++r)
-#pragma unroll
-                    for (int k = 0; k < kLgKeys; ++k) acc[k][r] = __builtin_fma(s_q[r][d], kx[k], acc[k][r]);
-            }
+        for (int k = 0; k < kLgTiles; ++k) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, kr[k].get(s, q), acc[k], 0, 0, 0);
     }
 #pragma unroll
-    for (int r = 0; r < kLgRows; ++r) {
-        if (r >= nr) break;
-        const int i = rows.row[t0 + r];
+    for (int v = 0; v < 4; ++v) {    // element v of a lane: row 4 v + q, key n
+        const int r = 4 * v + q, i = __shfl(my_row, r);
 #pragma unroll
-        for (int k = 0; k < kLgKeys; ++k) {
-            const int j = j0 + k * 256 + tid;
-            double x = acc[k][r];
+        for (int k = 0; k < kLgTiles; ++k) {
+            const int j = j0 + 16 * k + n16;
+            double x = acc[k][v];
             if (x == 0.0) x = 0.0;                       // -0.0 ties with +0.0
             const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-            if (j <= i) ws[(int64_t)(t0 + r) * L + j] = (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+            if (r < nr && j <= i) ws[(int64_t)(t0 + r) * L + j] = (u >> 63) ? ~u : (u | 0x8000000000000000ull);
         }
     }
 }
@@ -124,8 +137,8 @@ __global__ __launch_bounds__(256) void k_recall_logits(PlanView pv, const T *__r
 // the mantissa: narrower ones would put most logits into two or three counters) and are
 // counted from memory; a region of at most kRcCand keys moves into LDS and is finished there
 // with 8-bit digits.  The select ends early when every key of the region belongs to the
-// top set.  Bound by latency: one CU reads the row's keys twice (256 KB each time at n = 32768;
-// 21 us for 48 rows).  Ties at the threshold: where the last equal key of the top set lies is found once, by counting.
+// top set.  Bound by the instructions of one CU, which goes through the row's keys twice (256 KB each time at n = 32768;
+// 17 us for 48 rows).  Ties at the threshold: where the last equal key of the top set lies is found once, by counting.
 // ---------------------------------------------------------------------------
 constexpr int kRcThreads = 1024;
 constexpr int kRcBits = 14;
@@ -135,7 +148,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
                                                              const unsigned long long *__restrict__ ws,
                                                              int32_t *__restrict__ hits_out,
                                                              int32_t *__restrict__ size_out) {
-    __shared__ int s_hist[1 << kRcBits];
+    __shared__ __align__(16) int s_hist[1 << kRcBits];
     __shared__ unsigned long long s_cand[kRcCand];
     __shared__ int s_wave[kRcThreads / 64];
     __shared__ unsigned long long s_bits[kRcThreads / 64][2];
@@ -148,6 +161,37 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     const unsigned long long *key = ws + (int64_t)t * L;
     for (int x = tid; x < pv.N_q; x += kRcThreads)       // the row's query group
         if (pv.RB[x] <= i && i < pv.RB[x + 1]) s_l = x;
+    // All keys of a row, eight requested at a time
+    const auto for_keys = [&](const auto &get, const auto &body) {
+        for (int j0 = tid; j0 < n; j0 += 8 * kRcThreads) {
+            decltype(get(0)) u[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) u[e] = get(j0 + e * kRcThreads < n ? j0 + e * kRcThreads : 0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (j0 + e * kRcThreads < n) body(u[e]);
+        }
+    };
+    const auto whole = [&](int j) { return key[j]; };
+    const auto upper = [&](int j) { return reinterpret_cast<const unsigned *>(key)[2 * j + 1]; };
+    __syncthreads();
+    // Lane x of a wave has plan entry 64 wave + x of every 1024: its chunk's first token and the tokens the row takes
+    const int l = s_l;
+    const int v = i + 1 - pv.RB[l];
+    const int E = pv.count[(int64_t)head * pv.N_q + l];
+    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)head * pv.N_q + l) * pv.stride;
+    const auto entry = [&](int e, int &b0, int &take) {
+        const int2 w = e < E ? ent[e] : int2{0, 0};
+        const int k = w.x & kChunkMask, pos = w.x >> kPosShift;
+        b0 = pv.B[k];
+        take = e < E ? entry_take(pos, w.y, pv.B[k + 1] - b0, v) : 0;
+        if (pos == 3) {                                  // row-block form: listed keys above the row are masked
+            const int vis = i + 1 - b0;
+            if (vis < take) take = vis > 0 ? vis : 0;
+        }
+    };
+    int b0_e, take_e;                                    // of the first 1024: their loads do not wait for the threshold
+    entry(lane * (kRcThreads / 64) + wave, b0_e, take_e);
 
     // ---- threshold: the k_top-th largest key is the want-th largest of the region, the keys whose bits from
     // `shift` up equal `prefix`; above = keys larger than the region's, equal = keys of the region ----
@@ -158,14 +202,11 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
         if (!in_lds && equal <= kRcCand) {
             if (tid == 0) s_n = 0;
             __syncthreads();
-            for (int j0 = tid; j0 < n; j0 += 8 * kRcThreads) {
-                unsigned long long u[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) u[e] = j0 + e * kRcThreads < n ? key[j0 + e * kRcThreads] : 0ull;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (j0 + e * kRcThreads < n && (shift == 64 || (u[e] >> shift) == prefix)) s_cand[atomicAdd(&s_n, 1)] = u[e];
-            }
+            const auto take = [&](unsigned long long u) { s_cand[atomicAdd(&s_n, 1)] = u; };
+            if (shift == 64) for_keys(whole, take);
+            else if (shift >= 32)        // (one CU goes through all keys of the row: 32-bit instructions where they do)
+                for_keys(whole, [&](unsigned long long u) { if ((unsigned)(u >> 32) >> (shift - 32) == (unsigned)prefix) take(u); });
+            else for_keys(whole, [&](unsigned long long u) { if ((u >> shift) == prefix) take(u); });
             in_lds = true;
             __syncthreads();
         }
@@ -200,33 +241,57 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
                 if (shift == 64 || (u >> shift) == prefix) atomicAdd(&s_hist[(int)(u >> lower) & (bins - 1)], 1);
             }
         } else {
-            for (int j0 = tid; j0 < n; j0 += 8 * kRcThreads) {
-                unsigned long long u[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) u[e] = j0 + e * kRcThreads < n ? key[j0 + e * kRcThreads] : 0ull;
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (j0 + e * kRcThreads < n && (shift == 64 || (u[e] >> shift) == prefix))
-                        atomicAdd(&s_hist[(int)(u[e] >> lower) & (bins - 1)], 1);
-            }
+            if (shift == 64) for_keys(upper, [&](unsigned u) { atomicAdd(&s_hist[u >> (32 - kRcBits)], 1); });
+            else for_keys(whole, [&](unsigned long long u) { if ((u >> shift) == prefix) atomicAdd(&s_hist[(int)(u >> lower) & (bins - 1)], 1); });
         }
         __syncthreads();
-        // counts from the largest digit down: thread t holds the digits below bins - per t
-        const int per = bins > kRcThreads ? bins / kRcThreads : 1;
+        // counts from the largest digit down
         const int want = k_top - above;                  // 1 <= want < equal
-        int local = 0;
-        if (tid * per < bins)
-            for (int e = 0; e < per; ++e) local += s_hist[bins - 1 - tid * per - e];
-        const int inc = wave_incl_scan(local);
-        if (lane == 63) s_wave[wave] = inc;
-        __syncthreads();
-        int gt = inc - local;                            // keys of the region with a larger digit
+        if (bins <= kRcThreads) {                        // thread t holds digit bins - 1 - t
+            const int local = tid < bins ? s_hist[bins - 1 - tid] : 0;
+            const int inc = wave_incl_scan(local);
+            if (lane == 63) s_wave[wave] = inc;
+            __syncthreads();
+            int gt = inc - local;                        // keys of the region with a larger digit
 #pragma unroll
-        for (int w = 0; w < kRcThreads / 64; ++w) gt += w < wave ? s_wave[w] : 0;
-        if (gt < want && gt + local >= want) {           // one thread
-            int d = bins - 1 - tid * per;
-            while (gt + s_hist[d] < want) gt += s_hist[d--];
-            s_digit = d; s_above = gt; s_equal = s_hist[d];
+            for (int w = 0; w < kRcThreads / 64; ++w) gt += w < wave ? s_wave[w] : 0;
+            if (gt < want && gt + local >= want) { s_digit = bins - 1 - tid; s_above = gt; s_equal = local; }   // one thread
+        } else {
+            // A wave adds up 1024 digits, 16 bytes a lane from one place to the next (16 digits a thread, 16 words apart, met on
+            // few banks: 8700 of the kernel's 45000 cycles), then the one that holds the digit looks for it.
+            static_assert(1 << kRcBits == kRcThreads / 64 * 1024, "all digits");
+            const int4 *top = reinterpret_cast<const int4 *>(s_hist) + (bins - 1024 * wave) / 4 - 1 - lane;   // the lane's largest four
+            int4 c[4];
+            int sum[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                c[x] = top[-64 * x];
+                sum[x] = (c[x].x + c[x].y) + (c[x].z + c[x].w);
+            }
+            const int all = wave_incl_scan((sum[0] + sum[1]) + (sum[2] + sum[3]));
+            if (lane == 63) s_wave[wave] = all;
+            __syncthreads();
+            int gt = 0;
+#pragma unroll
+            for (int w = 0; w < kRcThreads / 64; ++w) gt += w < wave ? s_wave[w] : 0;
+            if (gt < want && gt + s_wave[wave] >= want) {    // one wave
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int inc = wave_incl_scan(sum[x]);
+                    int before = gt + inc - sum[x];
+                    if (before < want && before + sum[x] >= want) {
+                        const int four[4] = {c[x].w, c[x].z, c[x].y, c[x].x};
+                        int d = bins - 1024 * wave - 256 * x - 4 * lane - 1;
+                        bool found = false;
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) {
+                            if (!found && before + four[y] >= want) { found = true; s_digit = d - y; s_above = before; s_equal = four[y]; }
+                            before += four[y];
+                        }
+                    }
+                    gt += __builtin_amdgcn_readlane(inc, 63);
+                }
+            }
         }
         __syncthreads();
         stuck = in_lds && s_equal == equal;
@@ -239,7 +304,6 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     // for the whole region, or (then shift = 0: equal keys) for the lowest-indexed need_eq of it.
     const int need_eq = k_top - above;
     const bool all_eq = need_eq >= equal;
-    __syncthreads();                                     // s_l, where the loop did not run
     int cut = n;                                         // the last of them; equal keys from there on are not in the top set
     if (!all_eq) {                                       // a tie cut by the budget
         constexpr int kPer = 8, kW = kRcThreads / 64;    // slabs of kPer rounds of kRcThreads keys; counts of a (round, wave)
@@ -268,25 +332,29 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
         cut = s_cut;
     }
 
-    // ---- the row's selected keys: one wave per plan entry ----
-    const int l = s_l;
-    const int v = i + 1 - pv.RB[l];
-    const int E = pv.count[(int64_t)head * pv.N_q + l];
-    const int32_t *ent = pv.entries + ((int64_t)head * pv.N_q + l) * pv.stride * 2;
+    // ---- the row's selected keys: a wave takes its entries four at a time, 64 keys of each ----
     int hits = 0;
-    for (int e = wave; e < E; e += kRcThreads / 64) {
-        const int w0 = ent[2 * e], rem = ent[2 * e + 1];
-        const int k = w0 & kChunkMask, pos = w0 >> kPosShift;
-        const int b0 = pv.B[k];
-        int take = entry_take(pos, rem, pv.B[k + 1] - b0, v);
-        if (pos == 3) {                                  // row-block form: listed keys above the row are masked
-            const int vis = i + 1 - b0;
-            if (vis < take) take = vis > 0 ? vis : 0;
-        }
-        for (int x = lane; x < take; x += 64) {
-            const int j = b0 + x;
-            const unsigned long long u = shift == 64 ? 0ull : key[j] >> shift;   // shift 64: every key is in the top set
-            hits += u > prefix || (u == prefix && j <= cut);
+    const auto hit = [&](int j, unsigned long long u64) {
+        const unsigned long long u = shift == 64 ? 0ull : u64 >> shift;   // shift 64: every key is in the top set
+        return (int)(u > prefix || (u == prefix && j <= cut));
+    };
+    for (int e0 = 0; e0 < E; e0 += kRcThreads) {
+        if (e0 > 0) entry(e0 + lane * (kRcThreads / 64) + wave, b0_e, take_e);
+        const int n_e = E - e0 - wave <= 0 ? 0 : (E - e0 - wave + kRcThreads / 64 - 1) / (kRcThreads / 64);   // of this wave
+        for (int x = 0; x < n_e && x < 64; x += 4) {
+            int b0[4], take[4];
+            unsigned long long u[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {                // (lanes past the wave's last entry take nothing)
+                b0[c] = __builtin_amdgcn_readlane(b0_e, (x + c) & 63);
+                take[c] = x + c < 64 ? __builtin_amdgcn_readlane(take_e, (x + c) & 63) : 0;
+                u[c] = lane < take[c] ? key[b0[c] + lane] : 0ull;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (lane < take[c]) hits += hit(b0[c] + lane, u[c]);
+                for (int y = lane + 64; y < take[c]; y += 64) hits += hit(b0[c] + y, key[b0[c] + y]);
+            }
         }
     }
 #pragma unroll
@@ -311,7 +379,7 @@ hipError_t launch_recall(const Prob &p, const PlanView &pv, const void *Q, const
         for (int t = 0; t < rr.n; ++t) last = std::max(last, rr.row[t] = (int32_t)rows_host[t0 + t]);
         for (int t = rr.n; t < kRecallRows; ++t) rr.row[t] = 0;
         unsigned long long *w = ws + (int64_t)t0 * p.L;
-        const dim3 grid((last + 256 * kLgKeys) / (256 * kLgKeys), (rr.n + kLgRows - 1) / kLgRows), block(256);
+        const dim3 grid((last + kLgKeys) / kLgKeys, (rr.n + kLgRows - 1) / kLgRows), block(256);
 #define DHSA_LOGITS(T, DD)                                                                                       \
     hipLaunchKernelGGL((k_recall_logits<T, DD>), grid, block, 0, s, pv, (const T *)Q, (const T *)K, p.G, head, rr, \
                        p.L, w, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
