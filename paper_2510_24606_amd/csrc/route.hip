@@ -404,7 +404,7 @@ hipError_t launch_scores(const Prob &p, const double *Qc, const double *Kc, cons
 }
 
 template <int NW>
-__global__ __launch_bounds__(256, 7) void k_select(const double *__restrict__ Sc, SelectArgs a) {
+__global__ __launch_bounds__(NW <= 4 ? 256 : 64 * NW, NW <= 4 ? 7 : 4) void k_select(const double *__restrict__ Sc, SelectArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned long long s_red[NW];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -618,7 +618,10 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
     // step).  Fewer waves with more scores each repeat less, but leave fewer rows in flight: 1634 chunks x 32
     // heads take 250 us with four waves, 315 us with one of 32 scores a lane.
     const int cap = select_cap(pl.stride);
-    const int nw = n_rows < 512 ? 4 : p.N_c <= 512 ? 1 : p.N_c <= 1024 ? 2 : 4;
+    // Eight waves where a CU has one row at most and that is long: a decoding step over 1634 chunks, 32 heads 46.6 -> 44.9 us, over
+    // 4000, 16 heads 44.7 -> 34.8, over 1000, 8 heads 25.1 -> 24.2; over 400, 32 heads 25.4 -> 25.0, over 200 22.1 -> 22.3.  Sixteen
+    // take 44.8, 33.8, 24.6, 25.6 and 23.0.
+    const int nw = n_rows <= 256 && p.N_c > 512 ? 8 : n_rows < 512 ? 4 : p.N_c <= 512 ? 1 : p.N_c <= 1024 ? 2 : 4;
     const int row_bytes = select_row_bytes(nw, cap, p.N_c);
     const size_t shmem = nw == 1 ? (size_t)4 * row_bytes : row_bytes;
     const int per = nw == 1 ? 4 : 1;                     // rows per workgroup
@@ -640,6 +643,7 @@ hipError_t launch_select_groups(const Prob &p, const PlanLayout &pl, const doubl
     } while (0)
     if (nw == 1) DHSA_SELECT(1);
     else if (nw == 2) DHSA_SELECT(2);
+    else if (nw == 8) DHSA_SELECT(8);
     else DHSA_SELECT(4);
 #undef DHSA_SELECT
     return hipSuccess;

@@ -70,3 +70,23 @@ def test_joined_decoding_steps_give_what_separate_ones_give(N_c, n_new, D, dtype
         got = dhsa.dhsa_decode_step(prob, q, k, v, B, ws2, *caps, valid, want_idx=True)
         for x, y in zip(got, want):
             assert torch.equal(x, y), valid
+
+
+@pytest.mark.parametrize("N_c,dtype,B_r", [(513, "bf16", 0), (1030, "f32", 0), (2049, "bf16", 0), (2600, "bf16", 40), (8192, "bf16", 0)])
+@pytest.mark.parametrize("values", ["normal", "equal"])
+def test_long_lists_of_few_rows(N_c, dtype, B_r, values):
+    """A step's ranking by eight waves gives the keys that the prefill's routing, of many rows, gives the last row."""
+    B = boundaries(N_c, 3, N_c)
+    L = int(B[-1])
+    q, k, v = tensors(2, 1, L, 64, dtype, N_c)
+    if values == "equal":
+        k = torch.ones_like(k)
+    prob = dhsa.problem(q, k, B, L // 6, B_r=B_r, V=v)
+    plan, ws = dhsa.alloc(prob, B)
+    dhsa.dhsa_route(prob, q, k, B, plan, ws)
+    caps = (N_c, L)
+    _, idx, cnt = dhsa.dhsa_decode_step(prob, q, k, v, B, dhsa.alloc_decode(prob, *caps), *caps, 0, want_idx=True)
+    for h in range(2):
+        want, n = (x.cpu().numpy()[0] for x in dhsa.dhsa_plan_expand_rows(prob, plan, h, np.array([L - 1], dtype=np.int64)))
+        want = want[:n][want[:n] <= L - 1]
+        assert np.array_equal(idx[h].cpu().numpy()[:len(want)], want) and int(cnt[h]) == len(want)
