@@ -261,7 +261,8 @@ dhsa_status dhsa_debug_scores(const dhsa_problem *prob, const int32_t *B_host, c
  * (Alg. 3) of the row tiles of more than 64 rows / of 33..64 rows / of at most 32
  * rows (fp32 inputs: all rows in slot 4), 7 the whole call.  Tiles of a class that
  * has at most 512 over all heads may run in the launch of a taller class: their
- * time is in its slot then, their own is about 0.  Creates and destroys events and BLOCKS until the work is done;
+ * time is in its slot then, their own is about 0.  (Of few chunks and tiles dhsa_prefill does 2 to 6 in one
+ * launch; they are launched apart here.)  Creates and destroys events and BLOCKS until the work is done;
  * arguments and results otherwise as dhsa_prefill. */
 dhsa_status dhsa_prefill_stage_times(const dhsa_problem *prob, const void *Q_dev, const void *K_dev,
                                      const void *V_dev, const int32_t *B_host, void *O_dev, void *plan_dev,

@@ -22,8 +22,9 @@
 // heads of D = 64, N_b = 256: 18 us; 135 us with one wave per row (no reuse of K and V, products on
 // the vector unit, one key of V at a time).
 #include <algorithm>
+#include <type_traits>
 
-#include "dhsa_internal.h"
+#include "select.h"
 
 namespace dhsa {
 
@@ -35,8 +36,16 @@ constexpr int kF32Seg = 256;     // plan entries per batch
 // D = 64, RW = 2 is held to three waves per SIMD (168 registers, nothing spilled; left to itself it takes 178): L = 8192,
 // N_b = 512, 16 heads 285 -> 250 us.  D = 128, RW = 2 spills nine registers, all of them lane addresses of the
 // prefix sum that a batch of entries needs once; the loop over the keys has none.
-template <int D, int RW>
-__global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(PlanView pv, const float *__restrict__ Q,
+// With F32RouteArgs the workgroup does its query group's routing itself (route_tile); what bounds problems of few tiles is the chain of
+// launches, and of the loads that each begins with.
+struct F32RouteArgs {
+    SelectArgs sel;
+    const double *Qc, *Kc;
+    double *Sc;
+};
+struct NoRoute {};
+template <int D, int RW, typename ROUTE>
+__global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(PlanView pv, ROUTE route, const float *__restrict__ Q,
                                                      const float *__restrict__ K, const float *__restrict__ V,
                                                      float *__restrict__ O, unsigned block0, int H_q, int G, float scale_log2e,
                                                      int64_t qs_h, int64_t qs_l, int64_t ks_h, int64_t ks_l,
@@ -82,13 +91,18 @@ __global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(Pl
     const int nrows = end - row0 < NR ? end - row0 : NR;
     if (nrows <= 0) return;          // the tile has fewer pieces than its class allows
     const int v_lo = row0 + 1 - b_l, v_hi = v_lo + nrows - 1;
-    const int E = pv.count[(int64_t)h * pv.N_q + l];
+    constexpr bool kRoute = !std::is_same<ROUTE, NoRoute>::value;
+    __shared__ std::conditional_t<kRoute, RouteScratch, NoRoute> rs;
+    TileList list;
+    if constexpr (kRoute) list = route_tile<D>(rs, pv, route.sel, route.Qc, route.Kc, route.Sc, G, h, l, row0 == b_l);
+    else list = plan_list(pv, h, l);
     // the entries of the first batch do not wait for their number, and the query rows are requested behind what the key
     // list hangs on
-    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)h * pv.N_q + l) * pv.stride;
+    const int E = list.E;
+    const int2 *ent = list.ent;
     int2 ent_e = ent[tid < pv.stride ? tid : 0];
     if (tid >= E) ent_e = int2{0, 0};   // past the list: nothing there has been written
-    int b0_e = pv.B[ent_e.x & kChunkMask], b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
+    int b0_e = list.B[ent_e.x & kChunkMask], b1_e = list.B[(ent_e.x & kChunkMask) + 1];
     const float *Kg = K + (int64_t)g * ks_h + 4 * q4;
     const float *Vg = V + (int64_t)g * vs_h + 4 * n16;
 
@@ -116,8 +130,8 @@ __global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(Pl
         // segments (entries some row takes a key from) of this batch, compacted
         if (e0 > 0) {
             ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0};
-            b0_e = pv.B[ent_e.x & kChunkMask];
-            b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
+            b0_e = list.B[ent_e.x & kChunkMask];
+            b1_e = list.B[(ent_e.x & kChunkMask) + 1];
         }
         int n_e = 0;
         const int pos_e = ent_e.x >> kPosShift, rem_e = ent_e.y;
@@ -302,8 +316,8 @@ __global__ __launch_bounds__(256, D == 64 && RW == 2 ? 3 : 2) void k_attn_f32(Pl
         if (none | sm.me.odd[0] | sm.me.odd[1] | sm.me.odd[2] | sm.me.odd[3]) {
             for (int e = 0; e < E; ++e) {
                 const int2 w = ent[e];
-                const int k = w.x & kChunkMask, pos = w.x >> kPosShift, b0 = pv.B[k];
-                int take = entry_take(pos, w.y, pv.B[k + 1] - b0, v_lo + r);
+                const int k = w.x & kChunkMask, pos = w.x >> kPosShift, b0 = list.B[k];
+                int take = entry_take(pos, w.y, list.B[k + 1] - b0, v_lo + r);
                 if (pos == 3 && row0 + r + 1 - b0 < take) take = row0 + r + 1 - b0;   // listed keys past the row
                 if (none) {
                     if (take > 0) acc = f32x4{NAN, NAN, NAN, NAN};
@@ -395,12 +409,39 @@ __global__ __launch_bounds__(256) void k_attn_f32_rows(PlanView pv, const float 
     for (int c = 0; c < NC; ++c) O[(int64_t)h * os_h + i * os_l + lane + 64 * c] = o[c] * inv;
 }
 
+// A wave per row is the faster one for row blocks of one row whatever the budget, of 2 up to about 100 keys (95 us
+// against 185 us with 16 keys, 408 against 344 us with 128; L = 6000, 8 heads, D = 64), of 3 up to 40, of 4 up to 25
+// (D = 128: 136 against 189 us with 16 keys, 614 against 329 us with 128): B_r^2 N_b of about 400
+static bool f32_by_rows(const Prob &p) { return p.B_r == 1 || (p.B_r > 0 && (int64_t)p.B_r * p.B_r * p.N_b <= 400); }
+// workgroups of 32 rows
+static int64_t f32_wg32(const Prob &p, const int32_t *T_cls) {
+    return (int64_t)p.H_q * (4 * (int64_t)T_cls[0] + 3 * (int64_t)T_cls[1] + 2 * (int64_t)T_cls[2] + T_cls[3]);
+}
+
+// Every 16 rows repeat their group's routing, so few of them only; less so at D = 128, whose products for the scores are
+// twice as many.  A call in us, three launches -> two: D = 64, 4 heads of 51 chunks of 40 tokens (408 workgroups of 32 rows) 26.5 ->
+// 25.7, 8 heads of 26 chunks (416) 21.1 -> 19.6; D = 128, 4 heads of 26 chunks (208) 24.2 -> 22.5, 8 heads (416) 36.4 -> 37.0, 4
+// heads in row blocks of 128 (256) 30.7 -> 29.1.
+bool f32_route_attend_ok(const Prob &p, const int32_t *T_cls) {
+    const int64_t wg32 = f32_wg32(p, T_cls);
+    return !f32_by_rows(p) && wg32 < 512 && wg32 * p.D <= 256 * 128;
+}
+
+hipError_t launch_f32_route_attend(const Prob &p, const PlanLayout &pl, const PlanView &pv, const double *Qc, const double *Kc,
+                                   double *Sc, int32_t *plan, const void *Q, const void *K, const void *V, void *O, hipStream_t s) {
+    const F32RouteArgs route = {{plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, p.H_q * p.N_q, 0, 0}, Qc, Kc, Sc};
+#define DHSA_F32_ROUTE(DD)                                                                                                        \
+    hipLaunchKernelGGL((k_attn_f32<DD, 1, F32RouteArgs>), dim3((unsigned)(2 * f32_wg32(p, pl.T_cls))), dim3(256), 0, s, pv, route, \
+                       (const float *)Q, (const float *)K, (const float *)V, (float *)O, 0u, p.H_q, p.G,                          \
+                       p.scale * 1.4426950408889634f, p.qs_h, p.qs_l, p.ks_h, p.ks_l, p.vs_h, p.vs_l, p.os_h, p.os_l)
+    if (p.D == 64) DHSA_F32_ROUTE(64); else DHSA_F32_ROUTE(128);
+#undef DHSA_F32_ROUTE
+    return hipGetLastError();
+}
+
 hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V, void *O,
                            hipStream_t s) {
-    // A wave per row is the faster one for row blocks of one row whatever the budget, of 2 up to about 100 keys (95 us
-    // against 185 us with 16 keys, 408 against 344 us with 128; L = 6000, 8 heads, D = 64), of 3 up to 40, of 4 up to 25
-    // (D = 128: 136 against 189 us with 16 keys, 614 against 329 us with 128): B_r^2 N_b of about 400
-    if (p.B_r == 1 || (p.B_r > 0 && (int64_t)p.B_r * p.B_r * p.N_b <= 400)) {
+    if (f32_by_rows(p)) {
         const dim3 grid((unsigned)((p.L + 3) / 4), p.H_q);      // at most 2^20 row blocks: fewer than 2^32 threads
 #define DHSA_F32_ROWS(DD)                                                                                      \
     hipLaunchKernelGGL(k_attn_f32_rows<DD>, grid, dim3(256), 0, s, pv, (const float *)Q, (const float *)K,     \
@@ -412,12 +453,12 @@ hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, con
     }
     // 32 rows per workgroup read K and V half as often as 16; while that leaves CUs with fewer than two
     // workgroups, 16-row ones fill the chip better and waste less on the last rows of a tile
-    const int64_t wg32 = (int64_t)p.H_q * (4 * (int64_t)pv.T_cls[0] + 3 * pv.T_cls[1] + 2 * pv.T_cls[2] + pv.T_cls[3]);
+    const int64_t wg32 = f32_wg32(p, pv.T_cls);
     const bool small = wg32 < 512;
     const int64_t n_wg = small ? 2 * wg32 : wg32;
     const dim3 block(256);
 #define DHSA_F32_ATTN(DD, RW)                                                                                 \
-    hipLaunchKernelGGL((k_attn_f32<DD, RW>), grid, block, 0, s, pv, (const float *)Q, (const float *)K,       \
+    hipLaunchKernelGGL((k_attn_f32<DD, RW, NoRoute>), grid, block, 0, s, pv, NoRoute{}, (const float *)Q, (const float *)K,       \
                        (const float *)V, (float *)O, block0, p.H_q, p.G, p.scale * 1.4426950408889634f, p.qs_h, p.qs_l, \
                        p.ks_h, p.ks_l, p.vs_h, p.vs_l, p.os_h, p.os_l)
     for (int64_t first = 0; first < n_wg; first += kGridMax) {

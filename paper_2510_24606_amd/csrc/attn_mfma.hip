@@ -42,6 +42,7 @@
 #include <stddef.h>
 
 #include "attn_mfma.h"
+#include "select.h"
 #include "dhsa_internal.h"
 
 namespace dhsa {
@@ -86,8 +87,8 @@ struct AttnSmem {
 #define DHSA_SEGMENT_TABLE(e0) \
     if (e0 > 0) { \
         ent_e = e0 + tid < E ? ent[e0 + tid] : int2{0, 0}; \
-        b0_e = pv.B[ent_e.x & kChunkMask]; \
-        b1_e = pv.B[(ent_e.x & kChunkMask) + 1]; \
+        b0_e = list.B[ent_e.x & kChunkMask]; \
+        b1_e = list.B[(ent_e.x & kChunkMask) + 1]; \
     } \
     int n_e = 0; \
     const int pos_e = ent_e.x >> kPosShift, rem_e = ent_e.y; \
@@ -176,17 +177,17 @@ struct AttnSmem {
 #define DHSA_TILE_PROLOGUE                                                                      \
     const int b_l = pv.RB[l];                                                                   \
     const int rows_left = pv.RB[l + 1] - row0;                                                  \
-    const int E = pv.count[(int64_t)h * pv.N_q + l];                                            \
-    const int2 *ent = reinterpret_cast<const int2 *>(pv.entries) + ((int64_t)h * pv.N_q + l) * pv.stride; \
+    const int E = list.E;                                                                       \
+    const int2 *ent = list.ent;                                                                 \
     int2 ent_e = ent[tid < pv.stride ? tid : 0];                                                \
     if (tid >= E) ent_e = int2{0, 0};   /* past the list: nothing there has been written */     \
-    int b0_e = pv.B[ent_e.x & kChunkMask], b1_e = pv.B[(ent_e.x & kChunkMask) + 1];
+    int b0_e = list.B[ent_e.x & kChunkMask], b1_e = list.B[(ent_e.x & kChunkMask) + 1];
 
 // One row tile of more than 64 rows (any tile of up to 128 rows is handled correctly): see the
 // header of this file.
 template <int D>
-__device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const int h,
-                                             const int l, const int row0) {
+__device__ __forceinline__ void attn_tile_32(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const TileList &list,
+                                             const int h, const int l, const int row0) {
     using Smem = AttnSmem<D>;
     constexpr int OPR = D / 8;          // 16-byte pieces per row
     constexpr int KPT = OPR / 4;        // load instructions per wave per tile (K and V each)
@@ -528,8 +529,8 @@ __device__ __forceinline__ int piece_swizzle_k16(int r, int pieces_per_row) {
 }
 
 template <int D, int RW>
-__device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const int h,
-                                             const int l, const int row0) {
+__device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv, const AttnArgs &a, const TileList &list,
+                                             const int h, const int l, const int row0) {
     using Smem = AttnSmem<D>;
     constexpr int OPR = D / 8;          // 16-byte pieces per row
     constexpr int KPT = OPR / 4;        // load instructions per wave per tile (K and V each)
@@ -861,9 +862,29 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, i
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
     const int cls = !MIX || pos < T0 ? CLS : tile < pv.T_big + pv.T_cls[2] ? 1 : 2;
-    if (CLS == 0 && cls == 0) attn_tile_32<D>(sm, pv, a, h, l, row0);
-    else if (CLS <= 1 && cls == 1) attn_tile_16<D, 2>(sm, pv, a, h, l, row0);
-    else attn_tile_16<D, 1>(sm, pv, a, h, l, row0);
+    const TileList list = plan_list(pv, h, l);
+    if (CLS == 0 && cls == 0) attn_tile_32<D>(sm, pv, a, list, h, l, row0);
+    else if (CLS <= 1 && cls == 1) attn_tile_16<D, 2>(sm, pv, a, list, h, l, row0);
+    else attn_tile_16<D, 1>(sm, pv, a, list, h, l, row0);
+}
+
+// ---------------------------------------------------------------------------
+// Scores, ranking and attention of a row tile, for problems of few tiles and few chunks: what bounds those is the chain of
+// launches, and of the loads that each begins with.  The routing's scratch lies where keys are staged later.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_route_attend(PlanView pv, AttnArgs a, SelectArgs sel, const double *__restrict__ Qc,
+                                                         const double *__restrict__ Kc, double *__restrict__ Sc, int act, int T) {
+    __shared__ AttnSmem<D> sm;
+    static_assert(sizeof(RouteScratch) <= sizeof(sm.K), "scratch must fit K");
+    RouteScratch &rs = *reinterpret_cast<RouteScratch *>(sm.K);
+    int h, tile;
+    if (!decode_block(act, blockIdx.x, a.G, T, &h, &tile)) return;
+    const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];
+    const TileList list = route_tile<D>(rs, pv, sel, Qc, Kc, Sc, a.G, h, l, row0 == pv.RB[l]);
+    if (tile < pv.T_big) attn_tile_32<D>(sm, pv, a, list, h, l, row0);
+    else if (tile < pv.T_big + pv.T_cls[2]) attn_tile_16<D, 2>(sm, pv, a, list, h, l, row0);
+    else attn_tile_16<D, 1>(sm, pv, a, list, h, l, row0);
 }
 
 AttnLaunches attn_launches(const Prob &p, const int32_t *T_cls) {
@@ -908,6 +929,36 @@ void attn_mfma_kernels(const Prob &p, const int32_t *T_cls, int32_t *kernel, int
     }
 }
 
+static AttnArgs attn_args(const Prob &p, const void *Q, const void *K, const void *V, void *O) {
+    AttnArgs a;
+    a.Q = (const uint16_t *)Q; a.K = (const uint16_t *)K; a.V = (const uint16_t *)V; a.O = (uint16_t *)O;
+    a.G = p.G;
+    a.scale_log2e = p.scale * 1.4426950408889634f;
+    a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
+    a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
+    return a;
+}
+
+// A call in us, three launches -> two, heads of 128: 8 heads of 26 chunks of 40 tokens (208 tiles) 18.4 -> 15.6, of 60 chunks 27.7 ->
+// 24.2, of 64 chunks of 64 tokens 35.8 -> 29.0; 32 heads of 16 chunks (512 tiles) 25.7 -> 19.5, of 32 chunks (1024) 43.2 -> 39.8; 8
+// heads of 64 chunks in row blocks 59.3 -> 52.0; 2 heads of 8 chunks of 2000 tokens, 16 tiles a group, 98.3 -> 96.4.
+bool route_attend_ok(const Prob &p, const int32_t *T_cls) {
+    const int T1 = T_cls[0] + T_cls[1] + T_cls[2] + T_cls[3];
+    return p.N_c <= kRouteAttendMax && (p.dtype == DHSA_BF16 ? (int64_t)p.H_q * T1 <= 1024 : f32_route_attend_ok(p, T_cls));
+}
+
+hipError_t launch_route_attend(const Prob &p, const PlanLayout &pl, const PlanView &pv, const double *Qc, const double *Kc, double *Sc,
+                               int32_t *plan, const void *Q, const void *K, const void *V, void *O, hipStream_t s) {
+    if (p.dtype != DHSA_BF16) return launch_f32_route_attend(p, pl, pv, Qc, Kc, Sc, plan, Q, K, V, O, s);
+    const AttnArgs a = attn_args(p, Q, K, V, O);
+    const SelectArgs sel = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, p.H_q * p.N_q, 0, 0};
+    const int act = attn_order(8, p.H_kv);
+    const dim3 grid(attn_grid(act, p.H_kv, p.G, pl.T1));
+    if (p.D == 64) hipLaunchKernelGGL(k_route_attend<64>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, act, pl.T1);
+    else hipLaunchKernelGGL(k_route_attend<128>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, act, pl.T1);
+    return hipGetLastError();
+}
+
 hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
                             void *O, hipStream_t s, hipEvent_t *ev) {
     // kv-heads in flight: one per XCD (most workgroups walking the same K / V per L2).  Row blocks of
@@ -918,12 +969,7 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // 1.52 / 1.55 / 1.62, 65536 tokens of groups of seven heads 9.3 / 10.0 / 9.6: those keep eight.
     const double kv_head_bytes = 2.0 * (double)p.L * (double)(p.ks_l + p.vs_l);
     const int act = attn_order((p.B_r >= kRowTile && 8 * kv_head_bytes > 288e6 && 4 * kv_head_bytes <= 288e6) ? 4 : 8, p.H_kv);
-    AttnArgs a;
-    a.Q = (const uint16_t *)Q; a.K = (const uint16_t *)K; a.V = (const uint16_t *)V; a.O = (uint16_t *)O;
-    a.G = p.G;
-    a.scale_log2e = p.scale * 1.4426950408889634f;
-    a.qs_h = p.qs_h; a.qs_l = p.qs_l; a.ks_h = p.ks_h; a.ks_l = p.ks_l;
-    a.vs_h = p.vs_h; a.vs_l = p.vs_l; a.os_h = p.os_h; a.os_l = p.os_l;
+    const AttnArgs a = attn_args(p, Q, K, V, O);
     const AttnLaunches at = attn_launches(p, pv.T_cls);
     const bool *wave = at.wave;
     const int *first = at.first, *own = at.own, *all = at.all;

@@ -240,6 +240,21 @@ void *static_scratch() {
     return g_scratch_ptr[dev];
 }
 
+// routing and attention on one stream
+dhsa_status prefill_impl(const Prob &p, const PlanLayout &pl, const WsLayout &wl, const void *Q, const void *K, const void *V,
+                         const int32_t *B_host, void *plan, void *ws, void *O, hipStream_t s) {
+    if (route_attend_ok(p, pl.T_cls)) {
+        int32_t *pw = static_cast<int32_t *>(plan);
+        double *wd = static_cast<double *>(ws);
+        hipError_t e = launch_setup_pool(p, pl, Q, K, B_host, pw, wd + wl.off_Qc, wd + wl.off_Kc, s, nullptr);
+        if (e == hipSuccess)
+            e = launch_route_attend(p, pl, plan_view(p, pl, plan), wd + wl.off_Qc, wd + wl.off_Kc, wd + wl.off_Sc, pw, Q, K, V, O, s);
+        return hip_status(e);
+    }
+    const dhsa_status st = route_impl(p, pl, wl, Q, K, B_host, plan, ws, s);
+    return st != DHSA_OK ? st : attend_impl(p, pl, Q, K, V, plan, O, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -304,9 +319,7 @@ __attribute__((visibility("default"))) dhsa_status dhsa_prefill(const dhsa_probl
     const WsLayout wl = ws_layout(p);
     if (plan_bytes < (size_t)pl.words * 4 || ws_bytes < (size_t)wl.doubles * 8) return DHSA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = route_impl(p, pl, wl, Q_dev, K_dev, B_host, plan_dev, ws_dev, s);
-    if (st != DHSA_OK) return st;
-    return attend_impl(p, pl, Q_dev, K_dev, V_dev, plan_dev, O_dev, s);
+    return prefill_impl(p, pl, wl, Q_dev, K_dev, V_dev, B_host, plan_dev, ws_dev, O_dev, s);
 }
 
 __attribute__((visibility("default"))) size_t dhsa_static_scratch_bytes(void) { return kStaticScratchBytes; }
@@ -331,9 +344,7 @@ __attribute__((visibility("default"))) dhsa_status dhsa_prefill_static(const dhs
     hipStream_t s = static_cast<hipStream_t>(stream);
     // nothing in the scratch has to start at zero: the pooled vectors and every score the ranking
     // reads are written by this call before they are read
-    st = route_impl(p, pl, wl, Q_dev, K_dev, B_host, plan_dev, ws, s);
-    if (st != DHSA_OK) return st;
-    return attend_impl(p, pl, Q_dev, K_dev, V_dev, plan_dev, O_dev, s);
+    return prefill_impl(p, pl, wl, Q_dev, K_dev, V_dev, B_host, plan_dev, ws, O_dev, s);
 }
 
 __attribute__((visibility("default"))) dhsa_status dhsa_plan_check(const dhsa_problem *prob, const int32_t *B_host,

@@ -140,6 +140,13 @@ hipError_t launch_attn_f32(const Prob &p, const PlanView &pv, const void *Q, con
 // 33..64 rows and of at most 32 rows
 hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, const void *K, const void *V,
                             void *O, hipStream_t s, hipEvent_t *ev = nullptr);
+// scores, ranking and attention in one launch, behind launch_setup_pool, for problems that route_attend_ok takes (T_cls row tiles a head)
+bool route_attend_ok(const Prob &p, const int32_t *T_cls);
+hipError_t launch_route_attend(const Prob &p, const PlanLayout &pl, const PlanView &pv, const double *Qc, const double *Kc, double *Sc,
+                               int32_t *plan, const void *Q, const void *K, const void *V, void *O, hipStream_t s);
+bool f32_route_attend_ok(const Prob &p, const int32_t *T_cls);   // of fp32 problems (attn.hip)
+hipError_t launch_f32_route_attend(const Prob &p, const PlanLayout &pl, const PlanView &pv, const double *Qc, const double *Kc,
+                                   double *Sc, int32_t *plan, const void *Q, const void *K, const void *V, void *O, hipStream_t s);
 // the kernels and events of launch_attn_mfma by height class (dhsa_attention_kernels)
 void attn_mfma_kernels(const Prob &p, const int32_t *T_cls, int32_t *kernel, int32_t *slot);
 

@@ -568,4 +568,60 @@ __device__ __forceinline__ double score_16(const f64x2 (&a)[D / 8], const f64x2 
     return acc[0];
 }
 
+// Plan entries of a query group and the boundaries, in memory or LDS.
+struct TileList {
+    const int2 *ent;
+    int E;
+    const int32_t *B;
+};
+__device__ __forceinline__ TileList plan_list(const PlanView &pv, int h, int l) {
+    const int64_t group = (int64_t)h * pv.N_q + l;
+    return {reinterpret_cast<const int2 *>(pv.entries) + group * pv.stride, pv.count[group], pv.B};
+}
+
+// ---------------------------------------------------------------------------
+// Scores and ranking for a row tile of group l of head h by its own workgroup of 256 threads, as k_score_select makes them; the
+// list stays in LDS, and the first tile of a group (`first`) also writes it, and the scores, where they always are.
+// ---------------------------------------------------------------------------
+constexpr int kRouteAttendMax = 64;   // chunks: 16 for each wave
+struct RouteScratch {
+    double row[kRouteAttendMax];
+    FewSmem<256, kRouteAttendMax> few;
+    int2 ent[kRouteAttendMax];
+    int32_t B[kRouteAttendMax + 1];
+    int count;
+};
+
+template <int D>
+__device__ __forceinline__ TileList route_tile(RouteScratch &rs, const PlanView &pv, const SelectArgs &sel, const double *Qc,
+                                               const double *Kc, double *Sc, int G, int h, int l, bool first) {
+    const int64_t group = (int64_t)h * pv.N_q + l;
+    const int tid = threadIdx.x, lane = tid & 63, k0 = (tid >> 6) * 16, k = k0 + (lane & 15);
+    const Visible vis = visible_chunks(sel, pv.B, l);
+    if (tid <= sel.N_c) rs.B[tid] = pv.B[tid];
+    if (k0 < vis.n) {
+        f64x2 q[D / 8], b[D / 8];
+        load_pooled<D>(b, Kc + ((int64_t)(h / G) * sel.N_c + (k < vis.n ? k : vis.n - 1)) * D);
+        load_pooled<D>(q, Qc + group * D);
+        __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
+        const double score = score_16<D>(q, b);
+        if (lane < 16 && k < vis.n) {
+            rs.row[k] = score;
+            if (first) Sc[group * sel.N_c + k] = score;
+        }
+    }
+    __syncthreads();
+    int2 *entries = reinterpret_cast<int2 *>(sel.plan + sel.pl.off_entries) + group * sel.pl.stride;
+    const int n = select_few<256, kRouteAttendMax>(sel, rs.row, rs.B, vis, rs.few, [&](int i, int w, int rem) {
+        rs.ent[i] = make_int2(w, rem);
+        if (first) entries[i] = make_int2(w, rem);
+    });
+    if (tid == 0) {
+        rs.count = n;
+        if (first) sel.plan[sel.pl.off_count + group] = n;
+    }
+    __syncthreads();
+    return {rs.ent, __builtin_amdgcn_readfirstlane(rs.count), rs.B};
+}
+
 }  // namespace dhsa

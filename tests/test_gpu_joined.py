@@ -90,3 +90,31 @@ def test_long_lists_of_few_rows(N_c, dtype, B_r, values):
         want, n = (x.cpu().numpy()[0] for x in dhsa.dhsa_plan_expand_rows(prob, plan, h, np.array([L - 1], dtype=np.int64)))
         want = want[:n][want[:n] <= L - 1]
         assert np.array_equal(idx[h].cpu().numpy()[:len(want)], want) and int(cnt[h]) == len(want)
+
+
+@pytest.mark.parametrize("N_c,longest,H_q,D,dtype,B_r", [
+    (1, 300, 2, 128, "bf16", 0), (3, 1, 2, 64, "f32", 0), (16, 40, 6, 128, "bf16", 0), (17, 150, 4, 64, "bf16", 0), (33, 60, 2, 128, "f32", 0),
+    (64, 130, 8, 128, "bf16", 0), (64, 20, 2, 64, "f32", 0), (40, 60, 4, 128, "bf16", 96), (50, 30, 2, 64, "f32", 17), (64, 9, 2, 128, "bf16", 300),
+    (65, 40, 2, 128, "bf16", 0)])
+def test_prefill_in_one_launch_gives_what_routing_and_attention_give(N_c, longest, H_q, D, dtype, B_r):
+    B = boundaries(N_c, longest, N_c + H_q)
+    L = int(B[-1])
+    q, k, v = tensors(H_q, 2, L, D, dtype, L)
+    prob = dhsa._with_vo(dhsa.problem(q, k, B, max(1, L // 3), B_r=B_r), v, q)
+
+    def plan_ws():
+        plan, ws = dhsa.alloc(prob, B)
+        plan.fill_(0x55)
+        ws.fill_(255)
+        return plan, ws
+
+    (p1, w1), (p2, w2) = plan_ws(), plan_ws()
+    O1, O2 = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    dhsa.dhsa_prefill(prob, q, k, v, B, O1, p1, w1)
+    dhsa.dhsa_route(prob, q, k, B, p2, w2)
+    dhsa.dhsa_sparse_prefill(prob, q, k, v, B, p2, O2)
+    assert torch.equal(O1, O2) and torch.equal(p1, p2) and bool(torch.isfinite(O1).all())
+    s1, s2 = dhsa.dhsa_debug_scores(prob, B, w1), dhsa.dhsa_debug_scores(prob, B, w2)
+    ends = np.minimum((np.arange(s1.shape[1]) + 1) * B_r, L) if B_r else B[1:]
+    seen = torch.from_numpy(B[None, :-1] < ends[:, None]).cuda().expand(H_q, -1, -1)
+    assert torch.equal(s1[seen], s2[seen]) and bool(torch.isfinite(s1[seen]).all())
