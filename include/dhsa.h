@@ -336,7 +336,8 @@ size_t dhsa_recall_workspace_bytes(const dhsa_problem *prob, int32_t n_rows);
  * and L <= L_cap.  It keeps the pooled keys between calls: kc_valid says that
  * the pooled keys of chunks [0, kc_valid) are already in ws_dev from earlier
  * calls with the same caps, the same K rows and the same boundaries B[0..kc_valid];
- * they are not read again.  0 <= kc_valid <= N_c - 1 (the open chunk is always
+ * they are not read again.  (Counters in it are left at zero by every call, and taken
+ * to be zero by one with kc_valid > 0.)  0 <= kc_valid <= N_c - 1 (the open chunk is always
  * pooled anew); pass 0 on the first call.  Asynchronous on `stream`; calls that
  * share a workspace must be ordered.  Errors as for dhsa_prefill; caps below
  * the problem's sizes or kc_valid out of range: DHSA_ERR_SHAPE. */
