@@ -11,7 +11,7 @@
 //                     step, pooled queries of the open group;
 //   k_scores_decode   that group's scores against every key chunk (fp64 MFMA, heads of a kv-group as rows);
 //   (the ranking and the walk are k_select of route.hip, launched for one group; with few chunks all of the routing
-//   is k_route_decode of that file)
+//   and often the step is k_decode_few)
 //   k_attn_decode     the selected keys are split into slices; one workgroup
 //                     per (slice, head) streams its K and V rows once, 16 bytes per
 //                     lane, several rows in flight, and keeps an online-softmax

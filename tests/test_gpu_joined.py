@@ -1,4 +1,4 @@
-"""Routing whose launches are joined because a problem is small (k_score_select, k_route_decode), against the same routing by
+"""Routing whose launches are joined because a problem is small (k_score_select, k_decode_few, k_route_attend), against the same routing by
 the launches of larger problems: scores, plans and outputs are the same bits."""
 import numpy as np
 import pytest
