@@ -34,8 +34,8 @@ constexpr int kF32Keys = 1024;   // selected keys whose positions and masks are 
 constexpr int kF32Seg = 256;     // plan entries per batch
 
 // D = 64, RW = 2 is held to three waves per SIMD (168 registers, nothing spilled; left to itself it takes 178): L = 8192,
-// N_b = 512, 16 heads 285 -> 250 us.  D = 128, RW = 2 spills five registers, all of them lane addresses of the
-// prefix sum that a batch of entries needs once; the loop over the keys has none.
+// N_b = 512, 16 heads 285 -> 250 us.  D = 128, RW = 2 spills four registers, once per window of
+// keys; the loop over the keys has none.
 // With F32RouteArgs the workgroup does its query group's routing itself (route_tile); what bounds problems of few tiles is the chain of
 // launches, and of the loads that each begins with.
 struct F32RouteArgs {
