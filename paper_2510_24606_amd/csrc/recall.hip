@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
         }
     };
     const auto whole = [&](int j) { return key[j]; };
-    const auto upper = [&](int j) { return reinterpret_cast<const unsigned *>(key)[2 * j + 1]; };
+    const auto upper = [&](int j) { return reinterpret_cast<const uint2 *>(key)[j].y; };   // (2 j may not fit in 32 bits)
     __syncthreads();
     // Lane x of a wave has plan entry 64 wave + x of every 1024: its chunk's first token and the tokens the row takes
     const int l = s_l;
@@ -379,18 +379,25 @@ hipError_t launch_recall(const Prob &p, const PlanView &pv, const void *Q, const
         for (int t = 0; t < rr.n; ++t) last = std::max(last, rr.row[t] = (int32_t)rows_host[t0 + t]);
         for (int t = rr.n; t < kRecallRows; ++t) rr.row[t] = 0;
         unsigned long long *w = ws + (int64_t)t0 * p.L;
-        const dim3 grid((last + kLgKeys) / kLgKeys, (rr.n + kLgRows - 1) / kLgRows), block(256);
-#define DHSA_LOGITS(T, DD)                                                                                       \
-    hipLaunchKernelGGL((k_recall_logits<T, DD>), grid, block, 0, s, pv, (const T *)Q, (const T *)K, p.G, head, rr, \
-                       p.L, w, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
-        if (p.dtype == DHSA_F32) {
-            if (p.D == 64) DHSA_LOGITS(float, 64); else DHSA_LOGITS(float, 128);
-        } else {
-            if (p.D == 64) DHSA_LOGITS(bf16_t, 64); else DHSA_LOGITS(bf16_t, 128);
-        }
+        hipError_t e;
+        // rows and keys counted from key0: a later launch gets Q, K and the keys' places moved by as much, and rows above it below 0
+        constexpr int64_t step = (int64_t)kGridMax * kLgKeys;
+        for (int64_t key0 = 0; key0 <= last; key0 += step) {
+            if (key0 > 0)
+                for (int t = 0; t < kRecallRows; ++t) rr.row[t] -= (int32_t)step;
+            const dim3 grid((unsigned)std::min<int64_t>(kGridMax, (last - key0) / kLgKeys + 1), (rr.n + kLgRows - 1) / kLgRows), block(256);
+#define DHSA_LOGITS(T, DD)                                                                                               \
+    hipLaunchKernelGGL((k_recall_logits<T, DD>), grid, block, 0, s, pv, (const T *)Q + key0 * p.qs_l,                    \
+                       (const T *)K + key0 * p.ks_l, p.G, head, rr, p.L, w + key0, p.qs_h, p.qs_l, p.ks_h, p.ks_l)
+            if (p.dtype == DHSA_F32) {
+                if (p.D == 64) DHSA_LOGITS(float, 64); else DHSA_LOGITS(float, 128);
+            } else {
+                if (p.D == 64) DHSA_LOGITS(bf16_t, 64); else DHSA_LOGITS(bf16_t, 128);
+            }
 #undef DHSA_LOGITS
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        for (int t = 0; last >= step && t < kRecallRows; ++t) rr.row[t] += (int32_t)(last / step * step);
         hipLaunchKernelGGL(k_recall_count, dim3(rr.n), dim3(kRcThreads), 0, s, pv, p.N_b, head, rr, p.L, w, hits + t0,
                            size + t0);
         if ((e = hipGetLastError()) != hipSuccess) return e;
