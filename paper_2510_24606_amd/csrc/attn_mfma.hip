@@ -871,6 +871,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, i
 // ---------------------------------------------------------------------------
 // Scores, ranking and attention of a row tile, for problems of few tiles and few chunks: what bounds those is the chain of
 // launches, and of the loads that each begins with.  The routing's scratch lies where keys are staged later.
+// The order is that of k_attn_mfma: kernels by height, inside each from the end of the sequence.  From its start, the longest
+// lists came last where a budget near the context lets them grow with the row: 16 heads of 60 row blocks of 128, heads of 64,
+// all keys 194.7 -> 156.4 us a call, heads of 128 305.2 -> 267.4; 32 heads of 24 chunks of 128, heads of 128 117.9 -> 99.1.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_route_attend(PlanView pv, AttnArgs a, SelectArgs sel, const double *__restrict__ Qc,
@@ -878,8 +881,11 @@ __global__ __launch_bounds__(256, 2) void k_route_attend(PlanView pv, AttnArgs a
     __shared__ AttnSmem<D> sm;
     static_assert(sizeof(RouteScratch) <= sizeof(sm.K), "scratch must fit K");
     RouteScratch &rs = *reinterpret_cast<RouteScratch *>(sm.K);
-    int h, tile;
-    if (!decode_block(act, blockIdx.x, a.G, T, &h, &tile)) return;
+    int h, pos;
+    if (!decode_block(act, blockIdx.x, a.G, T, &h, &pos)) return;
+    const int T_m = pv.T_big + pv.T_cls[2];
+    const int begin = pos < pv.T_big ? 0 : pos < T_m ? pv.T_big : T_m, end = pos < pv.T_big ? pv.T_big : pos < T_m ? T_m : T;
+    const int tile = begin + end - 1 - pos;
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];
     const TileList list = route_tile<D>(rs, pv, sel, Qc, Kc, Sc, a.G, h, l, row0 == pv.RB[l]);
     if (tile < pv.T_big) attn_tile_32<D>(sm, pv, a, list, h, l, row0);
@@ -939,9 +945,12 @@ static AttnArgs attn_args(const Prob &p, const void *Q, const void *K, const voi
     return a;
 }
 
-// A call in us, three launches -> two, heads of 128: 8 heads of 26 chunks of 40 tokens (208 tiles) 18.4 -> 15.6, of 60 chunks 27.7 ->
-// 24.2, of 64 chunks of 64 tokens 35.8 -> 29.0; 32 heads of 16 chunks (512 tiles) 25.7 -> 19.5, of 32 chunks (1024) 43.2 -> 39.8; 8
-// heads of 64 chunks in row blocks 59.3 -> 52.0; 2 heads of 8 chunks of 2000 tokens, 16 tiles a group, 98.3 -> 96.4.
+// A call in us, three launches -> two, with a budget of 1/16 of the context and of all of it.  Heads of 128: 8 heads of 26 chunks
+// of 20..60 tokens (208 tiles) 19.2 -> 15.6, 28.5 -> 25.7; 32 heads of 24 chunks of 128 (768) 47.0 -> 42.8, 105.4 -> 99.1; 16 heads
+// of 60 row blocks of 128 (960) 68.9 -> 65.3, 273.0 -> 267.4; 2 heads of 64 chunks of 300..800 (564) 124.4 -> 119.0, 706 -> 701.  Heads
+// of 64: 17.0 -> 13.6, 25.4 -> 22.3; 32.9 -> 25.8, 71.5 -> 65.4; 47.0 -> 42.4, 161.9 -> 156.4; (614 tiles) 84.9 -> 83.0, 563 -> 574.
+// Over 55 problems of 513..1024 tiles drawn at random: 1.19 and 1.08 times as fast in the mean, 1.06 and 0.91 at the least, where
+// the last long lists fall to the same CUs.
 bool route_attend_ok(const Prob &p, const int32_t *T_cls) {
     const int T1 = T_cls[0] + T_cls[1] + T_cls[2] + T_cls[3];
     return p.N_c <= kRouteAttendMax && (p.dtype == DHSA_BF16 ? (int64_t)p.H_q * T1 <= 1024 : f32_route_attend_ok(p, T_cls));
