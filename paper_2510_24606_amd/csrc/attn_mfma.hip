@@ -854,10 +854,10 @@ __device__ __forceinline__ void attn_tile_16(AttnSmem<D> &sm, const PlanView &pv
 // keys) to its start, so that the launch ends with the cheapest workgroups; T0 tiles of its own class first, then the
 // shorter ones.
 template <int D, int CLS, bool MIX>
-__global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, int act, int tile0, int T0, int T) {
+__global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, int order, int tile0, int T0, int T) {
     __shared__ AttnSmem<D> sm;
     int h, pos;
-    if (!decode_block(act, blockIdx.x, a.G, T, &h, &pos)) return;
+    if (!decode_block(order, blockIdx.x, a.G, T, &h, &pos)) return;
     const int tile = tile0 + (pos < T0 ? T0 - 1 - pos : T0 + T - 1 - pos);
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
@@ -877,12 +877,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(PlanView pv, AttnArgs a, i
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256, 2) void k_route_attend(PlanView pv, AttnArgs a, SelectArgs sel, const double *__restrict__ Qc,
-                                                         const double *__restrict__ Kc, double *__restrict__ Sc, int act, int T) {
+                                                         const double *__restrict__ Kc, double *__restrict__ Sc, int order, int T) {
     __shared__ AttnSmem<D> sm;
     static_assert(sizeof(RouteScratch) <= sizeof(sm.K), "scratch must fit K");
     RouteScratch &rs = *reinterpret_cast<RouteScratch *>(sm.K);
     int h, pos;
-    if (!decode_block(act, blockIdx.x, a.G, T, &h, &pos)) return;
+    if (!decode_block(order, blockIdx.x, a.G, T, &h, &pos)) return;
     const int T_m = pv.T_big + pv.T_cls[2];
     const int begin = pos < pv.T_big ? 0 : pos < T_m ? pv.T_big : T_m, end = pos < pv.T_big ? pv.T_big : pos < T_m ? T_m : T;
     const int tile = begin + end - 1 - pos;
@@ -961,10 +961,10 @@ hipError_t launch_route_attend(const Prob &p, const PlanLayout &pl, const PlanVi
     if (p.dtype != DHSA_BF16) return launch_f32_route_attend(p, pl, pv, Qc, Kc, Sc, plan, Q, K, V, O, s);
     const AttnArgs a = attn_args(p, Q, K, V, O);
     const SelectArgs sel = {plan, pl, p.N_c, p.N_b, p.B_r, 0, p.N_q, 0, p.H_q * p.N_q, 0, 0};
-    const int act = attn_order(8, p.H_kv);
-    const dim3 grid(attn_grid(act, p.H_kv, p.G, pl.T1));
-    if (p.D == 64) hipLaunchKernelGGL(k_route_attend<64>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, act, pl.T1);
-    else hipLaunchKernelGGL(k_route_attend<128>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, act, pl.T1);
+    const int order = attn_order(3, p, pl.T1);
+    const dim3 grid(attn_grid(order, p, pl.T1));
+    if (p.D == 64) hipLaunchKernelGGL(k_route_attend<64>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, order, pl.T1);
+    else hipLaunchKernelGGL(k_route_attend<128>, grid, dim3(256), 0, s, pv, a, sel, Qc, Kc, Sc, order, pl.T1);
     return hipGetLastError();
 }
 
@@ -977,7 +977,7 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // 17.6 / 17.0 / 17.1; on dynamic chunks, whose tiles have less in common, 22.7 / 24.1 / 25.1, 32768 tokens
     // 1.52 / 1.55 / 1.62, 65536 tokens of groups of seven heads 9.3 / 10.0 / 9.6: those keep eight.
     const double kv_head_bytes = 2.0 * (double)p.L * (double)(p.ks_l + p.vs_l);
-    const int act = attn_order((p.B_r >= kRowTile && 8 * kv_head_bytes > 288e6 && 4 * kv_head_bytes <= 288e6) ? 4 : 8, p.H_kv);
+    const int want = (p.B_r >= kRowTile && 8 * kv_head_bytes > 288e6 && 4 * kv_head_bytes <= 288e6) ? 2 : 3;
     const AttnArgs a = attn_args(p, Q, K, V, O);
     const AttnLaunches at = attn_launches(p, pv.T_cls);
     const bool *wave = at.wave;
@@ -986,12 +986,13 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     // the shorter tiles that joined (a tile has one result, whatever its launch)
     const int per_grid = p.H_q < kGridMax ? kGridMax / p.H_q : 1;
 #define DHSA_LAUNCH1(D_, CLS, MIX)                                                                           \
-    hipLaunchKernelGGL((k_attn_mfma<D_, CLS, MIX>), grid, dim3(256), 0, s, pv, a, act, tile0, T0, T)
+    hipLaunchKernelGGL((k_attn_mfma<D_, CLS, MIX>), grid, dim3(256), 0, s, pv, a, order, tile0, T0, T)
 #define DHSA_LAUNCH(CLS)                                                                                     \
     for (int left = all[CLS] > 0 ? own[CLS] : 0, T0; left > 0; left -= T0) {                                 \
         T0 = left < per_grid ? left : per_grid;                                                              \
         const int tile0 = first[CLS] + left - T0, T = T0 + (left == own[CLS] ? all[CLS] - own[CLS] : 0);     \
-        const dim3 grid(attn_grid(act, p.H_kv, p.G, T));                                                     \
+        const int order = attn_order(want, p, T);                                                            \
+        const dim3 grid(attn_grid(order, p, T));                                                             \
         const bool mix = T > T0;                                                                             \
         if (p.D == 64) { if (mix) DHSA_LAUNCH1(64, CLS, (CLS < 2)); else DHSA_LAUNCH1(64, CLS, false); }     \
         else { if (mix) DHSA_LAUNCH1(128, CLS, (CLS < 2)); else DHSA_LAUNCH1(128, CLS, false); }             \
@@ -1000,13 +1001,13 @@ hipError_t launch_attn_mfma(const Prob &p, const PlanView &pv, const void *Q, co
     for (int c = 0; c < 2; ++c)
         if (wave[c]) {
             const int T = pv.T_cls[c] + (c == 0 && at.middle_too ? pv.T_cls[1] : 0);
-            const hipError_t e = launch_attn_wave(p, pv, a, act, c, c == 0 ? 0 : pv.T_cls[0], T, s);
+            const hipError_t e = launch_attn_wave(p, pv, a, want, c, c == 0 ? 0 : pv.T_cls[0], T, s);
             if (e != hipSuccess) return e;
         }
     DHSA_LAUNCH(0)
     if (ev && hipEventRecord(ev[0], s) != hipSuccess) return hipErrorUnknown;
     if (wave[2]) {
-        const hipError_t e = launch_attn_wave(p, pv, a, act, 2, pv.T_big, pv.T_cls[2] + (at.short_too ? pv.T_cls[3] : 0), s);
+        const hipError_t e = launch_attn_wave(p, pv, a, want, 2, pv.T_big, pv.T_cls[2] + (at.short_too ? pv.T_cls[3] : 0), s);
         if (e != hipSuccess) return e;
     }
     DHSA_LAUNCH(1)

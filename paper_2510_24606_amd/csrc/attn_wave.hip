@@ -760,10 +760,10 @@ __device__ __forceinline__ void attn_wave(WaveSmem<W> &sm, const PlanView &pv, c
 }
 
 // Tiles tile0 .. tile0 + T - 1 of 97..128 rows (or 65..96 that ride along), two waves each, from the end of the sequence (most keys) to its start
-__global__ __launch_bounds__(128, 1) void k_attn_wave2(PlanView pv, AttnArgs a, int act, int tile0, int T) {
+__global__ __launch_bounds__(128, 1) void k_attn_wave2(PlanView pv, AttnArgs a, int order, int tile0, int T) {
     __shared__ WaveSmem<2> sm;
     int h, pos;
-    if (!decode_block(act, blockIdx.x, a.G, T, &h, &pos)) return;
+    if (!decode_block(order, blockIdx.x, a.G, T, &h, &pos)) return;
     const int tile = tile0 + T - 1 - pos;
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];   // query group, first row
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing else is used, O is not written
@@ -772,10 +772,10 @@ __global__ __launch_bounds__(128, 1) void k_attn_wave2(PlanView pv, AttnArgs a, 
 
 // Tiles tile0 .. tile0 + T - 1 of 65..96 (RB = 3) or 33..64 rows (RB = 2), a wave each
 template <int RB>
-__global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, int act, int tile0, int T) {
+__global__ __launch_bounds__(64, 1) void k_attn_wave1(PlanView pv, AttnArgs a, int order, int tile0, int T) {
     __shared__ WaveSmem<1> sm;
     int h, pos;
-    if (!decode_block(act, blockIdx.x, a.G, T, &h, &pos)) return;
+    if (!decode_block(order, blockIdx.x, a.G, T, &h, &pos)) return;
     const int tile = tile0 + T - 1 - pos;
     const int l = pv.tiles[2 * tile], row0 = pv.tiles[2 * tile + 1];
     if (!plan_matches(pv)) return;
@@ -843,11 +843,12 @@ int attn_wave_classes(const Prob &p, const int32_t *T_cls) {
 }
 
 // T tiles from tile0 on for the kernel of class cls: 0: 65..128 rows, 1: 65..96, 2: at most 64 rows
-hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int act, int cls, int tile0, int T, hipStream_t s) {
-    const dim3 grid(attn_grid(act, p.H_kv, p.G, T));
-    if (cls == 0) hipLaunchKernelGGL(k_attn_wave2, grid, dim3(128), 0, s, pv, a, act, tile0, T);
-    else if (cls == 1) hipLaunchKernelGGL((k_attn_wave1<3>), grid, dim3(64), 0, s, pv, a, act, tile0, T);
-    else hipLaunchKernelGGL((k_attn_wave1<2>), grid, dim3(64), 0, s, pv, a, act, tile0, T);
+hipError_t launch_attn_wave(const Prob &p, const PlanView &pv, const AttnArgs &a, int want, int cls, int tile0, int T, hipStream_t s) {
+    const int order = attn_order(want, p, T);
+    const dim3 grid(attn_grid(order, p, T));
+    if (cls == 0) hipLaunchKernelGGL(k_attn_wave2, grid, dim3(128), 0, s, pv, a, order, tile0, T);
+    else if (cls == 1) hipLaunchKernelGGL((k_attn_wave1<3>), grid, dim3(64), 0, s, pv, a, order, tile0, T);
+    else hipLaunchKernelGGL((k_attn_wave1<2>), grid, dim3(64), 0, s, pv, a, order, tile0, T);
     return hipGetLastError();
 }
 
