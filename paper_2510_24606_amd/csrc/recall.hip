@@ -35,7 +35,8 @@ struct RecallRows {
 // keys; the four lanes of a key read a quarter of its row each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024
 // multiply-adds takes 64 cycles) and the memory latency in front of it: 48 rows of L = 32768, D = 128 16 us; 24.6 us on the
 // vector unit, with the rows' elements broadcast from LDS, whose reads were what took the time; 26 us when every lane read all
-// of its key's row.
+// of its key's row.  fp32, D = 128, 82 rows of L = 50760: 30 us; 85 us when a lane read its elements one by one, 16 bytes of a row to
+// an instruction; 58 us on the vector unit.
 constexpr int kLgRows = 16, kLgTiles = 1, kLgKeys = 4 * 16 * kLgTiles;   // rows, keys of a wave in 16s, keys of a workgroup
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -43,13 +44,26 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // This lane's elements d = 4 s + q of a row, in fp64
 template <typename T, int D> struct RecallRow;
 template <int D> struct RecallRow<float, D> {
-    float v[D / 4];
+    unsigned v[D / 4];       // the 16-byte pieces 4 m + q of the row, four words each; dealt: v[s] is the element of product s
     __device__ void load(const float *row, int q) {
 #pragma unroll
-        for (int s = 0; s < D / 4; ++s) v[s] = row[4 * s + q];
+        for (int m = 0; m < D / 16; ++m) {
+            const uint4 u = reinterpret_cast<const uint4 *>(row)[4 * m + q];
+            v[4 * m] = u.x; v[4 * m + 1] = u.y; v[4 * m + 2] = u.z; v[4 * m + 3] = u.w;
+        }
     }
-    __device__ void deal() {}
-    __device__ double get(int s, int) const { return (double)v[s]; }
+    // Product 4 m + i takes word q of piece 4 m + i: words against pieces, of two halves of the wave, then of two 16s of each
+    __device__ void deal() {
+#pragma unroll
+        for (int m = 0; m < D / 16; ++m) {
+            const auto a = __builtin_amdgcn_permlane32_swap(v[4 * m], v[4 * m + 2], false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(v[4 * m + 1], v[4 * m + 3], false, false);
+            const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+            const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+            v[4 * m] = c[0]; v[4 * m + 1] = c[1]; v[4 * m + 2] = d[0]; v[4 * m + 3] = d[1];
+        }
+    }
+    __device__ double get(int s, int) const { return (double)__uint_as_float(v[s]); }
 };
 template <int D> struct RecallRow<bf16_t, D> {
     // w: the 16-byte pieces 4 m + q of the row; v[m][i]: two elements, one of them this lane's, of product 8 m + i
