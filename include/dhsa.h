@@ -337,7 +337,8 @@ size_t dhsa_recall_workspace_bytes(const dhsa_problem *prob, int32_t n_rows);
  * the pooled keys of chunks [0, kc_valid) are already in ws_dev from earlier
  * calls with the same caps, the same K rows and the same boundaries B[0..kc_valid];
  * they are not read again.  (Counters in it are left at zero by every call, and taken
- * to be zero by one with kc_valid > 0.)  0 <= kc_valid <= N_c - 1 (the open chunk is always
+ * to be zero by one with kc_valid > 0: a workspace that this version of the library has
+ * not filled itself starts with kc_valid = 0.)  0 <= kc_valid <= N_c - 1 (the open chunk is always
  * pooled anew); pass 0 on the first call.  Asynchronous on `stream`; calls that
  * share a workspace must be ordered.  Errors as for dhsa_prefill; caps below
  * the problem's sizes or kc_valid out of range: DHSA_ERR_SHAPE. */
@@ -349,7 +350,7 @@ dhsa_status dhsa_decode_step(const dhsa_problem *prob, const void *Q_dev, const 
 size_t dhsa_decode_workspace_bytes(const dhsa_problem *prob, int32_t N_c_cap, int64_t L_cap);
 
 const char *dhsa_status_string(dhsa_status s);
-int dhsa_version(void);
+int dhsa_version(void);   /* 201: counters in the decoding workspace lie in front of what depends on the budget */
 
 #ifdef __cplusplus
 }

@@ -576,6 +576,6 @@ __attribute__((visibility("default"))) const char *dhsa_status_string(dhsa_statu
     return "unknown status";
 }
 
-__attribute__((visibility("default"))) int dhsa_version(void) { return 200; }
+__attribute__((visibility("default"))) int dhsa_version(void) { return 201; }
 
 }  // extern "C"

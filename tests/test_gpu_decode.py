@@ -138,6 +138,27 @@ def test_generation_loop_reuses_the_pooled_keys(B_r, pooling):
     print(f"\n   {steps} steps, N_c {len(w.B) - 1} -> {len(B) - 1}; max |O_row - oracle| = {worst:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("lens,B_r", [(("uniform", 20, 90), 0), (("uniform", 4, 30), 0), (("uniform", 20, 90), 64)],
+                         ids=["few_chunks", "many_chunks", "row_blocks"])
+def test_budgets_that_change_between_the_steps_of_a_workspace(lens, B_r):
+    """Slices so short that the last of a head merges them, which counts them in the workspace, and longer ones in turn: every step
+    gives what it gives in a workspace of its own."""
+    w = dhsa_inputs.make("c3", L=3000, H_q=32, H_kv=8, N_b=2900, lens=lens)
+    Q, K, V = (t.cuda() for t in (w.Q, w.K, w.V))
+    caps = (w.N_c + 3, w.L + 10)
+    ws = None
+    for t, N_b in enumerate((2900, 500, 1500, 130, 513, 512, 2900, 33, 33)):
+        prob = dhsa.problem(Q, K, w.B, N_b, B_r=B_r, V=V)
+        if ws is None:
+            ws = dhsa.alloc_decode(prob, *caps)      # of the largest budget
+        got = dhsa.dhsa_decode_step(prob, Q, K, V, w.B, ws, *caps, w.N_c - 1 if t else 0, want_idx=True)
+        fresh = dhsa.alloc_decode(prob, *caps)
+        fresh.fill_(0x55)
+        want = dhsa.dhsa_decode_step(prob, Q, K, V, w.B, fresh, *caps, 0, want_idx=True)
+        for x, y in zip(got, want):
+            assert torch.equal(x, y), N_b
+
+
 @pytest.mark.parametrize("name", ["c3", "c4"])
 def test_full_size_decode_step(name):
     """The step at the full context length of the workload (131072 / 100000 tokens)."""
