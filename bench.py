@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_mfma_traffic.json")
 KERNEL_SOURCES = tuple(f"paper_2510_24606_amd/csrc/{f}" for f in ("attn_mfma.hip", "attn_wave.hip", "attn_mfma.h",
-                                                                  "dhsa_internal.h"))
+                                                                  "select.h", "dhsa_internal.h"))
 PAPER_CONTEXT = {"what": "paper Tab. 11, DHSA 6.25% @128K, LLaMA-3.1-8B bf16, attention kernel only",
                  "ms_per_layer": 214.5, "hardware": "RTX 3090"}
 ROW_CLASSES = (("rows_gt64", "attn_rows_gt64"), ("rows_33_64", "attn_rows_33_64"), ("rows_le32", "attn_rows_le32"))

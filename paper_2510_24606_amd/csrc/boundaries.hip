@@ -169,8 +169,8 @@ __global__ __launch_bounds__(kNmsThreads) void k_nms_finish(const float *__restr
 
     // how many candidates the windows left undecided (state kUndecided; no other state has been written yet
     // with its low bit set)
-    // A sequence of one slab leaves its kept positions in LDS by the way: reading the states again, 128 bytes in a row for a
-    // thread, made 10.0 us of the kernel's 6.2 at L = 131072.
+    // A sequence of one slab leaves its kept positions in LDS by the way: with the states read again, 128 bytes in a row for a
+    // thread, the kernel took 10.0 us at L = 131072 instead of 6.2.
     const bool once = n16 <= (int64_t)kNmsThreads * 8;
     const auto kept_bits = [](const uint4 &v) {   // kKept is bit 1 of a state byte: gather the bits of 16
         const unsigned w[4] = {(v.x >> 1) & 0x01010101u, (v.y >> 1) & 0x01010101u, (v.z >> 1) & 0x01010101u, (v.w >> 1) & 0x01010101u};

@@ -31,13 +31,12 @@ struct RecallRows {
 // Logits by the fp64 matrix unit, 16 sampled rows x 16 keys a product: v_mfma_f64_16x16x4_f64 adds the products of its four d
 // to the sum one after the other, d ascending, each rounded once -- the fused multiply-adds of the order above, bit for bit
 // (checked against them over 650000 sums of bf16 and fp32 values; infinities and NaN included).  Lane 16 q + n supplies d = 4 s + q
-// of row n and of key n to product s.  A wave keeps its rows in registers, converted, and takes kLgTiles times 16
-// keys; the four lanes of a key read a quarter of its row each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024
+// of row n and of key n to product s.  A wave takes 16 keys; the four lanes of a key read a quarter of its row each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024
 // multiply-adds takes 64 cycles) and the memory latency in front of it: 48 rows of L = 32768, D = 128 16 us; 24.6 us on the
 // vector unit, with the rows' elements broadcast from LDS, whose reads were what took the time; 26 us when every lane read all
 // of its key's row.  fp32, D = 128, 82 rows of L = 50760: 30 us; 85 us when a lane read its elements one by one, 16 bytes of a row to
-// an instruction; 58 us on the vector unit.
-constexpr int kLgRows = 16, kLgTiles = 1, kLgKeys = 4 * 16 * kLgTiles;   // rows, keys of a wave in 16s, keys of a workgroup
+// an instruction; 58 us on the vector unit.  With 32 or 64 keys a wave 48 rows of L = 32768 take 1.3 and 5.2 us longer.
+constexpr int kLgRows = 16, kLgKeys = 4 * 16;   // rows, keys of a workgroup
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -109,40 +108,25 @@ __global__ __launch_bounds__(256, 2) void k_recall_logits(PlanView pv, const T *
         my_row = n16 == r ? i : my_row;
         last = i > last ? i : last;
     }
-    const int j0 = blockIdx.x * kLgKeys + wave * 16 * kLgTiles;
+    const int j0 = blockIdx.x * kLgKeys + wave * 16, j = j0 + n16;   // the lane's key
     if (!plan_matches(pv)) return;   // not this problem's plan: nothing is written
     if (j0 > last) return;           // no row sees these keys
-    RecallRow<T, D> kr[kLgTiles], qr;
+    RecallRow<T, D> kr, qr;
     qr.load(Q + (int64_t)head * qs_h + (int64_t)my_row * qs_l, q);
-#pragma unroll
-    for (int k = 0; k < kLgTiles; ++k) {
-        const int j = j0 + 16 * k + n16;
-        kr[k].load(K + (int64_t)(head / G) * ks_h + (int64_t)(j < last ? j : last) * ks_l, q);   // a row that exists
-    }
+    kr.load(K + (int64_t)(head / G) * ks_h + (int64_t)(j < last ? j : last) * ks_l, q);   // a row that exists
     __builtin_amdgcn_sched_barrier(0);   // left alone, the scheduler moves the loads next to their use
     qr.deal();
+    kr.deal();
+    f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < kLgTiles; ++k) kr[k].deal();
-    f64x4 acc[kLgTiles];
-#pragma unroll
-    for (int k = 0; k < kLgTiles; ++k) acc[k] = (f64x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s = 0; s < D / 4; ++s) {
-        const double a = qr.get(s, q);
-#pragma unroll
-        for (int k = 0; k < kLgTiles; ++k) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, kr[k].get(s, q), acc[k], 0, 0, 0);
-    }
+    for (int s = 0; s < D / 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qr.get(s, q), kr.get(s, q), acc, 0, 0, 0);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {    // element v of a lane: row 4 v + q, key n
         const int r = 4 * v + q, i = __shfl(my_row, r);
-#pragma unroll
-        for (int k = 0; k < kLgTiles; ++k) {
-            const int j = j0 + 16 * k + n16;
-            double x = acc[k][v];
-            if (x == 0.0) x = 0.0;                       // -0.0 ties with +0.0
-            const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-            if (r < nr && j <= i) ws[(int64_t)(t0 + r) * L + j] = (u >> 63) ? ~u : (u | 0x8000000000000000ull);
-        }
+        double x = acc[v];
+        if (x == 0.0) x = 0.0;                       // -0.0 ties with +0.0
+        const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+        if (r < nr && j <= i) ws[(int64_t)(t0 + r) * L + j] = (u >> 63) ? ~u : (u | 0x8000000000000000ull);
     }
 }
 
@@ -189,7 +173,7 @@ __global__ __launch_bounds__(kRcThreads) void k_recall_count(PlanView pv, int N_
     const auto whole = [&](int j) { return key[j]; };
     const auto upper = [&](int j) { return reinterpret_cast<const uint2 *>(key)[j].y; };   // (2 j may not fit in 32 bits)
     __syncthreads();
-    // Lane x of a wave has plan entry 64 wave + x of every 1024: its chunk's first token and the tokens the row takes
+    // Lane x of a wave has plan entry 16 x + wave of every 1024: its chunk's first token and the tokens the row takes
     const int l = s_l;
     const int v = i + 1 - pv.RB[l];
     const int E = pv.count[(int64_t)head * pv.N_q + l];

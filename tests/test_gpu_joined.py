@@ -75,15 +75,30 @@ def test_joined_decoding_steps_give_what_separate_ones_give(N_c, n_new, D, dtype
 @pytest.mark.parametrize("N_c,dtype,B_r", [(513, "bf16", 0), (1030, "f32", 0), (2049, "bf16", 0), (2600, "bf16", 40), (8192, "bf16", 0)])
 @pytest.mark.parametrize("values", ["normal", "equal"])
 def test_long_lists_of_few_rows(N_c, dtype, B_r, values):
-    """A step's ranking by eight waves gives the keys that the prefill's routing, of many rows, gives the last row."""
+    """A step's ranking by eight waves gives the keys that the prefill's routing, of many rows, gives the last row.  (8192 chunks:
+    the list may hold more than 1024 of them, which the kernel that sorts the whole row ranks in both.)"""
+    long_lists(N_c, dtype, B_r, values, None)
+
+
+@pytest.mark.parametrize("N_c,dtype,B_r", [(4097, "f32", 0), (5000, "bf16", 33), (8192, "bf16", 0)])
+@pytest.mark.parametrize("values", ["normal", "equal", "two"])
+def test_rows_of_more_chunks_than_eight_waves_hold(N_c, dtype, B_r, values):
+    """More than 4096 scores are read again in every pass; the list is short enough for the ranking by eight waves."""
+    long_lists(N_c, dtype, B_r, values, 700)
+
+
+def long_lists(N_c, dtype, B_r, values, N_b):
     B = boundaries(N_c, 3, N_c)
     L = int(B[-1])
     q, k, v = tensors(2, 1, L, 64, dtype, N_c)
     if values == "equal":
         k = torch.ones_like(k)
-    prob = dhsa.problem(q, k, B, L // 6, B_r=B_r, V=v)
+    elif values == "two":                                 # scores that tie by the thousand
+        k = torch.where(k[..., :1] > 0.5, 2.0, 1.0).to(k.dtype).expand_as(k).contiguous()
+    prob = dhsa.problem(q, k, B, N_b or L // 6, B_r=B_r, V=v)
     plan, ws = dhsa.alloc(prob, B)
     dhsa.dhsa_route(prob, q, k, B, plan, ws)
+    assert (dhsa.parse_plan(plan.cpu().numpy())["stride"] <= 1024) == (N_b is not None or N_c <= 2600)
     caps = (N_c, L)
     _, idx, cnt = dhsa.dhsa_decode_step(prob, q, k, v, B, dhsa.alloc_decode(prob, *caps), *caps, 0, want_idx=True)
     for h in range(2):

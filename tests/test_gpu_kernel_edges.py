@@ -36,8 +36,9 @@ def test_boundary_windows_and_slabs(L, W, levels):
                                                        (20000, 64, "bf16", 5, True), (700, 64, "f32", 9, True),
                                                        (4097, 128, "f32", 513, False)])
 def test_recall_row_groups_ties_and_candidate_list(L, D, dtype, n_rows, integers):
-    """Row groups of 8, 512 rows per launch, key blocks of 512, regions above and below the 4096 keys the select
-    finishes in LDS; small integers tie by the thousand, so the threshold falls into a tie."""
+    """512 rows per launch, regions above and below the 4096 keys the select finishes in LDS; small integers tie by the
+    thousand, so the threshold falls into a tie.  (The edges of the 16 rows and 64 keys of a workgroup of the logits are
+    test_gpu_recall_edges.py's.)"""
     w = dhsa_inputs.make("c1" if dtype == "f32" else "c3", L=L, H_q=2, H_kv=1, D=D, N_b=max(64, L // 8))
     Qh, Kh = w.Q, w.K
     if integers:
@@ -359,7 +360,8 @@ def test_rows_of_other_16_row_blocks_keep_their_bits(rows, D):
 def test_a_tile_has_one_result_in_every_launch(tall, middle, short, D):
     """A class of few row tiles joins the launch of the next taller one.  The more heads, the fewer classes are that
     small: with 4 heads all join, with 512 (1536 workgroups and more of each) none, with 128 of them the shortest may.
-    The rows of the first heads keep their bits, so the parity tests of joined launches hold for separate ones too."""
+    The rows of the first heads keep their bits, so the parity tests of joined launches hold for separate ones too.
+    dhsa_prefill does the routing of few tiles in the same launch (k_route_attend), so attention is called apart, too."""
     # the launcher's rule, so that another line in it cannot empty this test
     src = open(os.path.join(os.path.dirname(dhsa.__file__), "csrc", "attn_mfma.hip")).read()
     (most,) = re.findall(r"p\.H_q \* all\[c\] <= (\d+)\)", src)
@@ -376,8 +378,10 @@ def test_a_tile_has_one_result_in_every_launch(tall, middle, short, D):
         q, k, v = Q[:H_q], K[:H_q // 4], V[:H_q // 4]
         prob = dhsa.problem(q, k, B, 300, B_r=B_r)
         plan, ws = dhsa.alloc(prob, B)
-        O = torch.full_like(q, float("nan"))
+        O, apart = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
         dhsa.dhsa_prefill(prob, q, k, v, B, O, plan, ws)
+        dhsa.dhsa_sparse_prefill(prob, q, k, v, B, plan, apart)
+        assert torch.equal(O, apart), (H_q, B_r)
         return O[:4]
 
     for B_r in (0, 72):                            # row blocks: tiles of 72 rows and one of the rest
