@@ -61,12 +61,13 @@ __device__ __forceinline__ bool decode_block(int order, unsigned b, unsigned G, 
 // an odd number of tiles of four kv-heads with seven query heads each is no multiple of 8 workgroups, and such a launch,
 // dealt out head by head, has every XCD walk all kv-heads: 65536 tokens, 8192 keys 10207 -> 8778 us a call where the numbers
 // of all its launches are odd, 9350 -> 8718 where those of some are.
-// Where some kv-heads would have to wait for others (numbers that are no power of two, nor a multiple of 2^want), each begins
-// with long lists again, and the chip is left to the last one's.  That costs more than the L2 gives while a head's K and V
-// are a small part of it anyway, or there are few rounds of workgroups.  Attention in us, kv-heads x query heads of each, one kv-head
-// or two at a time -> all: 20 x 1 of 3000 tokens, heads of 64, all keys 87.0 -> 71.5; 5 x 4 of 3500, heads of 128, all keys 161 -> 142; 3 x 1 of
-// 8191, heads of 128 (411 workgroups), 511 keys 27.4 -> 24.0; 6 x 1 of 4500, heads of 64 (714), 1125 keys 27.1 -> 23.9; on the other
-// side 7 x 4 of 4096, heads of 128 (3108), 256 keys 71.7 -> 74.8, of 8191 (4032), 511 keys 159 -> 172; 10 x 4 of 12000 (8520) 392 -> 429.
+// Where some kv-heads would have to wait for others (numbers that are no power of two, nor a multiple of 2^want), each
+// begins with long lists again, and the chip is left to the last one's.  That costs more than the L2 gives while a head's K
+// and V are a small part of it anyway, or there are few rounds of workgroups.  Attention in us, kv-heads x query heads of
+// each, one kv-head or two at a time -> all: 20 x 1 of 3000 tokens, heads of 64, all keys 87.0 -> 71.5; 5 x 4 of 3500, heads
+// of 128, all keys 161 -> 142; 3 x 1 of 8191, heads of 128 (411 workgroups), 511 keys 27.4 -> 24.0; 6 x 1 of 4500, heads of
+// 64 (714), 1125 keys 27.1 -> 23.9; on the other side 7 x 4 of 4096, heads of 128 (3108), 256 keys 71.7 -> 74.8, of 8191
+// (4032), 511 keys 159 -> 172; 10 x 4 of 12000 (8520) 392 -> 429.
 inline int attn_order(int want, const Prob &p, int T) {
     int order = want;
     while (p.H_kv % (1 << order) != 0) --order;

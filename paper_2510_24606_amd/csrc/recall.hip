@@ -28,14 +28,15 @@ struct RecallRows {
     int32_t row[kRecallRows];
 };
 
-// Logits by the fp64 matrix unit, 16 sampled rows x 16 keys a product: v_mfma_f64_16x16x4_f64 adds the products of its four d
-// to the sum one after the other, d ascending, each rounded once -- the fused multiply-adds of the order above, bit for bit
-// (checked against them over 650000 sums of bf16 and fp32 values; infinities and NaN included).  Lane 16 q + n supplies d = 4 s + q
-// of row n and of key n to product s.  A wave takes 16 keys; the four lanes of a key read a quarter of its row each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024
-// multiply-adds takes 64 cycles) and the memory latency in front of it: 48 rows of L = 32768, D = 128 16 us; 24.6 us on the
-// vector unit, with the rows' elements broadcast from LDS, whose reads were what took the time; 26 us when every lane read all
-// of its key's row.  fp32, D = 128, 82 rows of L = 50760: 30 us; 85 us when a lane read its elements one by one, 16 bytes of a row to
-// an instruction; 58 us on the vector unit.  With 32 or 64 keys a wave 48 rows of L = 32768 take 1.3 and 5.2 us longer.
+// Logits by the fp64 matrix unit, 16 sampled rows x 16 keys a product: v_mfma_f64_16x16x4_f64 adds the products of its four
+// d to the sum one after the other, d ascending, each rounded once -- the fused multiply-adds of the order above, bit for
+// bit (checked against them over 650000 sums of bf16 and fp32 values; infinities and NaN included).  Lane 16 q + n supplies
+// d = 4 s + q of row n and of key n to product s.  A wave takes 16 keys; the four lanes of a key read a quarter of its row
+// each and deal the elements out among them.  Bound by the rate of the unit (a product of 1024 multiply-adds takes 64
+// cycles) and the memory latency in front of it: 48 rows of L = 32768, D = 128 16 us; 24.6 us on the vector unit, with the
+// rows' elements broadcast from LDS, whose reads were what took the time; 26 us when every lane read all of its key's row.
+// fp32, D = 128, 82 rows of L = 50760: 30 us; 85 us when a lane read its elements one by one, 16 bytes of a row to an
+// instruction; 58 us on the vector unit.  With 32 or 64 keys a wave 48 rows of L = 32768 take 1.3 and 5.2 us longer.
 constexpr int kLgRows = 16, kLgKeys = 4 * 16;   // rows, keys of a workgroup
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
